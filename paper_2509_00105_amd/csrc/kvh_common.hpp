@@ -9,6 +9,7 @@
 #include "../../include/kvh.h"
 
 #include <cstddef>
+#include <utility>
 
 // The kernels read job descriptors as raw 16-byte words and the binding builds them as packed records:
 // the layouts below are part of the ABI.
@@ -115,6 +116,20 @@ __device__ __forceinline__ T sload(const void* p) {
   return *reinterpret_cast<const __attribute__((address_space(4))) T*>(reinterpret_cast<uintptr_t>(p));
 }
 
+// ---- lanes ------------------------------------------------------------------------------------------
+template <typename F, int... I>
+__device__ __forceinline__ void for_each_index(F&& f, std::integer_sequence<int, I...>) {
+  (f(std::integral_constant<int, I>{}), ...);
+}
+// The value of lane I of each 16-lane row, in every lane of that row (row_newbcast, one move).  Taken with the whole
+// wave enabled.
+template <int I>
+__device__ __forceinline__ int row_bcast(int v) { return __builtin_amdgcn_mov_dpp(v, 0x150 + I, 0xf, 0xf, true); }
+template <int I>
+__device__ __forceinline__ float row_bcast(float v) {
+  return __builtin_bit_cast(float, row_bcast<I>(__builtin_bit_cast(int, v)));
+}
+
 // ---- the two quotients of a group -------------------------------------------------------------
 // scale = r / L and inv = L / r are defined as correctly rounded fp32 divisions.  The IEEE division sequence costs
 // about eleven instructions; the forms below cost four (a reciprocal, a product, the exact residual by one fma, one
@@ -180,7 +195,10 @@ struct DecodeParams {
   int32_t* status;                     // nullable; indexed by item
   int l, c, block_tokens;
   int max_tokens;  // rows the grid covers per item: an item with more tokens is refused on the device
-  int row_tile;  // block order chosen by the launcher: blocks of a plane that are taken before the next plane (see decode_kernel)
+  // block order chosen by the launcher (see decode_kernel)
+  int plane_group;  // (layer, K|V) planes that are taken through all items before the next ones
+  int plane_blocks; // blocks of an item's plane
+  int row_tile;     // of these, how many are taken before the next plane of the group
   // Token-dropped entries (single-item calls only): token t >= split lands `jump` rows further on,
   // and the header must carry these three words (all zero for an ordinary blob).
   int32_t split;

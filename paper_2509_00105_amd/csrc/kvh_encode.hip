@@ -303,10 +303,6 @@ __device__ __forceinline__ void encode_raw_block(const EncodeParams& a, const kv
 // halving steps so that lane j of a head ends up with the minimum and maximum of row j alone: 15 combine-and-select
 // steps per lane for all 16 rows, parameters prepared once per (row, head), and row i's two parameters fetched
 // back by every lane with a row broadcast when row i is quantised.
-template <typename F, int... I>
-__device__ __forceinline__ void for_each_index(F&& f, std::integer_sequence<int, I...>) {
-  (f(std::integral_constant<int, I>{}), ...);
-}
 template <int CTRL>
 __device__ __forceinline__ float dpp_f(float v) {
   return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), CTRL, 0xf, 0xf, false));
