@@ -223,7 +223,10 @@ struct EncodeParams {
   int64_t jump;
   uint32_t hdr_orig_tokens, hdr_sink, hdr_window;
   int n_inline;  // > 0: the jobs are inline_items[0 .. n_inline), read from the kernel-argument segment
-  int plane_group;  // block order: (layer, K|V) planes that consecutive blocks cycle through (set by the launcher)
+  // block order chosen by the launcher (see encode_kernel)
+  int plane_group;   // (layer, K|V) planes that consecutive blocks cycle through
+  int plane_blocks;  // blocks of an item's plane
+  int k_slots;       // K blocks are sets of (row, head) slots instead of strips
   kvh_enc_item inline_items[kInlineItems];
 };
 

@@ -8,6 +8,7 @@
 //     quantises its own registers.
 //   V (statistics over the 128 channels of a head): a head is 16 lanes x 8 channels, reduced
 //     with a 4-step rotate-and-combine inside the 16-lane DPP row.
+// Rows that do not fill 512-channel strips take units of (row, head) slots, see encode_k_slots and encode_row_slots.
 // Quantised codes are produced with the packed float->u8 convert, which rounds to nearest even
 // and inserts the byte in one instruction; narrow codes are routed to their byte at that point.
 #include "kvh_common.hpp"
@@ -111,46 +112,28 @@ __device__ __forceinline__ uint32_t codes2(float t0, float t1) {
 // narrow codes are routed at that point: word i receives, in its byte k, the code that belongs i
 // fields above the bottom of output byte k, and the words are merged with one shift-or each.
 // (For finite input every code is <= L, so fields never overlap.)
-template <int BITS, typename P>
+template <int BITS, bool PLAIN = false, typename P>
 __device__ __forceinline__ void quantise_store8(uint8_t* p, const float (&x)[8], P&& param) {
+  auto store = [](uint8_t* q, auto v) {
+    if constexpr (PLAIN) gstore<decltype(v)>(q, v); else gstore_codes<decltype(v)>(q, v);
+  };
   float t[8];
 #pragma unroll
   for (int j = 0; j < 8; ++j) t[j] = position(x[j], param(j).x, param(j).y);
   if constexpr (BITS == 8) {
     uintx2 w = {codes4(t[0], t[1], t[2], t[3]), codes4(t[4], t[5], t[6], t[7])};
-    gstore_codes<uintx2>(p, w);
+    store(p, w);
   } else if constexpr (BITS == 4) {
-    gstore_codes<uint32_t>(p, codes4(t[0], t[2], t[4], t[6]) | codes4(t[1], t[3], t[5], t[7]) << 4);
+    store(p, codes4(t[0], t[2], t[4], t[6]) | codes4(t[1], t[3], t[5], t[7]) << 4);
   } else {
-    gstore_codes<uint16_t>(p, (uint16_t)(codes2(t[0], t[4]) | codes2(t[1], t[5]) << 2 | codes2(t[2], t[6]) << 4 |
+    store(p, (uint16_t)(codes2(t[0], t[4]) | codes2(t[1], t[5]) << 2 | codes2(t[2], t[6]) << 4 |
                                    codes2(t[3], t[7]) << 6));
   }
 }
 
-template <int DT, int BITS>
-__device__ __forceinline__ void encode_k_block(const EncodeParams& a, const kvh_enc_item& it, uint8_t* layer_base,
-                                               const LayerGeom& geo, int lam, int g, int strip, float* red,
-                                               int split, int64_t jump) {
-  const int lane = threadIdx.x & (kWave - 1);
-  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int n = it.n_tokens;
-  const int c = a.c;
-  const int ch_raw = strip * kStripCh + lane * kLaneCh;
-  const bool active = ch_raw < c;
-  const int ch0 = active ? ch_raw : 0;  // idle lanes of a partial strip shadow lane 0 and never store
-  const int t_first = g * kGroup + wave * kEncRows;
-  const uint8_t* src = reinterpret_cast<const uint8_t*>(a.k + (int64_t)lam * a.layer_stride);  // wave-uniform
-  const uint32_t lane_src_off = (uint32_t)ch0 * 2u;
-
-  // Rows past the end of the blob re-read its last row: a duplicate never changes a min or max.
-  uintx4 d[kEncRows];
-#pragma unroll
-  for (int i = 0; i < kEncRows; ++i) {
-    int t = t_first + i;
-    t = t < n ? t : n - 1;
-    d[i] = gload_rows<uintx4>(uniform(src + (it.src_token0 + t + (t >= split ? jump : 0)) * a.token_stride * 2) + lane_src_off);
-  }
-  float mn[8], mx[8];
+// Minimum and maximum of each of a lane's 8 channels over its 16 rows.
+template <int DT>
+__device__ __forceinline__ void channel_minmax(const uintx4 (&d)[kEncRows], float (&mn)[8], float (&mx)[8]) {
   if constexpr (DT == KVH_BF16) {
     // bf16: the odd channels (upper halves) are compared in their words as they are, the even ones after a shift;
     // the lower half of a word only extends the mantissa and never carries a value past its 16-bit neighbour
@@ -201,6 +184,51 @@ __device__ __forceinline__ void encode_k_block(const EncodeParams& a, const kvh_
       __builtin_amdgcn_sched_barrier(0);  // keep the unpacked floats of different rows from piling up in registers
     }
   }
+}
+
+// K metadata words and {mn, inv} of a lane's 8 channels from their group minima and maxima.
+template <int DT, int BITS>
+__device__ __forceinline__ void channel_params(float (&mn)[8], float (&mx)[8], uint32_t (&meta)[8], float2 (&par)[8]) {
+#pragma unroll
+  for (int j = 0; j < 8; ++j) {
+    uint32_t lo = exact_bits<DT>(mn[j]), hi = exact_bits<DT>(mx[j]);
+    meta[j] = lo | hi << 16;
+    par[j].x = t16_to_f32<DT>(lo);
+    par[j].y = encode_inv<BITS>(par[j].x, t16_to_f32<DT>(hi));
+    // The eight channels are independent, and the scheduler would interleave them all, which costs more registers
+    // than the kernel has left here (the 16 rows stay in registers across this point).  Spilled registers come back
+    // through loads in the middle of the store loop, and a wait for such a load also waits for every store issued
+    // before it: 3-5 such stalls per block, 3 points of throughput.  The empty statement ties the next channel's
+    // inputs to this channel's results, so the channels are prepared one after the other and nothing spills.
+    if (j + 1 < 8) asm volatile("" : "+v"(par[j].x), "+v"(par[j].y), "+v"(meta[j]), "+v"(mn[j + 1]), "+v"(mx[j + 1]));
+  }
+}
+
+template <int DT, int BITS>
+__device__ __forceinline__ void encode_k_block(const EncodeParams& a, const kvh_enc_item& it, uint8_t* layer_base,
+                                               const LayerGeom& geo, int lam, int g, int strip, float* red,
+                                               int split, int64_t jump) {
+  const int lane = threadIdx.x & (kWave - 1);
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int n = it.n_tokens;
+  const int c = a.c;
+  const int ch_raw = strip * kStripCh + lane * kLaneCh;
+  const bool active = ch_raw < c;
+  const int ch0 = active ? ch_raw : 0;  // idle lanes of a partial strip shadow lane 0 and never store
+  const int t_first = g * kGroup + wave * kEncRows;
+  const uint8_t* src = reinterpret_cast<const uint8_t*>(a.k + (int64_t)lam * a.layer_stride);  // wave-uniform
+  const uint32_t lane_src_off = (uint32_t)ch0 * 2u;
+
+  // Rows past the end of the blob re-read its last row: a duplicate never changes a min or max.
+  uintx4 d[kEncRows];
+#pragma unroll
+  for (int i = 0; i < kEncRows; ++i) {
+    int t = t_first + i;
+    t = t < n ? t : n - 1;
+    d[i] = gload_rows<uintx4>(uniform(src + (it.src_token0 + t + (t >= split ? jump : 0)) * a.token_stride * 2) + lane_src_off);
+  }
+  float mn[8], mx[8];
+  channel_minmax<DT>(d, mn, mx);
   // red[0][wave][512] = partial minima, red[1][wave][512] = partial maxima
   float* rmn = red + (0 * kEncWaves + wave) * kStripCh + lane * kLaneCh;
   float* rmx = red + (1 * kEncWaves + wave) * kStripCh + lane * kLaneCh;
@@ -234,19 +262,7 @@ __device__ __forceinline__ void encode_k_block(const EncodeParams& a, const kvh_
 
   uint32_t meta[8];
   float2 par[8];  // {mn, inv}
-#pragma unroll
-  for (int j = 0; j < 8; ++j) {
-    uint32_t lo = exact_bits<DT>(mn[j]), hi = exact_bits<DT>(mx[j]);
-    meta[j] = lo | hi << 16;
-    par[j].x = t16_to_f32<DT>(lo);
-    par[j].y = encode_inv<BITS>(par[j].x, t16_to_f32<DT>(hi));
-    // The eight channels are independent, and the scheduler would interleave them all, which costs more registers
-    // than the kernel has left here (the 16 rows stay in registers across this point).  Spilled registers come back
-    // through loads in the middle of the store loop, and a wait for such a load also waits for every store issued
-    // before it: 3-5 such stalls per block, 3 points of throughput.  The empty statement ties the next channel's
-    // inputs to this channel's results, so the channels are prepared one after the other and nothing spills.
-    if (j + 1 < 8) asm volatile("" : "+v"(par[j].x), "+v"(par[j].y), "+v"(meta[j]), "+v"(mn[j + 1]), "+v"(mx[j + 1]));
-  }
+  channel_params<DT, BITS>(mn, mx, meta, par);
   if (!active) return;
   if (wave == 0) {
     uint8_t* mp = layer_base + ((size_t)g * c + ch0) * 4;
@@ -276,9 +292,7 @@ __device__ __forceinline__ void encode_raw_block(const EncodeParams& a, const kv
   const int lane = threadIdx.x & (kWave - 1);
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int n = it.n_tokens;
-  const int ch_raw = strip * kStripCh + lane * kLaneCh;
-  const bool active = ch_raw < a.c;
-  const int ch0 = active ? ch_raw : 0;
+  const int ch0 = strip * kStripCh + lane * kLaneCh;
   const int t_first = tile * kEncTile + wave * kEncRows;
   if (t_first >= n) return;  // wave-uniform
   const uint8_t* src = reinterpret_cast<const uint8_t*>((is_v ? a.v : a.k) + (int64_t)lam * a.layer_stride);
@@ -293,7 +307,7 @@ __device__ __forceinline__ void encode_raw_block(const EncodeParams& a, const kv
 #pragma unroll
   for (int i = 0; i < kEncRows; ++i) {
     const int t = t_first + i;
-    if (t < n && active) gstore_codes<uintx4>(uniform(rows + (size_t)t * geo.row_bytes) + (uint32_t)ch0 * 2u, d[i]);
+    if (t < n) gstore_codes<uintx4>(uniform(rows + (size_t)t * geo.row_bytes) + (uint32_t)ch0 * 2u, d[i]);
   }
 }
 
@@ -392,6 +406,26 @@ __device__ __forceinline__ void row_minmax(const uintx4& d, float& mn, float& mx
   }
 }
 
+// Statistics of rows r0 .. r0 + R - 1 of a wave: lane r of a head gets the metadata word and {mn, inv} of row r0 + r.
+template <int DT, int BITS, int R, int R0>
+__device__ __forceinline__ uint32_t batch_stats(const uintx4 (&d)[kEncRows], int lane, float2& own) {
+  float pmn[R / 2], pmx[R / 2];
+#pragma unroll
+  for (int k = 0; k < R / 2; ++k) {
+    float mn0, mx0, mn1, mx1;
+    row_minmax<DT>(d[R0 + 2 * k], mn0, mx0);
+    row_minmax<DT>(d[R0 + 2 * k + 1], mn1, mx1);
+    pmn[k] = fold16<true, kDppXor1, kDppXor1>(mn0, mn1, (lane & 1) != 0);
+    pmx[k] = fold16<false, kDppXor1, kDppXor1>(mx0, mx1, (lane & 1) != 0);
+  }
+  const float mn_own = reduce_scatter<true, R>(pmn, lane);
+  const float mx_own = reduce_scatter<false, R>(pmx, lane);
+  const uint32_t lo = exact_bits<DT>(mn_own), hi = exact_bits<DT>(mx_own);
+  own.x = t16_to_f32<DT>(lo);
+  own.y = encode_inv<BITS>(own.x, t16_to_f32<DT>(hi));
+  return lo | hi << 16;
+}
+
 template <int DT, int BITS>
 __device__ __forceinline__ void encode_v_block(const EncodeParams& a, const kvh_enc_item& it, uint8_t* layer_base,
                                                const LayerGeom& geo, int lam, int tile, int strip, int split,
@@ -401,9 +435,10 @@ __device__ __forceinline__ void encode_v_block(const EncodeParams& a, const kvh_
   const int n = it.n_tokens;
   const int c = a.c;
   const int heads = c / kGroup;
-  const int ch_raw = strip * kStripCh + lane * kLaneCh;
-  const bool active = ch_raw < c;  // uniform over the 16 lanes of a head
-  const int ch0 = active ? ch_raw : 0;
+  // Holds for every lane (this form takes whole strips).  The test is there for what it does to the generated code: each
+  // row's quantisation and store are a block of their own.  Without it 4 and 2 bits are 1 % slower on six shapes.
+  const int ch0 = strip * kStripCh + lane * kLaneCh;
+  const bool active = ch0 < c;
   const int t_first = tile * kEncTile + wave * kEncRows;
   const uint8_t* src = reinterpret_cast<const uint8_t*>(a.v + (int64_t)lam * a.layer_stride);  // wave-uniform
   const uint32_t lane_src_off = (uint32_t)ch0 * 2u;
@@ -426,24 +461,10 @@ __device__ __forceinline__ void encode_v_block(const EncodeParams& a, const kvh_
     static_assert(kEncRows % R == 0 && (R == 16 || R == 8 || R == 4 || R == 2), "batches of 16, 8, 4 or 2 rows");
     auto batch = [&](auto b_idx) {
       constexpr int r0 = decltype(b_idx)::value * R;
-      float pmn[R / 2], pmx[R / 2];
-#pragma unroll
-      for (int k = 0; k < R / 2; ++k) {
-        float mn0, mx0, mn1, mx1;
-        row_minmax<DT>(d[r0 + 2 * k], mn0, mx0);
-        row_minmax<DT>(d[r0 + 2 * k + 1], mn1, mx1);
-        pmn[k] = fold16<true, kDppXor1, kDppXor1>(mn0, mn1, (lane & 1) != 0);
-        pmx[k] = fold16<false, kDppXor1, kDppXor1>(mx0, mx1, (lane & 1) != 0);
-      }
-      const float mn_own = reduce_scatter<true, R>(pmn, lane);
-      const float mx_own = reduce_scatter<false, R>(pmx, lane);
-      const uint32_t lo = exact_bits<DT>(mn_own), hi = exact_bits<DT>(mx_own);
-      const int t_own = t_first + r0 + (lane & (R - 1));
-      if (active && (lane & 15) < R && t_own < n)
-        gstore<uint32_t>(vmeta + ((size_t)t_own * heads + ch0 / kGroup) * 4, lo | hi << 16);
       float2 own;
-      own.x = t16_to_f32<DT>(lo);
-      own.y = encode_inv<BITS>(own.x, t16_to_f32<DT>(hi));
+      const uint32_t word = batch_stats<DT, BITS, R, r0>(d, lane, own);
+      const int t_own = t_first + r0 + (lane & (R - 1));
+      if ((lane & 15) < R && t_own < n) gstore<uint32_t>(vmeta + ((size_t)t_own * heads + ch0 / kGroup) * 4, word);
       auto row = [&](auto idx) {
         constexpr int r = decltype(idx)::value;
         constexpr int i = r0 + r;
@@ -475,17 +496,179 @@ __device__ __forceinline__ void encode_v_block(const EncodeParams& a, const kvh_
   }
 }
 
+// ---- rows that are not a multiple of 512 channels --------------------------------------------------------
+// Strips of 512 channels leave lanes without work when a row ends inside one: three of four with rows of 128 channels.
+// Here the 64 lanes x 16 accesses of a wave are 64 (row, head) slots, slot 4 i + j being lanes 16 j .. 16 j + 15 of
+// access i.
+//   K: S = 2 heads or 1 (the largest of these that divides the row) x 64 / S rows; 2 S waves make up a set of S heads x
+//     128 tokens, a block holds 4 / S sets.  A channel's statistics are spread over 8 (wave, 16-lane row) partials
+//     whatever S is, and meet in LDS as they do for strips.
+//   V, raw level: 64 consecutive (row, head) pairs in memory order, so codes and metadata are contiguous.
+// Consecutive slots are consecutive rows or heads, so that an access covers whole cache lines of codes where it can.
+// 80 layers x 8192 tokens x 128 channels in 512-token items, 2 bits: 168 -> 70 us (2.3 -> 5.4 TB/s); 20 x 3001 x 640 fp16
+// in one item, 4 bits: 47.4 -> 39.5 us; 32 x 12000 x 256, 4 bits: 106 -> 89 us.  Bound by memory now, as strips are.
+template <int DT, int BITS, bool PLAIN = false>
+__device__ __forceinline__ void encode_k_slots(const EncodeParams& a, const kvh_enc_item& it, uint8_t* layer_base,
+                                               const LayerGeom& geo, int lam, int bx, float* red, int split, int64_t jump) {
+  const int lane = threadIdx.x & (kWave - 1);
+  const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const uint32_t sub = lane & 15, quad = lane >> 4;
+  const uint32_t n = (uint32_t)it.n_tokens, heads = (uint32_t)a.c / kGroup;
+  const uint32_t log_s = (heads & 1) ? 0u : 1u;
+  const uint32_t s_mask = (1u << log_s) - 1, set_waves = 2u << log_s, step = 4u >> log_s;  // rows per access
+  const uint32_t sets = heads >> log_s;                                                    // per token-group
+  const uint32_t set = (uint32_t)bx * step + wave / set_waves;
+  const uint32_t g = set / sets;
+  const uint32_t head = ((set - g * sets) << log_s) + (quad & s_mask);
+  const uint32_t ch0 = head * kGroup + sub * kLaneCh;
+  const uint32_t part = wave & (set_waves - 1);
+  const uint32_t t_lane = g * kGroup + part * (kWave >> log_s) + (quad >> log_s);  // row of access 0; access i is i * step on
+  const uint8_t* src = reinterpret_cast<const uint8_t*>(a.k + (int64_t)lam * a.layer_stride) + ch0 * 2u;
 
-// grid = (token-groups x strips, 2 * l, items)
-template <int DT>
+  uintx4 d[kEncRows];
+#pragma unroll
+  for (uint32_t i = 0; i < kEncRows; ++i) {
+    uint32_t t = t_lane + i * step;
+    t = t < n ? t : n - 1;  // a duplicate never changes a min or max
+    d[i] = gload_rows<uintx4>(src + (it.src_token0 + (int64_t)t + ((int)t >= split ? jump : 0)) * a.token_stride * 2);
+  }
+  float mn[8], mx[8];
+  channel_minmax<DT>(d, mn, mx);
+  float* rmn = red + (0 * kEncWaves + wave) * kStripCh + lane * kLaneCh;
+  float* rmx = red + (1 * kEncWaves + wave) * kStripCh + lane * kLaneCh;
+  *reinterpret_cast<float4*>(rmn) = make_float4(mn[0], mn[1], mn[2], mn[3]);
+  *reinterpret_cast<float4*>(rmn + 4) = make_float4(mn[4], mn[5], mn[6], mn[7]);
+  *reinterpret_cast<float4*>(rmx) = make_float4(mx[0], mx[1], mx[2], mx[3]);
+  *reinterpret_cast<float4*>(rmx + 4) = make_float4(mx[4], mx[5], mx[6], mx[7]);
+  __syncthreads();
+#pragma unroll
+  for (int i = 0; i < kEncRows; ++i) asm volatile("" : "+v"(d[i]));  // unpacked a second time below, see encode_k_block
+  const uint32_t first_wave = wave & ~(set_waves - 1);
+#pragma unroll
+  for (uint32_t q = 0; q < 8; ++q) {
+    const uint32_t pw = first_wave + (q >> (2 - log_s)), pq = (quad & s_mask) + ((q & (step - 1)) << log_s);
+    const float* pmn = red + (0 * kEncWaves + pw) * kStripCh + (pq * 16 + sub) * kLaneCh;
+    const float* pmx = pmn + kEncWaves * kStripCh;
+    float4 a0 = *reinterpret_cast<const float4*>(pmn), a1 = *reinterpret_cast<const float4*>(pmn + 4);
+    float4 b0 = *reinterpret_cast<const float4*>(pmx), b1 = *reinterpret_cast<const float4*>(pmx + 4);
+    const float am[8] = {a0.x, a0.y, a0.z, a0.w, a1.x, a1.y, a1.z, a1.w};
+    const float bm[8] = {b0.x, b0.y, b0.z, b0.w, b1.x, b1.y, b1.z, b1.w};
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+      mn[j] = __builtin_fminf(mn[j], am[j]);
+      mx[j] = __builtin_fmaxf(mx[j], bm[j]);
+    }
+  }
+  uint32_t meta[8];
+  float2 par[8];  // {mn, inv}
+  channel_params<DT, BITS>(mn, mx, meta, par);
+  if (g * kGroup >= n) return;  // wave-uniform: a set past the end of the blob
+  if (part == 0 && quad <= s_mask) {
+    uint8_t* mp = layer_base + ((size_t)g * (uint32_t)a.c + ch0) * 4;
+    uintx4 m0 = {meta[0], meta[1], meta[2], meta[3]}, m1 = {meta[4], meta[5], meta[6], meta[7]};
+    gstore<uintx4>(mp, m0);
+    gstore<uintx4>(mp + 16, m1);
+  }
+  uint8_t* out = layer_base + geo.kmeta + (size_t)t_lane * geo.row_bytes + ch0 * BITS / 8;
+  const size_t out_step = geo.row_bytes * step;
+#pragma unroll
+  for (uint32_t i = 0; i < kEncRows; ++i) {
+    if (t_lane + i * step < n) {
+      float x[8];
+      unpack8<DT>(d[i], x);
+      quantise_store8<BITS, PLAIN>(out, x, [&](int j) { return par[j]; });
+    }
+    out += out_step;
+    __builtin_amdgcn_sched_barrier(0);
+  }
+}
+
+// Slots in memory order: V at the quantised levels, both tensors at the raw level (BITS = 16).
+template <int DT, int BITS>
+__device__ __forceinline__ void encode_row_slots(const EncodeParams& a, const kvh_enc_item& it, uint8_t* layer_base,
+                                                 const LayerGeom& geo, int lam, bool is_v, int bx, int split, int64_t jump) {
+  constexpr uint32_t kGroupBytes = kGroup * BITS / 8;
+  const int lane = threadIdx.x & (kWave - 1);
+  const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const uint32_t sub = lane & 15, quad = lane >> 4;
+  const uint32_t n = (uint32_t)it.n_tokens, heads = (uint32_t)a.c / kGroup;
+  // slot k of the unit is row t0 + (y0 + k) / heads, head (y0 + k) % heads
+  const uint32_t unit = (uint32_t)bx * kEncWaves + wave;
+  const uint32_t q = unit / heads, x0 = (unit - q * heads) * kWave;
+  const uint32_t t0 = (uint32_t)uniform((int32_t)(q * kWave + x0 / heads)), y0 = (uint32_t)uniform((int32_t)(x0 % heads));
+  if (t0 >= n) return;  // wave-uniform
+  const uint64_t left64 = (uint64_t)(n - t0) * heads - y0;  // slots from the unit's first to the end of the section
+  const uint32_t left = left64 < kWave ? (uint32_t)left64 : (uint32_t)kWave;
+
+  // lane 16 j + i finds the source of slot 4 i + j, which access i fetches by a row broadcast from lane i; slots past the
+  // end re-read the last one and are not stored
+  const uint8_t* src = reinterpret_cast<const uint8_t*>((is_v ? a.v : a.k) + (int64_t)lam * a.layer_stride) + sub * (kLaneCh * 2u);
+  const uint32_t k_own = sub * 4 + quad;
+  const uint32_t y = y0 + (k_own < left ? k_own : left - 1);
+  const uint32_t t_own = t0 + y / heads, head_own = y % heads;
+  const int64_t off = (it.src_token0 + (int64_t)t_own + ((int)t_own >= split ? jump : 0)) * a.token_stride * 2 + head_own * (kGroup * 2u);
+  const int off_lo = (int)(uint32_t)(uint64_t)off, off_hi = (int)(off >> 32);
+  uintx4 d[kEncRows];
+  for_each_index(
+      [&](auto idx) {
+        constexpr int i = decltype(idx)::value;
+        const uint32_t lo = (uint32_t)row_bcast<i>(off_lo);
+        const int hi = row_bcast<i>(off_hi);
+        d[i] = gload_rows<uintx4>(src + (int64_t)((uint64_t)(uint32_t)hi << 32 | lo));
+      },
+      std::make_integer_sequence<int, kEncRows>{});
+
+  const size_t first = (size_t)t0 * heads + y0;
+  if constexpr (BITS == 16) {
+    uint8_t* rows = layer_base + (is_v ? geo.codes : 0) + first * kGroupBytes + quad * kGroupBytes + sub * (kLaneCh * 2u);
+#pragma unroll
+    for (uint32_t i = 0; i < kEncRows; ++i)
+      if (4 * i + quad < left) gstore_codes<uintx4>(rows + i * (4 * kGroupBytes), d[i]);
+  } else {
+    uint8_t* vmeta = layer_base + geo.kmeta + geo.codes;
+    uint8_t* codes = vmeta + geo.vmeta + first * kGroupBytes + quad * kGroupBytes + sub * BITS;
+    constexpr int R = KVH_ENC_VBATCH;
+    auto batch = [&](auto b_idx) {
+      constexpr int r0 = decltype(b_idx)::value * R;
+      float2 own;
+      const uint32_t word = batch_stats<DT, BITS, R, r0>(d, lane, own);
+      const uint32_t k = 4 * (r0 + (sub & (R - 1))) + quad;
+      if (sub < R && k < left) gstore<uint32_t>(vmeta + (first + k) * 4, word);
+      auto row = [&](auto idx) {
+        constexpr int r = decltype(idx)::value;
+        constexpr uint32_t i = r0 + r;
+        float2 par;
+        par.x = row_bcast<r>(own.x);
+        par.y = row_bcast<r>(own.y);
+        if (4 * i + quad < left) {
+          uintx4 w = d[i];
+          asm volatile("" : "+v"(w));  // unpacked a second time, see encode_v_block
+          float x[8];
+          unpack8<DT>(w, x);
+          quantise_store8<BITS>(codes + i * (4 * kGroupBytes), x, [&](int) { return par; });
+        }
+      };
+      for_each_index(row, std::make_integer_sequence<int, R>{});
+    };
+    for_each_index(batch, std::make_integer_sequence<int, kEncRows / R>{});
+    // zero the padding that rounds the vmeta section up to 16 bytes
+    if (left64 <= kWave && lane == 0) {
+      for (size_t o = (size_t)n * heads * 4; o < geo.vmeta; o += 4) gstore<uint32_t>(vmeta + o, 0u);
+    }
+  }
+}
+
+// grid = (blocks of a plane x planes of a group, plane groups, items)
+template <int DT, bool SLOTS>
 __global__ __launch_bounds__(kEncThreads) __attribute__((amdgpu_waves_per_eu(4, 4))) void encode_kernel(EncodeParams a) {
   __shared__ float red[2 * kEncWaves * kStripCh];  // 32 KiB
+  const int item_idx = blockIdx.z;
   kvh_enc_item it;
   DropInfo drop = {kNoSplit, 0, 0u, 0u, 0u};  // ordinary batch items are never token-dropped
   const kvh_enc_item* items = a.items;
   if (a.n_inline > 0) items = reinterpret_cast<const kvh_enc_item*>(KVH_KERNARG_MEMBER(EncodeParams, inline_items));
   if (items != nullptr) {
-    const kvh_enc_item* p = items + blockIdx.z;
+    const kvh_enc_item* p = items + item_idx;
 #if KVH_SCALAR_DESC
     uintx4 lo = sload<uintx4>(p);
     uintx2 hi = sload<uintx2>(reinterpret_cast<const uint8_t*>(p) + 16);
@@ -498,7 +681,7 @@ __global__ __launch_bounds__(kEncThreads) __attribute__((amdgpu_waves_per_eu(4, 
     it.n_tokens = (int32_t)hi.x;
     it.level = (int32_t)hi.y;
   } else if (a.kept_items != nullptr) {
-    const kvh_kept_enc_item* p = a.kept_items + blockIdx.z;
+    const kvh_kept_enc_item* p = a.kept_items + item_idx;
 #if KVH_SCALAR_DESC
     uintx4 lo = sload<uintx4>(p), hi = sload<uintx4>(reinterpret_cast<const uint8_t*>(p) + 16);
 #else
@@ -529,28 +712,24 @@ __global__ __launch_bounds__(kEncThreads) __attribute__((amdgpu_waves_per_eu(4, 
   const int split = drop.split;
   const int64_t jump = drop.jump;
   const int nstrips = (a.c + kStripCh - 1) / kStripCh;
-  // Block order: consecutive blocks of the dispatch order take the same tile of the `plane_group` consecutive
-  // (layer, K|V) planes of a group, then the next tile of those planes; the groups follow each other (the last one
-  // may be smaller).  The launcher chooses the group size.
+  // Block order (see the launcher): consecutive blocks take the same tile of the `plane_group` consecutive (layer, K|V)
+  // planes of a group, then the next tile of those planes; the groups of an item follow each other (the last one may be
+  // smaller).
   int lay_kv, bx;
   {
-    const int lin_xy = blockIdx.y * gridDim.x + blockIdx.x;
-    const int planes = gridDim.y, per_plane = gridDim.x;
-    const int group = a.plane_group < 1 ? 1 : a.plane_group < planes ? a.plane_group : planes;
-    const int full = planes / group;
-    const int g = lin_xy / (group * per_plane);
-    const int first = (g < full ? g : full) * group;            // first plane of this block's group
-    const int size = g < full ? group : planes - full * group;  // planes in it
-    const int j = lin_xy - first * per_plane;
-    lay_kv = first + j % size;
-    bx = j / size;
+    const int lin = blockIdx.x, first = (int)blockIdx.y * a.plane_group;
+    const int size = 2 * a.l - first < a.plane_group ? 2 * a.l - first : a.plane_group;
+    if (lin >= a.plane_blocks * size) return;
+    bx = lin / size;
+    lay_kv = first + (lin - bx * size);
   }
   const int tile = bx / nstrips;
   const int strip = bx - tile * nstrips;
   const int bits = level_bits(it.level);
   // block-uniform; an item with more tokens than the grid covers is skipped as a whole (no header either), so
   // that a later decode of its blob reports a mismatch instead of reading sections that were never written
-  if (bits < 0 || it.n_tokens < 1 || it.n_tokens > a.max_tokens || tile * kEncTile >= it.n_tokens) return;
+  if (bits < 0 || it.n_tokens < 1 || it.n_tokens > a.max_tokens) return;
+  if (!SLOTS && tile * kEncTile >= it.n_tokens) return;
   const LayerGeom geo = layer_geom(it.n_tokens, a.c, bits);
   uint8_t* blob = static_cast<uint8_t*>(it.blob);
   const int lam = lay_kv >> 1;
@@ -576,31 +755,74 @@ __global__ __launch_bounds__(kEncThreads) __attribute__((amdgpu_waves_per_eu(4, 
     gstore<uint32_t>(blob + 4 * threadIdx.x, w);
   }
   uint8_t* layer_base = blob + kHeaderBytes + (size_t)lam * geo.layer_bytes();
-  if (bits == 16) {
-    encode_raw_block<DT>(a, it, layer_base, geo, lam, is_v, tile, strip, split, jump);
-    return;
+  if constexpr (SLOTS) {
+    if (is_v || bits == 16) {
+      switch (bits) {
+        case 16: encode_row_slots<DT, 16>(a, it, layer_base, geo, lam, is_v, bx, split, jump); break;
+        case 8: encode_row_slots<DT, 8>(a, it, layer_base, geo, lam, true, bx, split, jump); break;
+        case 4: encode_row_slots<DT, 4>(a, it, layer_base, geo, lam, true, bx, split, jump); break;
+        default: encode_row_slots<DT, 2>(a, it, layer_base, geo, lam, true, bx, split, jump); break;
+      }
+      return;
+    }
+    if (a.k_slots) {
+      // block-uniform: the first set of the block is past the end
+      const int heads = a.c / kGroup, log_s = (heads & 1) ? 0 : 1;
+      if ((int64_t)(bx * (4 >> log_s) / (heads >> log_s)) * kGroup >= it.n_tokens) return;
+      switch (bits) {
+        case 8: encode_k_slots<DT, 8>(a, it, layer_base, geo, lam, bx, red, split, jump); break;
+        case 4: encode_k_slots<DT, 4>(a, it, layer_base, geo, lam, bx, red, split, jump); break;
+        default:
+          // Rows of an odd number of heads leave gaps between the 32-byte pieces an access writes, which other waves fill;
+          // ordinary stores let the L2 put them together (5 heads: 310 -> 303 us in 512-token items of 32 x 16384 tokens,
+          // 233 -> 209 in one item of 12,000; with 1 head, where there are no gaps, and with 6, 1 to 7 % slower).
+          if (heads == 5) encode_k_slots<DT, 2, true>(a, it, layer_base, geo, lam, bx, red, split, jump);
+          else encode_k_slots<DT, 2>(a, it, layer_base, geo, lam, bx, red, split, jump);
+          break;
+      }
+      return;
+    }
+    if (tile * kEncTile >= it.n_tokens) return;  // block-uniform
   }
-  if (!is_v) {
-    switch (bits) {
-      case 8: encode_k_block<DT, 8>(a, it, layer_base, geo, lam, tile, strip, red, split, jump); break;
-      case 4: encode_k_block<DT, 4>(a, it, layer_base, geo, lam, tile, strip, red, split, jump); break;
-      default: encode_k_block<DT, 2>(a, it, layer_base, geo, lam, tile, strip, red, split, jump); break;
+  if constexpr (!SLOTS) {
+    if (bits == 16) {
+      encode_raw_block<DT>(a, it, layer_base, geo, lam, is_v, tile, strip, split, jump);
+      return;
     }
-  } else {
-    switch (bits) {
-      case 8: encode_v_block<DT, 8>(a, it, layer_base, geo, lam, tile, strip, split, jump); break;
-      case 4: encode_v_block<DT, 4>(a, it, layer_base, geo, lam, tile, strip, split, jump); break;
-      default: encode_v_block<DT, 2>(a, it, layer_base, geo, lam, tile, strip, split, jump); break;
+    if (is_v) {
+      switch (bits) {
+        case 8: encode_v_block<DT, 8>(a, it, layer_base, geo, lam, tile, strip, split, jump); break;
+        case 4: encode_v_block<DT, 4>(a, it, layer_base, geo, lam, tile, strip, split, jump); break;
+        default: encode_v_block<DT, 2>(a, it, layer_base, geo, lam, tile, strip, split, jump); break;
+      }
+      return;
     }
+  }
+  switch (bits) {
+    case 8: encode_k_block<DT, 8>(a, it, layer_base, geo, lam, tile, strip, red, split, jump); break;
+    case 4: encode_k_block<DT, 4>(a, it, layer_base, geo, lam, tile, strip, red, split, jump); break;
+    default: encode_k_block<DT, 2>(a, it, layer_base, geo, lam, tile, strip, red, split, jump); break;
   }
 }
 
 int launch_encode(const EncodeParams& a, int dt, int n_items, int max_tokens, hipStream_t stream) {
-  const int nstrips = (a.c + kStripCh - 1) / kStripCh;
-  const int tiles = (max_tokens + kEncTile - 1) / kEncTile;
-  dim3 grid((unsigned)(tiles * nstrips), (unsigned)(2 * a.l), (unsigned)n_items);
+  // Rows of whole 512-channel strips: a block is one token-group of a strip.  Any other row length: V and raw blocks are 8
+  // units of 64 (row, head) slots.  K blocks are sets of slots for 1, 2, 5 and 6 heads, where strips keep 25 to 75 % of
+  // their lanes; with 3 heads (75 %, but one head at a time here) and from 7 on (81 % and more) strips are the faster
+  // ones.  32 layers x 2,048 to 16,384 tokens in items of 256 to 12,000, strips (with slots for V) against slots: 1 head
+  // 1.35 to 2.3 times faster, 2 heads 1.1 to 1.25, 5 heads 1.02 to 1.24, 6 heads 0.99 to 1.16, 3 heads 0.9 to 0.95, 7 to 18
+  // heads 0.89 to 1.01.
+  const int heads = a.c / kGroup, nstrips = (a.c + kStripCh - 1) / kStripCh;
+  const bool slots = heads % (kStripCh / kGroup) != 0;
+  const int64_t groups = ((int64_t)max_tokens + kEncTile - 1) / kEncTile;
+  int64_t gx = groups * nstrips;  // never fewer than the blocks of slots in memory order
   EncodeParams b = a;
   b.max_tokens = max_tokens;
+  b.k_slots = heads == 1 || heads == 2 || heads == 5 || heads == 6;
+  if (b.k_slots) {
+    const int log_s = (heads & 1) ? 0 : 1, per_block = 4 >> log_s;
+    gx = (groups * (heads >> log_s) + per_block - 1) / per_block;
+  }
   // Plane group.  With the dispatcher dealing consecutive blocks to the 8 XCDs in turn, groups of 8 make every XCD
   // stream through one plane at a time; that is the default.  Long items do better with the two planes of a layer
   // alone (their sections of a blob are megabytes apart, and fewer planes at a time keep the writes together), and
@@ -612,10 +834,15 @@ int launch_encode(const EncodeParams& a, int dt, int n_items, int max_tokens, hi
   //   32 x 32768 tokens in 2048-token items, all / 8 / 2:               74.7 / 75.5 / 69.3   75.5 / 77.5 / 78.0   74.3 / 76.5 / 75.9
   const bool near = (int64_t)a.l * a.layer_stride * 2 <= ((int64_t)1 << 29);
   b.plane_group = max_tokens >= 8192 ? 2 : near && max_tokens <= 512 ? 2 * a.l : 8;
-  if (dt == KVH_F16)
-    launch_kernel(encode_kernel<KVH_F16>, grid, dim3(kEncThreads), 0u, stream, b);
-  else
-    launch_kernel(encode_kernel<KVH_BF16>, grid, dim3(kEncThreads), 0u, stream, b);
+  b.plane_blocks = (int)gx;
+  if (b.plane_group > 2 * a.l) b.plane_group = 2 * a.l;
+  // the x dimension counts threads in 32 bits
+  while (b.plane_group > 1 && gx * b.plane_group * kEncThreads > 0xffffffffLL) b.plane_group = (b.plane_group + 1) / 2;
+  const unsigned n_groups = (unsigned)((2 * a.l + b.plane_group - 1) / b.plane_group);
+  const dim3 grid((unsigned)(gx * b.plane_group), n_groups, (unsigned)n_items);
+  auto kernel = dt == KVH_F16 ? (slots ? encode_kernel<KVH_F16, true> : encode_kernel<KVH_F16, false>)
+                              : (slots ? encode_kernel<KVH_BF16, true> : encode_kernel<KVH_BF16, false>);
+  launch_kernel(kernel, grid, dim3(kEncThreads), 0u, stream, b);
   KVH_HIP_CHECK_LAUNCH();
   return KVH_OK;
 }
