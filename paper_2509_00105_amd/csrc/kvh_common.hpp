@@ -180,6 +180,22 @@ __device__ __forceinline__ float encode_inv(float mn, float mx) {
   return r < 0x1p-100f ? 0.0f : levels_over_range<BITS>(r);
 }
 
+// Division of values below 2^31 by a number that is fixed for a launch, as a product with a rounded-up reciprocal of 31
+// + shift binary places (shift = the divisor's bits minus the bit of an exact power of two), prepared on the host: the
+// quotient's error x * (m d - 2^(31 + shift)) / (d 2^(31 + shift)) stays below 1 / d because m d exceeds 2^(31 + shift)
+// by at most d <= 2^shift and x < 2^31.  Two instructions of the scalar unit where the operand is wave-uniform; the
+// division sequence takes some twenty vector instructions before a wave can form its first address (2 to 3 % of the
+// transcoder's time).
+struct Divisor {
+  uint32_t d, m, shift;
+  Divisor() = default;
+  explicit Divisor(uint32_t divisor) : d(divisor), shift(0) {
+    while (shift < 31 && (uint32_t(1) << shift) < d) ++shift;
+    m = (uint32_t)(((uint64_t(1) << (31 + shift)) + d - 1) / d);
+  }
+  __host__ __device__ uint32_t quotient(uint32_t x) const { return (uint32_t)((uint64_t)x * m >> 31 >> shift); }
+};
+
 // ---- kernel parameter blocks and launchers (defined next to their kernels) -----------------------
 // Jobs that travel inside the kernel arguments: the chunked calls have their descriptors in host arrays, and
 // this many per launch reach the kernel without any device memory of the library's own.
@@ -250,6 +266,8 @@ struct TranscodeParams {
   int32_t* status;           // nullable; indexed by item
   int l, c;
   int max_tokens;            // rows the grid covers per item: an item with more tokens is refused on the device
+  int k_log_s;               // K sets are 2^k_log_s heads (rows that are not whole 1024-channel spans)
+  Divisor by_heads, by_sets; // heads of a row, K sets of a token-group
 };
 
 int launch_decode(const DecodeParams& a, int dt, int n_items, int max_tokens, hipStream_t stream);

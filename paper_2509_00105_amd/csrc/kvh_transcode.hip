@@ -19,6 +19,12 @@
 // of a group fits one register (4 -> 2 and the pairs that start from 2 bits) the "parameters"
 // are that map, built by running the arithmetic once per input code, and an element costs a
 // shift and a funnel shift.
+//
+// Rows that are not a multiple of 1024 channels (SLOTS) would leave lanes of the span idle, 56 of 64 with 128 channels.
+// An access then covers 8 (row, head) slots of 8 lanes each, 128 slots per wave: V slots are consecutive in memory; K
+// slots are sets of 1, 2 or 4 heads x a token-group, several sets to a block, so that a lane keeps its channels, or spans
+// with idle lanes where that is the faster form (see the launcher).  32 layers, 8 -> 4 bits, 2,048 tokens x 128 channels:
+// 30.4 -> 13.7 us, 16,384 x 256: 228 -> 80 us; 4 -> 2 bits, 12,000 x 128: 103 -> 22 us, 8,192 x 1280: 157 -> 119 us.
 #include <type_traits>
 
 #include "kvh_common.hpp"
@@ -42,9 +48,11 @@ constexpr int kTcWaves = 8;
 constexpr int kTcThreads = kTcWaves * kWave;      // 512
 constexpr int kTcLaneCh = 16;                     // channels per lane
 constexpr int kTcSpanCh = kWave * kTcLaneCh;      // 1024 channels per wave access
-constexpr int kTcRows = kGroup / kTcWaves;        // 16 rows per wave
-constexpr int kTcBatch = 8;                       // rows in flight per wave
-constexpr int kTcSpanHeads = kTcSpanCh / kGroup;  // 8 V groups per row of a span
+constexpr int kTcRows = kGroup / kTcWaves;        // 16 accesses per wave
+constexpr int kTcBatch = 8;                       // accesses in flight per wave
+constexpr int kTcSpanHeads = kTcSpanCh / kGroup;  // 8 (row, head) slots per access
+constexpr int kTcSlots = kTcRows * kTcSpanHeads;  // 128 slots per wave
+constexpr int kSlotLanes = kGroup / kTcLaneCh;    // 8 lanes per slot
 static_assert(kTcBatch * kTcSpanHeads == kWave, "one lane per V group of a batch");
 static_assert(kTcThreads * 2 == kTcSpanCh, "two K channels per thread");
 
@@ -442,58 +450,120 @@ __device__ __forceinline__ bool source_header_ok(const HeaderWords& h, int dt, i
   return fields && (plain || dropped);
 }
 
-template <int DT, int BI, int BO>
-__device__ __forceinline__ void transcode_block(const TranscodeParams& a, const kvh_tc_item& it, int item_idx, int lam,
-                                                bool is_v, int g, int span, TcParams* kpar, float* kquad,
-                                                uint32_t* kflags) {
+// SLOTS: rows that are not a multiple of 1024 channels (see the head of the file).
+template <int DT, int BI, int BO, bool SLOTS>
+__device__ __forceinline__ void transcode_block(const TranscodeParams& a, const kvh_tc_item& it, int item_idx, int lay_kv,
+                                                int bx, TcParams* kpar, float* kquad, uint32_t* kflags) {
   using Yes = std::integral_constant<bool, true>;
   using No = std::integral_constant<bool, false>;
   const int lane = threadIdx.x & (kWave - 1);
-  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int n = it.n_tokens;
-  const int c = a.c;
-  const int heads = c / kGroup;
+  const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const uint32_t sub = lane % kSlotLanes, slot = lane / kSlotLanes;
+  const uint32_t n = (uint32_t)it.n_tokens, c = (uint32_t)a.c, heads = c / kGroup;
+  const int lam = lay_kv >> 1;
+  const bool is_v = lay_kv & 1;
+
+  // K: a set is 2^log_s heads x one token-group, shared by as many waves; a block holds 8 >> log_s sets
+  const uint32_t log_s = SLOTS ? (uint32_t)a.k_log_s : 3u;
+  const uint32_t sets = SLOTS ? (heads + (1u << log_s) - 1) >> log_s : heads >> 3;  // per token-group; the last may be smaller
+  const uint32_t first_set = (uint32_t)bx * (8u >> log_s);
+  const uint32_t first_g = a.by_sets.quotient(first_set);
+  if ((!SLOTS || !is_v) && (uint64_t)first_g * kGroup >= n) return;  // block-uniform
+  auto set_of = [&](uint32_t s, uint32_t& g, uint32_t& head0) {  // the s-th set of the block
+    g = SLOTS ? a.by_sets.quotient(first_set + s) : first_g;
+    head0 = (first_set + s - g * sets) << log_s;
+  };
+  // V: the wave's slots start at row t0, head y0.  With whole spans they are 16 rows x 8 heads, otherwise 128 in memory
+  // order; access i is `v_step` slots of the section on.
+  uint32_t t0 = 0, y0 = 0, left = 0;
+  uint64_t left64 = 0;  // SLOTS: slots from the wave's first to the end of the section
+  const uint32_t v_step = SLOTS ? (uint32_t)kTcSpanHeads : heads;
+  if (is_v) {
+    if constexpr (SLOTS) {
+      const uint32_t unit = (uint32_t)bx * kTcWaves + wave;
+      const uint32_t q = a.by_heads.quotient(unit), x = (unit - q * heads) * kTcSlots, xq = a.by_heads.quotient(x);
+      t0 = q * kTcSlots + xq;
+      y0 = x - xq * heads;
+      if (t0 < n) left64 = (uint64_t)(n - t0) * heads - y0;
+      left = left64 < kTcSlots ? (uint32_t)left64 : (uint32_t)kTcSlots;
+    } else {
+      t0 = first_g * kGroup + wave * kTcRows;
+      y0 = (first_set - first_g * sets) << 3;
+      left = t0 >= n ? 0 : n - t0 < kTcRows ? (n - t0) * kTcSpanHeads : (uint32_t)kTcSlots;
+    }
+  }
+
   const uint8_t* src = static_cast<const uint8_t*>(it.src);
   uint8_t* dst = static_cast<uint8_t*>(it.dst);
-  const LayerGeom gi = layer_geom(n, c, BI), go = layer_geom(n, c, BO);
+  const LayerGeom gi = layer_geom(it.n_tokens, a.c, BI), go = layer_geom(it.n_tokens, a.c, BO);
   const HeaderWords hdr = {gload<uintx4>(src), gload<uintx4>(src + 16), gload<uintx4>(src + 32)};
-
-  const int ch_raw = span * kTcSpanCh + lane * kTcLaneCh;
-  const bool active = ch_raw < c;  // idle lanes of a partial span shadow channel 0 and never store
-  const uint32_t ch = active ? (uint32_t)ch_raw : 0u;
-  const int t_first = g * kGroup + wave * kTcRows;
-
   const uint8_t* in_layer = src + kHeaderBytes + (size_t)lam * gi.layer_bytes();
   uint8_t* out_layer = dst + kHeaderBytes + (size_t)lam * go.layer_bytes();
-  const uint8_t* in_codes = in_layer + gi.kmeta + (is_v ? gi.codes + gi.vmeta : 0) + ch * BI / 8;
-  uint8_t* out_codes = out_layer + go.kmeta + (is_v ? go.codes + go.vmeta : 0) + ch * BO / 8;
 
-  // Rows in flight per wave.  Narrow codes (2 registers a row or less) are loaded for all 16 rows of
+  // A lane's codes: access i is i strides on; accesses beyond `last` (-1: none) re-read it and are not stored.  `count`
+  // (wave-uniform) accesses have a slot to store.
+  const uint8_t* in_codes;
+  uint8_t* out_codes;
+  const size_t in_stride_k = gi.row_bytes << (3 - log_s), out_stride_k = go.row_bytes << (3 - log_s);
+  const size_t in_stride_v = (size_t)v_step * (kGroup * BI / 8), out_stride_v = (size_t)v_step * (kGroup * BO / 8);
+  int last, count;
+  bool full = true;  // SLOTS, wave-uniform: every lane has all its accesses, or none
+  uint32_t par_lane = 0;  // K: where the parameters of this lane's channels lie in LDS
+  if (!is_v) {
+    const uint32_t sib = wave >> log_s;
+    uint32_t g, head0;
+    set_of(sib, g, head0);
+    const uint32_t t_wave = g * kGroup + (wave & ((1u << log_s) - 1)) * (kGroup >> log_s);
+    const uint32_t t = t_wave + (slot >> log_s), t_in = t < n ? t : n - 1;
+    const uint32_t head = head0 + (slot & ((1u << log_s) - 1));
+    const bool active = !SLOTS || head < heads;
+    const uint32_t ch = (active ? head : 0u) * kGroup + sub * kTcLaneCh;
+    in_codes = in_layer + gi.kmeta + (size_t)t_in * gi.row_bytes + ch * BI / 8;
+    out_codes = out_layer + go.kmeta + (size_t)t_in * go.row_bytes + ch * BO / 8;
+    full = t_wave + (kGroup >> log_s) <= n;
+    last = active && t < n ? (int)((n - 1 - t) >> (3 - log_s)) : -1;
+    count = t_wave < n ? (int)((n - 1 - t_wave) >> (3 - log_s)) + 1 : 0;
+    par_lane = (sib << (3 + log_s)) + ((uint32_t)lane & ((8u << log_s) - 1));
+  } else {
+    const size_t first = left == 0 ? 0 : (size_t)t0 * heads + y0 + (!SLOTS || slot < left ? slot : left - 1);
+    in_codes = in_layer + gi.kmeta + gi.codes + gi.vmeta + first * (kGroup * BI / 8) + sub * (kTcLaneCh * BI / 8);
+    out_codes = out_layer + go.kmeta + go.codes + go.vmeta + first * (kGroup * BO / 8) + sub * (kTcLaneCh * BO / 8);
+    full = left == kTcSlots;
+    count = (int)((left + kTcSpanHeads - 1) / kTcSpanHeads);
+    last = !SLOTS ? count - 1 : slot < left ? (int)((left - 1 - slot) / kTcSpanHeads) : -1;
+  }
+
+  // Accesses in flight per wave.  Narrow codes (2 registers an access or less) are loaded for all 16 accesses of
   // the wave at once: one round trip to memory instead of two, and twice the bytes in flight.  With
-  // 8-bit input a row takes 4 registers; a K wave also holds the parameters of its 16 channels
-  // (48 registers), so it takes 4 rows at a time and a V wave 8.
+  // 8-bit input an access takes 4 registers; a K wave also holds the parameters of its 16 channels
+  // (48 registers), so it takes 4 at a time and a V wave 8.
   constexpr int kRowsK = BI == 8 ? kTcBatch / 2 : kTcRows;
   constexpr int kRowsV = BI == 8 ? kTcBatch : kTcRows;
   InCodes<BI> cw[kRowsV];
-  auto load_batch = [&](int t0, auto rows_tag) {
+  auto load_batch = [&](int a0, auto rows_tag, size_t in_stride) {
+    if (SLOTS && full) {  // no per-lane clamp
+#pragma unroll
+      for (int i = 0; i < decltype(rows_tag)::value; ++i) cw[i].load(in_codes + (size_t)(uint32_t)(a0 + i) * in_stride);
+      return;
+    }
 #pragma unroll
     for (int i = 0; i < decltype(rows_tag)::value; ++i) {
-      int t = t0 + i;
-      t = t < n ? t : n - 1;  // rows past the end re-read the last row and are not stored
-      cw[i].load(in_codes + (size_t)t * gi.row_bytes);
+      int k = a0 + i;
+      k = k <= last ? k : last < 0 ? 0 : last;
+      cw[i].load(in_codes + (size_t)(uint32_t)k * in_stride);
     }
   };
-  // rows t0 .. t0 + rows - 1, held in cw[first ..]
-  auto run_batch = [&](int t0, auto first_tag, auto rows_tag, auto fix_tag, auto&& param_of) {
+  // accesses a0 .. a0 + rows - 1, held in cw[first ..]
+  auto run_batch = [&](int a0, auto first_tag, auto rows_tag, auto fix_tag, size_t out_stride, auto&& param_of) {
     constexpr bool FIX = decltype(fix_tag)::value;
     constexpr int kFirst = decltype(first_tag)::value;
 #pragma unroll
     for (int i = 0; i < decltype(rows_tag)::value; ++i) {
-      if (t0 + i < n) {  // wave-uniform
+      if (a0 + i < count) {  // wave-uniform
         auto param = param_of(i);  // may shuffle across lanes: taken with the whole wave enabled
-        if (active) transcode_row<DT, BI, BO, FIX>(out_codes + (size_t)(t0 + i) * go.row_bytes, cw[kFirst + i], param);
+        if (a0 + i <= last) transcode_row<DT, BI, BO, FIX>(out_codes + (size_t)(uint32_t)(a0 + i) * out_stride, cw[kFirst + i], param);
       }
-      __builtin_amdgcn_sched_barrier(0);  // one row at a time: keeps the temporaries of different rows apart
+      __builtin_amdgcn_sched_barrier(0);  // one access at a time: keeps the temporaries of different ones apart
     }
   };
   using Zero = std::integral_constant<int, 0>;
@@ -504,29 +574,55 @@ __device__ __forceinline__ void transcode_block(const TranscodeParams& a, const 
 
   // The caller guarantees kvh_blob_size(l, n_tokens, c, level_in) readable bytes at the source,
   // so the loads issued before the header verdict stay inside the buffer whatever it says.
-  if (t_first < n) {
-    if (is_v) load_batch(t_first, RowsV{}); else load_batch(t_first, RowsK{});
+  // V metadata: lane l prepares the l-th of the 64 slots of a batch of 8 accesses.  On the table routes the words are
+  // requested with the codes, and by every lane (lanes without a slot read the wave's first), so that the wait for
+  // them, which takes in the codes, is on every path: a wait that some path skips is repeated before each access, where
+  // it also waits for the stores before (4 -> 2: 100 instead of 88 us on 32 x 8192 x 1024).
+  const uint32_t m_lane = ((uint32_t)lane / kTcSpanHeads * v_step + lane % kTcSpanHeads) * 4, m_batch = v_step * (kTcBatch * 4);
+  const size_t vfirst = ((size_t)t0 * heads + y0) * 4;  // metadata word of the wave's first slot
+  const uint8_t* in_vmeta = in_layer + gi.kmeta + gi.codes + vfirst;
+  auto owns = [&](int batch) { return (uint32_t)(batch * kWave + lane) < left; };
+  [[maybe_unused]] uint32_t vm[2] = {0u, 0u};
+  if (count > 0) {
+    if (is_v) {
+      load_batch(0, RowsV{}, in_stride_v);
+      if constexpr (kUseTable<BI, BO>) {
+#pragma unroll
+        for (int sb = 0; sb < 2; ++sb) vm[sb] = gload<uint32_t>(in_vmeta + (owns(sb) ? (size_t)sb * m_batch + m_lane : 0));
+      }
+    } else {
+      load_batch(0, RowsK{}, in_stride_k);
+    }
   }
 
+  // the two K channels this thread prepares
   uintx2 km = {0u, 0u};
-  const int pc = span * kTcSpanCh + (int)threadIdx.x * 2;  // the two K channels this thread prepares
-  const bool pact = !is_v && pc < c;
-  if (pact) km = gload<uintx2>(in_layer + ((size_t)g * c + pc) * 4);
+  bool pact = false;
+  size_t pmeta = 0;  // offset of their metadata words
+  if (!is_v) {
+    const uint32_t lc = threadIdx.x * 2;  // channel within the block's sets
+    uint32_t g, head0;
+    set_of(lc >> (7 + log_s), g, head0);
+    const uint32_t pc = head0 * kGroup + (lc & ((128u << log_s) - 1));
+    pact = (uint64_t)g * kGroup < n && (!SLOTS || pc < c);
+    pmeta = ((size_t)g * c + pc) * 4;
+    if (pact) km = gload<uintx2>(in_layer + pmeta);
+  }
 
   // block-uniform verdict: every thread reads the same header
-  if (!source_header_ok(hdr, DT, BI, a.l, n, c, kHeaderBytes + (size_t)a.l * gi.layer_bytes())) {
+  if (!source_header_ok(hdr, DT, BI, a.l, it.n_tokens, a.c, kHeaderBytes + (size_t)a.l * gi.layer_bytes())) {
     if (a.status != nullptr && threadIdx.x == 0) a.status[item_idx] = KVH_DEV_HEADER_MISMATCH;
     return;
   }
-  if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x < kHeaderBytes / 4) {
+  if (bx == 0 && lay_kv == 0 && threadIdx.x < kHeaderBytes / 4) {
     const uint64_t total = kHeaderBytes + (uint64_t)a.l * go.layer_bytes();
     uint32_t w = 0;
     switch (threadIdx.x) {
       case 0: w = kMagic; break;
       case 1: w = 1u | (uint32_t)DT << 16 | (uint32_t)BO << 24; break;
       case 2: w = (uint32_t)a.l; break;
-      case 3: w = (uint32_t)n; break;
-      case 4: w = (uint32_t)c; break;
+      case 3: w = n; break;
+      case 4: w = c; break;
       case 5: w = (uint32_t)kGroup | (uint32_t)kGroup << 16; break;
       case 6: w = (uint32_t)total; break;
       case 7: w = (uint32_t)(total >> 32); break;
@@ -550,17 +646,17 @@ __device__ __forceinline__ void transcode_block(const TranscodeParams& a, const 
       }
       if (pact) {
         uintx2 o = {om[0], om[1]};
-        gstore<uintx2>(out_layer + ((size_t)g * c + pc) * 4, o);
+        gstore<uintx2>(out_layer + pmeta, o);
       }
       __syncthreads();
-      if (t_first >= n) return;  // wave-uniform, after the barrier
+      if (count == 0) return;  // wave-uniform, after the barrier
       uint32_t tab[kTcLaneCh];
 #pragma unroll
-      for (int j = 0; j < kTcLaneCh; ++j) tab[j] = ktab[j * kWave + lane];
+      for (int j = 0; j < kTcLaneCh; ++j) tab[j] = ktab[j * kWave + par_lane];
 #pragma unroll
-      for (int i = 0; i < kRowsK; ++i) {  // kRowsK == kTcRows here: the wave's rows are all loaded
-        if (t_first + i < n && active)
-          lookup_row<BI, BO>(out_codes + (size_t)(t_first + i) * go.row_bytes, cw[i], [&tab](int j) { return tab[j]; });
+      for (int i = 0; i < kRowsK; ++i) {  // kRowsK == kTcRows here: the wave's accesses are all loaded
+        if (i <= last)
+          lookup_row<BI, BO>(out_codes + (size_t)i * out_stride_k, cw[i], [&tab](int j) { return tab[j]; });
         __builtin_amdgcn_sched_barrier(0);
       }
       return;
@@ -586,7 +682,7 @@ __device__ __forceinline__ void transcode_block(const TranscodeParams& a, const 
     }
     if (pact) {
       uintx2 o = {om[0], om[1]};
-      gstore<uintx2>(out_layer + ((size_t)g * c + pc) * 4, o);
+      gstore<uintx2>(out_layer + pmeta, o);
     }
     bool any_fix;
     if constexpr (BI == 8 && BO == 2) {
@@ -602,27 +698,27 @@ __device__ __forceinline__ void transcode_block(const TranscodeParams& a, const 
       all = (uint32_t)__builtin_amdgcn_readfirstlane((int)all);
       any_fix = (all & 1u) != 0;
       if ((all & 4u) == 0) {  // no hard group in the block: the polynomial route
-        if (t_first >= n) return;  // wave-uniform, after the barrier
+        if (count == 0) return;  // wave-uniform, after the barrier
         auto poly_rows = [&](auto standard_tag) {
           constexpr bool STANDARD = decltype(standard_tag)::value;
           Quad gq[kTcLaneCh];
 #pragma unroll
           for (int j = 0; j < kTcLaneCh; ++j) {
-            gq[j].a = STANDARD ? 0.0f : kquad[j * kWave + lane];
-            gq[j].b = STANDARD ? 0.0f : kquad[(kTcLaneCh + j) * kWave + lane];
-            gq[j].c = STANDARD ? 0.0f : kquad[(2 * kTcLaneCh + j) * kWave + lane];
+            gq[j].a = STANDARD ? 0.0f : kquad[j * kWave + par_lane];
+            gq[j].b = STANDARD ? 0.0f : kquad[(kTcLaneCh + j) * kWave + par_lane];
+            gq[j].c = STANDARD ? 0.0f : kquad[(2 * kTcLaneCh + j) * kWave + par_lane];
           }
 #pragma unroll 1
-          for (int t0 = t_first;;) {
+          for (int a0 = 0;;) {
 #pragma unroll
             for (int i = 0; i < kRowsK; ++i) {
-              if (t0 + i < n && active)
-                poly_row82<STANDARD>(out_codes + (size_t)(t0 + i) * go.row_bytes, cw[i], [&gq](int j) -> const Quad& { return gq[j]; });
+              if (a0 + i <= last)
+                poly_row82<STANDARD>(out_codes + (size_t)(uint32_t)(a0 + i) * out_stride_k, cw[i], [&gq](int j) -> const Quad& { return gq[j]; });
               __builtin_amdgcn_sched_barrier(0);
             }
-            t0 += kRowsK;
-            if (t0 >= t_first + kTcRows || t0 >= n) break;
-            load_batch(t0, RowsK{});
+            a0 += kRowsK;
+            if (a0 >= kTcRows || a0 >= count) break;
+            load_batch(a0, RowsK{}, in_stride_k);
           }
         };
         if ((all & 2u) == 0) poly_rows(Yes{}); else poly_rows(No{});
@@ -631,7 +727,7 @@ __device__ __forceinline__ void transcode_block(const TranscodeParams& a, const 
     } else {
       any_fix = __syncthreads_or(fix);
     }
-    if (t_first >= n) return;  // wave-uniform, after the barrier
+    if (count == 0) return;  // wave-uniform, after the barrier
     // The common path never touches `top`; reading it only where the rule is needed keeps that path's
     // register count down.
     auto k_rows = [&](auto fix_tag) {
@@ -639,7 +735,7 @@ __device__ __forceinline__ void transcode_block(const TranscodeParams& a, const 
       TcParams p[kTcLaneCh];
 #pragma unroll
       for (int j = 0; j < kTcLaneCh; ++j) {
-        const TcParams& s = kpar[j * kWave + lane];
+        const TcParams& s = kpar[j * kWave + par_lane];
         p[j].mn = s.mn;
         p[j].scale = s.scale;
         p[j].inv = s.inv;
@@ -647,64 +743,49 @@ __device__ __forceinline__ void transcode_block(const TranscodeParams& a, const 
       }
       auto param_of = [&](int) { return [&p](int j) -> const TcParams& { return p[j]; }; };
 #pragma unroll 1
-      for (int t0 = t_first;;) {
-        run_batch(t0, Zero{}, RowsK{}, fix_tag, param_of);
-        t0 += kRowsK;
-        if (t0 >= t_first + kTcRows || t0 >= n) break;
-        load_batch(t0, RowsK{});
+      for (int a0 = 0;;) {
+        run_batch(a0, Zero{}, RowsK{}, fix_tag, out_stride_k, param_of);
+        a0 += kRowsK;
+        if (a0 >= kTcRows || a0 >= count) break;
+        load_batch(a0, RowsK{}, in_stride_k);
       }
     };
     if (any_fix) k_rows(Yes{}); else k_rows(No{});
   } else {
-    if (t_first >= n) return;  // wave-uniform; V waves never meet at a barrier
-    const uint8_t* in_vmeta = in_layer + gi.kmeta + gi.codes;
-    uint8_t* out_vmeta = out_layer + go.kmeta + go.codes;
+    if (count == 0) return;  // wave-uniform; V waves never meet at a barrier
+    uint8_t* out_vmeta = out_layer + go.kmeta + go.codes + vfirst;
     if constexpr (kUseTable<BI, BO>) {
-      // the wave's 16 rows are loaded; their groups are prepared 8 rows (= 64 groups, one per lane) at a time
-      uint32_t vm[2] = {0u, 0u};
-      bool own[2];
-#pragma unroll
-      for (int sb = 0; sb < 2; ++sb) {
-        const int t = t_first + sb * kTcBatch + lane / kTcSpanHeads;
-        const int head = span * kTcSpanHeads + lane % kTcSpanHeads;
-        own[sb] = t < n && head < heads;
-        if (own[sb]) vm[sb] = gload<uint32_t>(in_vmeta + ((size_t)t * heads + head) * 4);
-      }
+      // the wave's 16 accesses are loaded; their groups are prepared 8 accesses (= 64 groups, one per lane) at a time
+      asm volatile("" : "+v"(vm[0]), "+v"(vm[1]));  // both words, and with them all codes, have arrived from here on
       auto eight_rows = [&](auto sb_tag) {
         constexpr int sb = decltype(sb_tag)::value;
-        const int t0 = t_first + sb * kTcBatch;
-        uint32_t mine = 0;
-        if (own[sb]) {
-          const int t = t0 + lane / kTcSpanHeads;
-          const int head = span * kTcSpanHeads + lane % kTcSpanHeads;
-          uint32_t om;
-          mine = code_table<DT, BI, BO>(vm[sb], om);
-          gstore<uint32_t>(out_vmeta + ((size_t)t * heads + head) * 4, om);
-        }
+        constexpr int a0 = sb * kTcBatch;
+        uint32_t om;
+        const uint32_t mine = code_table<DT, BI, BO>(vm[sb], om);
+        if (owns(sb)) gstore<uint32_t>(out_vmeta + (size_t)sb * m_batch + m_lane, om);
 #pragma unroll
         for (int i = 0; i < kTcBatch; ++i) {
-          if (t0 + i < n) {  // wave-uniform; the shuffle is taken with the whole wave enabled
-            const uint32_t tab = __shfl(mine, i * kTcSpanHeads + lane / (kGroup / kTcLaneCh));
-            if (active)
-              lookup_row<BI, BO>(out_codes + (size_t)(t0 + i) * go.row_bytes, cw[sb * kTcBatch + i], [tab](int) { return tab; });
+          if (a0 + i < count) {  // wave-uniform; the shuffle is taken with the whole wave enabled
+            const uint32_t tab = __shfl(mine, i * kTcSpanHeads + (int)slot);
+            if (a0 + i <= last)
+              lookup_row<BI, BO>(out_codes + (size_t)(a0 + i) * out_stride_v, cw[a0 + i], [tab](int) { return tab; });
           }
           __builtin_amdgcn_sched_barrier(0);
         }
       };
       eight_rows(std::integral_constant<int, 0>{});
-      if (t_first + kTcBatch < n) eight_rows(std::integral_constant<int, 1>{});
+      if (kTcBatch < count) eight_rows(std::integral_constant<int, 1>{});
     } else {
 #pragma unroll 1
-      for (int t0 = t_first;;) {  // kRowsV rows from t0 on are loaded
+      for (int a0 = 0;;) {  // kRowsV accesses from a0 on are loaded
         auto eight_rows = [&](auto first_tag) {
-          const int tb = t0 + decltype(first_tag)::value;
-          // lane -> the group (row tb + lane / 8, head lane % 8 of this span)
-          const int t = tb + lane / kTcSpanHeads;
-          const int head = span * kTcSpanHeads + lane % kTcSpanHeads;
+          const int tb = a0 + decltype(first_tag)::value;
+          const int batch = tb / kTcBatch;
+          const bool own = owns(batch);
           TcParams mine = {0.0f, 0.0f, 0.0f, 0.0f};
           bool fix = false;
-          if (t < n && head < heads) {
-            const size_t off = ((size_t)t * heads + head) * 4;
+          if (own) {
+            const size_t off = (size_t)(uint32_t)batch * m_batch + m_lane;
             uint32_t om;
             mine = tc_params<DT, BI, BO>(gload<uint32_t>(in_vmeta + off), om, fix);
             gstore<uint32_t>(out_vmeta + off, om);
@@ -713,20 +794,20 @@ __device__ __forceinline__ void transcode_block(const TranscodeParams& a, const 
           if constexpr (BI == 8 && BO == 2) {
             Quad gq;
             uint32_t cls = classify82<DT>(mine, gq);
-            if (!(t < n && head < heads)) cls = kStandard;  // a lane without a group has no say
+            if (!own) cls = kStandard;  // a lane without a group has no say
             if (__builtin_amdgcn_ballot_w64(cls == kHard) == 0) {
               const bool all_standard = __builtin_amdgcn_ballot_w64(cls != kStandard) == 0;
               constexpr int kFirst = decltype(first_tag)::value;
 #pragma unroll
               for (int i = 0; i < kTcBatch; ++i) {
-                if (tb + i < n) {  // wave-uniform; the shuffles are taken with the whole wave enabled
-                  const int owner = i * kTcSpanHeads + lane / (kGroup / kTcLaneCh);
-                  uint8_t* out_row = out_codes + (size_t)(tb + i) * go.row_bytes;
+                if (tb + i < count) {  // wave-uniform; the shuffles are taken with the whole wave enabled
+                  const int owner = i * kTcSpanHeads + (int)slot;
+                  uint8_t* out_row = out_codes + (size_t)(uint32_t)(tb + i) * out_stride_v;
                   if (all_standard) {
-                    if (active) poly_row82<true>(out_row, cw[kFirst + i], [&gq](int) -> const Quad& { return gq; });
+                    if (tb + i <= last) poly_row82<true>(out_row, cw[kFirst + i], [&gq](int) -> const Quad& { return gq; });
                   } else {
                     const Quad gr = {__shfl(gq.a, owner), __shfl(gq.b, owner), __shfl(gq.c, owner)};
-                    if (active) poly_row82<false>(out_row, cw[kFirst + i], [&gr](int) -> const Quad& { return gr; });
+                    if (tb + i <= last) poly_row82<false>(out_row, cw[kFirst + i], [&gr](int) -> const Quad& { return gr; });
                   }
                 }
                 __builtin_amdgcn_sched_barrier(0);
@@ -735,7 +816,7 @@ __device__ __forceinline__ void transcode_block(const TranscodeParams& a, const 
             }
           }
           auto param_of = [&](int i) {
-            const int owner = i * kTcSpanHeads + lane / (kGroup / kTcLaneCh);
+            const int owner = i * kTcSpanHeads + (int)slot;
             TcParams p;
             p.mn = __shfl(mine.mn, owner);
             p.scale = __shfl(mine.scale, owner);
@@ -743,28 +824,28 @@ __device__ __forceinline__ void transcode_block(const TranscodeParams& a, const 
             p.top = __shfl(mine.top, owner);
             return [p](int) -> const TcParams& { return p; };
           };
-          if (any_fix) run_batch(tb, first_tag, Batch{}, Yes{}, param_of); else run_batch(tb, first_tag, Batch{}, No{}, param_of);
+          if (any_fix) run_batch(tb, first_tag, Batch{}, Yes{}, out_stride_v, param_of); else run_batch(tb, first_tag, Batch{}, No{}, out_stride_v, param_of);
         };
         eight_rows(Zero{});
         if constexpr (kRowsV > kTcBatch) {
-          if (t0 + kTcBatch < n) eight_rows(Eight{});
+          if (a0 + kTcBatch < count) eight_rows(Eight{});
         }
-        t0 += kRowsV;
-        if (t0 >= t_first + kTcRows || t0 >= n) break;
-        load_batch(t0, RowsV{});
+        a0 += kRowsV;
+        if (a0 >= kTcRows || a0 >= count) break;
+        load_batch(a0, RowsV{}, in_stride_v);
       }
     }
     // zero the padding that rounds the vmeta section up to 16 bytes
-    if (span == 0 && threadIdx.x == 0 && (g + 1) * kGroup >= n) {
-      for (size_t o = (size_t)n * heads * 4; o < go.vmeta; o += 4) gstore<uint32_t>(out_vmeta + o, 0u);
+    if (SLOTS ? left64 <= kTcSlots && lane == 0 : y0 == 0 && threadIdx.x == 0 && t0 + kGroup >= n) {
+      for (size_t o = (size_t)n * heads * 4; o < go.vmeta; o += 4) gstore<uint32_t>(out_vmeta - vfirst + o, 0u);
     }
   }
 }
 
 }  // namespace
 
-// grid = (token-groups x spans, 2 * l, items)
-template <int DT>
+// grid = (blocks of a plane, 2 * l, items)
+template <int DT, bool SLOTS>
 __global__ __launch_bounds__(kTcThreads) KVH_TC_OCC void transcode_kernel(TranscodeParams a) {
   __shared__ TcParams kpar[kTcLaneCh * kWave];  // 16 KiB, [slot][lane]
   __shared__ float kquad[3 * kTcLaneCh * kWave];  // 12 KiB, [coefficient][slot][lane]: the 8 -> 2 polynomials
@@ -787,12 +868,8 @@ __global__ __launch_bounds__(kTcThreads) KVH_TC_OCC void transcode_kernel(Transc
   it.n_tokens = uniform(it.n_tokens);
   it.level_in = uniform(it.level_in);
   it.level_out = uniform(it.level_out);
-  const int nspans = (a.c + kTcSpanCh - 1) / kTcSpanCh;
-  const int g = blockIdx.x / nspans;
-  const int span = blockIdx.x - g * nspans;
-  if (it.n_tokens < 1 || g * kGroup >= it.n_tokens) return;  // block-uniform
-  const int lam = blockIdx.y >> 1;
-  const bool is_v = blockIdx.y & 1;
+  const int bx = blockIdx.x, lay_kv = blockIdx.y;
+  if (it.n_tokens < 1) return;  // block-uniform
   const int bi = level_bits(it.level_in), bo = level_bits(it.level_out);
   // refused: a level out of range, the raw level (no codes to transcode), more tokens than the grid covers
   if (bi < 0 || bo < 0 || bi > 8 || bo > 8 || it.n_tokens > a.max_tokens) {
@@ -800,7 +877,7 @@ __global__ __launch_bounds__(kTcThreads) KVH_TC_OCC void transcode_kernel(Transc
     return;
   }
 #define KVH_TC_CASE(BI, BO) \
-  case BI * 16 + BO: transcode_block<DT, BI, BO>(a, it, blockIdx.z, lam, is_v, g, span, kpar, kquad, kflags); break;
+  case BI * 16 + BO: transcode_block<DT, BI, BO, SLOTS>(a, it, blockIdx.z, lay_kv, bx, kpar, kquad, kflags); break;
   switch (bi * 16 + bo) {
     KVH_TC_CASE(8, 8) KVH_TC_CASE(8, 4) KVH_TC_CASE(8, 2)
     KVH_TC_CASE(4, 8) KVH_TC_CASE(4, 4) KVH_TC_CASE(4, 2)
@@ -811,15 +888,27 @@ __global__ __launch_bounds__(kTcThreads) KVH_TC_OCC void transcode_kernel(Transc
 }
 
 int launch_transcode(const TranscodeParams& a, int dt, int n_items, int max_tokens, hipStream_t stream) {
-  const int nspans = (a.c + kTcSpanCh - 1) / kTcSpanCh;
-  const int groups = (max_tokens + kGroup - 1) / kGroup;
-  dim3 grid((unsigned)(groups * nspans), (unsigned)(2 * a.l), (unsigned)n_items);
+  // 8 >> log_s sets of 2^log_s heads x a token-group per K block; the V units, which are not rounded up per head, are
+  // never more numerous
+  const int heads = a.c / kGroup;
+  const bool slots = heads % kTcSpanHeads != 0;
+  // Heads of a K set: the largest power of two that divides the row, or 8 with idle lanes where that is the faster form.
+  // 32 layers x 2,048 to 12,000 tokens, against the spans with idle lanes that all of these took: 1 to 4 heads 1.3 to 4.6
+  // times faster, 9 and 10 heads 1.2 to 1.4, 12 heads 1.15 to 1.25, 6 and 11 heads 0.9 to 1.15; 5, 7 and from 13 heads on
+  // single heads are as slow as 0.67 (they write 32- or 64-byte pieces), idle lanes 0.93 to 1.09 (V has none).
+  const bool fit = heads <= 4 || heads == 6 || (heads >= 9 && heads <= 12);
+  const int log_s = slots && fit ? __builtin_ctz((unsigned)heads) : 3;
+  const int64_t groups = ((int64_t)max_tokens + kGroup - 1) / kGroup;
+  const int64_t gx = (groups * ((heads + (1 << log_s) - 1) >> log_s) + (8 >> log_s) - 1) / (8 >> log_s);
   TranscodeParams b = a;
   b.max_tokens = max_tokens;
-  if (dt == KVH_F16)
-    launch_kernel(transcode_kernel<KVH_F16>, grid, dim3(kTcThreads), 0u, stream, b);
-  else
-    launch_kernel(transcode_kernel<KVH_BF16>, grid, dim3(kTcThreads), 0u, stream, b);
+  b.k_log_s = log_s;
+  b.by_heads = Divisor((uint32_t)heads);
+  b.by_sets = Divisor((uint32_t)((heads + (1 << log_s) - 1) >> log_s));
+  const dim3 grid((unsigned)gx, (unsigned)(2 * a.l), (unsigned)n_items);
+  auto kernel = dt == KVH_F16 ? (slots ? transcode_kernel<KVH_F16, true> : transcode_kernel<KVH_F16, false>)
+                              : (slots ? transcode_kernel<KVH_BF16, true> : transcode_kernel<KVH_BF16, false>);
+  launch_kernel(kernel, grid, dim3(kTcThreads), 0u, stream, b);
   KVH_HIP_CHECK_LAUNCH();
   return KVH_OK;
 }
