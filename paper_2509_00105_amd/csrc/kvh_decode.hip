@@ -527,17 +527,17 @@ __device__ __forceinline__ void decode_slots(const DecodeParams& a, const kvh_it
   if (by_head) {
     const uint32_t log_s = (uint32_t)__builtin_ctz(heads);  // at most 2 here
     const uint32_t sets = heads >> log_s;
-    const uint32_t rb = unit / sets;
+    const uint32_t rb = a.by_sets.quotient(unit);
     per_row = 1u << log_s;
     t0 = rb * (kWave >> log_s);
     y0 = 0;
     h0 = (unit - rb * sets) << log_s;
   } else {
-    const uint32_t q = unit / heads;
-    const uint32_t x = (unit - q * heads) * kWave;
+    const uint32_t q = a.by_heads.quotient(unit);
+    const uint32_t x = (unit - q * heads) * kWave, xq = a.by_heads.quotient(x);
     per_row = heads;
-    t0 = q * kWave + x / heads;
-    y0 = x % heads;
+    t0 = q * kWave + xq;
+    y0 = x - xq * heads;
     h0 = 0;
   }
   per_row = (uint32_t)uniform((int32_t)per_row);
@@ -553,7 +553,7 @@ __device__ __forceinline__ void decode_slots(const DecodeParams& a, const kvh_it
 
   // the slot this lane owns
   const uint32_t y = y0 + sub * 4 + quad;
-  const uint32_t own_row = y / per_row;
+  const uint32_t own_row = by_head ? y >> __builtin_ctz(per_row) : a.by_heads.quotient(y);
   const uint32_t t = t0 + own_row, head = h0 + (y - own_row * per_row);
   const bool valid = t < n;
   RowRef ref = {0, 0};
@@ -646,7 +646,7 @@ __device__ __forceinline__ void decode_slots(const DecodeParams& a, const kvh_it
 
 // grid = (blocks of a plane x planes of a group, items, plane groups).  Rows of whole spans: a block is 64 rows of a span
 // (span fastest), wave w takes rows 8 w .. 8 w + 7; otherwise (SLOTS) a block is 8 consecutive units of slots.
-// Waves per SIMD the register allocation is held to (0 = compiler's choice).  The kernel needs about 100 registers,
+// Waves per SIMD the register allocation is held to.  The kernel needs about 100 registers,
 // which would let two blocks (16 waves) share a CU; the write stream does better with fewer waves in flight.  Measured
 // on the 8K-token shape with plain non-temporal stores, 8 / 4 / 2 bits, % of HBM peak in the benchmark's rotation:
 // 16 waves per CU 68.4 / 71.6 / 71.3, this setting (allocation raised to three waves per SIMD, one block per CU)
@@ -656,13 +656,10 @@ __device__ __forceinline__ void decode_slots(const DecodeParams& a, const kvh_it
 #ifndef KVH_DEC_WPE
 #define KVH_DEC_WPE 3
 #endif
-#if KVH_DEC_WPE
-#define KVH_DEC_OCC __attribute__((amdgpu_waves_per_eu(KVH_DEC_WPE, KVH_DEC_WPE)))
-#else
-#define KVH_DEC_OCC
-#endif
-template <int DT, bool SLOTS>
-__global__ __launch_bounds__(kDecThreads) KVH_DEC_OCC void decode_kernel(DecodeParams a) {
+#define KVH_DEC_OCC(SHORT) __attribute__((amdgpu_waves_per_eu((SHORT) ? 4 : KVH_DEC_WPE, (SHORT) ? 4 : KVH_DEC_WPE)))
+// SHORT: two blocks per CU, for launches that write little (see the launcher).
+template <int DT, bool SLOTS, bool SHORT>
+__global__ __launch_bounds__(kDecThreads) KVH_DEC_OCC(SHORT) void decode_kernel(DecodeParams a) {
   const int item_idx = blockIdx.y;
   // Block order: the (layer, K|V) planes are taken in groups of `plane_group` (grid z), a group through all items (grid
   // y) before the next.  Within an item and group (grid x): `row_tile` consecutive blocks of a plane, then the same
@@ -674,14 +671,19 @@ __global__ __launch_bounds__(kDecThreads) KVH_DEC_OCC void decode_kernel(DecodeP
     const int per_plane = a.plane_blocks;
     const int planes = 2 * a.l - first_plane < a.plane_group ? 2 * a.l - first_plane : a.plane_group;
     if (lin >= per_plane * planes) return;  // the last group may be smaller
-    const int rt = a.row_tile < per_plane ? a.row_tile : per_plane;
-    const int full = per_plane / rt;
-    const int tile = lin / (rt * planes);
-    const int first = (tile < full ? tile : full) * rt;          // first block (within a plane) of this tile
-    const int size = tile < full ? rt : per_plane - full * rt;   // blocks per plane in it
-    const int j = lin - first * planes;
-    lay_kv = first_plane + j / size;
-    bx = first + j % size;
+    if (a.row_tile == 1) {
+      bx = planes == a.plane_group ? (int)a.by_group.quotient((uint32_t)lin) : lin / planes;
+      lay_kv = first_plane + (lin - bx * planes);
+    } else {
+      const int rt = a.row_tile < per_plane ? a.row_tile : per_plane;
+      const int full = per_plane / rt;
+      const int tile = lin / (rt * planes);
+      const int first = (tile < full ? tile : full) * rt;          // first block (within a plane) of this tile
+      const int size = tile < full ? rt : per_plane - full * rt;   // blocks per plane in it
+      const int j = lin - first * planes;
+      lay_kv = first_plane + j / size;
+      bx = first + j % size;
+    }
   }
   kvh_item it;
   DropInfo drop = {kNoSplit, 0, 0u, 0u, 0u};  // ordinary batch items are never token-dropped
@@ -802,25 +804,40 @@ int launch_decode(const DecodeParams& a, int dt, int n_items, int max_tokens, hi
   // 2 are a point below tiles of 4, tiles of 8 two to four, tiles of 16 are the hole again.
   const bool near = (int64_t)a.l * a.layer_stride * 2 <= ((int64_t)1 << 29);
   b.row_tile = near ? 1 : max_tokens <= 8192 ? 4 : 0x7fffffff;
-  // Plane group.  Rows of whole spans: all planes, i.e. item by item.  Slots: groups of at most 8 planes of one size, one
-  // block per plane and turn, through all items before the next group.  The dispatcher deals consecutive blocks to the 8
-  // XCDs in turn, so that with 8 planes each XCD writes one plane and keeps to its address translations.  Against item by
-  // item in the row tiles above, 40 shapes (128 to 2560 channels, 2,048 to 24,000 tokens, chunks of 256 tokens to one item):
-  // 8 % faster on average, between -1 (512 channels) and +19 %; groups of 4 +7.6 %, but better by 1 to 3 % for 512
-  // channels, plane by plane +4.6 %.  With 10 planes two groups of 5 take 55 us where 8 and 2 take 61.
+  // Plane group.  Groups of at most 8 planes of one size, one block per plane and turn, through all items before the next
+  // group; or all planes, i.e. item by item in the row tiles above.  The dispatcher deals consecutive blocks to the 8 XCDs
+  // in turn, so that with 8 planes each XCD writes one plane and keeps to its address translations.
+  //   Slots always take groups: against item by item, 40 shapes (128 to 2560 channels, 2,048 to 24,000 tokens, chunks of 256
+  //   tokens to one item) 8 % faster on average, between -1 (512 channels) and +19 %; groups of 4 +7.6 %, but better by 1
+  //   to 3 % for 512 channels, plane by plane +4.6 %.  With 10 planes two groups of 5 take 55 us where 8 and 2 take 61.
+  //   Whole spans take groups for launches of up to 896 MiB of 16-bit rows.  32 layers x 1024 channels in 256-token items,
+  //   five mixes of levels and destinations: 512 tokens +2 to +10 %, 1,024 +2 to +7, 2,048 +4 to +12, 4,096 +1 to +5,
+  //   6,144 (768 MiB) 0 to +4, 8,192 (1 GiB) -8 to -2.
+  // Launches of whole spans of up to 256 MiB also get two blocks per CU: what they write is gone before the write stream
+  // has settled, and more waves in flight hide the start.  Both together: 64 MiB +11 to +21 %, 128 MiB +14 to +17, 256 MiB
+  // +4 to +23; two blocks alone 512 MiB -4 to 0.
+  const int64_t row_bytes_all = (int64_t)4 * a.l * a.c * max_tokens * n_items;
+  const bool groups_first = slots || row_bytes_all <= ((int64_t)896 << 20);
+  const bool short_launch = !slots && row_bytes_all <= ((int64_t)256 << 20);
   b.plane_blocks = (int)gx;
   b.plane_group = 2 * a.l;
-  if (slots) {
+  if (groups_first) {
     b.row_tile = 1;
-    const int most = heads == 4 ? 4 : 8;
+    const int most = slots && heads == 4 ? 4 : 8;
     const int groups = (2 * a.l + most - 1) / most;
     b.plane_group = (2 * a.l + groups - 1) / groups;
   }
   // the x dimension counts threads in 32 bits
   while (b.plane_group > 1 && (int64_t)gx * b.plane_group * kDecThreads > 0xffffffffLL) b.plane_group = (b.plane_group + 1) / 2;
   const dim3 grid(gx * (unsigned)b.plane_group, (unsigned)n_items, (unsigned)((2 * a.l + b.plane_group - 1) / b.plane_group));
-  auto kernel = dt == KVH_F16 ? (slots ? decode_kernel<KVH_F16, true> : decode_kernel<KVH_F16, false>)
-                              : (slots ? decode_kernel<KVH_BF16, true> : decode_kernel<KVH_BF16, false>);
+  b.by_group = Divisor((uint32_t)b.plane_group);
+  b.by_heads = Divisor((uint32_t)heads);
+  b.by_sets = Divisor((uint32_t)(heads >> __builtin_ctz((unsigned)heads)));
+  auto pick = [&](auto dt_tag) {
+    constexpr int D = decltype(dt_tag)::value;
+    return slots ? decode_kernel<D, true, false> : short_launch ? decode_kernel<D, false, true> : decode_kernel<D, false, false>;
+  };
+  auto kernel = dt == KVH_F16 ? pick(std::integral_constant<int, KVH_F16>{}) : pick(std::integral_constant<int, KVH_BF16>{});
   launch_kernel(kernel, grid, dim3(kDecThreads), 0u, stream, b);
   KVH_HIP_CHECK_LAUNCH();
   return KVH_OK;

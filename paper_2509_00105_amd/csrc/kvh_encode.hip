@@ -518,7 +518,7 @@ __device__ __forceinline__ void encode_k_slots(const EncodeParams& a, const kvh_
   const uint32_t s_mask = (1u << log_s) - 1, set_waves = 2u << log_s, step = 4u >> log_s;  // rows per access
   const uint32_t sets = heads >> log_s;                                                    // per token-group
   const uint32_t set = (uint32_t)bx * step + wave / set_waves;
-  const uint32_t g = set / sets;
+  const uint32_t g = a.by_sets.quotient(set);
   const uint32_t head = ((set - g * sets) << log_s) + (quad & s_mask);
   const uint32_t ch0 = head * kGroup + sub * kLaneCh;
   const uint32_t part = wave & (set_waves - 1);
@@ -594,8 +594,8 @@ __device__ __forceinline__ void encode_row_slots(const EncodeParams& a, const kv
   const uint32_t n = (uint32_t)it.n_tokens, heads = (uint32_t)a.c / kGroup;
   // slot k of the unit is row t0 + (y0 + k) / heads, head (y0 + k) % heads
   const uint32_t unit = (uint32_t)bx * kEncWaves + wave;
-  const uint32_t q = unit / heads, x0 = (unit - q * heads) * kWave;
-  const uint32_t t0 = (uint32_t)uniform((int32_t)(q * kWave + x0 / heads)), y0 = (uint32_t)uniform((int32_t)(x0 % heads));
+  const uint32_t q = a.by_heads.quotient(unit), x0 = (unit - q * heads) * kWave, xq = a.by_heads.quotient(x0);
+  const uint32_t t0 = q * kWave + xq, y0 = x0 - xq * heads;
   if (t0 >= n) return;  // wave-uniform
   const uint64_t left64 = (uint64_t)(n - t0) * heads - y0;  // slots from the unit's first to the end of the section
   const uint32_t left = left64 < kWave ? (uint32_t)left64 : (uint32_t)kWave;
@@ -605,7 +605,8 @@ __device__ __forceinline__ void encode_row_slots(const EncodeParams& a, const kv
   const uint8_t* src = reinterpret_cast<const uint8_t*>((is_v ? a.v : a.k) + (int64_t)lam * a.layer_stride) + sub * (kLaneCh * 2u);
   const uint32_t k_own = sub * 4 + quad;
   const uint32_t y = y0 + (k_own < left ? k_own : left - 1);
-  const uint32_t t_own = t0 + y / heads, head_own = y % heads;
+  const uint32_t yq = a.by_heads.quotient(y);
+  const uint32_t t_own = t0 + yq, head_own = y - yq * heads;
   const int64_t off = (it.src_token0 + (int64_t)t_own + ((int)t_own >= split ? jump : 0)) * a.token_stride * 2 + head_own * (kGroup * 2u);
   const int off_lo = (int)(uint32_t)(uint64_t)off, off_hi = (int)(off >> 32);
   uintx4 d[kEncRows];
@@ -720,10 +721,10 @@ __global__ __launch_bounds__(kEncThreads) __attribute__((amdgpu_waves_per_eu(4, 
     const int lin = blockIdx.x, first = (int)blockIdx.y * a.plane_group;
     const int size = 2 * a.l - first < a.plane_group ? 2 * a.l - first : a.plane_group;
     if (lin >= a.plane_blocks * size) return;
-    bx = lin / size;
+    bx = size == a.plane_group ? (int)a.by_group.quotient((uint32_t)lin) : lin / size;
     lay_kv = first + (lin - bx * size);
   }
-  const int tile = bx / nstrips;
+  const int tile = (int)a.by_strips.quotient((uint32_t)bx);
   const int strip = bx - tile * nstrips;
   const int bits = level_bits(it.level);
   // block-uniform; an item with more tokens than the grid covers is skipped as a whole (no header either), so
@@ -768,7 +769,7 @@ __global__ __launch_bounds__(kEncThreads) __attribute__((amdgpu_waves_per_eu(4, 
     if (a.k_slots) {
       // block-uniform: the first set of the block is past the end
       const int heads = a.c / kGroup, log_s = (heads & 1) ? 0 : 1;
-      if ((int64_t)(bx * (4 >> log_s) / (heads >> log_s)) * kGroup >= it.n_tokens) return;
+      if ((int64_t)a.by_sets.quotient((uint32_t)bx * (4 >> log_s)) * kGroup >= it.n_tokens) return;
       switch (bits) {
         case 8: encode_k_slots<DT, 8>(a, it, layer_base, geo, lam, bx, red, split, jump); break;
         case 4: encode_k_slots<DT, 4>(a, it, layer_base, geo, lam, bx, red, split, jump); break;
@@ -838,6 +839,10 @@ int launch_encode(const EncodeParams& a, int dt, int n_items, int max_tokens, hi
   if (b.plane_group > 2 * a.l) b.plane_group = 2 * a.l;
   // the x dimension counts threads in 32 bits
   while (b.plane_group > 1 && gx * b.plane_group * kEncThreads > 0xffffffffLL) b.plane_group = (b.plane_group + 1) / 2;
+  b.by_group = Divisor((uint32_t)b.plane_group);
+  b.by_strips = Divisor((uint32_t)nstrips);
+  b.by_heads = Divisor((uint32_t)heads);
+  b.by_sets = Divisor((uint32_t)((heads & 1) ? heads : heads / 2));
   const unsigned n_groups = (unsigned)((2 * a.l + b.plane_group - 1) / b.plane_group);
   const dim3 grid((unsigned)(gx * b.plane_group), n_groups, (unsigned)n_items);
   auto kernel = dt == KVH_F16 ? (slots ? encode_kernel<KVH_F16, true> : encode_kernel<KVH_F16, false>)

@@ -94,3 +94,20 @@ def test_row_lengths_batch(kvh, heads):
         assert np.array_equal(blobs[offs[i]:offs[i + 1]], want), ("encode", i)
         wk, wv = oracle.decode(want, dt, l, n, c, lv)
         assert np.array_equal(got[0, :, t0:t0 + n], wk) and np.array_equal(got[1, :, t0:t0 + n], wv), ("decode", i)
+
+
+@pytest.mark.parametrize("l,n", [(9, 8191), (20, 15000)])
+def test_launch_sizes(kvh, l, n):
+    """Whole spans on both sides of the sizes at which the decoder changes its block order and occupancy (288 MiB and 1.1 GiB
+    of rows here; the other tests decode less than 256 MiB): every row equals what 640-token pieces of the entry give."""
+    c = 1024
+    kv = gen.make_kv_device(l, n, c, gen.BF16, seed=n)
+    for level in range(4):
+        out, ref = torch.zeros_like(kv), torch.zeros_like(kv)
+        kvh.decode(kvh.encode(kv[0], kv[1], level), level, n, out[0], out[1])
+        starts = list(range(0, n, 640))  # pieces of whole token-groups, so that their K statistics are the entry's
+        for t0 in starts:
+            m = min(640, n - t0)
+            kvh.decode(kvh.encode(kv[0][:, t0:t0 + m], kv[1][:, t0:t0 + m], level), level, m, ref[0], ref[1], dst_token0=t0)
+        torch.cuda.synchronize()
+        assert torch.equal(out.view(torch.int16), ref.view(torch.int16)), (l, n, level)
