@@ -139,9 +139,18 @@ def blob_size(l: int, n_tokens: int, c: int, level: int) -> int:
     return lib().kvh_blob_size(l, n_tokens, c, level)
 
 
+# The current stream as a raw pointer.  torch.cuda.current_stream() builds a Stream object for it, 2.7 us of the 10 a
+# call of a small chunk took on the host, more than the kernel; the raw query is 0.14 us (one chunk of 4 layers, decode:
+# 10.5 -> 7.6 us a call).
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
 def _stream_ptr(stream) -> int:
-    s = torch.cuda.current_stream() if stream is None else stream
-    return s.cuda_stream
+    if stream is not None:
+        return stream.cuda_stream
+    if _raw_stream is not None and torch.cuda.is_initialized():
+        return _raw_stream(torch.cuda.current_device())
+    return torch.cuda.current_stream().cuda_stream
 
 
 def _require_cuda(*tensors):
