@@ -671,7 +671,9 @@ __global__ __launch_bounds__(kDecThreads) KVH_DEC_OCC(SHORT) void decode_kernel(
     const int per_plane = a.plane_blocks;
     const int planes = 2 * a.l - first_plane < a.plane_group ? 2 * a.l - first_plane : a.plane_group;
     if (lin >= per_plane * planes) return;  // the last group may be smaller
-    if (a.row_tile == 1) {
+    // Slots always have tiles of 1.  Whole spans take the general form for them as well: with the short one the compiler
+    // allocates the row loops differently, and the 4-bit level loses 2 % (75.1 against 76.1 to 77.2 % of HBM peak in the benchmark).
+    if constexpr (SLOTS) {
       bx = planes == a.plane_group ? (int)a.by_group.quotient((uint32_t)lin) : lin / planes;
       lay_kv = first_plane + (lin - bx * planes);
     } else {
