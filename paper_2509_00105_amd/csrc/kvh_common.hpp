@@ -268,7 +268,7 @@ struct TranscodeParams {
   int32_t* status;           // nullable; indexed by item
   int l, c;
   int max_tokens;            // rows the grid covers per item: an item with more tokens is refused on the device
-  int k_log_s;               // K sets are 2^k_log_s heads (rows that are not whole 1024-channel spans)
+  int k_log_s;               // K sets are 2^k_log_s heads (3: a span)
   Divisor by_heads, by_sets; // heads of a row, K sets of a token-group
 };
 

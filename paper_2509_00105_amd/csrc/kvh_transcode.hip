@@ -20,14 +20,15 @@
 // are that map, built by running the arithmetic once per input code, and an element costs a
 // shift and a funnel shift.
 //
-// Rows that are not a multiple of 1024 channels (SLOTS) would leave lanes of the span idle, 56 of 64 with 128 channels.
-// An access then covers 8 (row, head) slots of 8 lanes each, 128 slots per wave: V slots are consecutive in memory; K
-// slots are sets of 1, 2 or 4 heads x a token-group, several sets to a block, so that a lane keeps its channels, or spans
-// with idle lanes where that is the faster form (see the launcher).  32 layers, 8 -> 4 bits, 2,048 tokens x 128 channels:
-// 30.4 -> 13.7 us, 16,384 x 256: 228 -> 80 us; 4 -> 2 bits, 12,000 x 128: 103 -> 22 us, 8,192 x 1280: 157 -> 119 us.
+// Rows that are not a multiple of 1024 channels leave lanes of the last span idle, 56 of 64 with 128 channels.  Where that
+// costs more than it saves (transcode_plan has the rule and its figures) an access covers 8 (row, head) slots of 8 lanes
+// each instead (SLOTS), 128 slots per wave: V slots are consecutive in memory; K slots are sets of 1, 2 or 4 heads x a
+// token-group, several sets to a block, so that a lane keeps its channels.  32 layers, 8 -> 4 bits, 2,048 tokens x 128
+// channels: 30.3 -> 13.2 us, 8,192 x 256: 115 -> 41 us; 4 -> 2 bits, 12,000 x 128: 101 -> 21 us, 8,192 x 1280: 157 -> 116 us.
 #include <type_traits>
 
 #include "kvh_common.hpp"
+#include "kvh_plan.hpp"
 
 namespace kvh {
 
@@ -450,7 +451,8 @@ __device__ __forceinline__ bool source_header_ok(const HeaderWords& h, int dt, i
   return fields && (plain || dropped);
 }
 
-// SLOTS: rows that are not a multiple of 1024 channels (see the head of the file).
+// SLOTS: the lanes are cut into (row, head) slots (see the head of the file); otherwise a span's lanes keep its channels
+// and those beyond the row idle.
 template <int DT, int BI, int BO, bool SLOTS>
 __device__ __forceinline__ void transcode_block(const TranscodeParams& a, const kvh_tc_item& it, int item_idx, int lay_kv,
                                                 int bx, TcParams* kpar, float* kquad, uint32_t* kflags) {
@@ -463,9 +465,10 @@ __device__ __forceinline__ void transcode_block(const TranscodeParams& a, const 
   const int lam = lay_kv >> 1;
   const bool is_v = lay_kv & 1;
 
-  // K: a set is 2^log_s heads x one token-group, shared by as many waves; a block holds 8 >> log_s sets
+  // K: a set is 2^log_s heads (a span's 8 without SLOTS) x one token-group, shared by as many waves; a block holds
+  // 8 >> log_s sets
   const uint32_t log_s = SLOTS ? (uint32_t)a.k_log_s : 3u;
-  const uint32_t sets = SLOTS ? (heads + (1u << log_s) - 1) >> log_s : heads >> 3;  // per token-group; the last may be smaller
+  const uint32_t sets = SLOTS ? heads >> log_s : (heads + 7) >> 3;  // per token-group
   const uint32_t first_set = (uint32_t)bx * (8u >> log_s);
   const uint32_t first_g = a.by_sets.quotient(first_set);
   if ((!SLOTS || !is_v) && (uint64_t)first_g * kGroup >= n) return;  // block-uniform
@@ -473,8 +476,8 @@ __device__ __forceinline__ void transcode_block(const TranscodeParams& a, const 
     g = SLOTS ? a.by_sets.quotient(first_set + s) : first_g;
     head0 = (first_set + s - g * sets) << log_s;
   };
-  // V: the wave's slots start at row t0, head y0.  With whole spans they are 16 rows x 8 heads, otherwise 128 in memory
-  // order; access i is `v_step` slots of the section on.
+  // V: the wave's slots start at row t0, head y0.  In spans they are 16 rows x 8 heads, with SLOTS 128 in memory order;
+  // access i is `v_step` slots of the section on.
   uint32_t t0 = 0, y0 = 0, left = 0;
   uint64_t left64 = 0;  // SLOTS: slots from the wave's first to the end of the section
   const uint32_t v_step = SLOTS ? (uint32_t)kTcSpanHeads : heads;
@@ -501,13 +504,13 @@ __device__ __forceinline__ void transcode_block(const TranscodeParams& a, const 
   uint8_t* out_layer = dst + kHeaderBytes + (size_t)lam * go.layer_bytes();
 
   // A lane's codes: access i is i strides on; accesses beyond `last` (-1: none) re-read it and are not stored.  `count`
-  // (wave-uniform) accesses have a slot to store.
+  // (wave-uniform) accesses have something to store.
   const uint8_t* in_codes;
   uint8_t* out_codes;
   const size_t in_stride_k = gi.row_bytes << (3 - log_s), out_stride_k = go.row_bytes << (3 - log_s);
   const size_t in_stride_v = (size_t)v_step * (kGroup * BI / 8), out_stride_v = (size_t)v_step * (kGroup * BO / 8);
   int last, count;
-  bool full = true;  // SLOTS, wave-uniform: every lane has all its accesses, or none
+  bool active = true;  // without SLOTS: the lane's channels exist
   uint32_t par_lane = 0;  // K: where the parameters of this lane's channels lie in LDS
   if (!is_v) {
     const uint32_t sib = wave >> log_s;
@@ -516,19 +519,18 @@ __device__ __forceinline__ void transcode_block(const TranscodeParams& a, const 
     const uint32_t t_wave = g * kGroup + (wave & ((1u << log_s) - 1)) * (kGroup >> log_s);
     const uint32_t t = t_wave + (slot >> log_s), t_in = t < n ? t : n - 1;
     const uint32_t head = head0 + (slot & ((1u << log_s) - 1));
-    const bool active = !SLOTS || head < heads;
+    if (!SLOTS) active = head < heads;
     const uint32_t ch = (active ? head : 0u) * kGroup + sub * kTcLaneCh;
     in_codes = in_layer + gi.kmeta + (size_t)t_in * gi.row_bytes + ch * BI / 8;
     out_codes = out_layer + go.kmeta + (size_t)t_in * go.row_bytes + ch * BO / 8;
-    full = t_wave + (kGroup >> log_s) <= n;
-    last = active && t < n ? (int)((n - 1 - t) >> (3 - log_s)) : -1;
+    last = t < n ? (int)((n - 1 - t) >> (3 - log_s)) : -1;
     count = t_wave < n ? (int)((n - 1 - t_wave) >> (3 - log_s)) + 1 : 0;
     par_lane = (sib << (3 + log_s)) + ((uint32_t)lane & ((8u << log_s) - 1));
   } else {
-    const size_t first = left == 0 ? 0 : (size_t)t0 * heads + y0 + (!SLOTS || slot < left ? slot : left - 1);
+    if (!SLOTS) active = y0 + slot < heads;
+    const size_t first = left == 0 ? 0 : (size_t)t0 * heads + y0 + (!SLOTS ? (active ? slot : 0) : slot < left ? slot : left - 1);
     in_codes = in_layer + gi.kmeta + gi.codes + gi.vmeta + first * (kGroup * BI / 8) + sub * (kTcLaneCh * BI / 8);
     out_codes = out_layer + go.kmeta + go.codes + go.vmeta + first * (kGroup * BO / 8) + sub * (kTcLaneCh * BO / 8);
-    full = left == kTcSlots;
     count = (int)((left + kTcSpanHeads - 1) / kTcSpanHeads);
     last = !SLOTS ? count - 1 : slot < left ? (int)((left - 1 - slot) / kTcSpanHeads) : -1;
   }
@@ -540,12 +542,8 @@ __device__ __forceinline__ void transcode_block(const TranscodeParams& a, const 
   constexpr int kRowsK = BI == 8 ? kTcBatch / 2 : kTcRows;
   constexpr int kRowsV = BI == 8 ? kTcBatch : kTcRows;
   InCodes<BI> cw[kRowsV];
+  auto stores = [&](int k) { return SLOTS ? k <= last : k < count && active; };
   auto load_batch = [&](int a0, auto rows_tag, size_t in_stride) {
-    if (SLOTS && full) {  // no per-lane clamp
-#pragma unroll
-      for (int i = 0; i < decltype(rows_tag)::value; ++i) cw[i].load(in_codes + (size_t)(uint32_t)(a0 + i) * in_stride);
-      return;
-    }
 #pragma unroll
     for (int i = 0; i < decltype(rows_tag)::value; ++i) {
       int k = a0 + i;
@@ -561,7 +559,7 @@ __device__ __forceinline__ void transcode_block(const TranscodeParams& a, const 
     for (int i = 0; i < decltype(rows_tag)::value; ++i) {
       if (a0 + i < count) {  // wave-uniform
         auto param = param_of(i);  // may shuffle across lanes: taken with the whole wave enabled
-        if (a0 + i <= last) transcode_row<DT, BI, BO, FIX>(out_codes + (size_t)(uint32_t)(a0 + i) * out_stride, cw[kFirst + i], param);
+        if (stores(a0 + i)) transcode_row<DT, BI, BO, FIX>(out_codes + (size_t)(uint32_t)(a0 + i) * out_stride, cw[kFirst + i], param);
       }
       __builtin_amdgcn_sched_barrier(0);  // one access at a time: keeps the temporaries of different ones apart
     }
@@ -581,7 +579,7 @@ __device__ __forceinline__ void transcode_block(const TranscodeParams& a, const 
   const uint32_t m_lane = ((uint32_t)lane / kTcSpanHeads * v_step + lane % kTcSpanHeads) * 4, m_batch = v_step * (kTcBatch * 4);
   const size_t vfirst = ((size_t)t0 * heads + y0) * 4;  // metadata word of the wave's first slot
   const uint8_t* in_vmeta = in_layer + gi.kmeta + gi.codes + vfirst;
-  auto owns = [&](int batch) { return (uint32_t)(batch * kWave + lane) < left; };
+  auto owns = [&](int batch) { return (uint32_t)(batch * kWave + lane) < left && (SLOTS || y0 + lane % kTcSpanHeads < heads); };
   [[maybe_unused]] uint32_t vm[2] = {0u, 0u};
   if (count > 0) {
     if (is_v) {
@@ -604,7 +602,7 @@ __device__ __forceinline__ void transcode_block(const TranscodeParams& a, const 
     uint32_t g, head0;
     set_of(lc >> (7 + log_s), g, head0);
     const uint32_t pc = head0 * kGroup + (lc & ((128u << log_s) - 1));
-    pact = (uint64_t)g * kGroup < n && (!SLOTS || pc < c);
+    pact = (uint64_t)g * kGroup < n && (SLOTS || pc < c);
     pmeta = ((size_t)g * c + pc) * 4;
     if (pact) km = gload<uintx2>(in_layer + pmeta);
   }
@@ -655,7 +653,7 @@ __device__ __forceinline__ void transcode_block(const TranscodeParams& a, const 
       for (int j = 0; j < kTcLaneCh; ++j) tab[j] = ktab[j * kWave + par_lane];
 #pragma unroll
       for (int i = 0; i < kRowsK; ++i) {  // kRowsK == kTcRows here: the wave's accesses are all loaded
-        if (i <= last)
+        if (stores(i))
           lookup_row<BI, BO>(out_codes + (size_t)i * out_stride_k, cw[i], [&tab](int j) { return tab[j]; });
         __builtin_amdgcn_sched_barrier(0);
       }
@@ -712,7 +710,7 @@ __device__ __forceinline__ void transcode_block(const TranscodeParams& a, const 
           for (int a0 = 0;;) {
 #pragma unroll
             for (int i = 0; i < kRowsK; ++i) {
-              if (a0 + i <= last)
+              if (stores(a0 + i))
                 poly_row82<STANDARD>(out_codes + (size_t)(uint32_t)(a0 + i) * out_stride_k, cw[i], [&gq](int j) -> const Quad& { return gq[j]; });
               __builtin_amdgcn_sched_barrier(0);
             }
@@ -767,7 +765,7 @@ __device__ __forceinline__ void transcode_block(const TranscodeParams& a, const 
         for (int i = 0; i < kTcBatch; ++i) {
           if (a0 + i < count) {  // wave-uniform; the shuffle is taken with the whole wave enabled
             const uint32_t tab = __shfl(mine, i * kTcSpanHeads + (int)slot);
-            if (a0 + i <= last)
+            if (stores(a0 + i))
               lookup_row<BI, BO>(out_codes + (size_t)(a0 + i) * out_stride_v, cw[a0 + i], [tab](int) { return tab; });
           }
           __builtin_amdgcn_sched_barrier(0);
@@ -804,10 +802,10 @@ __device__ __forceinline__ void transcode_block(const TranscodeParams& a, const 
                   const int owner = i * kTcSpanHeads + (int)slot;
                   uint8_t* out_row = out_codes + (size_t)(uint32_t)(tb + i) * out_stride_v;
                   if (all_standard) {
-                    if (tb + i <= last) poly_row82<true>(out_row, cw[kFirst + i], [&gq](int) -> const Quad& { return gq; });
+                    if (stores(tb + i)) poly_row82<true>(out_row, cw[kFirst + i], [&gq](int) -> const Quad& { return gq; });
                   } else {
                     const Quad gr = {__shfl(gq.a, owner), __shfl(gq.b, owner), __shfl(gq.c, owner)};
-                    if (tb + i <= last) poly_row82<false>(out_row, cw[kFirst + i], [&gr](int) -> const Quad& { return gr; });
+                    if (stores(tb + i)) poly_row82<false>(out_row, cw[kFirst + i], [&gr](int) -> const Quad& { return gr; });
                   }
                 }
                 __builtin_amdgcn_sched_barrier(0);
@@ -888,26 +886,16 @@ __global__ __launch_bounds__(kTcThreads) KVH_TC_OCC void transcode_kernel(Transc
 }
 
 int launch_transcode(const TranscodeParams& a, int dt, int n_items, int max_tokens, hipStream_t stream) {
-  // 8 >> log_s sets of 2^log_s heads x a token-group per K block; the V units, which are not rounded up per head, are
-  // never more numerous
   const int heads = a.c / kGroup;
-  const bool slots = heads % kTcSpanHeads != 0;
-  // Heads of a K set: the largest power of two that divides the row, or 8 with idle lanes where that is the faster form.
-  // 32 layers x 2,048 to 12,000 tokens, against the spans with idle lanes that all of these took: 1 to 4 heads 1.3 to 4.6
-  // times faster, 9 and 10 heads 1.2 to 1.4, 12 heads 1.15 to 1.25, 6 and 11 heads 0.9 to 1.15; 5, 7 and from 13 heads on
-  // single heads are as slow as 0.67 (they write 32- or 64-byte pieces), idle lanes 0.93 to 1.09 (V has none).
-  const bool fit = heads <= 4 || heads == 6 || (heads >= 9 && heads <= 12);
-  const int log_s = slots && fit ? __builtin_ctz((unsigned)heads) : 3;
-  const int64_t groups = ((int64_t)max_tokens + kGroup - 1) / kGroup;
-  const int64_t gx = (groups * ((heads + (1 << log_s) - 1) >> log_s) + (8 >> log_s) - 1) / (8 >> log_s);
+  const TcPlan plan = transcode_plan(heads, a.l, n_items, max_tokens);
   TranscodeParams b = a;
   b.max_tokens = max_tokens;
-  b.k_log_s = log_s;
+  b.k_log_s = plan.log_s;
   b.by_heads = Divisor((uint32_t)heads);
-  b.by_sets = Divisor((uint32_t)((heads + (1 << log_s) - 1) >> log_s));
-  const dim3 grid((unsigned)gx, (unsigned)(2 * a.l), (unsigned)n_items);
-  auto kernel = dt == KVH_F16 ? (slots ? transcode_kernel<KVH_F16, true> : transcode_kernel<KVH_F16, false>)
-                              : (slots ? transcode_kernel<KVH_BF16, true> : transcode_kernel<KVH_BF16, false>);
+  b.by_sets = Divisor((uint32_t)plan.sets);
+  const dim3 grid((unsigned)plan.blocks, (unsigned)(2 * a.l), (unsigned)n_items);
+  auto kernel = dt == KVH_F16 ? (plan.slots ? transcode_kernel<KVH_F16, true> : transcode_kernel<KVH_F16, false>)
+                              : (plan.slots ? transcode_kernel<KVH_BF16, true> : transcode_kernel<KVH_BF16, false>);
   launch_kernel(kernel, grid, dim3(kTcThreads), 0u, stream, b);
   KVH_HIP_CHECK_LAUNCH();
   return KVH_OK;

@@ -1,0 +1,57 @@
+"""The launchers' rules (csrc/kvh_plan.hpp), compiled for the host: every row and head of an item is covered, and the
+layouts that measured slower than another one are not chosen again."""
+import ctypes
+import os
+import subprocess
+
+import pytest
+
+CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "paper_2509_00105_amd", "csrc")
+SHIM = r"""
+#include "kvh_plan.hpp"
+using namespace kvh;
+extern "C" void tc_plan(int heads, int l, int items, int tokens, int64_t* o) {
+  const TcPlan p = transcode_plan(heads, l, items, tokens);
+  o[0] = p.slots; o[1] = p.log_s; o[2] = p.sets; o[3] = p.blocks;
+}
+"""
+
+
+@pytest.fixture(scope="module")
+def plans(tmp_path_factory):
+    d = tmp_path_factory.mktemp("plans")
+    (d / "shim.cpp").write_text(SHIM)
+    so = str(d / "plans.so")
+    subprocess.run(["g++", "-std=c++17", "-O1", "-Wall", "-Werror", "-shared", "-fPIC", "-I", CSRC, "-o", so, str(d / "shim.cpp")], check=True)
+    lib = ctypes.CDLL(so)
+
+    def call(name, *args):
+        out = (ctypes.c_int64 * 8)()
+        getattr(lib, name)(*[ctypes.c_int64(a) if abs(a) > 2**31 - 1 else a for a in args], out)
+        return list(out)
+
+    return call
+
+
+def ceil(a, b):
+    return -(-a // b)
+
+
+@pytest.mark.parametrize("heads", list(range(1, 26)) + [33, 64, 255])
+def test_transcode_plan_covers_rows_and_heads(plans, heads):
+    for l, items in ((1, 1), (4, 1), (32, 1), (32, 16)):
+        for n in (1, 127, 128, 129, 300, 3001, 40003):
+            slots, log_s, sets, blocks = plans("tc_plan", heads, l, items, n)[:4]
+            assert sets << log_s >= heads and (not slots or sets << log_s == heads)
+            assert slots or log_s == 3
+            assert blocks * (8 >> log_s) >= ceil(n, 128) * sets          # K sets
+            assert not slots or blocks * 8 * 128 >= n * heads            # V: 128 slots a wave
+
+
+def test_transcode_slots_only_where_they_are_the_faster_form(plans):
+    """5, 6, 7, 11 and from 13 heads on spans with idle lanes are as fast as they were or faster, slots down to 0.65 of it;
+    launches of few blocks lose lanes of the chip instead."""
+    chosen = [h for h in range(1, 25) if plans("tc_plan", h, 32, 16, 512)[0]]
+    assert chosen == [1, 2, 3, 4, 9, 10, 12]
+    assert [h for h in range(1, 13) if plans("tc_plan", h, 4, 1, 3001)[0]] == [1, 2, 9, 10, 12]
+    assert [h for h in range(1, 13) if plans("tc_plan", h, 32, 1, 256)[0]] == [1, 2, 9, 10, 12]
