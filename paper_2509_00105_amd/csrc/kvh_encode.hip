@@ -12,6 +12,7 @@
 // Quantised codes are produced with the packed float->u8 convert, which rounds to nearest even
 // and inserts the byte in one instruction; narrow codes are routed to their byte at that point.
 #include "kvh_common.hpp"
+#include "kvh_plan.hpp"
 
 namespace kvh {
 
@@ -501,7 +502,7 @@ __device__ __forceinline__ void encode_v_block(const EncodeParams& a, const kvh_
 // Here the 64 lanes x 16 accesses of a wave are 64 (row, head) slots, slot 4 i + j being lanes 16 j .. 16 j + 15 of
 // access i.
 //   K: S = 2 heads or 1 (the largest of these that divides the row) x 64 / S rows; 2 S waves make up a set of S heads x
-//     128 tokens, a block holds 4 / S sets.  A channel's statistics are spread over 8 (wave, 16-lane row) partials
+//     128 tokens, a block holds as many sets as it has waves for.  A channel's statistics are spread over 8 (wave, 16-lane row) partials
 //     whatever S is, and meet in LDS as they do for strips.
 //   V, raw level: 64 consecutive (row, head) pairs in memory order, so codes and metadata are contiguous.
 // Consecutive slots are consecutive rows or heads, so that an access covers whole cache lines of codes where it can.
@@ -517,7 +518,7 @@ __device__ __forceinline__ void encode_k_slots(const EncodeParams& a, const kvh_
   const uint32_t log_s = (heads & 1) ? 0u : 1u;
   const uint32_t s_mask = (1u << log_s) - 1, set_waves = 2u << log_s, step = 4u >> log_s;  // rows per access
   const uint32_t sets = heads >> log_s;                                                    // per token-group
-  const uint32_t set = (uint32_t)bx * step + wave / set_waves;
+  const uint32_t set = (uint32_t)bx * ((uint32_t)a.waves / set_waves) + wave / set_waves;
   const uint32_t g = a.by_sets.quotient(set);
   const uint32_t head = ((set - g * sets) << log_s) + (quad & s_mask);
   const uint32_t ch0 = head * kGroup + sub * kLaneCh;
@@ -593,7 +594,7 @@ __device__ __forceinline__ void encode_row_slots(const EncodeParams& a, const kv
   const uint32_t sub = lane & 15, quad = lane >> 4;
   const uint32_t n = (uint32_t)it.n_tokens, heads = (uint32_t)a.c / kGroup;
   // slot k of the unit is row t0 + (y0 + k) / heads, head (y0 + k) % heads
-  const uint32_t unit = (uint32_t)bx * kEncWaves + wave;
+  const uint32_t unit = (uint32_t)bx * (uint32_t)a.waves + wave;
   const uint32_t q = a.by_heads.quotient(unit), x0 = (unit - q * heads) * kWave, xq = a.by_heads.quotient(x0);
   const uint32_t t0 = q * kWave + xq, y0 = x0 - xq * heads;
   if (t0 >= n) return;  // wave-uniform
@@ -769,7 +770,7 @@ __global__ __launch_bounds__(kEncThreads) __attribute__((amdgpu_waves_per_eu(4, 
     if (a.k_slots) {
       // block-uniform: the first set of the block is past the end
       const int heads = a.c / kGroup, log_s = (heads & 1) ? 0 : 1;
-      if ((int64_t)a.by_sets.quotient((uint32_t)bx * (4 >> log_s)) * kGroup >= it.n_tokens) return;
+      if ((int64_t)a.by_sets.quotient((uint32_t)bx * ((uint32_t)a.waves >> (1 + log_s))) * kGroup >= it.n_tokens) return;
       switch (bits) {
         case 8: encode_k_slots<DT, 8>(a, it, layer_base, geo, lam, bx, red, split, jump); break;
         case 4: encode_k_slots<DT, 4>(a, it, layer_base, geo, lam, bx, red, split, jump); break;
@@ -807,23 +808,13 @@ __global__ __launch_bounds__(kEncThreads) __attribute__((amdgpu_waves_per_eu(4, 
 }
 
 int launch_encode(const EncodeParams& a, int dt, int n_items, int max_tokens, hipStream_t stream) {
-  // Rows of whole 512-channel strips: a block is one token-group of a strip.  Any other row length: V and raw blocks are 8
-  // units of 64 (row, head) slots.  K blocks are sets of slots for 1, 2, 5 and 6 heads, where strips keep 25 to 75 % of
-  // their lanes; with 3 heads (75 %, but one head at a time here) and from 7 on (81 % and more) strips are the faster
-  // ones.  32 layers x 2,048 to 16,384 tokens in items of 256 to 12,000, strips (with slots for V) against slots: 1 head
-  // 1.35 to 2.3 times faster, 2 heads 1.1 to 1.25, 5 heads 1.02 to 1.24, 6 heads 0.99 to 1.16, 3 heads 0.9 to 0.95, 7 to 18
-  // heads 0.89 to 1.01.
   const int heads = a.c / kGroup, nstrips = (a.c + kStripCh - 1) / kStripCh;
-  const bool slots = heads % (kStripCh / kGroup) != 0;
-  const int64_t groups = ((int64_t)max_tokens + kEncTile - 1) / kEncTile;
-  int64_t gx = groups * nstrips;  // never fewer than the blocks of slots in memory order
+  const EncPlan plan = encode_plan(heads, a.l, n_items, max_tokens);
+  const int64_t gx = plan.blocks;
   EncodeParams b = a;
   b.max_tokens = max_tokens;
-  b.k_slots = heads == 1 || heads == 2 || heads == 5 || heads == 6;
-  if (b.k_slots) {
-    const int log_s = (heads & 1) ? 0 : 1, per_block = 4 >> log_s;
-    gx = (groups * (heads >> log_s) + per_block - 1) / per_block;
-  }
+  b.k_slots = plan.k_slots;
+  b.waves = plan.waves;
   // Plane group.  With the dispatcher dealing consecutive blocks to the 8 XCDs in turn, groups of 8 make every XCD
   // stream through one plane at a time; that is the default.  Long items do better with the two planes of a layer
   // alone (their sections of a blob are megabytes apart, and fewer planes at a time keep the writes together), and
@@ -845,9 +836,9 @@ int launch_encode(const EncodeParams& a, int dt, int n_items, int max_tokens, hi
   b.by_sets = Divisor((uint32_t)((heads & 1) ? heads : heads / 2));
   const unsigned n_groups = (unsigned)((2 * a.l + b.plane_group - 1) / b.plane_group);
   const dim3 grid((unsigned)(gx * b.plane_group), n_groups, (unsigned)n_items);
-  auto kernel = dt == KVH_F16 ? (slots ? encode_kernel<KVH_F16, true> : encode_kernel<KVH_F16, false>)
-                              : (slots ? encode_kernel<KVH_BF16, true> : encode_kernel<KVH_BF16, false>);
-  launch_kernel(kernel, grid, dim3(kEncThreads), 0u, stream, b);
+  auto kernel = dt == KVH_F16 ? (plan.slots ? encode_kernel<KVH_F16, true> : encode_kernel<KVH_F16, false>)
+                              : (plan.slots ? encode_kernel<KVH_BF16, true> : encode_kernel<KVH_BF16, false>);
+  launch_kernel(kernel, grid, dim3((unsigned)(plan.waves * kWave)), 0u, stream, b);
   KVH_HIP_CHECK_LAUNCH();
   return KVH_OK;
 }

@@ -40,4 +40,40 @@ inline TcPlan transcode_plan(int heads, int l, int n_items, int max_tokens) {
   return p;
 }
 
+// ---- encoder ----------------------------------------------------------------------------------------------------
+struct EncPlan {
+  bool slots;      // V and raw rows in units of 64 (row, head) slots, otherwise in 512-channel strips
+  bool k_slots;    // K in sets of slots (then `slots` holds), otherwise in strips
+  int waves;       // of a block
+  int64_t blocks;  // of a (layer, K|V) plane
+};
+
+// Rows of whole strips: a block is one token-group of a strip.  Any other row length: V and raw blocks are units of slots,
+// a wave each.  K blocks are sets of slots for 1, 2, 5 and 6 heads, where strips keep 25 to 75 % of their lanes; with 3
+// heads (75 %, but one head at a time here) and from 7 on (81 % and more) strips are the faster ones.  32 layers x 2,048 to
+// 16,384 tokens in items of 256 to 12,000, strips (with slots for V) against slots: 1 head 1.35 to 2.3 times faster, 2 heads
+// 1.1 to 1.25, 5 heads 1.02 to 1.24, 6 heads 0.99 to 1.16, 3 heads 0.9 to 0.95, 7 to 18 heads 0.89 to 1.01.
+// Waves of a block: a set of slots takes 2 a head, so that the token-group of 1 or 2 heads is 2 or 4 waves.  Blocks of 8
+// hold several token-groups of them, which leaves compute units without a block in small launches and half a block empty in
+// short items; blocks of 4 are 0.97 to 1.37 times as fast on 19 shapes from 4 x 256 to 80 x 4,096 tokens (2 heads 4 x 3,001
+// raw: 8.5 -> 6.3 us, 32 x 256 at 4 bits: 8.0 -> 6.6, 32 x 8,192 raw: 105.6 -> 97.9).  Items of up to 256 tokens keep one
+// block an item where the launch is not small (2 heads, 32 x 2,048 in 256-token items with K and V rows in turn: blocks of 4
+// 0.81 to 0.89; 80 x 256: 0.96 to 1.0; 32 x 256 and 4 x 256 on the other hand 1.15 to 1.34).
+inline EncPlan encode_plan(int heads, int l, int n_items, int max_tokens) {
+  const int strips = (heads + 3) / 4;
+  const int64_t groups = ((int64_t)max_tokens + 127) / 128;
+  EncPlan p;
+  p.slots = heads % 4 != 0;
+  p.k_slots = heads == 1 || heads == 2 || heads == 5 || heads == 6;
+  p.waves = 8;
+  p.blocks = groups * strips;  // never fewer than the blocks of slots in memory order
+  if (p.k_slots) {
+    const int s = (heads & 1) ? 1 : 2;
+    auto blocks = [&](int waves) { return (groups * (heads / s) + waves / (2 * s) - 1) / (waves / (2 * s)); };
+    if (heads <= 2) p.waves = max_tokens <= 256 && (double)blocks(8) * 2 * l * n_items >= 160 ? 4 * heads : 4;
+    p.blocks = blocks(p.waves);
+  }
+  return p;
+}
+
 }  // namespace kvh
