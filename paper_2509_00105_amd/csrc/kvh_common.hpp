@@ -243,7 +243,7 @@ struct EncodeParams {
   // block order chosen by the launcher (see encode_kernel)
   int plane_group;   // (layer, K|V) planes that consecutive blocks cycle through
   int plane_blocks;  // blocks of an item's plane
-  int k_slots;       // K blocks are sets of (row, head) slots instead of strips
+  int k_slots;       // K blocks: 0 strips, 1 sets of (row, head) slots, 2 these with ordinary stores at 2 bits
   int waves;         // of a block
   Divisor by_group, by_strips, by_heads, by_sets;  // plane_group; strips and heads of a row; K sets of slots in a row
   kvh_enc_item inline_items[kInlineItems];

@@ -285,15 +285,18 @@ __device__ __forceinline__ void encode_k_block(const EncodeParams& a, const kvh_
   }
 }
 
-// Raw level: the rows of the block's tile and strip go into the blob as they are (K rows, then V rows, per layer).
-template <int DT>
+// Raw level: the rows of the block's tile and strip go into the blob as they are (K rows, then V rows, per layer).  Rows of
+// whole strips have a form without idle lanes (a test per store: 2 % slower on average, up to 10 on small launches).
+template <int DT, bool IDLE>
 __device__ __forceinline__ void encode_raw_block(const EncodeParams& a, const kvh_enc_item& it, uint8_t* layer_base,
                                                  const LayerGeom& geo, int lam, bool is_v, int tile, int strip, int split,
                                                  int64_t jump) {
   const int lane = threadIdx.x & (kWave - 1);
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int n = it.n_tokens;
-  const int ch0 = strip * kStripCh + lane * kLaneCh;
+  const int ch_raw = strip * kStripCh + lane * kLaneCh;
+  const bool active = !IDLE || ch_raw < a.c;
+  const int ch0 = active ? ch_raw : 0;
   const int t_first = tile * kEncTile + wave * kEncRows;
   if (t_first >= n) return;  // wave-uniform
   const uint8_t* src = reinterpret_cast<const uint8_t*>((is_v ? a.v : a.k) + (int64_t)lam * a.layer_stride);
@@ -308,7 +311,7 @@ __device__ __forceinline__ void encode_raw_block(const EncodeParams& a, const kv
 #pragma unroll
   for (int i = 0; i < kEncRows; ++i) {
     const int t = t_first + i;
-    if (t < n) gstore_codes<uintx4>(uniform(rows + (size_t)t * geo.row_bytes) + (uint32_t)ch0 * 2u, d[i]);
+    if (t < n && active) gstore_codes<uintx4>(uniform(rows + (size_t)t * geo.row_bytes) + (uint32_t)ch0 * 2u, d[i]);
   }
 }
 
@@ -436,10 +439,11 @@ __device__ __forceinline__ void encode_v_block(const EncodeParams& a, const kvh_
   const int n = it.n_tokens;
   const int c = a.c;
   const int heads = c / kGroup;
-  // Holds for every lane (this form takes whole strips).  The test is there for what it does to the generated code: each
-  // row's quantisation and store are a block of their own.  Without it 4 and 2 bits are 1 % slower on six shapes.
-  const int ch0 = strip * kStripCh + lane * kLaneCh;
-  const bool active = ch0 < c;
+  // Rows of whole strips have no idle lanes; the test is there for what it does to the generated code as well: each row's
+  // quantisation and store are a block of their own.  Without it 4 and 2 bits are 1 % slower on six shapes.
+  const int ch_raw = strip * kStripCh + lane * kLaneCh;
+  const bool active = ch_raw < c;  // uniform over the 16 lanes of a head
+  const int ch0 = active ? ch_raw : 0;
   const int t_first = tile * kEncTile + wave * kEncRows;
   const uint8_t* src = reinterpret_cast<const uint8_t*>(a.v + (int64_t)lam * a.layer_stride);  // wave-uniform
   const uint32_t lane_src_off = (uint32_t)ch0 * 2u;
@@ -465,7 +469,7 @@ __device__ __forceinline__ void encode_v_block(const EncodeParams& a, const kvh_
       float2 own;
       const uint32_t word = batch_stats<DT, BITS, R, r0>(d, lane, own);
       const int t_own = t_first + r0 + (lane & (R - 1));
-      if ((lane & 15) < R && t_own < n) gstore<uint32_t>(vmeta + ((size_t)t_own * heads + ch0 / kGroup) * 4, word);
+      if (active && (lane & 15) < R && t_own < n) gstore<uint32_t>(vmeta + ((size_t)t_own * heads + ch0 / kGroup) * 4, word);
       auto row = [&](auto idx) {
         constexpr int r = decltype(idx)::value;
         constexpr int i = r0 + r;
@@ -775,10 +779,10 @@ __global__ __launch_bounds__(kEncThreads) __attribute__((amdgpu_waves_per_eu(4, 
         case 8: encode_k_slots<DT, 8>(a, it, layer_base, geo, lam, bx, red, split, jump); break;
         case 4: encode_k_slots<DT, 4>(a, it, layer_base, geo, lam, bx, red, split, jump); break;
         default:
-          // Rows of an odd number of heads leave gaps between the 32-byte pieces an access writes, which other waves fill;
+          // Single heads out of a longer row leave gaps between the 32-byte pieces an access writes, which other waves fill;
           // ordinary stores let the L2 put them together (5 heads: 310 -> 303 us in 512-token items of 32 x 16384 tokens,
           // 233 -> 209 in one item of 12,000; with 1 head, where there are no gaps, and with 6, 1 to 7 % slower).
-          if (heads == 5) encode_k_slots<DT, 2, true>(a, it, layer_base, geo, lam, bx, red, split, jump);
+          if (a.k_slots == 2) encode_k_slots<DT, 2, true>(a, it, layer_base, geo, lam, bx, red, split, jump);
           else encode_k_slots<DT, 2>(a, it, layer_base, geo, lam, bx, red, split, jump);
           break;
       }
@@ -788,7 +792,8 @@ __global__ __launch_bounds__(kEncThreads) __attribute__((amdgpu_waves_per_eu(4, 
   }
   if constexpr (!SLOTS) {
     if (bits == 16) {
-      encode_raw_block<DT>(a, it, layer_base, geo, lam, is_v, tile, strip, split, jump);
+      if (a.c % kStripCh == 0) encode_raw_block<DT, false>(a, it, layer_base, geo, lam, is_v, tile, strip, split, jump);
+      else encode_raw_block<DT, true>(a, it, layer_base, geo, lam, is_v, tile, strip, split, jump);
       return;
     }
     if (is_v) {
@@ -813,7 +818,7 @@ int launch_encode(const EncodeParams& a, int dt, int n_items, int max_tokens, hi
   const int64_t gx = plan.blocks;
   EncodeParams b = a;
   b.max_tokens = max_tokens;
-  b.k_slots = plan.k_slots;
+  b.k_slots = plan.k_slots ? 1 + plan.plain_stores : 0;
   b.waves = plan.waves;
   // Plane group.  With the dispatcher dealing consecutive blocks to the 8 XCDs in turn, groups of 8 make every XCD
   // stream through one plane at a time; that is the default.  Long items do better with the two planes of a layer

@@ -44,15 +44,18 @@ inline TcPlan transcode_plan(int heads, int l, int n_items, int max_tokens) {
 struct EncPlan {
   bool slots;      // V and raw rows in units of 64 (row, head) slots, otherwise in 512-channel strips
   bool k_slots;    // K in sets of slots (then `slots` holds), otherwise in strips
+  bool plain_stores;  // with k_slots: single heads out of longer rows, see encode_kernel
   int waves;       // of a block
   int64_t blocks;  // of a (layer, K|V) plane
 };
 
-// Rows of whole strips: a block is one token-group of a strip.  Any other row length: V and raw blocks are units of slots,
-// a wave each.  K blocks are sets of slots for 1, 2, 5 and 6 heads, where strips keep 25 to 75 % of their lanes; with 3
-// heads (75 %, but one head at a time here) and from 7 on (81 % and more) strips are the faster ones.  32 layers x 2,048 to
-// 16,384 tokens in items of 256 to 12,000, strips (with slots for V) against slots: 1 head 1.35 to 2.3 times faster, 2 heads
-// 1.1 to 1.25, 5 heads 1.02 to 1.24, 6 heads 0.99 to 1.16, 3 heads 0.9 to 0.95, 7 to 18 heads 0.89 to 1.01.
+// Rows of whole strips, and of 3 heads: a block is one token-group of a strip.  Any other row length: V and raw blocks are
+// units of slots, a wave each.  K slots take idle lanes away but read and write single heads or pairs: taken where more than
+// a quarter of the strips' lanes idle, or a quarter and the heads come in pairs.  32 layers x 2,048 to 16,384 tokens in
+// items of 256 to 12,000, strips (with slots for V) against slots: 1 head 1.35 to 2.3 times faster, 2 heads 1.1 to 1.25, 5
+// heads 1.02 to 1.24, 6 heads 0.99 to 1.16, 3 heads 0.9 to 0.95, 7 to 18 heads 0.89 to 1.01.  With 3 heads slots bring V
+// and the raw level nothing either (15 shapes, all levels: strips 1.00 to 1.11 times as fast as before slots, slots 0.89 to
+// 1.14: 4 x 3,001 raw 8.9 -> 10.0 us, 32 x 1,024 in 256-token items raw 19.2 -> 21.0).
 // Waves of a block: a set of slots takes 2 a head, so that the token-group of 1 or 2 heads is 2 or 4 waves.  Blocks of 8
 // hold several token-groups of them, which leaves compute units without a block in small launches and half a block empty in
 // short items; blocks of 4 are 0.97 to 1.37 times as fast on 19 shapes from 4 x 256 to 80 x 4,096 tokens (2 heads 4 x 3,001
@@ -60,11 +63,12 @@ struct EncPlan {
 // block an item where the launch is not small (2 heads, 32 x 2,048 in 256-token items with K and V rows in turn: blocks of 4
 // 0.81 to 0.89; 80 x 256: 0.96 to 1.0; 32 x 256 and 4 x 256 on the other hand 1.15 to 1.34).
 inline EncPlan encode_plan(int heads, int l, int n_items, int max_tokens) {
-  const int strips = (heads + 3) / 4;
+  const int strips = (heads + 3) / 4, lanes = strips * 4, idle = lanes - heads;
   const int64_t groups = ((int64_t)max_tokens + 127) / 128;
   EncPlan p;
-  p.slots = heads % 4 != 0;
-  p.k_slots = heads == 1 || heads == 2 || heads == 5 || heads == 6;
+  p.k_slots = 4 * idle > lanes || (4 * idle == lanes && heads % 2 == 0);
+  p.slots = p.k_slots || (idle > 0 && heads > 3);
+  p.plain_stores = p.k_slots && heads % 2 == 1 && heads > 1;
   p.waves = 8;
   p.blocks = groups * strips;  // never fewer than the blocks of slots in memory order
   if (p.k_slots) {

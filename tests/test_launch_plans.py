@@ -83,3 +83,9 @@ def test_encode_blocks_of_few_heads_are_small(plans):
         assert plans("enc_plan", heads, 32, 1, 256)[2:4] == [4, heads]
         assert plans("enc_plan", heads, 32, 16, 512)[2:4] == [4, 2 * heads]
         assert plans("enc_plan", heads, 32, 8, 256)[2:4] == [4 * heads, 1]
+
+
+def test_encode_slots_only_where_they_are_the_faster_form(plans):
+    """Rows of 3 heads stay in one strip: slots were down to 0.89 of it (raw), never above 1.14."""
+    assert [h for h in range(1, 25) if plans("enc_plan", h, 32, 16, 512)[0]] == [h for h in range(1, 25) if h % 4 and h != 3]
+    assert [h for h in range(1, 25) if plans("enc_plan", h, 32, 16, 512)[1]] == [1, 2, 5, 6]
