@@ -17,6 +17,7 @@
 #include <type_traits>
 
 #include "kvh_common.hpp"
+#include "kvh_plan.hpp"
 
 namespace kvh {
 
@@ -782,62 +783,20 @@ __global__ __launch_bounds__(kDecThreads) KVH_DEC_OCC(SHORT) void decode_kernel(
 }
 
 int launch_decode(const DecodeParams& a, int dt, int n_items, int max_tokens, hipStream_t stream) {
-  // Rows of whole 1024-channel spans: a block is 64 rows of a span.  Any other row length: 8 units of 64 (row, head)
-  // slots; the K units, whose row blocks are rounded up per set of heads, are the more numerous.
   const int heads = a.c / kGroup;
-  const bool slots = heads % kDecHeads != 0;
-  unsigned gx;  // blocks of a plane
-  if (slots) {
-    const int log_s = __builtin_ctz((unsigned)heads);
-    const int64_t units = (((int64_t)max_tokens + (kWave >> log_s) - 1) / (kWave >> log_s)) * (heads >> log_s);
-    gx = (unsigned)((units + kDecWaves - 1) / kDecWaves);
-  } else {
-    gx = (unsigned)(((max_tokens + kDecBlockRows - 1) / kDecBlockRows) * (a.c / kDecSpanCh));
-  }
+  const DecPlan plan = decode_plan(heads, a.l, n_items, max_tokens, a.layer_stride, a.token_stride);
   DecodeParams b = a;
   b.max_tokens = max_tokens;
-  // Row tile.  Destination planes within 1 GiB of each other: planes first (one block per plane and turn), worth
-  // 1-2 % there over anything longer.  Beyond that: four blocks (256 rows) per plane and turn for items of up to
-  // 8,192 tokens, plane by plane for longer ones.  Measured on ten tensors of 2.5 to 16 GiB (8 to 80 layers, 8K to
-  // 128K tokens) against walking plane by plane, the kernel alone, 8 / 4 / 2 bits in points of HBM peak: items of 512
-  // tokens -1.4 to +3.9 / -1.6 to +5.3 / -0.4 to +4.9, of 1,024 tokens +0.9 to +8.9 / +1.0 to +11.8 / +2.2 to +9.2
-  // (walking plane by plane has a hole there, 67-69 % on most tensors), of 4,096 tokens -1.8 to +5.1 / -1.0 to +6.9 /
-  // -3.6 to +6.2; one item of 16,384 tokens +0.8 to +4.3 / -6.3 to +1.0 / -3.4 to +1.1, hence the limit.  Tiles of
-  // 2 are a point below tiles of 4, tiles of 8 two to four, tiles of 16 are the hole again.
-  const bool near = (int64_t)a.l * a.layer_stride * 2 <= ((int64_t)1 << 29);
-  b.row_tile = near ? 1 : max_tokens <= 8192 ? 4 : 0x7fffffff;
-  // Plane group.  Groups of at most 8 planes of one size, one block per plane and turn, through all items before the next
-  // group; or all planes, i.e. item by item in the row tiles above.  The dispatcher deals consecutive blocks to the 8 XCDs
-  // in turn, so that with 8 planes each XCD writes one plane and keeps to its address translations.
-  //   Slots always take groups: against item by item, 40 shapes (128 to 2560 channels, 2,048 to 24,000 tokens, chunks of 256
-  //   tokens to one item) 8 % faster on average, between -1 (512 channels) and +19 %; groups of 4 +7.6 %, but better by 1
-  //   to 3 % for 512 channels, plane by plane +4.6 %.  With 10 planes two groups of 5 take 55 us where 8 and 2 take 61.
-  //   Whole spans take groups for launches of up to 896 MiB of 16-bit rows.  32 layers x 1024 channels in 256-token items,
-  //   five mixes of levels and destinations: 512 tokens +2 to +10 %, 1,024 +2 to +7, 2,048 +4 to +12, 4,096 +1 to +5,
-  //   6,144 (768 MiB) 0 to +4, 8,192 (1 GiB) -8 to -2.
-  // Launches of whole spans of up to 256 MiB also get two blocks per CU: what they write is gone before the write stream
-  // has settled, and more waves in flight hide the start.  Both together: 64 MiB +11 to +21 %, 128 MiB +14 to +17, 256 MiB
-  // +4 to +23; two blocks alone 512 MiB -4 to 0.
-  const int64_t row_bytes_all = (int64_t)4 * a.l * a.c * max_tokens * n_items;
-  const bool groups_first = slots || row_bytes_all <= ((int64_t)896 << 20);
-  const bool short_launch = !slots && row_bytes_all <= ((int64_t)256 << 20);
-  b.plane_blocks = (int)gx;
-  b.plane_group = 2 * a.l;
-  if (groups_first) {
-    b.row_tile = 1;
-    const int most = slots && heads == 4 ? 4 : 8;
-    const int groups = (2 * a.l + most - 1) / most;
-    b.plane_group = (2 * a.l + groups - 1) / groups;
-  }
-  // the x dimension counts threads in 32 bits
-  while (b.plane_group > 1 && (int64_t)gx * b.plane_group * kDecThreads > 0xffffffffLL) b.plane_group = (b.plane_group + 1) / 2;
-  const dim3 grid(gx * (unsigned)b.plane_group, (unsigned)n_items, (unsigned)((2 * a.l + b.plane_group - 1) / b.plane_group));
+  b.row_tile = plan.row_tile;
+  b.plane_blocks = (int)plan.blocks;
+  b.plane_group = plan.plane_group;
+  const dim3 grid((unsigned)(plan.blocks * b.plane_group), (unsigned)n_items, (unsigned)((2 * a.l + b.plane_group - 1) / b.plane_group));
   b.by_group = Divisor((uint32_t)b.plane_group);
   b.by_heads = Divisor((uint32_t)heads);
-  b.by_sets = Divisor((uint32_t)(heads >> __builtin_ctz((unsigned)heads)));
+  b.by_sets = Divisor((uint32_t)(heads >> lowest_bit(heads)));
   auto pick = [&](auto dt_tag) {
     constexpr int D = decltype(dt_tag)::value;
-    return slots ? decode_kernel<D, true, false> : short_launch ? decode_kernel<D, false, true> : decode_kernel<D, false, false>;
+    return plan.slots ? decode_kernel<D, true, false> : plan.short_launch ? decode_kernel<D, false, true> : decode_kernel<D, false, false>;
   };
   auto kernel = dt == KVH_F16 ? pick(std::integral_constant<int, KVH_F16>{}) : pick(std::integral_constant<int, KVH_BF16>{});
   launch_kernel(kernel, grid, dim3(kDecThreads), 0u, stream, b);

@@ -8,6 +8,71 @@ namespace kvh {
 
 inline int lowest_bit(int x) { return __builtin_ctz((unsigned)x); }
 
+// ---- decoder ----------------------------------------------------------------------------------------------------
+struct DecPlan {
+  bool slots;           // rows in units of 64 (row, head) slots, otherwise in 1024-channel spans
+  bool short_launch;    // spans with two blocks per CU
+  int waves;            // of a block
+  int64_t blocks;       // of a (layer, K|V) plane
+  int plane_group, row_tile;  // block order, see decode_kernel
+};
+
+// Rows of whole 1024-channel spans: a block is 64 rows of a span.  Any other row length: units of 64 (row, head) slots, a
+// wave each; the K units, whose row blocks are rounded up per set of heads, are the more numerous.
+//
+// Row tile.  Destination planes within 1 GiB of each other: planes first (one block per plane and turn), worth
+// 1-2 % there over anything longer.  Beyond that: four blocks (256 rows) per plane and turn for items of up to
+// 8,192 tokens, plane by plane for longer ones.  Measured on ten tensors of 2.5 to 16 GiB (8 to 80 layers, 8K to
+// 128K tokens) against walking plane by plane, the kernel alone, 8 / 4 / 2 bits in points of HBM peak: items of 512
+// tokens -1.4 to +3.9 / -1.6 to +5.3 / -0.4 to +4.9, of 1,024 tokens +0.9 to +8.9 / +1.0 to +11.8 / +2.2 to +9.2
+// (walking plane by plane has a hole there, 67-69 % on most tensors), of 4,096 tokens -1.8 to +5.1 / -1.0 to +6.9 /
+// -3.6 to +6.2; one item of 16,384 tokens +0.8 to +4.3 / -6.3 to +1.0 / -3.4 to +1.1, hence the limit.  Tiles of
+// 2 are a point below tiles of 4, tiles of 8 two to four, tiles of 16 are the hole again.
+// Plane group.  Groups of at most 8 planes of one size, one block per plane and turn, through all items before the next
+// group; or all planes, i.e. item by item in the row tiles above.  The dispatcher deals consecutive blocks to the 8 XCDs
+// in turn, so that with 8 planes each XCD writes one plane and keeps to its address translations.
+//   Slots always take groups: against item by item, 40 shapes (128 to 2560 channels, 2,048 to 24,000 tokens, chunks of 256
+//   tokens to one item) 8 % faster on average, between -1 (512 channels) and +19 %; groups of 4 +7.6 %, but better by 1
+//   to 3 % for 512 channels, plane by plane +4.6 %.  With 10 planes two groups of 5 take 55 us where 8 and 2 take 61.
+//   Whole spans take groups for launches of up to 896 MiB of 16-bit rows.  32 layers x 1024 channels in 256-token items,
+//   five mixes of levels and destinations: 512 tokens +2 to +10 %, 1,024 +2 to +7, 2,048 +4 to +12, 4,096 +1 to +5,
+//   6,144 (768 MiB) 0 to +4, 8,192 (1 GiB) -8 to -2.
+//   A destination in which a token's rows of all layers lie side by side (layer stride below token stride) always takes all
+//   planes: consecutive blocks then fill a token's rows, groups leave holes between them.  32 layers, 256 to 8,192 tokens,
+//   1 to 16 heads, all levels: groups 0.74 to 1.07 times as fast on all but the smallest launches (1024 channels, 2,048
+//   tokens at 8 bits 77 us, in groups 88; 640 channels, 8,192 tokens at 2 bits 108 and 145).
+// Launches of whole spans of up to 256 MiB also get two blocks per CU: what they write is gone before the write stream
+// has settled, and more waves in flight hide the start.  Both together: 64 MiB +11 to +21 %, 128 MiB +14 to +17, 256 MiB
+// +4 to +23; two blocks alone 512 MiB -4 to 0.
+inline DecPlan decode_plan(int heads, int l, int n_items, int max_tokens, int64_t layer_stride, int64_t token_stride) {
+  DecPlan p;
+  p.slots = heads % 8 != 0;
+  p.waves = 8;
+  if (p.slots) {
+    const int log_s = lowest_bit(heads);
+    const int64_t units = (((int64_t)max_tokens + (64 >> log_s) - 1) / (64 >> log_s)) * (heads >> log_s);
+    p.blocks = (units + p.waves - 1) / p.waves;
+  } else {
+    p.blocks = (((int64_t)max_tokens + 63) / 64) * (heads / 8);
+  }
+  const int planes = 2 * l;
+  const bool near = (int64_t)l * layer_stride * 2 <= ((int64_t)1 << 29);
+  const bool side_by_side = layer_stride < token_stride;
+  const double mib = 4.0 * l * heads * 128 * max_tokens * n_items / (1 << 20);  // of 16-bit rows
+  p.short_launch = !p.slots && mib <= 256;
+  p.row_tile = near || side_by_side || p.slots ? 1 : max_tokens <= 8192 ? 4 : 0x7fffffff;
+  p.plane_group = planes;
+  if (!side_by_side && (p.slots || mib <= 896)) {
+    p.row_tile = 1;
+    const int most = p.slots && heads == 4 ? 4 : 8;
+    const int groups = (planes + most - 1) / most;
+    p.plane_group = (planes + groups - 1) / groups;
+  }
+  // a grid's x dimension counts threads in 32 bits
+  while (p.plane_group > 1 && p.blocks * p.plane_group * 64 * p.waves > 0xffffffffLL) p.plane_group = (p.plane_group + 1) / 2;
+  return p;
+}
+
 // ---- transcoder -------------------------------------------------------------------------------------------------
 struct TcPlan {
   bool slots;      // (row, head) slots; otherwise 1024-channel spans, in which the lanes beyond the row idle

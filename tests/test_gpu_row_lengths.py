@@ -111,3 +111,24 @@ def test_launch_sizes(kvh, l, n):
             kvh.decode(kvh.encode(kv[0][:, t0:t0 + m], kv[1][:, t0:t0 + m], level), level, m, ref[0], ref[1], dst_token0=t0)
         torch.cuda.synchronize()
         assert torch.equal(out.view(torch.int16), ref.view(torch.int16)), (l, n, level)
+
+
+@pytest.mark.parametrize("heads", (1, 4, 5, 8, 16))
+def test_layers_side_by_side(kvh, heads):
+    """[tokens][layers][channels] sources and destinations: the layer stride is below the token stride, and the decoder walks
+    all planes instead of groups of them."""
+    l, n, c, dt = 5, 300, 128 * heads, gen.BF16
+    k, v = gen.make_kv(l, n, c, dt, seed=heads)
+    src = torch.stack([device(k, dt).transpose(0, 1), device(v, dt).transpose(0, 1)]).contiguous().transpose(1, 2)
+    for level in range(4):
+        blob = kvh.encode(src[0], src[1], level)
+        out = torch.zeros((2, n + 3, l, c), dtype=TDT[dt], device="cuda").transpose(1, 2)
+        status = torch.zeros(1, dtype=torch.int32, device="cuda")
+        kvh.decode(blob, level, n, out[0], out[1], dst_token0=2, status=status)
+        torch.cuda.synchronize()
+        want = oracle.encode(k, v, dt, level)
+        wk, wv = oracle.decode(want, dt, l, n, c, level)
+        got = host(out)
+        assert status.item() == 0 and np.array_equal(blob.cpu().numpy(), want), level
+        assert np.array_equal(got[0, :, 2:2 + n], wk) and np.array_equal(got[1, :, 2:2 + n], wv), level
+        assert not got[:, :, :2].any() and not got[:, :, 2 + n:].any(), level

@@ -18,6 +18,10 @@ extern "C" void enc_plan(int heads, int l, int items, int tokens, int64_t* o) {
   const EncPlan p = encode_plan(heads, l, items, tokens);
   o[0] = p.slots; o[1] = p.k_slots; o[2] = p.waves; o[3] = p.blocks;
 }
+extern "C" void dec_plan(int heads, int l, int items, int tokens, int64_t layer_stride, int64_t token_stride, int64_t* o) {
+  const DecPlan p = decode_plan(heads, l, items, tokens, layer_stride, token_stride);
+  o[0] = p.slots; o[1] = p.short_launch; o[2] = p.waves; o[3] = p.blocks; o[4] = p.plane_group; o[5] = p.row_tile;
+}
 """
 
 
@@ -31,7 +35,8 @@ def plans(tmp_path_factory):
 
     def call(name, *args):
         out = (ctypes.c_int64 * 8)()
-        getattr(lib, name)(*[ctypes.c_int64(a) if abs(a) > 2**31 - 1 else a for a in args], out)
+        wide = 4 if name == "dec_plan" else len(args)  # the strides
+        getattr(lib, name)(*[ctypes.c_int64(a) if i >= wide else a for i, a in enumerate(args)], out)
         return list(out)
 
     return call
@@ -89,3 +94,51 @@ def test_encode_slots_only_where_they_are_the_faster_form(plans):
     """Rows of 3 heads stay in one strip: slots were down to 0.89 of it (raw), never above 1.14."""
     assert [h for h in range(1, 25) if plans("enc_plan", h, 32, 16, 512)[0]] == [h for h in range(1, 25) if h % 4 and h != 3]
     assert [h for h in range(1, 25) if plans("enc_plan", h, 32, 16, 512)[1]] == [1, 2, 5, 6]
+
+
+def dense(c, tokens):
+    return tokens * c, c
+
+
+@pytest.mark.parametrize("heads", list(range(1, 26)) + [33, 64, 255])
+def test_decode_plan_covers_rows_and_planes(plans, heads):
+    """The kernel's own block -> (plane, block of the plane) arithmetic, repeated here, reaches every block of every plane
+    once, whatever the last plane group and the last row tile are."""
+    c = 128 * heads
+    for l in (1, 3, 4, 5, 6, 9, 10, 11, 13):
+        for n, items in ((1, 1), (129, 2), (300, 1), (3001, 1)):
+            for strides in (dense(c, n), dense(c, 40000), (c, l * c)):
+                slots, _, waves, blocks, group, tile = plans("dec_plan", heads, l, items, n, *strides)[:6]
+                s = 1 << (heads & -heads).bit_length() - 1
+                if slots:
+                    assert blocks * waves >= ceil(n, 64 // s) * (heads // s) and blocks * waves * 64 >= n * heads and tile == 1
+                else:
+                    assert blocks >= ceil(n, 64) * (heads // 8)
+                if blocks > 400:
+                    continue
+                seen = set()
+                for z in range(ceil(2 * l, group)):
+                    first = z * group
+                    planes = min(2 * l - first, group)
+                    for lin in range(blocks * planes):
+                        rt = min(tile, blocks)
+                        full, t = blocks // rt, lin // (rt * planes)
+                        size, start = (rt, t * rt) if t < full else (blocks - full * rt, full * rt)
+                        j = lin - start * planes
+                        seen.add((first + j // size, start + j % size))
+                assert seen == {(p, b) for p in range(2 * l) for b in range(blocks)}
+
+
+def test_decode_grid_fits_the_dispatcher(plans):
+    for heads, l, n in ((8, 32767, 64), (1, 32767, 100000), (8, 80, 2**28), (5, 80, 2**26)):
+        slots, _, waves, blocks, group, _ = plans("dec_plan", heads, l, 65535, n, *dense(128 * heads, n))[:6]
+        assert ceil(2 * l, group) <= 65535 and (group == 1 or blocks * group * 64 * waves < 2**32)
+
+
+def test_decode_takes_all_planes_where_layers_lie_side_by_side(plans):
+    """[tokens][layers][channels]: plane groups leave holes between the rows that consecutive blocks write."""
+    for heads in (1, 2, 4, 5, 8, 16):
+        c = 128 * heads
+        for n, items in ((256, 1), (256, 8), (8192, 1)):
+            assert plans("dec_plan", heads, 32, items, n, c, 32 * c)[4:6] == [64, 1]
+            assert plans("dec_plan", heads, 32, items, n, *dense(c, n))[4] <= 8 or (heads % 8 == 0 and n * heads > 7 * 8192)
