@@ -28,15 +28,20 @@ struct DecPlan {
 // (walking plane by plane has a hole there, 67-69 % on most tensors), of 4,096 tokens -1.8 to +5.1 / -1.0 to +6.9 /
 // -3.6 to +6.2; one item of 16,384 tokens +0.8 to +4.3 / -6.3 to +1.0 / -3.4 to +1.1, hence the limit.  Tiles of
 // 2 are a point below tiles of 4, tiles of 8 two to four, tiles of 16 are the hole again.
-// Plane group.  Groups of at most 8 planes of one size, one block per plane and turn, through all items before the next
-// group; or all planes, i.e. item by item in the row tiles above.  The dispatcher deals consecutive blocks to the 8 XCDs
-// in turn, so that with 8 planes each XCD writes one plane and keeps to its address translations.
-//   Slots always take groups: against item by item, 40 shapes (128 to 2560 channels, 2,048 to 24,000 tokens, chunks of 256
-//   tokens to one item) 8 % faster on average, between -1 (512 channels) and +19 %; groups of 4 +7.6 %, but better by 1
-//   to 3 % for 512 channels, plane by plane +4.6 %.  With 10 planes two groups of 5 take 55 us where 8 and 2 take 61.
+// Plane group.  Groups of 8 planes, one block per plane and turn, through all items before the next group; or all planes,
+// i.e. item by item in the row tiles above.  The dispatcher deals consecutive blocks to the 8 XCDs in turn, so that with 8
+// planes each XCD writes one plane and keeps to its address translations.
+//   Slots always take groups, of one size: against item by item, 40 shapes (128 to 2560 channels, 2,048 to 24,000 tokens,
+//   chunks of 256 tokens to one item) 8 % faster on average, between -1 (512 channels) and +19 %; groups of 4 +7.6 %, but
+//   better by 1 to 3 % for 512 channels, plane by plane +4.6 %.  With 10 planes two groups of 5 are 15 % (128 channels) to
+//   4 % (640) faster than 8 and 2.
 //   Whole spans take groups for launches of up to 896 MiB of 16-bit rows.  32 layers x 1024 channels in 256-token items,
 //   five mixes of levels and destinations: 512 tokens +2 to +10 %, 1,024 +2 to +7, 2,048 +4 to +12, 4,096 +1 to +5,
-//   6,144 (768 MiB) 0 to +4, 8,192 (1 GiB) -8 to -2.
+//   6,144 (768 MiB) 0 to +4, 8,192 (1 GiB) -8 to -2.  Here it has to be 8: groups of 5 to 7 planes spread each plane over
+//   all XCDs (6 layers in two groups of 6: 0.75 to 1.0 of the speed of all planes at once).  Where 8 does not divide the
+//   planes, the smaller last group costs what the others gain unless there are two full groups before it and the launch
+//   is over 80 MiB (13 layer counts from 5 to 42 that are no multiple of 4, 1024 to 4096 channels, 16 to 400 MiB: with this
+//   rule 0.91 to 1.25 of the speed of all planes, 1.02 on average; groups of one size 0.75 to 1.2).
 //   A destination in which a token's rows of all layers lie side by side (layer stride below token stride) always takes all
 //   planes: consecutive blocks then fill a token's rows, groups leave holes between them.  32 layers, 256 to 8,192 tokens,
 //   1 to 16 heads, all levels: groups 0.74 to 1.07 times as fast on all but the smallest launches (1024 channels, 2,048
@@ -62,11 +67,12 @@ inline DecPlan decode_plan(int heads, int l, int n_items, int max_tokens, int64_
   p.short_launch = !p.slots && mib <= 256;
   p.row_tile = near || side_by_side || p.slots ? 1 : max_tokens <= 8192 ? 4 : 0x7fffffff;
   p.plane_group = planes;
-  if (!side_by_side && (p.slots || mib <= 896)) {
-    p.row_tile = 1;
-    const int most = p.slots && heads == 4 ? 4 : 8;
-    const int groups = (planes + most - 1) / most;
+  if (p.slots && !side_by_side) {
+    const int most = heads == 4 ? 4 : 8, groups = (planes + most - 1) / most;
     p.plane_group = (planes + groups - 1) / groups;
+  } else if (!p.slots && !side_by_side && mib <= 896 && (planes % 8 == 0 || (planes > 16 && mib > 80))) {
+    p.row_tile = 1;
+    p.plane_group = 8;
   }
   // a grid's x dimension counts threads in 32 bits
   while (p.plane_group > 1 && p.blocks * p.plane_group * 64 * p.waves > 0xffffffffLL) p.plane_group = (p.plane_group + 1) / 2;

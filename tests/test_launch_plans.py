@@ -142,3 +142,14 @@ def test_decode_takes_all_planes_where_layers_lie_side_by_side(plans):
         for n, items in ((256, 1), (256, 8), (8192, 1)):
             assert plans("dec_plan", heads, 32, items, n, c, 32 * c)[4:6] == [64, 1]
             assert plans("dec_plan", heads, 32, items, n, *dense(c, n))[4] <= 8 or (heads % 8 == 0 and n * heads > 7 * 8192)
+
+
+def test_decode_whole_spans_take_groups_of_eight_planes_or_none(plans):
+    """Groups of 5 to 7 planes put every plane on all XCDs: 6 layers in two groups of 6 took up to a third longer."""
+    for l in range(1, 81):
+        for n in (128, 512, 2048, 4096):
+            mib = l * n / 256
+            group, tile = plans("dec_plan", 8, l, 1, n, *dense(1024, n))[4:6]
+            assert group in (8, 2 * l)
+            grouped = mib <= 896 and (l % 4 == 0 or (l > 8 and mib > 80))
+            assert group == (8 if grouped else 2 * l) and (not grouped or tile == 1), (l, n)
