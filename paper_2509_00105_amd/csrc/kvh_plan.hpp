@@ -46,9 +46,10 @@ struct DecPlan {
 //   planes: consecutive blocks then fill a token's rows, groups leave holes between them.  32 layers, 256 to 8,192 tokens,
 //   1 to 16 heads, all levels: groups 0.74 to 1.07 times as fast on all but the smallest launches (1024 channels, 2,048
 //   tokens at 8 bits 77 us, in groups 88; 640 channels, 8,192 tokens at 2 bits 108 and 145).
-// Launches of whole spans of up to 256 MiB also get two blocks per CU: what they write is gone before the write stream
-// has settled, and more waves in flight hide the start.  Both together: 64 MiB +11 to +21 %, 128 MiB +14 to +17, 256 MiB
-// +4 to +23; two blocks alone 512 MiB -4 to 0.
+// Launches of whole spans of up to 80 MiB also get two blocks per CU: what they write is gone before the write stream
+// has settled, and more waves in flight hide the start.  Nine layer counts from 2 to 80, 1024 to 4096 channels, all levels,
+// two blocks against one in the same order: 48 MiB +3 to +8 % on average, 64 MiB +1 to +4, 80 MiB -1, 96 MiB -1 to -3, 128
+// MiB 0 to -2, 192 and 256 MiB -1 to -2 (single cases down to -8 %).
 inline DecPlan decode_plan(int heads, int l, int n_items, int max_tokens, int64_t layer_stride, int64_t token_stride) {
   DecPlan p;
   p.slots = heads % 8 != 0;
@@ -64,7 +65,7 @@ inline DecPlan decode_plan(int heads, int l, int n_items, int max_tokens, int64_
   const bool near = (int64_t)l * layer_stride * 2 <= ((int64_t)1 << 29);
   const bool side_by_side = layer_stride < token_stride;
   const double mib = 4.0 * l * heads * 128 * max_tokens * n_items / (1 << 20);  // of 16-bit rows
-  p.short_launch = !p.slots && mib <= 256;
+  p.short_launch = !p.slots && mib <= 80;
   p.row_tile = near || side_by_side || p.slots ? 1 : max_tokens <= 8192 ? 4 : 0x7fffffff;
   p.plane_group = planes;
   if (p.slots && !side_by_side) {

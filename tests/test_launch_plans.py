@@ -153,3 +153,14 @@ def test_decode_whole_spans_take_groups_of_eight_planes_or_none(plans):
             assert group in (8, 2 * l)
             grouped = mib <= 896 and (l % 4 == 0 or (l > 8 and mib > 80))
             assert group == (8 if grouped else 2 * l) and (not grouped or tile == 1), (l, n)
+
+
+def test_decode_two_blocks_per_cu_only_for_small_launches(plans):
+    """Above 80 MiB of rows a second block per CU costs up to 8 %."""
+    for heads, l in ((8, 4), (8, 32), (16, 4), (32, 80), (16, 24)):
+        row_mib = 4 * l * heads * 128 / 2**20
+        for mib in (16, 48, 79, 81, 96, 128, 255):
+            n = int(mib / row_mib)
+            if n:
+                assert plans("dec_plan", heads, l, 1, n, *dense(128 * heads, n))[1] == int(n * row_mib <= 80), (heads, l, mib)
+    assert not any(plans("dec_plan", heads, 4, 1, 256, *dense(128 * heads, 256))[1] for heads in (1, 2, 4, 5, 12))
