@@ -646,7 +646,7 @@ __device__ __forceinline__ void decode_slots(const DecodeParams& a, const kvh_it
 }
 
 // grid = (blocks of a plane x planes of a group, items, plane groups).  Rows of whole spans: a block is 64 rows of a span
-// (span fastest), wave w takes rows 8 w .. 8 w + 7; otherwise (SLOTS) a block is 8 consecutive units of slots.
+// (span fastest), wave w takes rows 8 w .. 8 w + 7; otherwise (SLOTS) a block is `waves` consecutive units of slots.
 // Waves per SIMD the register allocation is held to.  The kernel needs about 100 registers,
 // which would let two blocks (16 waves) share a CU; the write stream does better with fewer waves in flight.  Measured
 // on the 8K-token shape with plain non-temporal stores, 8 / 4 / 2 bits, % of HBM peak in the benchmark's rotation:
@@ -751,7 +751,7 @@ __global__ __launch_bounds__(kDecThreads) KVH_DEC_OCC(SHORT) void decode_kernel(
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   if constexpr (SLOTS) {
     if (it.n_tokens < 1) return;
-    const uint32_t unit = (uint32_t)bx * kDecWaves + (uint32_t)wave;
+    const uint32_t unit = (uint32_t)bx * (uint32_t)a.waves + (uint32_t)wave;
     switch (consistent ? it.level : -1) {
       case 0: decode_slots<DT, 8>(a, it, item_idx, lay_kv >> 1, lay_kv & 1, unit, drop); break;
       case 1: decode_slots<DT, 4>(a, it, item_idx, lay_kv >> 1, lay_kv & 1, unit, drop); break;
@@ -789,6 +789,7 @@ int launch_decode(const DecodeParams& a, int dt, int n_items, int max_tokens, hi
   b.max_tokens = max_tokens;
   b.row_tile = plan.row_tile;
   b.plane_blocks = (int)plan.blocks;
+  b.waves = plan.waves;
   b.plane_group = plan.plane_group;
   const dim3 grid((unsigned)(plan.blocks * b.plane_group), (unsigned)n_items, (unsigned)((2 * a.l + b.plane_group - 1) / b.plane_group));
   b.by_group = Divisor((uint32_t)b.plane_group);
@@ -799,7 +800,7 @@ int launch_decode(const DecodeParams& a, int dt, int n_items, int max_tokens, hi
     return plan.slots ? decode_kernel<D, true, false> : plan.short_launch ? decode_kernel<D, false, true> : decode_kernel<D, false, false>;
   };
   auto kernel = dt == KVH_F16 ? pick(std::integral_constant<int, KVH_F16>{}) : pick(std::integral_constant<int, KVH_BF16>{});
-  launch_kernel(kernel, grid, dim3(kDecThreads), 0u, stream, b);
+  launch_kernel(kernel, grid, dim3((unsigned)(plan.waves * kWave)), 0u, stream, b);
   KVH_HIP_CHECK_LAUNCH();
   return KVH_OK;
 }

@@ -19,6 +19,11 @@ struct DecPlan {
 
 // Rows of whole 1024-channel spans: a block is 64 rows of a span.  Any other row length: units of 64 (row, head) slots, a
 // wave each; the K units, whose row blocks are rounded up per set of heads, are the more numerous.
+// Waves of a block of slots.  The waves are independent of each other.  With 8 a block holds 512 (row, head) pairs, four
+// times what a block of spans holds of 2 heads, and a small launch leaves compute units without one.  Below 384 such blocks
+// (three for two compute units) a block is one wave: 1 to 12 heads, 4 x 256 to 4 x 3,001 and 80 x 256 tokens, all levels
+// 0.96 to 1.5 times as fast as blocks of 8 (2 heads 4 x 256 raw 5.2 -> 3.9 us, 3 heads 80 x 256 at 4 bits 10.9 -> 8.3); from
+// 384 blocks on 0.87 to 1.06 (2 heads 32 x 2,048 raw 27 -> 31).
 //
 // Row tile.  Destination planes within 1 GiB of each other: planes first (one block per plane and turn), worth
 // 1-2 % there over anything longer.  Beyond that: four blocks (256 rows) per plane and turn for items of up to
@@ -45,7 +50,9 @@ struct DecPlan {
 //   A destination in which a token's rows of all layers lie side by side (layer stride below token stride) always takes all
 //   planes: consecutive blocks then fill a token's rows, groups leave holes between them.  32 layers, 256 to 8,192 tokens,
 //   1 to 16 heads, all levels: groups 0.74 to 1.07 times as fast on all but the smallest launches (1024 channels, 2,048
-//   tokens at 8 bits 77 us, in groups 88; 640 channels, 8,192 tokens at 2 bits 108 and 145).
+//   tokens at 8 bits 77 us, in groups 88; 640 channels, 8,192 tokens at 2 bits 108 and 145).  Only small launches of 4 heads
+//   (blocks of one wave) keep groups of 4: 32 x 256, 80 x 256 and 4 x 1,000 tokens 1.04 of the speed of all planes on
+//   average, 0.92 to 1.24.
 // Launches of whole spans of up to 80 MiB also get two blocks per CU: what they write is gone before the write stream
 // has settled, and more waves in flight hide the start.  Nine layer counts from 2 to 80, 1024 to 4096 channels, all levels,
 // two blocks against one in the same order: 48 MiB +3 to +8 % on average, 64 MiB +1 to +4, 80 MiB -1, 96 MiB -1 to -3, 128
@@ -58,6 +65,10 @@ inline DecPlan decode_plan(int heads, int l, int n_items, int max_tokens, int64_
     const int log_s = lowest_bit(heads);
     const int64_t units = (((int64_t)max_tokens + (64 >> log_s) - 1) / (64 >> log_s)) * (heads >> log_s);
     p.blocks = (units + p.waves - 1) / p.waves;
+    if ((double)p.blocks * 2 * l * n_items < 384) {
+      p.waves = 1;
+      p.blocks = units;
+    }
   } else {
     p.blocks = (((int64_t)max_tokens + 63) / 64) * (heads / 8);
   }
@@ -68,7 +79,7 @@ inline DecPlan decode_plan(int heads, int l, int n_items, int max_tokens, int64_
   p.short_launch = !p.slots && mib <= 80;
   p.row_tile = near || side_by_side || p.slots ? 1 : max_tokens <= 8192 ? 4 : 0x7fffffff;
   p.plane_group = planes;
-  if (p.slots && !side_by_side) {
+  if (p.slots && (!side_by_side || (heads == 4 && p.waves == 1))) {
     const int most = heads == 4 ? 4 : 8, groups = (planes + most - 1) / most;
     p.plane_group = (planes + groups - 1) / groups;
   } else if (!p.slots && !side_by_side && mib <= 896 && (planes % 8 == 0 || (planes > 16 && mib > 80))) {
