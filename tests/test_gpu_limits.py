@@ -114,9 +114,9 @@ def test_one_long_entry_in_a_single_blob(kvh):
 
 @pytest.mark.parametrize("l,n_big", [(5, 56000), (9, 32000)])
 def test_planes_far_apart(kvh, l, n_big):
-    """Entries cut out of a tensor whose (layer, K|V) planes lie more than 1 GiB apart in all: the kernels then walk
-    the planes in another block order (the encoder in groups of 8 planes, here one or two full groups and a last
-    group of 2; the decoder plane by plane), which must not change a byte."""
+    """Entries cut out of a tensor whose (layer, K|V) planes lie more than 1 GiB apart in all: the encoder then walks the
+    planes in groups of 8, here one or two full groups and a last group of 2, which must not change a byte.  (The decoder,
+    whose order follows the size of the launch as well, keeps its tiles of one block here.)"""
     dt, n, c, t0 = BF16, 300, 1024, 100
     k, v = gen.make_kv(l, n, c, dt, seed=100 + l)
     kbig = torch.zeros((l, n_big, c), dtype=TDT[dt], device="cuda"); vbig = torch.zeros_like(kbig)

@@ -1,6 +1,7 @@
 """GPU parity over row lengths: heads per row that do and do not fill a wave's span, token counts at the edges of the
-units that rows of 1, 2, 4 and 8 heads are cut into, layer counts that split unevenly into plane groups.  Bit equality
-with the oracle throughout (the definition fixes every bit)."""
+units that rows of 1, 2, 4 and 8 heads are cut into, layer counts whose last plane group is a smaller one (5 layers of 4
+heads: groups of 4, 4 and 2 planes; 10 and 11 of 5 heads: 7, 7, 6 and 8, 8, 6).  Bit equality with the oracle throughout (the
+definition fixes every bit)."""
 import numpy as np
 import pytest
 
@@ -12,7 +13,8 @@ pytestmark = pytest.mark.gpu
 
 TDT = {gen.F16: torch.float16, gen.BF16: torch.bfloat16}
 CASES = [(heads, l, dt) for heads, l, dt in (
-    (1, 2, gen.BF16), (1, 5, gen.F16), (2, 1, gen.F16), (2, 9, gen.BF16), (3, 3, gen.BF16), (4, 4, gen.F16), (5, 7, gen.BF16),
+    (1, 2, gen.BF16), (1, 5, gen.F16), (2, 1, gen.F16), (2, 9, gen.BF16), (3, 3, gen.BF16), (4, 4, gen.F16), (4, 5, gen.BF16), (5, 7, gen.BF16),
+    (5, 10, gen.F16), (5, 11, gen.BF16),
     (6, 2, gen.F16), (7, 1, gen.BF16), (8, 2, gen.F16), (10, 2, gen.BF16), (12, 1, gen.F16), (16, 1, gen.BF16))]
 
 
@@ -98,8 +100,9 @@ def test_row_lengths_batch(kvh, heads):
 
 @pytest.mark.parametrize("l,n", [(9, 8191), (20, 15000)])
 def test_launch_sizes(kvh, l, n):
-    """Whole spans on both sides of the sizes at which the decoder changes its block order and occupancy (288 MiB and 1.1 GiB
-    of rows here; the other tests decode less than 256 MiB): every row equals what 640-token pieces of the entry give."""
+    """Whole spans on both sides of the sizes at which the decoder changes its block order and occupancy: 288 MiB of rows walk
+    groups of 8, 8 and 2 planes, 1.1 GiB plane by plane, the pieces (18 to 54 MiB) all planes or groups of 8 with two blocks
+    per CU.  Every row equals what 640-token pieces of the entry give."""
     c = 1024
     kv = gen.make_kv_device(l, n, c, gen.BF16, seed=n)
     for level in range(4):
@@ -132,3 +135,94 @@ def test_layers_side_by_side(kvh, heads):
         assert status.item() == 0 and np.array_equal(blob.cpu().numpy(), want), level
         assert np.array_equal(got[0, :, 2:2 + n], wk) and np.array_equal(got[1, :, 2:2 + n], wv), level
         assert not got[:, :, :2].any() and not got[:, :, 2 + n:].any(), level
+
+
+def test_row_tiles_with_a_remainder(kvh):
+    """A batch of whole spans above 896 MiB over planes more than 1 GiB apart: row tiles of 4 blocks, and 300 tokens are 5
+    blocks, so that the last tile holds one.  Every row equals what the items give one at a time."""
+    l, m, items, c = 9, 300, 100, 1024
+    kv = gen.make_kv_device(l, m * items, c, gen.BF16, seed=3)
+    starts, lengths, levels = [m * i for i in range(items)], [m] * items, [i % 4 for i in range(items)]
+    offs = np.concatenate([[0], np.cumsum([kvh.blob_size(l, m, c, lv) for lv in levels])]).astype(np.int64)
+    blobs = torch.zeros(int(offs[-1]), dtype=torch.uint8, device="cuda")
+    ptrs = [blobs.data_ptr() + int(o) for o in offs[:-1]]
+    kvh.encode_batch(kvh.make_enc_items(ptrs, starts, lengths, levels, "cuda"), items, m, kv[0], kv[1])
+    out, ref = torch.zeros_like(kv), torch.zeros_like(kv)
+    status = torch.zeros(items, dtype=torch.int32, device="cuda")
+    kvh.decode_batch(kvh.make_dec_items(ptrs, lengths, levels, starts, [0] * items, "cuda"), items, m, out[0], out[1], status=status)
+    for i, lv in enumerate(levels):
+        kvh.decode(blobs[int(offs[i]):int(offs[i + 1])], lv, m, ref[0], ref[1], dst_token0=starts[i])
+    torch.cuda.synchronize()
+    assert not status.any() and torch.equal(out.view(torch.int16), ref.view(torch.int16))
+    assert out.any()
+
+
+@pytest.mark.parametrize("heads", (1, 2, 3, 5, 6, 12))
+def test_refused_items(kvh, heads):
+    """Items that break a batched call's limits are refused as a whole in the layouts of these rows too: more tokens than the
+    launch covers, rows outside the 31-bit range, a bad level.  Their buffers keep every byte."""
+    l, c, dt, bound = 3, 128 * heads, gen.F16, 200
+    lengths, levels, starts = [200, 201, 70, 64, 65], [0, 1, 2, 3, 1], [0, 200, 420, 500, 600]
+    k, v = gen.make_kv(l, 700, c, dt, seed=heads)
+    kd, vd = device(k, dt), device(v, dt)
+    wants = [oracle.encode(np.ascontiguousarray(k[:, t:t + n]), np.ascontiguousarray(v[:, t:t + n]), dt, lv)
+             for t, n, lv in zip(starts, lengths, levels)]
+    bufs = [torch.full((w.size,), 0xA7, dtype=torch.uint8, device="cuda") for w in wants]
+    ptrs = [b.data_ptr() for b in bufs]
+    kvh.encode_batch(kvh.make_enc_items(ptrs, starts, lengths, [0, 1, 7, 3, 1], "cuda"), 5, bound, kd, vd)
+    torch.cuda.synchronize()
+    for i, (b, w) in enumerate(zip(bufs, wants)):
+        assert (b.cpu().numpy() == 0xA7).all() if i in (1, 2) else np.array_equal(b.cpu().numpy(), w), ("encode", i)
+    blobs = [torch.from_numpy(w).cuda() for w in wants]
+    out = torch.full((2, l, 700, c), 9.0, dtype=TDT[dt], device="cuda")
+    rows = [0, 200, 420, 2**31 - 60, -8]
+    status = torch.zeros(5, dtype=torch.int32, device="cuda")
+    kvh.decode_batch(kvh.make_dec_items([b.data_ptr() for b in blobs], lengths, levels, rows, [0] * 5, "cuda"), 5, bound, out[0], out[1],
+                     status=status)
+    torch.cuda.synchronize()
+    assert status.tolist() == [0, 1, 0, 1, 1]
+    got, untouched = host(out), np.ones(700, bool)
+    for i in (0, 2):
+        wk, wv = oracle.decode(wants[i], dt, l, lengths[i], c, levels[i])
+        at = slice(rows[i], rows[i] + lengths[i])
+        assert np.array_equal(got[0, :, at], wk) and np.array_equal(got[1, :, at], wv), ("decode", i)
+        untouched[at] = False
+    assert (got[:, :, untouched] == got[0, 0, 699, 0]).all() and got[0, 0, 699, 0] == np.float16(9.0).view(np.uint16)
+    lows = [torch.full((kvh.blob_size(l, n, c, 2),), 0x3C, dtype=torch.uint8, device="cuda") for n in lengths]
+    status.zero_()
+    kvh.transcode_batch(kvh.make_tc_items([b.data_ptr() for b in blobs], [b.data_ptr() for b in lows], lengths, levels, [2, 2, 2, 2, 9], "cuda"),
+                        5, bound, dt, l, c, status=status)
+    torch.cuda.synchronize()
+    assert status.tolist() == [0, 1, 0, 1, 1]
+    for i, low in enumerate(lows):
+        want = oracle.transcode(wants[i], dt, l, lengths[i], c, levels[i], 2) if i in (0, 2) else 0x3C
+        assert (low.cpu().numpy() == want).all(), ("transcode", i)
+
+
+@pytest.mark.parametrize("heads", (1, 2, 3, 5, 6))
+def test_non_finite_rows_stay_inside_the_blob(kvh, heads):
+    """Codes of non-finite input are unspecified, but nothing is written outside the blob, the header is as for finite input,
+    and a V group of finite values is stored as the oracle stores it."""
+    l, n, c = 2, 129, 128 * heads
+    for dt, bad in ((gen.F16, (0x7C00, 0xFC00, 0x7E00)), (gen.BF16, (0x7F80, 0xFF80, 0x7FC0))):
+        k, v = gen.make_kv(l, n, c, dt, seed=heads)
+        hit = np.random.default_rng(heads).random(v.shape) < 1 / 256
+        k0, v0 = np.where(hit, 0, k).astype(np.uint16), np.where(hit, 0, v).astype(np.uint16)
+        values = np.resize(np.array(bad, np.uint16), v.shape)
+        k, v = np.where(hit, values, k), np.where(hit, values, v)
+        clean = ~hit.reshape(l, n, heads, 128).any(-1)
+        for level in range(3):
+            size, bits = kvh.blob_size(l, n, c, level), kvh.level_bits(level)
+            buf = torch.full((size + 8192,), 0xEE, dtype=torch.uint8, device="cuda")
+            kvh.encode(device(k, dt), device(v, dt), level, blob=buf[4096:4096 + size])
+            torch.cuda.synchronize()
+            got, want = buf.cpu().numpy(), oracle.encode(k0, v0, dt, level)
+            assert (got[:4096] == 0xEE).all() and (got[4096 + size:] == 0xEE).all(), (dt, level)
+            got = got[4096:4096 + size]
+            assert np.array_equal(got[:64], want[:64])
+            for lam in range(l):
+                off = oracle.section_offsets(l, n, c, level, lam)
+                for section, width in (("vcodes", 16 * bits), ("vmeta", 4)):
+                    a, b = (x[off[section]:off[section] + n * heads * width].reshape(n, heads, width) for x in (got, want))
+                    assert np.array_equal(a[clean[lam]], b[clean[lam]]), (dt, level, lam, section)
+        assert 0.3 < clean.mean() < 0.9

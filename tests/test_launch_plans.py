@@ -175,3 +175,13 @@ def test_decode_small_launches_of_slots_take_small_blocks(plans):
     for heads, l, items, n in ((2, 32, 8, 256), (2, 80, 16, 512), (10, 32, 8, 256), (5, 80, 1, 256)):
         assert plans("dec_plan", heads, l, items, n, *dense(128 * heads, n * items))[2] == 8, (heads, l, items, n)
     assert all(plans("dec_plan", h, 4, 1, 256, *dense(128 * h, 256))[2] == 8 for h in (8, 16, 24))
+
+
+def test_gpu_tests_reach_the_orders_they_name(plans):
+    """The shapes of tests/test_gpu_row_lengths.py: uneven last plane groups, row tiles with a remainder, plane by plane."""
+    groups = {(h, l): plans("dec_plan", h, l, 1, 300, *dense(128 * h, 300))[4] for h, l in ((4, 5), (5, 10), (5, 11))}
+    assert groups == {(4, 5): 4, (5, 10): 7, (5, 11): 8}                                     # of 10, 20 and 22 planes
+    assert plans("dec_plan", 8, 9, 1, 8191, *dense(1024, 8191))[4:6] == [8, 1]               # of 18 planes
+    assert plans("dec_plan", 8, 20, 1, 15000, *dense(1024, 15000))[4:6] == [40, 0x7fffffff]
+    slots, short, _, blocks, group, tile = plans("dec_plan", 8, 9, 100, 300, *dense(1024, 30000))[:6]
+    assert (slots, short, blocks, group, tile) == (0, 0, 5, 18, 4)
