@@ -140,8 +140,8 @@ def blob_size(l: int, n_tokens: int, c: int, level: int) -> int:
 
 
 # The current stream as a raw pointer.  torch.cuda.current_stream() builds a Stream object for it, 2.7 us of the 10 a
-# call of a small chunk took on the host, more than the kernel; the raw query is 0.14 us (one chunk of 4 layers, decode:
-# 10.5 -> 7.6 us a call).
+# call of a small chunk took on the host; the raw query with the device is 0.3 us (one 256-token chunk of 4 layers,
+# decoded into pages: 10.7 -> 8.3 us a call).
 _raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
 
 

@@ -6,8 +6,8 @@ namespace kvh {
 
 namespace {
 
-constexpr int kMaxItems = 65535;   // gridDim.z
-constexpr int kMaxLayers = 32767;  // gridDim.y = 2 * l
+constexpr int kMaxItems = 65535;   // a grid's y (decoder) or z dimension (encoder, transcoder)
+constexpr int kMaxLayers = 32767;  // 2 l planes, or groups of them: y (encoder, transcoder) or z (decoder)
 
 bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
 

@@ -183,7 +183,7 @@ __device__ __forceinline__ float encode_inv(float mn, float mx) {
 // Division of values below 2^31 by a number that is fixed for a launch, as a product with a rounded-up reciprocal of 31
 // + shift binary places (shift = the divisor's bits minus the bit of an exact power of two), prepared on the host: the
 // quotient's error x * (m d - 2^(31 + shift)) / (d 2^(31 + shift)) stays below 1 / d because m d exceeds 2^(31 + shift)
-// by at most d <= 2^shift and x < 2^31.  Two instructions of the scalar unit where the operand is wave-uniform; the
+// by at most d <= 2^shift and x < 2^31.  A product and a shift on the scalar unit where the operand is wave-uniform; the
 // division sequence takes some twenty vector instructions before a wave can form its first address (2 to 3 % of the
 // transcoder's time).
 struct Divisor {
@@ -211,7 +211,7 @@ struct DecodeParams {
   int32_t* status;                     // nullable; indexed by item
   int l, c, block_tokens;
   int max_tokens;  // rows the grid covers per item: an item with more tokens is refused on the device
-  // block order chosen by the launcher (see decode_kernel)
+  // block order of the plan (see decode_kernel)
   int plane_group;  // (layer, K|V) planes that are taken through all items before the next ones
   int plane_blocks; // blocks of an item's plane
   int row_tile;     // of these, how many are taken before the next plane of the group
@@ -241,7 +241,7 @@ struct EncodeParams {
   int64_t jump;
   uint32_t hdr_orig_tokens, hdr_sink, hdr_window;
   int n_inline;  // > 0: the jobs are inline_items[0 .. n_inline), read from the kernel-argument segment
-  // block order chosen by the launcher (see encode_kernel)
+  // block order of the plan (see encode_kernel)
   int plane_group;   // (layer, K|V) planes that consecutive blocks cycle through
   int plane_blocks;  // blocks of an item's plane
   int k_slots;       // K blocks: 0 strips, 1 sets of (row, head) slots, 2 these with ordinary stores at 2 bits

@@ -647,7 +647,7 @@ __device__ __forceinline__ void decode_slots(const DecodeParams& a, const kvh_it
 
 // grid = (blocks of a plane x planes of a group, items, plane groups).  Rows of whole spans: a block is 64 rows of a span
 // (span fastest), wave w takes rows 8 w .. 8 w + 7; otherwise (SLOTS) a block is `waves` consecutive units of slots.
-// Waves per SIMD the register allocation is held to.  The kernel needs about 100 registers,
+// Waves per SIMD the register allocation is held to.  The kernel needs about 106 registers,
 // which would let two blocks (16 waves) share a CU; the write stream does better with fewer waves in flight.  Measured
 // on the 8K-token shape with plain non-temporal stores, 8 / 4 / 2 bits, % of HBM peak in the benchmark's rotation:
 // 16 waves per CU 68.4 / 71.6 / 71.3, this setting (allocation raised to three waves per SIMD, one block per CU)
@@ -658,7 +658,7 @@ __device__ __forceinline__ void decode_slots(const DecodeParams& a, const kvh_it
 #define KVH_DEC_WPE 3
 #endif
 #define KVH_DEC_OCC(SHORT) __attribute__((amdgpu_waves_per_eu((SHORT) ? 4 : KVH_DEC_WPE, (SHORT) ? 4 : KVH_DEC_WPE)))
-// SHORT: two blocks per CU, for launches that write little (see the launcher).
+// SHORT: two blocks per CU, for launches that write little (see decode_plan).
 template <int DT, bool SLOTS, bool SHORT>
 __global__ __launch_bounds__(kDecThreads) KVH_DEC_OCC(SHORT) void decode_kernel(DecodeParams a) {
   const int item_idx = blockIdx.y;

@@ -8,7 +8,7 @@
 //     quantises its own registers.
 //   V (statistics over the 128 channels of a head): a head is 16 lanes x 8 channels, reduced
 //     with a 4-step rotate-and-combine inside the 16-lane DPP row.
-// Rows that do not fill 512-channel strips take units of (row, head) slots, see encode_k_slots and encode_row_slots.
+// Rows that leave many lanes of the last strip idle take units of (row, head) slots, see encode_k_slots and encode_row_slots.
 // Quantised codes are produced with the packed float->u8 convert, which rounds to nearest even
 // and inserts the byte in one instruction; narrow codes are routed to their byte at that point.
 #include "kvh_common.hpp"
@@ -501,7 +501,7 @@ __device__ __forceinline__ void encode_v_block(const EncodeParams& a, const kvh_
   }
 }
 
-// ---- rows that are not a multiple of 512 channels --------------------------------------------------------
+// ---- rows that leave many lanes of a strip idle (encode_plan has the rule) -------------------------------
 // Strips of 512 channels leave lanes without work when a row ends inside one: three of four with rows of 128 channels.
 // Here the 64 lanes x 16 accesses of a wave are 64 (row, head) slots, slot 4 i + j being lanes 16 j .. 16 j + 15 of
 // access i.
@@ -510,8 +510,8 @@ __device__ __forceinline__ void encode_v_block(const EncodeParams& a, const kvh_
 //     whatever S is, and meet in LDS as they do for strips.
 //   V, raw level: 64 consecutive (row, head) pairs in memory order, so codes and metadata are contiguous.
 // Consecutive slots are consecutive rows or heads, so that an access covers whole cache lines of codes where it can.
-// 80 layers x 8192 tokens x 128 channels in 512-token items, 2 bits: 168 -> 70 us (2.3 -> 5.4 TB/s); 20 x 3001 x 640 fp16
-// in one item, 4 bits: 47.4 -> 39.5 us; 32 x 12000 x 256, 4 bits: 106 -> 89 us.  Bound by memory now, as strips are.
+// 80 layers x 8192 tokens x 128 channels in 512-token items, 2 bits: 168 -> 68 us (2.3 -> 5.6 TB/s); 20 x 3001 x 640 fp16
+// in one item, 4 bits: 47.2 -> 39.2 us; 32 x 12000 x 256, 4 bits: 107 -> 83 us.  Bound by memory now, as strips are.
 template <int DT, int BITS, bool PLAIN = false>
 __device__ __forceinline__ void encode_k_slots(const EncodeParams& a, const kvh_enc_item& it, uint8_t* layer_base,
                                                const LayerGeom& geo, int lam, int bx, float* red, int split, int64_t jump) {
@@ -718,7 +718,7 @@ __global__ __launch_bounds__(kEncThreads) __attribute__((amdgpu_waves_per_eu(4, 
   const int split = drop.split;
   const int64_t jump = drop.jump;
   const int nstrips = (a.c + kStripCh - 1) / kStripCh;
-  // Block order (see the launcher): consecutive blocks take the same tile of the `plane_group` consecutive (layer, K|V)
+  // Block order (see launch_encode): consecutive blocks take the same tile of the `plane_group` consecutive (layer, K|V)
   // planes of a group, then the next tile of those planes; the groups of an item follow each other (the last one may be
   // smaller).
   int lay_kv, bx;
