@@ -672,8 +672,8 @@ __global__ __launch_bounds__(kDecThreads) KVH_DEC_OCC(SHORT) void decode_kernel(
     const int per_plane = a.plane_blocks;
     const int planes = 2 * a.l - first_plane < a.plane_group ? 2 * a.l - first_plane : a.plane_group;
     if (lin >= per_plane * planes) return;  // the last group may be smaller
-    // Slots always have tiles of 1.  Whole spans take the general form for them as well: with the short one the compiler
-    // allocates the row loops differently, and the 4-bit level loses 2 % (75.1 against 76.1 to 77.2 % of HBM peak in the benchmark).
+    // Slots always have tiles of 1.  Whole spans take the general form for them as well: the short one lays their row loops
+    // out differently, and the 4-bit level is 0.5 to 1 point of HBM peak lower in the benchmark (75.1 against 75.4 to 76.1).
     if constexpr (SLOTS) {
       bx = planes == a.plane_group ? (int)a.by_group.quotient((uint32_t)lin) : lin / planes;
       lay_kv = first_plane + (lin - bx * planes);
