@@ -785,6 +785,7 @@ __global__ __launch_bounds__(kDecThreads) KVH_DEC_OCC(SHORT) void decode_kernel(
 int launch_decode(const DecodeParams& a, int dt, int n_items, int max_tokens, hipStream_t stream) {
   const int heads = a.c / kGroup;
   const DecPlan plan = decode_plan(heads, a.l, n_items, max_tokens, a.layer_stride, a.token_stride);
+  if (!grid_fits(plan.blocks, plan.plane_group, plan.waves)) return KVH_E_HIP;
   DecodeParams b = a;
   b.max_tokens = max_tokens;
   b.row_tile = plan.row_tile;

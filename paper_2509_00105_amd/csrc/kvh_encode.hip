@@ -833,8 +833,8 @@ int launch_encode(const EncodeParams& a, int dt, int n_items, int max_tokens, hi
   b.plane_group = max_tokens >= 8192 ? 2 : near && max_tokens <= 512 ? 2 * a.l : 8;
   b.plane_blocks = (int)gx;
   if (b.plane_group > 2 * a.l) b.plane_group = 2 * a.l;
-  // the x dimension counts threads in 32 bits
-  while (b.plane_group > 1 && gx * b.plane_group * kEncThreads > 0xffffffffLL) b.plane_group = (b.plane_group + 1) / 2;
+  while (b.plane_group > 1 && !grid_fits(gx, b.plane_group, plan.waves)) b.plane_group = (b.plane_group + 1) / 2;
+  if (!grid_fits(gx, b.plane_group, plan.waves)) return KVH_E_HIP;
   b.by_group = Divisor((uint32_t)b.plane_group);
   b.by_strips = Divisor((uint32_t)nstrips);
   b.by_heads = Divisor((uint32_t)heads);

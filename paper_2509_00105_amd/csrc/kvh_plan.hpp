@@ -8,6 +8,10 @@ namespace kvh {
 
 inline int lowest_bit(int x) { return __builtin_ctz((unsigned)x); }
 
+// A grid's x dimension counts threads in 32 bits.  A launch beyond that is refused by its launcher: cut down to 32 bits the
+// block count could pass for a small one that covers a part of the rows.
+inline bool grid_fits(int64_t blocks, int planes, int waves) { return blocks <= 0xffffffffLL / (64LL * waves * planes); }
+
 // ---- decoder ----------------------------------------------------------------------------------------------------
 struct DecPlan {
   bool slots;           // rows in units of 64 (row, head) slots, otherwise in 1024-channel spans
@@ -86,8 +90,7 @@ inline DecPlan decode_plan(int heads, int l, int n_items, int max_tokens, int64_
     p.row_tile = 1;
     p.plane_group = 8;
   }
-  // a grid's x dimension counts threads in 32 bits
-  while (p.plane_group > 1 && p.blocks * p.plane_group * 64 * p.waves > 0xffffffffLL) p.plane_group = (p.plane_group + 1) / 2;
+  while (p.plane_group > 1 && !grid_fits(p.blocks, p.plane_group, p.waves)) p.plane_group = (p.plane_group + 1) / 2;
   return p;
 }
 

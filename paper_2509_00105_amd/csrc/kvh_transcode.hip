@@ -888,6 +888,7 @@ __global__ __launch_bounds__(kTcThreads) KVH_TC_OCC void transcode_kernel(Transc
 int launch_transcode(const TranscodeParams& a, int dt, int n_items, int max_tokens, hipStream_t stream) {
   const int heads = a.c / kGroup;
   const TcPlan plan = transcode_plan(heads, a.l, n_items, max_tokens);
+  if (!grid_fits(plan.blocks, 1, kTcWaves)) return KVH_E_HIP;
   TranscodeParams b = a;
   b.max_tokens = max_tokens;
   b.k_log_s = plan.log_s;

@@ -21,6 +21,7 @@ extern "C" void enc_plan(int heads, int l, int items, int tokens, int64_t* o) {
 extern "C" void dec_plan(int heads, int l, int items, int tokens, int64_t layer_stride, int64_t token_stride, int64_t* o) {
   const DecPlan p = decode_plan(heads, l, items, tokens, layer_stride, token_stride);
   o[0] = p.slots; o[1] = p.short_launch; o[2] = p.waves; o[3] = p.blocks; o[4] = p.plane_group; o[5] = p.row_tile;
+  o[6] = grid_fits(p.blocks, p.plane_group, p.waves);
 }
 """
 
@@ -131,8 +132,10 @@ def test_decode_plan_covers_rows_and_planes(plans, heads):
 
 def test_decode_grid_fits_the_dispatcher(plans):
     for heads, l, n in ((8, 32767, 64), (1, 32767, 100000), (8, 80, 2**28), (5, 80, 2**26)):
-        slots, _, waves, blocks, group, _ = plans("dec_plan", heads, l, 65535, n, *dense(128 * heads, n))[:6]
-        assert ceil(2 * l, group) <= 65535 and (group == 1 or blocks * group * 64 * waves < 2**32)
+        slots, _, waves, blocks, group, _, fits = plans("dec_plan", heads, l, 65535, n, *dense(128 * heads, n))[:7]
+        assert ceil(2 * l, group) <= 65535 and fits and blocks * group * 64 * waves < 2**32
+    for heads, n in ((8, 2**31 - 1), (9, 2**31 - 1), (1025, 2**31 - 1), (2**24 - 1, 2**31 - 1)):  # refused, not cut down to 32 bits
+        assert not plans("dec_plan", heads, 1, 1, n, *dense(128 * heads, 1))[6]
 
 
 def test_decode_takes_all_planes_where_layers_lie_side_by_side(plans):
