@@ -791,7 +791,7 @@ int launch_decode(const DecodeParams& a, int dt, int n_items, int max_tokens, hi
   b.row_tile = plan.row_tile;
   b.plane_blocks = (int)plan.blocks;
   b.waves = plan.waves;
-  b.plane_group = plan.plane_group;
+  b.plane_group = plan.turn;
   const dim3 grid((unsigned)(plan.blocks * b.plane_group), (unsigned)n_items, (unsigned)((2 * a.l + b.plane_group - 1) / b.plane_group));
   b.by_group = Divisor((uint32_t)b.plane_group);
   b.by_heads = Divisor((uint32_t)heads);

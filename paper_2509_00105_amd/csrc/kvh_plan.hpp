@@ -19,6 +19,7 @@ struct DecPlan {
   int waves;            // of a block
   int64_t blocks;       // of a (layer, K|V) plane
   int plane_group, row_tile;  // block order, see decode_kernel
+  int turn;             // planes taken, one block each, before the next rows; below plane_group only for a single item
 };
 
 // Rows of whole 1024-channel spans: a block is 64 rows of a span.  Any other row length: units of 64 (row, head) slots, a
@@ -57,6 +58,19 @@ struct DecPlan {
 //   tokens at 8 bits 77 us, in groups 88; 640 channels, 8,192 tokens at 2 bits 108 and 145).  Only small launches of 4 heads
 //   (blocks of one wave) keep groups of 4: 32 x 256, 80 x 256 and 4 x 1,000 tokens 1.04 of the speed of all planes on
 //   average, 0.92 to 1.24.
+// Turns of whole spans.  Above 80 MiB the planes of a launch are better taken 4 (up to 1,400 MiB) or 8 at a time, one block
+// each, than 8 or all, where a plane is neither small nor large: what is written at one time then lies close together,
+// which counts most for pages of 16 tokens (32 KiB of 1024 channels, in random order: 8,192 tokens of 32 layers at 4 bits 231 ->
+// 219 us, contiguous 208 -> 206).  230 launches over 4 to 80 layers, 1024 and 2048 channels, items of 256 tokens to one item, all
+// levels, against groups of 8 or the row tiles below:
+//   above 896 MiB with planes of up to 40 MiB (items of less than 512 tokens), 64 MiB (1,024) or 128 MiB: 0.96 to 1.21 times as
+//   fast, 1.04 on average (70 layers x 7,362 tokens in pages 551 -> 500 us, 48 x 6,000 in one item 281 -> 242); with larger
+//   planes 0.89 to 1.07 (32 x 32,768 in 256-token items at 2 bits 787 -> 856), 2 planes at a time 0.87 to 1.2;
+//   80 to 896 MiB, 1024 channels, more than 10 planes of 4.5 to 16 MiB: turns of 4 0.98 to 1.2 times as fast as groups of 8, 1.02
+//   on average (10 x 5,000 at 4 bits 44.7 -> 41.5 us); smaller planes 0.88 to 1.06, larger ones 0.88 to 1.02, 2048 channels 0.98 to
+//   1.05, 10 planes 0.90 to 1.04.
+// For a single item groups and turns are the same order.  Items of more than 8,192 tokens that are alone stay plane by plane
+// (1.00 to 1.1).
 // Launches of whole spans of up to 80 MiB also get two blocks per CU: what they write is gone before the write stream
 // has settled, and more waves in flight hide the start.  Nine layer counts from 2 to 80, 1024 to 4096 channels, all levels,
 // two blocks against one in the same order: 48 MiB +3 to +8 % on average, 64 MiB +1 to +4, 80 MiB -1, 96 MiB -1 to -3, 128
@@ -90,7 +104,20 @@ inline DecPlan decode_plan(int heads, int l, int n_items, int max_tokens, int64_
     p.row_tile = 1;
     p.plane_group = 8;
   }
+  int turn = 0;
+  if (!p.slots && !side_by_side && mib > 80) {
+    const double plane = mib / planes;
+    if (mib <= 896) turn = heads == 8 && planes > 10 && plane >= 4.5 && plane <= 16 ? 4 : 0;
+    else if (plane <= (max_tokens < 512 ? 40 : max_tokens < 1024 ? 64 : 128)) turn = mib <= 1400 ? 4 : 8;
+  }
+  if (turn > 0 && turn < planes && (n_items > 1 || max_tokens <= 8192)) {
+    p.row_tile = 1;
+    if (n_items > 1) p.plane_group = turn;
+  } else {
+    turn = p.plane_group;
+  }
   while (p.plane_group > 1 && !grid_fits(p.blocks, p.plane_group, p.waves)) p.plane_group = (p.plane_group + 1) / 2;
+  p.turn = turn < p.plane_group ? turn : p.plane_group;
   return p;
 }
 

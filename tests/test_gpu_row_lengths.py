@@ -157,6 +157,27 @@ def test_row_tiles_with_a_remainder(kvh):
     assert out.any()
 
 
+@pytest.mark.parametrize("l,items,m", [(11, 8, 300), (31, 13, 600), (57, 10, 660)])
+def test_turns_of_planes_through_all_items(kvh, l, items, m):
+    """Batches of whole spans of 103 MiB to 1.4 GiB: planes 4 or 8 at a time through all items, the last turn a smaller one.  Every
+    row equals what the items give one at a time."""
+    c = 1024
+    kv = gen.make_kv_device(l, m * items, c, gen.BF16, seed=l)
+    starts, lengths, levels = [m * i for i in range(items)], [m - i for i in range(items)], [i % 4 for i in range(items)]
+    offs = np.concatenate([[0], np.cumsum([kvh.blob_size(l, n, c, lv) for n, lv in zip(lengths, levels)])]).astype(np.int64)
+    blobs = torch.zeros(int(offs[-1]), dtype=torch.uint8, device="cuda")
+    ptrs = [blobs.data_ptr() + int(o) for o in offs[:-1]]
+    kvh.encode_batch(kvh.make_enc_items(ptrs, starts, lengths, levels, "cuda"), items, m, kv[0], kv[1])
+    out, ref = torch.zeros_like(kv), torch.zeros_like(kv)
+    status = torch.zeros(items, dtype=torch.int32, device="cuda")
+    kvh.decode_batch(kvh.make_dec_items(ptrs, lengths, levels, starts, [0] * items, "cuda"), items, m, out[0], out[1], status=status)
+    for i, lv in enumerate(levels):
+        kvh.decode(blobs[int(offs[i]):int(offs[i + 1])], lv, lengths[i], ref[0], ref[1], dst_token0=starts[i])
+    torch.cuda.synchronize()
+    assert not status.any() and torch.equal(out.view(torch.int16), ref.view(torch.int16))
+    assert out.any()
+
+
 @pytest.mark.parametrize("heads", (1, 2, 3, 5, 6, 12))
 def test_refused_items(kvh, heads):
     """Items that break a batched call's limits are refused as a whole in the layouts of these rows too: more tokens than the

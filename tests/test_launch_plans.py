@@ -21,7 +21,7 @@ extern "C" void enc_plan(int heads, int l, int items, int tokens, int64_t* o) {
 extern "C" void dec_plan(int heads, int l, int items, int tokens, int64_t layer_stride, int64_t token_stride, int64_t* o) {
   const DecPlan p = decode_plan(heads, l, items, tokens, layer_stride, token_stride);
   o[0] = p.slots; o[1] = p.short_launch; o[2] = p.waves; o[3] = p.blocks; o[4] = p.plane_group; o[5] = p.row_tile;
-  o[6] = grid_fits(p.blocks, p.plane_group, p.waves);
+  o[6] = grid_fits(p.blocks, p.plane_group, p.waves); o[7] = p.turn;
 }
 """
 
@@ -188,3 +188,26 @@ def test_gpu_tests_reach_the_orders_they_name(plans):
     assert plans("dec_plan", 8, 20, 1, 15000, *dense(1024, 15000))[4:6] == [40, 0x7fffffff]
     slots, short, _, blocks, group, tile = plans("dec_plan", 8, 9, 100, 300, *dense(1024, 30000))[:6]
     assert (slots, short, blocks, group, tile) == (0, 0, 5, 18, 4)
+
+
+def test_decode_turns(plans):
+    """Turns of 4 or 8 planes where a launch is large and its planes are neither small nor large; they are the plane group where
+    there are several items, and a part of it for one item, whose row tiles they replace."""
+    def turn(heads, l, items, n, strides=None):
+        group, tile, _, t = plans("dec_plan", heads, l, items, n, *(strides or dense(128 * heads, n * items)))[4:8]
+        assert t == group or (items == 1 and t < group and tile == 1)
+        return t, group
+
+    assert turn(8, 32, 32, 256) == (4, 4) and turn(8, 32, 64, 256) == (8, 8)        # 1 and 2 GiB
+    assert turn(8, 32, 128, 256)[0] == 64                                           # planes of 64 MiB
+    assert turn(8, 32, 64, 512) == (8, 8) and turn(8, 32, 64, 1024) == (8, 8) and turn(8, 32, 256, 1024)[0] == 64
+    assert turn(8, 48, 1, 6000) == (4, 96) and turn(8, 80, 1, 8192) == (8, 160) and turn(8, 80, 1, 8193) == (160, 160)
+    assert turn(8, 11, 8, 300) == (4, 4) and turn(8, 11, 1, 2400) == (4, 8)
+    assert turn(8, 32, 16, 256) == (4, 4) and turn(8, 32, 4, 256) == (8, 8) and turn(16, 32, 8, 256) == (8, 8)
+    assert turn(8, 32, 32, 256, (1024, 32 * 1024)) == (64, 64) and turn(5, 32, 32, 256) == (8, 8)
+
+
+def test_gpu_tests_reach_the_turns_they_name(plans):
+    for l, items, n, group in ((11, 8, 300, 4), (31, 13, 600, 4), (57, 10, 660, 8)):
+        assert plans("dec_plan", 8, l, items, n, *dense(1024, n * items))[4:8:3] == [group, group] and 2 * l % group
+    assert plans("dec_plan", 8, 9, 1, 8191, *dense(1024, 8191))[7] == 4 and 18 % 4
