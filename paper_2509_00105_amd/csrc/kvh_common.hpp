@@ -272,6 +272,9 @@ struct TranscodeParams {
   int max_tokens;            // rows the grid covers per item: an item with more tokens is refused on the device
   int k_log_s;               // K sets are 2^k_log_s heads (3: a span)
   Divisor by_heads, by_sets; // heads of a row, K sets of a token-group
+  // units of slots (see transcode_units)
+  int waves, groups;         // of a block: units, and token-groups whose parameters it prepares
+  Divisor by_units, by_parts, by_period;  // units and blocks of a token-group (1 block where it holds several), accesses after which heads repeat
 };
 
 int launch_decode(const DecodeParams& a, int dt, int n_items, int max_tokens, hipStream_t stream);

@@ -137,7 +137,7 @@ struct TcPlan {
 // pieces are: over 3/8 of a row's lanes with single heads, over 1/4 with pairs, 1/4 with fours.  (V alone in slots, K in
 // spans: 5 to 33 heads 0.82 to 1.3.)
 // A small launch of slots has an eighth to a half of the blocks that spans have: below 128 blocks rows of 3 heads and more
-// keep spans (4 x 3,001 tokens x 384 channels, 8 -> 4 bits: spans 13.2 us, slots 14.6; 32 x 256: 12.4 and 13.3; rows of 1
+// would keep spans (most such launches are taken by units of slots, below; 4 x 3,001 tokens x 384 channels, 8 -> 4 bits: spans 13.2 us, slots 14.6; 32 x 256: 12.4 and 13.3; rows of 1
 // and 2 heads are 0.96 to 1.8 times as fast in slots even there).
 inline TcPlan transcode_plan(int heads, int l, int n_items, int max_tokens) {
   const int spans = (heads + 7) / 8, lanes = spans * 8, idle = lanes - heads;
@@ -151,6 +151,48 @@ inline TcPlan transcode_plan(int heads, int l, int n_items, int max_tokens) {
   const int per_block = 8 >> p.log_s;
   p.blocks = (groups * p.sets + per_block - 1) / per_block;
   return p;
+}
+
+// Small launches, and short items of one or two heads, run in units of slots instead (see transcode_units).
+struct TcUnits {
+  int accesses;    // of a unit, 0: the layouts above
+  int period;      // accesses (of 8 slots) after which the heads repeat
+  int units;       // of a token-group
+  int parts;       // blocks of a token-group
+  int groups;      // token-groups of a block
+  int waves;       // of a block
+  int64_t blocks;  // of a (layer, K|V) plane
+};
+
+// In the layouts above a wave takes 16 accesses, with 8-bit codes as a chain of loads, 4 or 8 accesses at a time, and blocks
+// are 8 such waves, so that a small launch has few of them (8 heads, 3 x 309 tokens, 8 -> 4 bits: 18 blocks, 11.8 us).
+// Units of 4 accesses, all requested at once, make 4 times the blocks (5.8 us), but prepare K's parameters 4 times over.
+// 380 launches of 2 to 80 layers and 256 to 65,536 tokens, all pairs of levels, by w, the number of 16-access waves they take:
+//   w <= 512: units of 4 accesses 1.09 to 2.4 times as fast, of 8 1.13 to 1.8;
+//   w <= 1,100: units of 8 0.95 to 1.8 (7 heads, 19 x 343, 4 -> 2: 1.27), 1.4 on average; of 4 0.85 to 1.85;
+//   beyond: 8 -> 4 and 8 -> 2 bits still gain (1.03 to 1.3 at w = 2,000), 4 -> 2 loses where the layouts above keep most lanes busy
+//   (8 heads 0.93 to 0.97, 15 and 16 heads 0.82).  With more than a quarter of the lanes idle there (3, 4, 5, 9, 10 and 11 heads) units of
+//   8 are 0.87 to 1.6 times as fast, 1.16 on average, up to 2,000;
+//   1 and 2 heads up to 2,900: 1.0 to 1.8 (2,900 to 10,000: 0.88 to 1.2); items of up to 256 tokens fill half or a quarter of a
+//   block of slots: 1 head 1.5 to 2.0 at any size (18 x 17,072, 4 -> 2: 30.2 -> 18.9 us), 2 heads 1.0 to 1.3 up to 10,000.
+inline TcUnits transcode_units_plan(int heads, int l, int n_items, int max_tokens) {
+  const int64_t groups = ((int64_t)max_tokens + 127) / 128;
+  const double w = 2.0 * l * n_items * (double)groups * heads;
+  const int lanes = (heads + 7) / 8 * 8, idle = lanes - heads;
+  double most = 4 * idle > lanes ? 2000 : 1100;
+  if (heads <= 2) most = max_tokens > 256 ? 2900 : heads == 1 ? 1e18 : 10000;
+  TcUnits u{};
+  if (heads > 16 || w > most) return u;  // (16: what a block's threads prepare and its LDS holds)
+  u.accesses = w <= 512 ? 4 : 8;
+  const int log_g = lowest_bit(heads) < 3 ? lowest_bit(heads) : 3;
+  u.period = heads >> log_g;
+  u.units = 16 * heads / u.accesses;
+  u.parts = (u.units + 7) / 8;
+  u.groups = u.parts > 1 ? 1 : 8 / u.units;
+  if (u.groups > groups) u.groups = (int)groups;
+  u.waves = u.parts > 1 ? (u.units + u.parts - 1) / u.parts : u.units * u.groups;
+  u.blocks = u.parts > 1 ? groups * u.parts : (groups + u.groups - 1) / u.groups;
+  return u;
 }
 
 // ---- encoder ----------------------------------------------------------------------------------------------------

@@ -25,6 +25,8 @@
 // each instead (SLOTS), 128 slots per wave: V slots are consecutive in memory; K slots are sets of 1, 2 or 4 heads x a
 // token-group, several sets to a block, so that a lane keeps its channels.  32 layers, 8 -> 4 bits, 2,048 tokens x 128
 // channels: 30.3 -> 13.2 us, 8,192 x 256: 115 -> 41 us; 4 -> 2 bits, 12,000 x 128: 101 -> 21 us, 8,192 x 1280: 157 -> 116 us.
+//
+// Small launches, where either layout makes few blocks, run in finer units of slots: see transcode_units.
 #include <type_traits>
 
 #include "kvh_common.hpp"
@@ -451,6 +453,28 @@ __device__ __forceinline__ bool source_header_ok(const HeaderWords& h, int dt, i
   return fields && (plain || dropped);
 }
 
+// One word a thread of the header of the result; the token-dropping words are carried over.
+template <int DT, int BO>
+__device__ __forceinline__ void write_header(uint8_t* dst, const TranscodeParams& a, uint32_t n, const LayerGeom& go, const HeaderWords& hdr) {
+  const uint64_t total = kHeaderBytes + (uint64_t)a.l * go.layer_bytes();
+  uint32_t w = 0;
+  switch (threadIdx.x) {
+    case 0: w = kMagic; break;
+    case 1: w = 1u | (uint32_t)DT << 16 | (uint32_t)BO << 24; break;
+    case 2: w = (uint32_t)a.l; break;
+    case 3: w = n; break;
+    case 4: w = (uint32_t)a.c; break;
+    case 5: w = (uint32_t)kGroup | (uint32_t)kGroup << 16; break;
+    case 6: w = (uint32_t)total; break;
+    case 7: w = (uint32_t)(total >> 32); break;
+    case 8: w = hdr.c.x; break;
+    case 9: w = hdr.c.y; break;
+    case 10: w = hdr.c.z; break;
+    default: break;
+  }
+  gstore<uint32_t>(dst + 4 * threadIdx.x, w);
+}
+
 // SLOTS: the lanes are cut into (row, head) slots (see the head of the file); otherwise a span's lanes keep its channels
 // and those beyond the row idle.
 template <int DT, int BI, int BO, bool SLOTS>
@@ -612,25 +636,7 @@ __device__ __forceinline__ void transcode_block(const TranscodeParams& a, const 
     if (a.status != nullptr && threadIdx.x == 0) a.status[item_idx] = KVH_DEV_HEADER_MISMATCH;
     return;
   }
-  if (bx == 0 && lay_kv == 0 && threadIdx.x < kHeaderBytes / 4) {
-    const uint64_t total = kHeaderBytes + (uint64_t)a.l * go.layer_bytes();
-    uint32_t w = 0;
-    switch (threadIdx.x) {
-      case 0: w = kMagic; break;
-      case 1: w = 1u | (uint32_t)DT << 16 | (uint32_t)BO << 24; break;
-      case 2: w = (uint32_t)a.l; break;
-      case 3: w = n; break;
-      case 4: w = c; break;
-      case 5: w = (uint32_t)kGroup | (uint32_t)kGroup << 16; break;
-      case 6: w = (uint32_t)total; break;
-      case 7: w = (uint32_t)(total >> 32); break;
-      case 8: w = hdr.c.x; break;  // token-dropping words are carried over
-      case 9: w = hdr.c.y; break;
-      case 10: w = hdr.c.z; break;
-      default: break;
-    }
-    gstore<uint32_t>(dst + 4 * threadIdx.x, w);
-  }
+  if (bx == 0 && lay_kv == 0 && threadIdx.x < kHeaderBytes / 4) write_header<DT, BO>(dst, a, n, go, hdr);
 
   if (!is_v) {
     uint32_t om[2] = {0u, 0u};
@@ -840,15 +846,291 @@ __device__ __forceinline__ void transcode_block(const TranscodeParams& a, const 
   }
 }
 
-}  // namespace
+// ---- units of slots ----------------------------------------------------------------------------------------------
+// Any row length with every lane at work.  The (row, head) slots of a section are consecutive in memory, 8 lanes each; an
+// access is 8 consecutive slots (1 KiB of 8-bit codes), and a unit, one wave, is ACC accesses.
+//   V: consecutive accesses.
+//   K: a lane has to keep its channels, that is the head of its slot, from access to access.  With H heads a row the heads of
+//     consecutive accesses repeat after P = H / gcd(H, 8) of them, so that a unit takes every P-th access of its token-group: unit
+//     u is accesses r + P (ACC j + i), i = 0 .. ACC - 1, with r = u mod P, j = u / P.  The 16 H / ACC units of a token-group are
+//     waves of one block, or of a few.
+// A block prepares the parameters of all heads of its token-groups.  Everything a unit reads is requested before anything of it is
+// used: what bounds a small launch is its chain of trips to memory.  8 -> 4 bits bf16: 3 x 309 tokens of 8 heads 11.8 -> 5.8 us, 11 x
+// 890 14.0 -> 12.0, 10 x 2,012 of 1 head in 512-token items 8 -> 8 bits 9.6 -> 5.5; an empty launch is 3.9.
+constexpr unsigned kUnitsHeadBytes = kGroup * (sizeof(TcParams) + sizeof(Quad));  // LDS for the parameters of one head
+template <int DT, int BI, int BO, int ACC>
+__device__ __forceinline__ void transcode_units(const TranscodeParams& a, const kvh_tc_item& it, int item_idx, int lay_kv,
+                                                uint32_t bx, uint8_t* lds, uint32_t* kflags) {
+  static_assert(ACC <= kTcBatch, "one lane per V group of a unit");
+  constexpr uint32_t kInBytes = kGroup * BI / 8, kOutBytes = kGroup * BO / 8;  // of a slot
+  const int lane = threadIdx.x & (kWave - 1);
+  const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const uint32_t sub = lane % kSlotLanes, slot = lane / kSlotLanes;
+  const uint32_t n = (uint32_t)it.n_tokens, heads = (uint32_t)a.c / kGroup;
+  const int lam = lay_kv >> 1;
+  const bool is_v = lay_kv & 1;
+  const uint64_t total = (uint64_t)n * heads;
 
-// grid = (blocks of a plane, 2 * l, items)
-template <int DT, bool SLOTS>
-__global__ __launch_bounds__(kTcThreads) KVH_TC_OCC void transcode_kernel(TranscodeParams a) {
-  __shared__ TcParams kpar[kTcLaneCh * kWave];  // 16 KiB, [slot][lane]
-  __shared__ float kquad[3 * kTcLaneCh * kWave];  // 12 KiB, [coefficient][slot][lane]: the 8 -> 2 polynomials
-  __shared__ uint32_t kflags[kTcWaves];
-  kvh_tc_item it;
+  // the unit: its first slot, the slots from one access to the next, and how many slots it has at most
+  uint32_t g0 = 0, gi = 0, block_unit = 0;  // K: first token-group of the block, this wave's among them, first unit of the block
+  uint64_t s0;
+  uint32_t step = kTcSpanHeads;
+  bool live = true;
+  if (is_v) {
+    s0 = ((uint64_t)bx * (uint32_t)a.waves + wave) * (uint32_t)(ACC * kTcSpanHeads);
+  } else {
+    const uint32_t q = a.by_parts.quotient(bx);
+    g0 = q * (uint32_t)a.groups;
+    if ((uint64_t)g0 * kGroup >= n) return;  // block-uniform
+    gi = a.by_units.quotient(wave);
+    block_unit = (bx - q * a.by_parts.d) * (uint32_t)a.waves;
+    const uint32_t u = block_unit + wave - gi * a.by_units.d;
+    live = u < a.by_units.d;
+    const uint32_t j = a.by_period.quotient(u);
+    step = kTcSpanHeads * a.by_period.d;
+    s0 = (uint64_t)(g0 + gi) * (kGroup * heads) + kTcSpanHeads * (u - j * a.by_period.d) + (uint64_t)j * (ACC * step);
+  }
+  uint32_t rem = 0;
+  if (live && s0 < total) rem = total - s0 < ACC * step ? (uint32_t)(total - s0) : ACC * step;
+  rem = (uint32_t)uniform((int32_t)rem);
+  s0 = uniform(rem > 0 ? s0 : 0);
+  // accesses with something to store
+  const int count = is_v ? (int)((rem + kTcSpanHeads - 1) / kTcSpanHeads) : (int)a.by_period.quotient((rem + step - 1) / kTcSpanHeads);
+
+  const uint8_t* src = static_cast<const uint8_t*>(it.src);
+  uint8_t* dst = static_cast<uint8_t*>(it.dst);
+  const LayerGeom gin = layer_geom(it.n_tokens, a.c, BI), gout = layer_geom(it.n_tokens, a.c, BO);
+  const HeaderWords hdr = {gload<uintx4>(src), gload<uintx4>(src + 16), gload<uintx4>(src + 32)};
+  const uint8_t* in_layer = src + kHeaderBytes + (size_t)lam * gin.layer_bytes();
+  uint8_t* out_layer = dst + kHeaderBytes + (size_t)lam * gout.layer_bytes();
+  const uint8_t* in_codes = in_layer + gin.kmeta + (is_v ? gin.codes + gin.vmeta : 0) + s0 * kInBytes;  // wave-uniform
+  uint8_t* out_codes = out_layer + gout.kmeta + (is_v ? gout.codes + gout.vmeta : 0) + s0 * kOutBytes;
+  const uint32_t in_sub = sub * (kTcLaneCh * BI / 8), in_lane = slot * kInBytes + in_sub;
+  const uint32_t out_lane = slot * kOutBytes + sub * (kTcLaneCh * BO / 8);
+
+  InCodes<BI> cw[ACC];
+  // Accesses past the last re-read it; lanes whose slot lies past the end read the access's first slot.  Neither is stored.
+  auto stores = [&](int k) { return slot + (uint32_t)k * step < rem; };
+  auto out_row = [&](int k) { return uniform(out_codes + (size_t)((uint32_t)k * step) * kOutBytes) + out_lane; };
+  auto rows = [&](auto fix_tag, auto&& param_of) {
+    constexpr bool FIX = decltype(fix_tag)::value;
+#pragma unroll
+    for (int i = 0; i < ACC; ++i) {
+      if (i < count) {  // wave-uniform
+        auto param = param_of(i);  // may shuffle across lanes: taken with the whole wave enabled
+        if (stores(i)) transcode_row<DT, BI, BO, FIX>(out_row(i), cw[i], param);
+      }
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  };
+  using Yes = std::integral_constant<bool, true>;
+  using No = std::integral_constant<bool, false>;
+
+  // V metadata: lane l prepares the l-th slot of the unit.  On the table routes every lane requests a word, and the wait for it
+  // is on every path (see transcode_block).
+  const uint8_t* in_vmeta = in_layer + gin.kmeta + gin.codes + s0 * 4;
+  const bool owns = (uint32_t)lane < rem;
+  uint32_t vm = 0;
+  if (count > 0) {
+#pragma unroll
+    for (int i = 0; i < ACC; ++i) {
+      const int k = i < count ? i : count - 1;
+      cw[i].load(uniform(in_codes + (size_t)((uint32_t)k * step) * kInBytes) + (stores(k) ? in_lane : in_sub));
+    }
+    if (is_v) vm = gload<uint32_t>(in_vmeta + (owns ? lane * 4 : 0));
+  }
+  // K: pairs of channels, this thread's first and second (all heads of the block's token-groups are 2 pairs a thread at most)
+  const uint32_t pairs = (uint32_t)a.groups * heads * (kGroup / 2), threads = (uint32_t)a.waves * kWave;
+  uintx2 km[2] = {};
+  bool pact[2] = {false, false};
+  size_t pmeta[2] = {0, 0};
+  if (!is_v) {
+#pragma unroll
+    for (int e = 0; e < 2; ++e) {
+      const uint32_t pr = threadIdx.x + e * threads;
+      const uint32_t pg = a.by_heads.quotient(pr / (kGroup / 2));
+      pact[e] = pr < pairs && (uint64_t)(g0 + pg) * kGroup < n;
+      pmeta[e] = ((size_t)(g0 + pg) * (uint32_t)a.c + (pr - pg * heads * (kGroup / 2)) * 2) * 4;
+      if (pact[e]) km[e] = gload<uintx2>(in_layer + pmeta[e]);
+    }
+  }
+
+  // block-uniform verdict: every thread reads the same header
+  if (!source_header_ok(hdr, DT, BI, a.l, it.n_tokens, a.c, kHeaderBytes + (size_t)a.l * gin.layer_bytes())) {
+    if (a.status != nullptr && threadIdx.x == 0) a.status[item_idx] = KVH_DEV_HEADER_MISMATCH;
+    return;
+  }
+  if (bx == 0 && lay_kv == 0 && threadIdx.x < kHeaderBytes / 4) write_header<DT, BO>(dst, a, n, gout, hdr);
+
+  if (!is_v) {
+    const uint32_t cols = (uint32_t)a.groups * heads * kSlotLanes;  // of the parameter tables: [channel mod 16][column]
+    const uint32_t col = gi * heads * kSlotLanes;                    // first column of the wave's token-group
+    uint32_t head0;  // of the lane's slot
+    {
+      const uint32_t x = kTcSpanHeads * (block_unit + wave - gi * a.by_units.d) + slot;  // 8 u + slot: u = r mod P, and 8 P is a multiple of H
+      head0 = x - a.by_heads.quotient(x) * heads;
+    }
+    const uint32_t par_lane = col + head0 * kSlotLanes + sub;
+    TcParams* kpar = reinterpret_cast<TcParams*>(lds);
+    [[maybe_unused]] uint32_t* ktab = reinterpret_cast<uint32_t*>(lds);
+    [[maybe_unused]] float* kquad = reinterpret_cast<float*>(lds + (size_t)cols * kTcLaneCh * sizeof(TcParams));
+    bool fix = false;
+    [[maybe_unused]] uint32_t worst = kStandard;
+#pragma unroll
+    for (int e = 0; e < 2; ++e) {
+      const uint32_t pr = threadIdx.x + e * threads;
+      if (pr >= pairs) break;
+      const uint32_t meta[2] = {km[e].x, km[e].y};
+      uint32_t om[2];
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        const uint32_t lc = pr * 2 + h, at = lc % kTcLaneCh * cols + lc / kTcLaneCh;
+        if constexpr (kUseTable<BI, BO>) {
+          ktab[at] = code_table<DT, BI, BO>(meta[h], om[h]);
+        } else {
+          bool f;
+          const TcParams p = tc_params<DT, BI, BO>(meta[h], om[h], f);
+          fix |= pact[e] && f;
+          kpar[at] = p;
+          if constexpr (BI == 8 && BO == 2) {
+            Quad gq;
+            const uint32_t cls = classify82<DT>(p, gq);
+            if (pact[e] && cls > worst) worst = cls;
+            kquad[at] = gq.a;
+            kquad[cols * kTcLaneCh + at] = gq.b;
+            kquad[2 * cols * kTcLaneCh + at] = gq.c;
+          }
+        }
+      }
+      if (pact[e] && block_unit == 0) {
+        uintx2 o = {om[0], om[1]};
+        gstore<uintx2>(out_layer + pmeta[e], o);
+      }
+    }
+    if constexpr (kUseTable<BI, BO>) {
+      __syncthreads();
+      if (count == 0) return;  // wave-uniform, after the barrier
+      uint32_t tab[kTcLaneCh];
+#pragma unroll
+      for (int j = 0; j < kTcLaneCh; ++j) tab[j] = ktab[j * cols + par_lane];
+#pragma unroll
+      for (int i = 0; i < ACC; ++i) {
+        if (stores(i)) lookup_row<BI, BO>(out_row(i), cw[i], [&tab](int j) { return tab[j]; });
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      return;
+    }
+    // block-wide verdicts through one barrier: every wave leaves its own in LDS
+    const uint32_t mine = (__builtin_amdgcn_ballot_w64(fix) != 0 ? 1u : 0u) |
+                          (__builtin_amdgcn_ballot_w64(worst != kStandard) != 0 ? 2u : 0u) |
+                          (__builtin_amdgcn_ballot_w64(worst == kHard) != 0 ? 4u : 0u);
+    if (lane == 0) kflags[wave] = mine;
+    __syncthreads();
+    uint32_t all = 0;
+    for (int w = 0; w < a.waves; ++w) all |= kflags[w];
+    all = (uint32_t)__builtin_amdgcn_readfirstlane((int)all);
+    if (count == 0) return;  // wave-uniform, after the barrier
+    if constexpr (BI == 8 && BO == 2) {
+      if ((all & 4u) == 0) {  // no hard group in the block: the polynomial route
+        auto poly_rows = [&](auto standard_tag) {
+          constexpr bool STANDARD = decltype(standard_tag)::value;
+          Quad gq[kTcLaneCh];
+#pragma unroll
+          for (int j = 0; j < kTcLaneCh; ++j) {
+            gq[j].a = STANDARD ? 0.0f : kquad[j * cols + par_lane];
+            gq[j].b = STANDARD ? 0.0f : kquad[(kTcLaneCh + j) * cols + par_lane];
+            gq[j].c = STANDARD ? 0.0f : kquad[(2 * kTcLaneCh + j) * cols + par_lane];
+          }
+#pragma unroll
+          for (int i = 0; i < ACC; ++i) {
+            if (stores(i)) poly_row82<STANDARD>(out_row(i), cw[i], [&gq](int j) -> const Quad& { return gq[j]; });
+            __builtin_amdgcn_sched_barrier(0);
+          }
+        };
+        if ((all & 2u) == 0) poly_rows(Yes{}); else poly_rows(No{});
+        return;
+      }
+    }
+    auto k_rows = [&](auto fix_tag) {
+      constexpr bool FIX = decltype(fix_tag)::value;
+      TcParams p[kTcLaneCh];
+#pragma unroll
+      for (int j = 0; j < kTcLaneCh; ++j) {
+        const TcParams& s = kpar[j * cols + par_lane];
+        p[j].mn = s.mn;
+        p[j].scale = s.scale;
+        p[j].inv = s.inv;
+        p[j].top = FIX ? s.top : 0.0f;
+      }
+      rows(fix_tag, [&](int) { return [&p](int j) -> const TcParams& { return p[j]; }; });
+    };
+    if ((all & 1u) != 0) k_rows(Yes{}); else k_rows(No{});
+    return;
+  }
+
+  if (count == 0) return;  // wave-uniform; V waves never meet at a barrier
+  uint8_t* out_vmeta = out_layer + gout.kmeta + gout.codes + s0 * 4;
+  auto finish = [&](uint32_t om) {
+    if (owns) gstore<uint32_t>(out_vmeta + lane * 4, om);
+    // zero the padding that rounds the vmeta section up to 16 bytes: the unit that holds the section's last slot
+    if (s0 + rem == total && lane == 0) {
+      for (size_t o = (size_t)total * 4; o < gout.vmeta; o += 4) gstore<uint32_t>(out_vmeta - s0 * 4 + o, 0u);
+    }
+  };
+  uint32_t om;
+  if constexpr (kUseTable<BI, BO>) {
+    const uint32_t mine = code_table<DT, BI, BO>(vm, om);
+    finish(om);
+#pragma unroll
+    for (int i = 0; i < ACC; ++i) {
+      if (i < count) {  // wave-uniform; the shuffle is taken with the whole wave enabled
+        const uint32_t tab = __shfl(mine, i * kTcSpanHeads + (int)slot);
+        if (stores(i)) lookup_row<BI, BO>(out_row(i), cw[i], [tab](int) { return tab; });
+      }
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  } else {
+    bool fix;
+    const TcParams mine = tc_params<DT, BI, BO>(vm, om, fix);
+    finish(om);
+    const bool any_fix = __builtin_amdgcn_ballot_w64(owns && fix) != 0;
+    if constexpr (BI == 8 && BO == 2) {
+      Quad gq;
+      uint32_t cls = classify82<DT>(mine, gq);
+      if (!owns) cls = kStandard;  // a lane without a group has no say
+      if (__builtin_amdgcn_ballot_w64(cls == kHard) == 0) {
+        const bool all_standard = __builtin_amdgcn_ballot_w64(cls != kStandard) == 0;
+#pragma unroll
+        for (int i = 0; i < ACC; ++i) {
+          if (i < count) {  // wave-uniform; the shuffles are taken with the whole wave enabled
+            const int owner = i * kTcSpanHeads + (int)slot;
+            if (all_standard) {
+              if (stores(i)) poly_row82<true>(out_row(i), cw[i], [&gq](int) -> const Quad& { return gq; });
+            } else {
+              const Quad gr = {__shfl(gq.a, owner), __shfl(gq.b, owner), __shfl(gq.c, owner)};
+              if (stores(i)) poly_row82<false>(out_row(i), cw[i], [&gr](int) -> const Quad& { return gr; });
+            }
+          }
+          __builtin_amdgcn_sched_barrier(0);
+        }
+        return;
+      }
+    }
+    auto param_of = [&](int i) {
+      const int owner = i * kTcSpanHeads + (int)slot;
+      TcParams p;
+      p.mn = __shfl(mine.mn, owner);
+      p.scale = __shfl(mine.scale, owner);
+      p.inv = __shfl(mine.inv, owner);
+      p.top = __shfl(mine.top, owner);
+      return [p](int) -> const TcParams& { return p; };
+    };
+    if (any_fix) rows(Yes{}, param_of); else rows(No{}, param_of);
+  }
+}
+
+// The job of this block's item; its level pair as bits in * 16 + bits out, or -1: nothing to do.
+__device__ __forceinline__ int load_job(const TranscodeParams& a, kvh_tc_item& it) {
   if (a.items != nullptr) {
     const uint8_t* p = reinterpret_cast<const uint8_t*>(a.items + blockIdx.z);
     uintx4 lo = gload<uintx4>(p), hi = gload<uintx4>(p + 16);
@@ -866,17 +1148,50 @@ __global__ __launch_bounds__(kTcThreads) KVH_TC_OCC void transcode_kernel(Transc
   it.n_tokens = uniform(it.n_tokens);
   it.level_in = uniform(it.level_in);
   it.level_out = uniform(it.level_out);
-  const int bx = blockIdx.x, lay_kv = blockIdx.y;
-  if (it.n_tokens < 1) return;  // block-uniform
+  if (it.n_tokens < 1) return -1;
   const int bi = level_bits(it.level_in), bo = level_bits(it.level_out);
   // refused: a level out of range, the raw level (no codes to transcode), more tokens than the grid covers
   if (bi < 0 || bo < 0 || bi > 8 || bo > 8 || it.n_tokens > a.max_tokens) {
     if (a.status != nullptr && threadIdx.x == 0) a.status[blockIdx.z] = KVH_DEV_HEADER_MISMATCH;
-    return;
+    return -1;
   }
+  return bi * 16 + bo;
+}
+
+}  // namespace
+
+// grid = (blocks of a plane, 2 * l, items)
+template <int DT, bool SLOTS>
+__global__ __launch_bounds__(kTcThreads) KVH_TC_OCC void transcode_kernel(TranscodeParams a) {
+  __shared__ TcParams kpar[kTcLaneCh * kWave];  // 16 KiB, [slot][lane]
+  __shared__ float kquad[3 * kTcLaneCh * kWave];  // 12 KiB, [coefficient][slot][lane]: the 8 -> 2 polynomials
+  __shared__ uint32_t kflags[kTcWaves];
+  kvh_tc_item it;
+  const int pair = load_job(a, it);
+  if (pair < 0) return;  // block-uniform
+  const int bx = blockIdx.x, lay_kv = blockIdx.y;
 #define KVH_TC_CASE(BI, BO) \
   case BI * 16 + BO: transcode_block<DT, BI, BO, SLOTS>(a, it, blockIdx.z, lay_kv, bx, kpar, kquad, kflags); break;
-  switch (bi * 16 + bo) {
+  switch (pair) {
+    KVH_TC_CASE(8, 8) KVH_TC_CASE(8, 4) KVH_TC_CASE(8, 2)
+    KVH_TC_CASE(4, 8) KVH_TC_CASE(4, 4) KVH_TC_CASE(4, 2)
+    KVH_TC_CASE(2, 8) KVH_TC_CASE(2, 4) KVH_TC_CASE(2, 2)
+    default: break;
+  }
+#undef KVH_TC_CASE
+}
+
+// grid = (blocks of a plane, 2 * l, items); a block is `waves` units
+template <int DT, int ACC>
+__global__ __launch_bounds__(kTcThreads) KVH_TC_OCC void transcode_units_kernel(TranscodeParams a) {
+  extern __shared__ __align__(16) uint8_t units_lds[];  // K parameters, then the 8 -> 2 polynomials; kUnitsHeadBytes a head
+  __shared__ uint32_t kflags[kTcWaves];
+  kvh_tc_item it;
+  const int pair = load_job(a, it);
+  if (pair < 0) return;  // block-uniform
+#define KVH_TC_CASE(BI, BO) \
+  case BI * 16 + BO: transcode_units<DT, BI, BO, ACC>(a, it, blockIdx.z, blockIdx.y, blockIdx.x, units_lds, kflags); break;
+  switch (pair) {
     KVH_TC_CASE(8, 8) KVH_TC_CASE(8, 4) KVH_TC_CASE(8, 2)
     KVH_TC_CASE(4, 8) KVH_TC_CASE(4, 4) KVH_TC_CASE(4, 2)
     KVH_TC_CASE(2, 8) KVH_TC_CASE(2, 4) KVH_TC_CASE(2, 2)
@@ -887,12 +1202,30 @@ __global__ __launch_bounds__(kTcThreads) KVH_TC_OCC void transcode_kernel(Transc
 
 int launch_transcode(const TranscodeParams& a, int dt, int n_items, int max_tokens, hipStream_t stream) {
   const int heads = a.c / kGroup;
+  TranscodeParams b = a;
+  b.by_heads = Divisor((uint32_t)heads);
+  const TcUnits u = transcode_units_plan(heads, a.l, n_items, max_tokens);
+  if (u.accesses != 0) {
+    b.max_tokens = max_tokens;
+    b.waves = u.waves;
+    b.groups = u.groups;
+    b.by_units = Divisor((uint32_t)u.units);
+    b.by_parts = Divisor((uint32_t)u.parts);
+    b.by_period = Divisor((uint32_t)u.period);
+    auto pick = [&](auto dt_tag) {
+      constexpr int D = decltype(dt_tag)::value;
+      return u.accesses == 4 ? transcode_units_kernel<D, 4> : transcode_units_kernel<D, 8>;
+    };
+    auto kernel = dt == KVH_F16 ? pick(std::integral_constant<int, KVH_F16>{}) : pick(std::integral_constant<int, KVH_BF16>{});
+    const dim3 grid((unsigned)u.blocks, (unsigned)(2 * a.l), (unsigned)n_items);
+    launch_kernel(kernel, grid, dim3((unsigned)(u.waves * kWave)), (unsigned)(u.groups * heads) * kUnitsHeadBytes, stream, b);
+    KVH_HIP_CHECK_LAUNCH();
+    return KVH_OK;
+  }
   const TcPlan plan = transcode_plan(heads, a.l, n_items, max_tokens);
   if (!grid_fits(plan.blocks, 1, kTcWaves)) return KVH_E_HIP;
-  TranscodeParams b = a;
   b.max_tokens = max_tokens;
   b.k_log_s = plan.log_s;
-  b.by_heads = Divisor((uint32_t)heads);
   b.by_sets = Divisor((uint32_t)plan.sets);
   const dim3 grid((unsigned)plan.blocks, (unsigned)(2 * a.l), (unsigned)n_items);
   auto kernel = dt == KVH_F16 ? (plan.slots ? transcode_kernel<KVH_F16, true> : transcode_kernel<KVH_F16, false>)

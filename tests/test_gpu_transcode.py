@@ -307,3 +307,58 @@ def test_transcode_4_to_2_tables(kvh, far, dt):
     torch.cuda.synchronize()
     assert status.item() == 0
     assert_same_blob(got.cpu().numpy(), want, "4 -> 2, far=%s" % far)
+
+
+# heads -> items of 2 layers x 300 tokens (12 * heads 16-access waves an item) that make launches of each form
+FORMS = {1: (1, 60, 260), 2: (1, 30, 130), 3: (1, 20, 60), 4: (1, 15, 45), 5: (1, 12, 36), 6: (1, 9, 20), 7: (1, 9, 15), 8: (1, 8, 12),
+         9: (1, 8, 20), 10: (1, 7, 18), 12: (1, 6, 8), 16: (1, 5, 7), 17: (1,)}
+
+
+@pytest.mark.parametrize("dt", [F16, BF16])
+@pytest.mark.parametrize("heads", list(FORMS))
+def test_transcode_forms(kvh, heads, dt):
+    """Launches of one blob repeated, so that it goes through units of 4 accesses, of 8, and the layout of large launches: all
+    pairs of levels, groups near and far from zero, constant ones and ones with a range of a few units in the last place, a last
+    token-group of 44 rows.  Every copy equals the oracle's blob, and nothing is written between them."""
+    l, n, c = 2, 300, 128 * heads
+    rng = np.random.default_rng(heads)
+    off = np.where(rng.random((l, 1, c)) < 0.5, 5.0, 0.0) * rng.standard_normal((l, 1, c))
+    kf = rng.standard_normal((l, n, c)) + off
+    vf = rng.standard_normal((l, n, c)) + np.where(rng.random((l, n, 1)) < 0.5, 5.0, 0.0)
+    kf[:, :, 5::64] = 3.25
+    vf[:, 7::50, :128] = -1.5
+    if heads != 8:  # there all 1024 channels take the polynomial route
+        kf[:, 128:, 9::97] = 100.0 + rng.integers(0, 3, kf[:, 128:, 9::97].shape) * (0.5 if dt == BF16 else 0.0625)
+    k, v = gen._cast_to_bits(kf.astype(np.float32), dt), gen._cast_to_bits(vf.astype(np.float32), dt)
+    for a, b in PAIRS:
+        src = oracle.encode(k, v, dt, a)
+        want = torch.from_numpy(oracle.transcode(src, dt, l, n, c, a, b)).cuda()
+        src_dev = torch.from_numpy(src).cuda()
+        for items in FORMS[heads]:
+            pitch = want.numel() + 32
+            out = torch.full((items, pitch), 0xAB, dtype=torch.uint8, device="cuda")
+            status = torch.zeros(items, dtype=torch.int32, device="cuda")
+            kvh.transcode_batch(kvh.make_tc_items([src_dev.data_ptr()] * items, [out.data_ptr() + i * pitch for i in range(items)], [n] * items,
+                                                  [a] * items, [b] * items, "cuda"), items, n, dt, l, c, status=status)
+            torch.cuda.synchronize()
+            assert not status.any() and torch.equal(out[:, : want.numel()], want.expand(items, -1)), (a, b, items)
+            assert (out[:, want.numel():] == 0xAB).all(), (a, b, items)
+
+
+@pytest.mark.parametrize("heads", [1, 2, 3, 5, 8, 10, 16])
+def test_transcode_units_at_the_edges_of_token_groups(kvh, heads):
+    """Single blobs whose last access or token-group is a partial one, in units of 4 and (many layers) of 8 accesses."""
+    for i, n in enumerate((1, 7, 9, 127, 128, 129, 255, 257, 385)):
+        l, (a, b), dt = (2, (0, 1), BF16) if i % 2 else (max(1, 800 // (2 * heads * -(-n // 128))), (1, 2), F16)
+        if n >= 255 and heads > 5:
+            l = 2
+        c = 128 * heads
+        k, v = gen.make_kv(l, n, c, dt, seed=heads + n)
+        src = oracle.encode(k, v, dt, a)
+        want = oracle.transcode(src, dt, l, n, c, a, b)
+        out = torch.full((want.size + 64,), 0xAB, dtype=torch.uint8, device="cuda")
+        kvh.transcode(torch.from_numpy(src).cuda(), dt, l, n, c, a, b, out=out)
+        torch.cuda.synchronize()
+        got = out.cpu().numpy()
+        assert_same_blob(got[: want.size], want, "%d heads, %d x %d tokens" % (heads, l, n))
+        assert (got[want.size:] == 0xAB).all()

@@ -14,6 +14,10 @@ extern "C" void tc_plan(int heads, int l, int items, int tokens, int64_t* o) {
   const TcPlan p = transcode_plan(heads, l, items, tokens);
   o[0] = p.slots; o[1] = p.log_s; o[2] = p.sets; o[3] = p.blocks;
 }
+extern "C" void tc_units(int heads, int l, int items, int tokens, int64_t* o) {
+  const TcUnits u = transcode_units_plan(heads, l, items, tokens);
+  o[0] = u.accesses; o[1] = u.period; o[2] = u.units; o[3] = u.parts; o[4] = u.groups; o[5] = u.waves; o[6] = u.blocks;
+}
 extern "C" void enc_plan(int heads, int l, int items, int tokens, int64_t* o) {
   const EncPlan p = encode_plan(heads, l, items, tokens);
   o[0] = p.slots; o[1] = p.k_slots; o[2] = p.waves; o[3] = p.blocks;
@@ -211,3 +215,62 @@ def test_gpu_tests_reach_the_turns_they_name(plans):
     for l, items, n, group in ((11, 8, 300, 4), (31, 13, 600, 4), (57, 10, 660, 8)):
         assert plans("dec_plan", 8, l, items, n, *dense(1024, n * items))[4:8:3] == [group, group] and 2 * l % group
     assert plans("dec_plan", 8, 9, 1, 8191, *dense(1024, 8191))[7] == 4 and 18 % 4
+
+
+@pytest.mark.parametrize("heads", range(1, 17))
+def test_transcode_units_cover_every_slot_once(plans, heads):
+    """The kernel's arithmetic, repeated here: the units of V and of K hold every (row, head) slot once, a lane of a K unit keeps its
+    head from access to access, and the parameters fit a block's threads."""
+    forms = set()
+    for l, items, n in ((1, 1, 1), (1, 1, 127), (1, 1, 300), (2, 1, 385), (2, 2, 129), (200 // heads, 1, 129), (150 // heads, 1, 300)):
+        acc, period, units, parts, groups, waves, blocks = plans("tc_units", heads, max(1, l), items, n)[:7]
+        if not acc:
+            continue
+        forms.add(acc)
+        total, step_k = n * heads, 8 * period
+        assert units * acc == 16 * heads and step_k % heads == 0 and waves <= 8
+        assert groups * heads * 64 <= 2 * 64 * waves  # two pairs of channels a thread
+        for is_v in (True, False):
+            seen, stored = [0] * total, set()
+            for bx in range(blocks):
+                for w in range(waves):
+                    if is_v:
+                        s0, step, g = (bx * waves + w) * acc * 8, 8, None
+                    else:
+                        q = bx // parts
+                        gi, first = w // units, (bx - q * parts) * waves
+                        u, g = first + w - gi * units, q * groups + gi
+                        if q * groups * 128 >= n or u >= units:
+                            continue
+                        s0, step = g * 128 * heads + 8 * (u % period) + u // period * acc * step_k, step_k
+                        if first == 0:
+                            stored.update(x for x in range(q * groups, q * groups + groups) if x * 128 < n)
+                    rem = max(0, min(total - s0, acc * step))
+                    count = -(-rem // 8) if is_v else (rem + step - 1) // 8 // period
+                    for k in range(acc):
+                        for slot in range(8):
+                            if slot + k * step < rem:
+                                x = s0 + k * step + slot
+                                assert k < count
+                                seen[x] += 1
+                                assert is_v or (x // (128 * heads) == g and x % heads == (8 * u + slot) % heads)
+            assert all(x == 1 for x in seen)
+            assert is_v or stored == set(range(ceil(n, 128)))
+    assert forms == {4, 8}
+
+
+def test_transcode_units_only_where_they_are_the_faster_form(plans):
+    """Beyond about 1,100 waves of 16 accesses units of 8 lose where spans keep their lanes busy (4 -> 2 bits 0.82 to 0.97)."""
+    acc = lambda *a: plans("tc_units", *a)[0]
+    assert [acc(8, l, 1, 300) for l in (10, 11, 22, 23)] == [4, 8, 8, 0]
+    assert [acc(5, l, 1, 300) for l in (17, 18, 66, 67)] == [4, 8, 8, 0]
+    assert acc(1, 32, 100, 256) == 8 and acc(1, 32, 100, 257) == 0 and acc(2, 32, 39, 256) == 8 and acc(2, 32, 40, 256) == 0
+    assert acc(16, 2, 1, 300) == 4 and acc(17, 1, 1, 1) == 0 and acc(8, 32, 32, 256) == 0
+    assert acc(2**24 - 1, 32767, 65535, 2**31 - 1) == 0
+
+
+def test_gpu_tests_reach_the_transcoder_forms_they_name(plans):
+    import test_gpu_transcode as t
+
+    for heads, items in t.FORMS.items():
+        assert [plans("tc_units", heads, 2, i, 300)[0] for i in items] == ([4, 8, 0] if heads <= 16 else [0])
