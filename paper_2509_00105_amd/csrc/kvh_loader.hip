@@ -5,7 +5,7 @@
 // Consecutive blobs are packed into groups that fill one staging slot.  A group is moved by ONE
 // launch of a small copy kernel that reads the pinned host memory over the bus (the blobs of a
 // group need not be contiguous on the host) and also writes the group's decode descriptors at the
-// head of the slot, then decoded by ONE batched decode launch.  Per-blob runtime copies were
+// head of the slot, then decoded by ONE batched decode launch; a run's last group is kept small.  Per-blob runtime copies were
 // measured to leave 30-60 us of idle bus between two copies on this platform; with groups the
 // fixed costs are paid once per slot.  Two streams (copy, caller's compute) and two events per slot
 // order the ring; one more event orders a run's copies after what the caller's stream already holds.
@@ -20,48 +20,64 @@ namespace {
 constexpr int kMaxSlots = 64;
 constexpr int kMaxGroup = 32;                                   // blobs per group
 constexpr size_t kDescBytes = (size_t)kMaxGroup * sizeof(kvh_kept_item);  // descriptor area at the head of a slot
-#ifndef KVH_LD_BLOCKS
-#define KVH_LD_BLOCKS 4   // copy blocks per blob (the bus, not the CUs, bounds the copy: few blocks leave the rest to the decode)
-#endif
-#ifndef KVH_LD_UNROLL
-#define KVH_LD_UNROLL 4   // 16-byte loads in flight per thread
-#endif
 constexpr int kCopyThreads = 256;
-constexpr int kCopyBlocksPerBlob = KVH_LD_BLOCKS;
-constexpr int kCopyUnroll = KVH_LD_UNROLL;
+constexpr int kCopyUnroll = 4;                                  // 16-byte loads in flight per thread
+constexpr uint64_t kTileWords = kCopyThreads * kCopyUnroll;     // 16-byte words of a tile: 16 KiB
+// Blocks of a copy.  A block reads about 3 GB/s over the bus whatever it has in flight (2, 4 or 8 loads a thread), so 24 fill
+// it; 64 MiB of pinned memory in blocks of 256 threads: 16 blocks 46.7 GB/s, 24 56.2, 32 57.0, 64 57.2, 96 55.7, 256 57.0, the
+// copy engine 56.7.  While a decode runs beside the copy more of them help (2,427 tokens of 27 layers at 8 bits: 24 blocks 2,664
+// us, 32 2,568, 40 2,530, 64 2,520), until a full bus holds up the decodes of short groups (41 blobs of 1.4 MB in groups
+// of 4: 40 blocks 1,201 us, 64 1,218).  Tiles are dealt over the whole group: with 4 blocks for each blob the bus ran at 50 GB/s on eight blobs
+// of mixed levels, because the last and largest had 4 blocks alone.
+constexpr uint32_t kCopyBlocks = 48;
 
 typedef uint32_t uintx4 __attribute__((ext_vector_type(4)));
 
 struct CopyGroup {
   int n;
-  const uint8_t* src[kMaxGroup];  // pinned host memory, device-visible
-  uint64_t off[kMaxGroup];        // byte offset of the blob inside the slot
-  uint64_t n16[kMaxGroup];        // blob size in 16-byte words
-  kvh_kept_item item[kMaxGroup];  // decode descriptor (blob = slot + off)
+  uint32_t tiles;                   // of the group
+  uint32_t tile_end[kMaxGroup];     // tiles up to the end of each blob; all ones beyond the last one
+  struct {
+    const uint8_t* src;             // pinned host memory, device-visible
+    uint64_t off, n16;              // byte offset inside the slot, size in 16-byte words
+    uint64_t first;                 // its first tile
+  } blob[kMaxGroup];
+  kvh_kept_item item[kMaxGroup];    // decode descriptors (blob = slot + off)
 };
 
-// grid = (kCopyBlocksPerBlob, blobs of the group)
+// Block b copies tiles b, b + gridDim.x - 1, ... of the group; the last block writes the descriptors.
 __global__ __launch_bounds__(kCopyThreads) void load_group_kernel(CopyGroup g, uint8_t* slot) {
-  const int j = blockIdx.y;
-  const uintx4* src = reinterpret_cast<const uintx4*>(g.src[j]);
-  uintx4* dst = reinterpret_cast<uintx4*>(slot + g.off[j]);
-  const uint64_t n16 = g.n16[j];
-  if (blockIdx.x == 0 && threadIdx.x < sizeof(kvh_kept_item) / 4) {
-    const uint32_t* d = reinterpret_cast<const uint32_t*>(&g.item[j]);
-    reinterpret_cast<uint32_t*>(slot)[j * (sizeof(kvh_kept_item) / 4) + threadIdx.x] = d[threadIdx.x];
+  const uint32_t stride = gridDim.x - 1;
+  if (blockIdx.x == stride) {
+    constexpr uint32_t kWords = sizeof(kvh_kept_item) / 4;
+    const uint32_t* d = reinterpret_cast<const uint32_t*>(&g.item[0]);
+    for (uint32_t i = threadIdx.x; i < (uint32_t)g.n * kWords; i += kCopyThreads) reinterpret_cast<uint32_t*>(slot)[i] = d[i];
+    return;
   }
-  const uint64_t stride = (uint64_t)gridDim.x * kCopyThreads;
-  for (uint64_t i = (uint64_t)blockIdx.x * kCopyThreads + threadIdx.x; i < n16; i += stride * kCopyUnroll) {
+  for (uint32_t t = blockIdx.x; t < g.tiles; t += stride) {
+    int j = 0;
+#pragma unroll
+    for (int i = 0; i < kMaxGroup - 1; ++i) j += t >= g.tile_end[i] ? 1 : 0;
+    const auto& b = g.blob[j];
+    const uintx4* src = reinterpret_cast<const uintx4*>(b.src);
+    uintx4* dst = reinterpret_cast<uintx4*>(slot + b.off);
+    const uint64_t n16 = b.n16, first = (t - b.first) * kTileWords + threadIdx.x;
     uintx4 r[kCopyUnroll];
 #pragma unroll
     for (int u = 0; u < kCopyUnroll; ++u)
-      if (i + u * stride < n16) r[u] = __builtin_nontemporal_load(src + i + u * stride);
+      if (first + u * kCopyThreads < n16) r[u] = __builtin_nontemporal_load(src + first + u * kCopyThreads);
 #pragma unroll
     for (int u = 0; u < kCopyUnroll; ++u)
-      if (i + u * stride < n16) dst[i + u * stride] = r[u];
+      if (first + u * kCopyThreads < n16) dst[first + u * kCopyThreads] = r[u];
   }
 }
 
+int launch_copy(const CopyGroup& g, uint8_t* slot, hipStream_t stream) {
+  const uint32_t blocks = g.tiles < kCopyBlocks ? g.tiles : kCopyBlocks;
+  hipLaunchKernelGGL(load_group_kernel, dim3(blocks + 1), dim3(kCopyThreads), 0, stream, g, slot);
+  KVH_HIP_CHECK_LAUNCH();
+  return KVH_OK;
+}
 
 // Everything kvh_loader_run and kvh_load_static check before they enqueue anything.  `capacity` = bytes a slot
 // offers to blobs.
@@ -106,13 +122,15 @@ int pack_group(const kvh_load_item* items, int first, int n_items, int l, int c,
   size_t used = 0;
   max_tokens = 0;
   g.n = 0;
+  g.tiles = 0;
+  for (uint32_t& end : g.tile_end) end = 0xffffffffu;
   while (first + g.n < n_items && g.n < kMaxGroup) {
     const kvh_load_item& it = items[first + g.n];
     const size_t bytes = kvh_blob_size(l, it.n_tokens, c, it.level);
     if (used + bytes > capacity) break;
-    g.src[g.n] = static_cast<const uint8_t*>(it.blob_host);
-    g.off[g.n] = kDescBytes + used;
-    g.n16[g.n] = bytes / 16;
+    g.blob[g.n] = {static_cast<const uint8_t*>(it.blob_host), kDescBytes + used, bytes / 16, g.tiles};
+    g.tiles += (uint32_t)((bytes / 16 + kTileWords - 1) / kTileWords);
+    g.tile_end[g.n] = g.tiles;
     g.item[g.n] = kvh_kept_item{slot + kDescBytes + used, it.n_tokens, it.level, it.dst_token0, it.page_table,
                                 it.orig_tokens, it.sink, it.window, it.compact};
     if (it.n_tokens > max_tokens) max_tokens = it.n_tokens;
@@ -120,6 +138,34 @@ int pack_group(const kvh_load_item* items, int first, int n_items, int l, int c,
     ++g.n;
   }
   return g.n;
+}
+
+bool fits_one_group(const kvh_load_item* items, int first, int n_items, int l, int c, size_t capacity) {
+  if (n_items - first > kMaxGroup) return false;
+  size_t used = 0;
+  for (int i = first; i < n_items && used <= capacity; ++i) used += kvh_blob_size(l, items[i].n_tokens, c, items[i].level);
+  return used <= capacity;
+}
+
+// A run's last group is decoded when nothing is left to copy.  Where all of items[first ..] fit into one slot, returns where
+// the group had better end so that a smaller one follows, whose copy hides this one's decode: before the shortest tail that
+// holds an eighth of the bytes (at 57 GB/s its copy takes longer than the decode of the rest), or n_items where that gains nothing.
+// A further group leaves the bus idle for 16 us, what decoding 80 MB of rows takes: cut from 128 MiB on.
+int cut_last_group(const kvh_load_item* items, int first, int n_items, int l, int c, size_t capacity, int n_slots) {
+  if (n_slots < 2 || n_items - first < 2 || !fits_one_group(items, first, n_items, l, c, capacity)) return n_items;
+  size_t total = 0, tail = 0;
+  double rows = 0;  // 16-bit bytes ahead of the tail
+  for (int i = first; i < n_items; ++i) {
+    total += kvh_blob_size(l, items[i].n_tokens, c, items[i].level);
+    rows += 4.0 * l * c * items[i].n_tokens;
+  }
+  int cut = n_items;
+  while (cut > first + 1 && tail * 8 < total) {
+    --cut;
+    tail += kvh_blob_size(l, items[cut].n_tokens, c, items[cut].level);
+    rows -= 4.0 * l * c * items[cut].n_tokens;
+  }
+  return rows >= 128.0 * (1 << 20) ? cut : n_items;
 }
 
 // ---- the allocation-free variant: its one staging slot lives in the code object -------------------------
@@ -236,9 +282,14 @@ int kvh_loader_run(kvh_loader* ld, const kvh_load_item* items, int n_items, kvh_
   if (ld == nullptr) return KVH_E_ARG;
   if (int rc = validate_load(items, n_items, dt, l, c, dst, block_tokens, ld->slot_bytes)) return rc;
   hipStream_t compute = static_cast<hipStream_t>(stream);
+  // A run that fits into one slot has no copy for a decode to hide behind and stays on the caller's stream: waits across streams
+  // would cost 25 us (4 MiB copied and decoded: 115 us on two streams, 90 on one).
+  const bool one_group = fits_one_group(items, 0, n_items, l, c, ld->slot_bytes);
+  hipStream_t copies = one_group ? compute : ld->copy_stream;
   // Stream order: the copies read host blobs that work already enqueued on the caller's stream may
   // still be writing (an encode straight into pinned memory), so they start after that work.
-  if (hipEventRecord(ld->entered, compute) != hipSuccess || hipStreamWaitEvent(ld->copy_stream, ld->entered, 0) != hipSuccess)
+  if (!one_group &&
+      (hipEventRecord(ld->entered, compute) != hipSuccess || hipStreamWaitEvent(copies, ld->entered, 0) != hipSuccess))
     return KVH_E_HIP;
   DecodeParams a{};
   a.k = static_cast<uint16_t*>(dst->k);
@@ -249,24 +300,29 @@ int kvh_loader_run(kvh_loader* ld, const kvh_load_item* items, int n_items, kvh_
   a.c = c;
   a.block_tokens = block_tokens;
   a.split = kNoSplit;
-  int first = 0;
+  int first = 0, last = n_items;  // last: where the group being packed has to end
   while (first < n_items) {
     const int s = ld->next_slot;
     uint8_t* slot = ld->staging + (size_t)s * ld->slot_pitch;
     CopyGroup g{};
     int max_tokens = 0;
-    pack_group(items, first, n_items, l, c, slot, ld->slot_bytes, g, max_tokens);
+    if (!one_group && last == n_items) last = cut_last_group(items, first, n_items, l, c, ld->slot_bytes, ld->n_slots);
+    pack_group(items, first, last, l, c, slot, ld->slot_bytes, g, max_tokens);
+    if (first + g.n == last) last = n_items;
     // the slot may still be read by the decode that used it last (in this run or an earlier one)
-    if (ld->in_use[s] && hipStreamWaitEvent(ld->copy_stream, ld->freed[s], 0) != hipSuccess) return KVH_E_HIP;
-    hipLaunchKernelGGL(load_group_kernel, dim3(kCopyBlocksPerBlob, (unsigned)g.n), dim3(kCopyThreads), 0,
-                       ld->copy_stream, g, slot);
-    KVH_HIP_CHECK_LAUNCH();
-    if (hipEventRecord(ld->copied[s], ld->copy_stream) != hipSuccess) return KVH_E_HIP;
-    if (hipStreamWaitEvent(compute, ld->copied[s], 0) != hipSuccess) return KVH_E_HIP;
+    if (ld->in_use[s] && hipStreamWaitEvent(copies, ld->freed[s], 0) != hipSuccess) return KVH_E_HIP;
+    if (int rc = launch_copy(g, slot, copies)) return rc;
     a.kept_items = reinterpret_cast<const kvh_kept_item*>(slot);
     a.status = status_dev != nullptr ? status_dev + first : nullptr;
-    if (int rc = launch_decode(a, dt, g.n, max_tokens, compute)) return rc;
-    if (hipEventRecord(ld->freed[s], compute) != hipSuccess) return KVH_E_HIP;
+    int rc = KVH_OK;
+    if (!one_group && (hipEventRecord(ld->copied[s], copies) != hipSuccess || hipStreamWaitEvent(compute, ld->copied[s], 0) != hipSuccess))
+      rc = KVH_E_HIP;
+    if (rc == KVH_OK) rc = launch_decode(a, dt, g.n, max_tokens, compute);
+    if (rc == KVH_OK && hipEventRecord(ld->freed[s], compute) != hipSuccess) rc = KVH_E_HIP;
+    if (rc != KVH_OK) {  // no event tells a later run, which may be on another stream, when the slot is free
+      (void)hipStreamSynchronize(copies);
+      return rc;
+    }
     ld->in_use[s] = true;
     ld->next_slot = (s + 1) % ld->n_slots;
     first += g.n;
@@ -297,9 +353,7 @@ int kvh_load_static(const kvh_load_item* items, int n_items, kvh_dtype dt, int l
     CopyGroup g{};
     int max_tokens = 0;
     pack_group(items, first, n_items, l, c, slot, capacity, g, max_tokens);
-    hipLaunchKernelGGL(load_group_kernel, dim3(kCopyBlocksPerBlob, (unsigned)g.n), dim3(kCopyThreads), 0, compute, g,
-                       slot);
-    KVH_HIP_CHECK_LAUNCH();
+    if (int rc = launch_copy(g, slot, compute)) return rc;
     a.kept_items = reinterpret_cast<const kvh_kept_item*>(slot);
     a.status = status_dev != nullptr ? status_dev + first : nullptr;
     if (int rc = launch_decode(a, dt, g.n, max_tokens, compute)) return rc;

@@ -216,3 +216,41 @@ def test_store_then_load_on_one_stream_without_a_sync_between(kvh):
         wk[:, sl], wv[:, sl] = oracle.decode(b, dt, l, chunk, c, lv)
     assert np.array_equal(to_host(ok), wk) and np.array_equal(to_host(ov), wv)
     ld.close()
+
+
+@pytest.mark.parametrize("blobs_per_slot", [20, 12, 7, 1])
+def test_groups_streams_and_the_cut_of_the_last_group(kvh, blobs_per_slot):
+    """20 blobs of mixed sizes: one group on the caller's stream; two slots of up to 12 or 7, whose last group is cut so that a
+    small one follows; a group a blob.  Runs alternate between two streams, so that slots pass from one to the other.  Every run
+    equals the batched decode of the same blobs."""
+    dt, l, c, m, items = torch.bfloat16, 32, 1024, 256, 20
+    levels, lengths = [i % 3 for i in range(items)], [m - 3 * i for i in range(items)]
+    kv = gen.make_kv_device(l, m * items, c, BF16, seed=5)
+    starts = [m * i for i in range(items)]
+    sizes = [kvh.blob_size(l, n, c, lv) for n, lv in zip(lengths, levels)]
+    offs = np.concatenate([[0], np.cumsum(sizes)]).astype(np.int64)
+    dev = torch.zeros(int(offs[-1]), dtype=torch.uint8, device="cuda")
+    ptrs = [dev.data_ptr() + int(o) for o in offs[:-1]]
+    kvh.encode_batch(kvh.make_enc_items(ptrs, starts, lengths, levels, "cuda"), items, m, kv[0], kv[1])
+    want = torch.zeros_like(kv)
+    kvh.decode_batch(kvh.make_dec_items(ptrs, lengths, levels, starts, [0] * items, "cuda"), items, m, want[0], want[1])
+    pinned = torch.empty(dev.numel(), dtype=torch.uint8, pin_memory=True)
+    pinned.copy_(dev)
+    hosts = [pinned[int(a):int(b)] for a, b in zip(offs[:-1], offs[1:])]
+    slot = (sum(sizes) if blobs_per_slot == items else blobs_per_slot * max(sizes)) + 1536
+    ld = kvh.Loader(torch.empty(2 * slot + 32, dtype=torch.uint8, device="cuda"), 2)
+    torch.cuda.synchronize()
+    streams = [torch.cuda.Stream(), torch.cuda.Stream()]
+    outs, statuses = [], []
+    for r in range(4):
+        with torch.cuda.stream(streams[r % 2]):
+            out, status = torch.zeros_like(kv), torch.ones(items, dtype=torch.int32, device="cuda").mul_(0)
+            order = list(range(items)) if r < 2 else list(range(items))[::-1]
+            ld.run([hosts[i] for i in order], [lengths[i] for i in order], [levels[i] for i in order], [starts[i] for i in order],
+                   out[0], out[1], status=status)
+        outs.append(out)
+        statuses.append(status)
+    torch.cuda.synchronize()
+    for out, status in zip(outs, statuses):
+        assert not status.any() and torch.equal(out.view(torch.int16), want.view(torch.int16))
+    ld.close()
