@@ -301,7 +301,8 @@ int kvh_loader_create(kvh_loader** out, void* staging_dev, size_t staging_bytes,
 /* Bytes a slot offers to blobs (0 for NULL). */
 size_t kvh_loader_slot_bytes(const kvh_loader* loader);
 /* Enqueue, group by group in item order: wait until the next slot is free, copy the group's blobs host ->
- * slot on the loader's copy stream, then decode them on `stream` into `dst` (contiguous or paged, as
+ * slot on the loader's copy stream (on `stream` itself where all blobs of the run fit into one slot), then decode
+ * them on `stream` into `dst` (contiguous or paged, as
  * kvh_decode_kept_batch: ordinary and token-dropped blobs may be mixed).  The copies start after the work already
  * enqueued on `stream` (so blobs that an earlier call on it writes into host memory are complete when they are
  * read).  Returns once everything is enqueued; results

@@ -46,14 +46,15 @@ assert ENC_ITEM.itemsize == 24 and DEC_ITEM.itemsize == 32 and TC_ITEM.itemsize 
 assert KEPT_ENC_ITEM.itemsize == 32 and KEPT_ITEM.itemsize == 48
 
 _lib = None
+_fast = None  # csrc/kvh_fastcall.cpp over the loaded library
 
 
 def lib() -> ctypes.CDLL:
     """Load libkvh.so (built in-tree by `python -m paper_2509_00105_amd.build`)."""
-    global _lib
+    global _lib, _fast
     if _lib is None:
-        if not os.path.exists(_LIB_PATH):
-            raise ImportError("libkvh.so is not built: run `python -m paper_2509_00105_amd.build` "
+        if not os.path.exists(_LIB_PATH) or not os.path.exists(os.path.join(_HERE, "_fastcall.so")):
+            raise ImportError("libkvh.so or _fastcall.so is not built: run `python -m paper_2509_00105_amd.build` "
                               "(there is no CPU fallback for the HIP path)")
         L = ctypes.CDLL(_LIB_PATH)
         vp, i32, i64, sz = ctypes.c_void_p, ctypes.c_int, ctypes.c_int64, ctypes.c_size_t
@@ -119,6 +120,12 @@ def lib() -> ctypes.CDLL:
                                          view, i64, vp, i32, vp, vp]
         L.kvh_strerror.restype = ctypes.c_char_p
         L.kvh_strerror.argtypes = [i32]
+        from . import _fastcall
+
+        if _raw_stream is not None:
+            _fast = _fastcall.Calls(torch.cuda.current_device, _raw_stream, *[
+                ctypes.cast(f, vp).value for f in (L.kvh_encode, L.kvh_encode_batch, L.kvh_decode, L.kvh_decode_batch,
+                                                   L.kvh_encode_kept, L.kvh_decode_kept)])
         _lib = L
     return _lib
 
@@ -187,9 +194,17 @@ def _check(rc: int, where: str):
         raise KVHError(rc, where)
 
 
+# The calls a program makes per chunk or per batch try _fast first: it takes ordinary arguments and returns the status, or None
+# for everything else, which goes through ctypes below and is accepted or refused there.
+
+
 def encode(k: torch.Tensor, v: torch.Tensor, level: int, blob: torch.Tensor | None = None, n_tokens: int | None = None,
            stream=None) -> torch.Tensor:
     """kvh_encode: tokens [0, n_tokens) of K/V [l][N][c] -> one blob (uint8 device tensor)."""
+    rc = _fast.encode(k, v, level, blob, n_tokens, stream) if _fast is not None and blob is not None else None
+    if rc is not None:
+        _check(rc, "kvh_encode")
+        return blob
     view, dt = _view(k, v)
     l, N, c = k.shape
     n = N if n_tokens is None else n_tokens
@@ -239,6 +254,9 @@ def make_dec_items(blob_ptrs, n_tokens, levels, dst_token0, page_table_ptrs, dev
 def encode_batch(items: torch.Tensor, n_items: int, max_tokens_per_item: int, k: torch.Tensor, v: torch.Tensor,
                  stream=None) -> None:
     """kvh_encode_batch: all items in one launch; `items` comes from make_enc_items."""
+    rc = _fast.encode_batch(items, n_items, max_tokens_per_item, k, v, stream) if _fast is not None else None
+    if rc is not None:
+        return _check(rc, "kvh_encode_batch")
     view, dt = _view(k, v)
     _require_cuda(items)
     l, _, c = k.shape
@@ -250,6 +268,9 @@ def decode(blob: torch.Tensor, level: int, n_tokens: int, k_dst: torch.Tensor, v
            page_table: torch.Tensor | None = None, block_tokens: int = 16, status: torch.Tensor | None = None,
            stream=None) -> None:
     """kvh_decode: one blob -> rows of a contiguous [l][N][c] or paged [l][P][block][c] destination."""
+    rc = _fast.decode(blob, level, n_tokens, k_dst, v_dst, dst_token0, page_table, block_tokens, status, stream) if _fast is not None else None
+    if rc is not None:
+        return _check(rc, "kvh_decode")
     paged = page_table is not None
     view, dt = _view(k_dst, v_dst, paged)
     _require_cuda(blob, page_table, status)
@@ -291,6 +312,9 @@ def decode_batch(items: torch.Tensor, n_items: int, max_tokens_per_item: int, k_
                  v_dst: torch.Tensor, paged: bool = False, block_tokens: int = 16,
                  status: torch.Tensor | None = None, stream=None) -> None:
     """kvh_decode_batch: all items in one launch; `items` comes from make_dec_items."""
+    rc = _fast.decode_batch(items, n_items, max_tokens_per_item, k_dst, v_dst, paged, block_tokens, status, stream) if _fast is not None else None
+    if rc is not None:
+        return _check(rc, "kvh_decode_batch")
     view, dt = _view(k_dst, v_dst, paged)
     _require_cuda(items, status)
     if status is not None and (status.dtype != torch.int32 or status.numel() < n_items):
@@ -308,6 +332,10 @@ def kept_tokens(N: int, sink: int, window: int) -> int:
 def encode_kept(k: torch.Tensor, v: torch.Tensor, sink: int, window: int, level: int,
                 blob: torch.Tensor | None = None, stream=None) -> torch.Tensor:
     """kvh_encode_kept: keep the first `sink` and last `window` tokens of K/V [l][N][c], encode them."""
+    rc = _fast.encode_kept(k, v, sink, window, level, blob, stream) if _fast is not None and blob is not None else None
+    if rc is not None:
+        _check(rc, "kvh_encode_kept")
+        return blob
     view, dt = _view(k, v)
     l, N, c = k.shape
     if blob is None:
@@ -325,6 +353,10 @@ def decode_kept(blob: torch.Tensor, level: int, N: int, sink: int, window: int, 
                 dst_token0: int = 0, compact: bool = False, page_table: torch.Tensor | None = None, block_tokens: int = 16,
                 status: torch.Tensor | None = None, stream=None) -> None:
     """kvh_decode_kept: a token-dropped blob -> original (or compact) rows of a contiguous or paged destination."""
+    rc = _fast.decode_kept(blob, level, N, sink, window, k_dst, v_dst, dst_token0, compact, page_table, block_tokens, status,
+                           stream) if _fast is not None else None
+    if rc is not None:
+        return _check(rc, "kvh_decode_kept")
     paged = page_table is not None
     view, dt = _view(k_dst, v_dst, paged)
     _require_cuda(blob, page_table, status)

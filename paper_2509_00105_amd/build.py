@@ -1,12 +1,14 @@
-"""Build the HIP library (libkvh.so) in-tree for gfx950 with hipcc."""
+"""Build the HIP library (libkvh.so) in-tree for gfx950 with hipcc, and the binding's call module (_fastcall.so) with g++."""
 from __future__ import annotations
 
 import os
 import subprocess
+import sysconfig
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libkvh.so")
+CALLS = os.path.join(HERE, "_fastcall.so")
 SOURCES = ["kvh_api.hip", "kvh_decode.hip", "kvh_encode.hip", "kvh_transcode.hip", "kvh_loader.hip", "kvh_policy.cpp"]
 
 # -ffp-contract=off: the codec's arithmetic fuses only where the source says fma.
@@ -19,18 +21,24 @@ HIPCC_FLAGS = [
 ]
 
 
-def build(verbose: bool = False) -> str:
-    hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
-    tmp = LIB + ".tmp.%d" % os.getpid()
-    cmd = [hipcc, *HIPCC_FLAGS, "-o", tmp, *[os.path.join(CSRC, s) for s in SOURCES]]
-    res = subprocess.run(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
+def _compile(target: str, cmd: list, verbose: bool) -> None:
+    """Run cmd with the output file appended and put the result in place of target."""
+    tmp = target + ".tmp.%d" % os.getpid()
+    res = subprocess.run([*cmd, "-o", tmp], stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
     noise = "is not a recognized feature for this target"
     out = "\n".join(ln for ln in res.stdout.splitlines() if noise not in ln)
     if res.returncode != 0:
-        raise RuntimeError("hipcc failed:\n" + out)
+        raise RuntimeError("%s failed:\n%s" % (os.path.basename(cmd[0]), out))
     if verbose and out.strip():
         print(out)
-    os.replace(tmp, LIB)
+    os.replace(tmp, target)
+
+
+def build(verbose: bool = False) -> str:
+    hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
+    _compile(LIB, [hipcc, *HIPCC_FLAGS, *[os.path.join(CSRC, s) for s in SOURCES]], verbose)
+    _compile(CALLS, [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-Wall", "-shared", "-fPIC", "-I", sysconfig.get_paths()["include"],
+                     os.path.join(CSRC, "kvh_fastcall.cpp")], verbose)
     return LIB
 
 

@@ -269,8 +269,11 @@ int kvh_loader_create(kvh_loader** out, void* staging_dev, size_t staging_bytes,
 
 int kvh_loader_destroy(kvh_loader* ld) {
   if (ld == nullptr) return KVH_E_ARG;
-  // the copies enqueued by this loader must not outlive its stream
+  // the copies enqueued by this loader must not outlive it: those on its stream, and those of runs of one group, which are
+  // done when their slot is free (the event of a captured run cannot be waited for, and need not be: nothing has run yet)
   const bool ok = hipStreamSynchronize(ld->copy_stream) == hipSuccess;
+  for (int s = 0; s < ld->n_slots; ++s)
+    if (ld->in_use[s] && hipEventSynchronize(ld->freed[s]) != hipSuccess) (void)hipGetLastError();
   destroy(ld);
   return ok ? KVH_OK : KVH_E_HIP;
 }

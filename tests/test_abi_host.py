@@ -301,3 +301,21 @@ def test_binding_records_have_the_layout_of_the_c_structs(tmp_path):
     assert seen == sum(len(dt.names) + 1 for dt in records.values())
     view = b._KVView
     assert ctypes.sizeof(view) == 32 and [f[0] for f in view._fields_] == ["k", "v", "layer_stride", "token_stride"]
+
+
+def test_native_calls_leave_host_tensors_to_the_binding(lib):
+    """The native call module takes device tensors only; with anything else it answers None and raises nothing."""
+    import torch
+
+    from paper_2509_00105_amd import binding as b
+
+    k = torch.zeros((1, 128, 128), dtype=torch.float16)
+    u = torch.zeros(1 << 16, dtype=torch.uint8)
+    for args in ((k, k, 0, u, None, None), (None, k, 0, u, None, None), (k, 3, "x", object(), 2**80, None)):
+        assert b._fast.encode(*args) is None
+    assert b._fast.decode(u, 0, 128, k, k, 0, None, 16, None, None) is None
+    assert b._fast.decode_batch(u, 1, 128, k, k, False, 16, None, None) is None and b._fast.encode_batch(u, 1, 128, k, k, None) is None
+    assert b._fast.encode_kept(k, k, 1, 1, 0, u, None) is None
+    assert b._fast.decode_kept(u, 0, 128, 1, 1, k, k, 0, False, None, 16, None, None) is None
+    with pytest.raises(TypeError):
+        b._fast.encode(k, k)
