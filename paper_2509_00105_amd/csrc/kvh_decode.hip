@@ -4,7 +4,7 @@
 //
 // Streaming kernel, in two forms by row length.  Rows of whole 1024-channel spans: the unit of work is one wave
 // decoding 8 consecutive token rows of a span (two 512-channel segments), i.e. 16 KiB of contiguous output when
-// c = 1024.  Any other row length takes units of 64 (row, head) slots, see decode_slots.
+// c = 1024.  Any other row length, and launches of up to 192 MiB, take units of 64 (row, head) slots, see decode_slots.
 // A lane owns 8 channels per segment, so each store is one 128-bit access and the wave writes
 // 1 KiB of a row per instruction.  A block is 8 such units: 64 consecutive rows of one span, which
 // always lie in one K token-group.  K metadata (per channel) is turned into fp32 parameters either
@@ -497,17 +497,18 @@ __device__ __forceinline__ void decode_raw_unit(const DecodeParams& a, const kvh
   }
 }
 
-// ---- rows that are not a multiple of 1024 channels ------------------------------------------------------
+// ---- rows that are not a multiple of 1024 channels, and small launches ------------------------------------
 // With the lanes of a wave spread over a 1024-channel span, a row of 128 channels keeps 16 of 64 lanes busy on one
 // of its two segments.  Here a wave takes 64 (row, head) slots instead, whatever the row length: 16 accesses of 4
 // heads each, slot 4 i + j being lanes 16 j .. 16 j + 15 of access i.
 //   V, raw level: 64 consecutive (row, head) pairs in memory order; codes, metadata and, in a dense destination, the
 //     rows are contiguous.
-//   K: S = 4, 2 or 1 heads (the largest that divides the row) x 64 / S rows, so that a lane keeps its 8 channels
+//   K: S = 4, 2 or 1 heads (the largest of these that divides the row) x 64 / S rows, so that a lane keeps its 8 channels
 //     and their parameters through the unit.  The rows of a unit lie in one token-group (64 / S divides 128).
 // 32 x 8192 tokens or the like, % of HBM peak before / after: 80 layers of 128 channels 8 bits 17 / 77, of 256 channels
 // 8 bits into pages 31 / 66, 4 bits 32 / 80, 32 layers of 512 channels 4 bits 55 / 75, of 640 channels 8 bits 58 / 70,
-// of 1280 channels 4 bits 54 / 68.  What bounds it now is the write stream, as for whole spans.
+// of 1280 channels 4 bits 54 / 68.  What bounds it now is the write stream, as for whole spans.  Launches of whole spans up to 192
+// MiB take the same units, a wave a block (decode_units_plan): what bounds those is the start, and the last blocks.
 // Lane 16 j + i owns slot 4 i + j: it finds its destination (page table included) and, for V, prepares its group;
 // access i fetches both by a row broadcast from lane i.  Waves are independent: no LDS, no barrier.
 template <int DT, int BITS>
@@ -526,7 +527,7 @@ __device__ __forceinline__ void decode_slots(const DecodeParams& a, const kvh_it
   const bool by_head = BITS != 16 && !is_v;
   uint32_t per_row, t0, y0, h0;
   if (by_head) {
-    const uint32_t log_s = (uint32_t)__builtin_ctz(heads);  // at most 2 here
+    const uint32_t log_s = (uint32_t)__builtin_ctz(heads | 4u);
     const uint32_t sets = heads >> log_s;
     const uint32_t rb = a.by_sets.quotient(unit);
     per_row = 1u << log_s;
@@ -657,10 +658,9 @@ __device__ __forceinline__ void decode_slots(const DecodeParams& a, const kvh_it
 #ifndef KVH_DEC_WPE
 #define KVH_DEC_WPE 3
 #endif
-#define KVH_DEC_OCC(SHORT) __attribute__((amdgpu_waves_per_eu((SHORT) ? 4 : KVH_DEC_WPE, (SHORT) ? 4 : KVH_DEC_WPE)))
-// SHORT: two blocks per CU, for launches that write little (see decode_plan).
-template <int DT, bool SLOTS, bool SHORT>
-__global__ __launch_bounds__(kDecThreads) KVH_DEC_OCC(SHORT) void decode_kernel(DecodeParams a) {
+// decode_slots, which needs about 85 registers, is held to the same (4 or 5 waves per SIMD make no difference to it).
+template <int DT, bool SLOTS>
+__global__ __launch_bounds__(kDecThreads) __attribute__((amdgpu_waves_per_eu(KVH_DEC_WPE, KVH_DEC_WPE))) void decode_kernel(DecodeParams a) {
   const int item_idx = blockIdx.y;
   // Block order: the (layer, K|V) planes are taken in groups of `plane_group` (grid z), a group through all items (grid
   // y) before the next.  Within an item and group (grid x): `row_tile` consecutive blocks of a plane, then the same
@@ -786,22 +786,28 @@ int launch_decode(const DecodeParams& a, int dt, int n_items, int max_tokens, hi
   const int heads = a.c / kGroup;
   const DecPlan plan = decode_plan(heads, a.l, n_items, max_tokens, a.layer_stride, a.token_stride);
   if (!grid_fits(plan.blocks, plan.plane_group, plan.waves)) return KVH_E_HIP;
+  const DecUnits units = decode_units_plan(heads, a.l, n_items, max_tokens, a.layer_stride, a.token_stride);
   DecodeParams b = a;
   b.max_tokens = max_tokens;
   b.row_tile = plan.row_tile;
   b.plane_blocks = (int)plan.blocks;
   b.waves = plan.waves;
   b.plane_group = plan.turn;
-  const dim3 grid((unsigned)(plan.blocks * b.plane_group), (unsigned)n_items, (unsigned)((2 * a.l + b.plane_group - 1) / b.plane_group));
+  if (units.blocks != 0) {
+    b.plane_blocks = (int)units.blocks;
+    b.waves = 1;
+    b.plane_group = units.plane_group;
+  }
+  const dim3 grid((unsigned)(b.plane_blocks * b.plane_group), (unsigned)n_items, (unsigned)((2 * a.l + b.plane_group - 1) / b.plane_group));
   b.by_group = Divisor((uint32_t)b.plane_group);
   b.by_heads = Divisor((uint32_t)heads);
-  b.by_sets = Divisor((uint32_t)(heads >> lowest_bit(heads)));
+  b.by_sets = Divisor((uint32_t)(heads >> lowest_bit(heads | 4)));
   auto pick = [&](auto dt_tag) {
     constexpr int D = decltype(dt_tag)::value;
-    return plan.slots ? decode_kernel<D, true, false> : plan.short_launch ? decode_kernel<D, false, true> : decode_kernel<D, false, false>;
+    return plan.slots || units.blocks != 0 ? decode_kernel<D, true> : decode_kernel<D, false>;
   };
   auto kernel = dt == KVH_F16 ? pick(std::integral_constant<int, KVH_F16>{}) : pick(std::integral_constant<int, KVH_BF16>{});
-  launch_kernel(kernel, grid, dim3((unsigned)(plan.waves * kWave)), 0u, stream, b);
+  launch_kernel(kernel, grid, dim3((unsigned)(b.waves * kWave)), 0u, stream, b);
   KVH_HIP_CHECK_LAUNCH();
   return KVH_OK;
 }

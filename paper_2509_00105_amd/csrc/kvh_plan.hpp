@@ -71,8 +71,8 @@ struct DecPlan {
 //   1.05, 10 planes 0.90 to 1.04.
 // For a single item groups and turns are the same order.  Items of more than 8,192 tokens that are alone stay plane by plane
 // (1.00 to 1.1).
-// Launches of whole spans of up to 80 MiB also get two blocks per CU: what they write is gone before the write stream
-// has settled, and more waves in flight hide the start.  Nine layer counts from 2 to 80, 1024 to 4096 channels, all levels,
+// Launches of whole spans of up to 80 MiB would also get two blocks per CU (they run in units of slots now, see
+// decode_units_plan): what they write is gone before the write stream has settled, and more waves in flight hide the start.  Nine layer counts from 2 to 80, 1024 to 4096 channels, all levels,
 // two blocks against one in the same order: 48 MiB +3 to +8 % on average, 64 MiB +1 to +4, 80 MiB -1, 96 MiB -1 to -3, 128
 // MiB 0 to -2, 192 and 256 MiB -1 to -2 (single cases down to -8 %).
 inline DecPlan decode_plan(int heads, int l, int n_items, int max_tokens, int64_t layer_stride, int64_t token_stride) {
@@ -119,6 +119,29 @@ inline DecPlan decode_plan(int heads, int l, int n_items, int max_tokens, int64_
   while (p.plane_group > 1 && !grid_fits(p.blocks, p.plane_group, p.waves)) p.plane_group = (p.plane_group + 1) / 2;
   p.turn = turn < p.plane_group ? turn : p.plane_group;
   return p;
+}
+
+// Whole spans, small launches.  A block of spans is 64 rows, 8 waves and (at 8 bits) a barrier, and its waves write 16 KiB a
+// piece: 4 layers x 256 tokens make 32 blocks.  Up to 192 MiB of rows they run in units of slots, one wave a block (4 heads x 16
+// rows, or 64 slots in memory order), which start sooner and spread evenly: 400 launches of 0.3 to 260 MiB over 2 to 80 layers, 8
+// to 32 heads, all levels, against spans (one or two blocks per CU, turns of planes): up to 12 MiB 1.05 to 1.65 times as fast (4 x
+// 256 tokens at 8 bits, pages: 6.9 -> 4.2 us), 12 to 40 MiB 0.93 to 1.24, 1.07 on average (below 1 mostly the raw level at 14 to 25
+// MiB, 0.94 to 0.99), 40 to 192 MiB 0.94 to 1.26, 1.05 on average (30 x 939 at 8 bits 34.8 -> 33.6, 9 x 2,817 at 2 bits 25.1 -> 20.0);
+// beyond, spans win: 256 MiB 0.93 to 1.07, 512 MiB 0.95 to 1.06, 1 GiB 0.83 to 1.08.
+// Planes 8 at a time up to 40 MiB, 4 at a time beyond (64 x 256 raw: 8 at a time 0.90 of the speed of spans, 4 at a time 1.05),
+// all at once where the layers of a token lie side by side (66 x 279 raw: 8 at a time 0.88, all 1.02).
+struct DecUnits {
+  int64_t blocks;   // of a (layer, K|V) plane, a wave each; 0: the layouts above
+  int plane_group;
+};
+inline DecUnits decode_units_plan(int heads, int l, int n_items, int max_tokens, int64_t layer_stride, int64_t token_stride) {
+  DecUnits u{};
+  const double mib = 4.0 * l * heads * 128 * max_tokens * n_items / (1 << 20);  // of 16-bit rows
+  if (heads % 8 != 0 || mib > 192) return u;
+  u.blocks = ((int64_t)max_tokens + 15) / 16 * (heads / 4);  // K: sets of 4 heads x 16 rows; V has no more units
+  const int most = layer_stride < token_stride ? 2 * l : mib <= 40 ? 8 : 4;
+  u.plane_group = most < 2 * l ? most : 2 * l;
+  return u;
 }
 
 // ---- transcoder -------------------------------------------------------------------------------------------------

@@ -101,8 +101,7 @@ def test_row_lengths_batch(kvh, heads):
 @pytest.mark.parametrize("l,n", [(9, 8191), (20, 15000)])
 def test_launch_sizes(kvh, l, n):
     """Whole spans on both sides of the sizes at which the decoder changes its block order and occupancy: 288 MiB of rows walk
-    groups of 8, 8 and 2 planes, 1.1 GiB plane by plane, the pieces (18 to 54 MiB) all planes or groups of 8 with two blocks
-    per CU.  Every row equals what 640-token pieces of the entry give."""
+    turns of 4 planes, the last of 2, 1.1 GiB plane by plane, the pieces (18 to 54 MiB) units of slots.  Every row equals what 640-token pieces of the entry give."""
     c = 1024
     kv = gen.make_kv_device(l, n, c, gen.BF16, seed=n)
     for level in range(4):
@@ -176,6 +175,52 @@ def test_turns_of_planes_through_all_items(kvh, l, items, m):
     torch.cuda.synchronize()
     assert not status.any() and torch.equal(out.view(torch.int16), ref.view(torch.int16))
     assert out.any()
+
+
+@pytest.mark.parametrize("dt", [gen.F16, gen.BF16])
+@pytest.mark.parametrize("heads,copies", [(8, 1), (8, 96), (16, 48)])
+def test_one_blob_many_times(kvh, heads, copies, dt):
+    """One blob decoded once (units of slots) and so often that the launch takes spans (over 192 MiB): groups whose maximum is close
+    to zero (the explicit top-code rule) among others, 300 tokens (a last block of 44 rows), contiguous, paged, and token-dropped
+    with the kept tokens back in their places.  Every copy equals the oracle."""
+    l, n, c = 2, 300, 128 * heads
+    k, v = gen.make_kv(l, n, c, dt, seed=heads + copies)
+    half = np.arange(c) < c // 2
+    k, v = np.where(half & (k & 0x7fff != 0), k | 0x8000, k), np.where(~half & (v & 0x7fff != 0), v | 0x8000, v)
+    orig, sink, window = 340, 100, 200
+    words = np.array([orig, sink, window], np.uint32).view(np.uint8)
+    pages = -(-n // 16)
+    for level in range(4):
+        blob = oracle.encode(k, v, dt, level)
+        wk, wv = (device(x, dt).view(torch.int16) for x in oracle.decode(blob, dt, l, n, c, level))
+        src, dropped = torch.from_numpy(blob).cuda(), torch.from_numpy(blob).cuda()
+        dropped[32:44] = torch.from_numpy(words).cuda()
+        status = torch.zeros(copies, dtype=torch.int32, device="cuda")
+        one = lambda x: [x] * copies
+
+        def check(out, at):
+            torch.cuda.synchronize()
+            assert not status.any(), (level, at)
+            got = out.view(torch.int16).view(2, l, copies, -1, c)
+            if at == "dropped":
+                assert not got[:, :, :, sink:orig - window].any()
+                got = torch.cat([got[:, :, :, :sink], got[:, :, :, orig - window:orig]], dim=3)
+            got = got[:, :, :, :n]
+            assert torch.equal(got[0], wk[:, None].expand_as(got[0])) and torch.equal(got[1], wv[:, None].expand_as(got[1])), (level, at)
+
+        out = torch.zeros((2, l, copies * n, c), dtype=TDT[dt], device="cuda")
+        kvh.decode_batch(kvh.make_dec_items(one(src.data_ptr()), one(n), one(level), [i * n for i in range(copies)], one(0), "cuda"), copies, n,
+                         out[0], out[1], status=status)
+        check(out, "contiguous")
+        out = torch.zeros((2, l, copies * pages, 16, c), dtype=TDT[dt], device="cuda")
+        tables = torch.arange(copies * pages, dtype=torch.int32, device="cuda").view(copies, pages)
+        kvh.decode_batch(kvh.make_dec_items(one(src.data_ptr()), one(n), one(level), one(0), [t.data_ptr() for t in tables], "cuda"), copies, n,
+                         out[0], out[1], paged=True, status=status)
+        check(out, "paged")
+        out = torch.zeros((2, l, copies * orig, c), dtype=TDT[dt], device="cuda")
+        kvh.decode_kept_batch(kvh.make_kept_items(one(dropped.data_ptr()), one(n), one(level), [i * orig for i in range(copies)], one(0), one(orig),
+                                                  one(sink), one(window), one(0), "cuda"), copies, n, out[0], out[1], status=status)
+        check(out, "dropped")
 
 
 @pytest.mark.parametrize("heads", (1, 2, 3, 5, 6, 12))

@@ -27,6 +27,10 @@ extern "C" void dec_plan(int heads, int l, int items, int tokens, int64_t layer_
   o[0] = p.slots; o[1] = p.short_launch; o[2] = p.waves; o[3] = p.blocks; o[4] = p.plane_group; o[5] = p.row_tile;
   o[6] = grid_fits(p.blocks, p.plane_group, p.waves); o[7] = p.turn;
 }
+extern "C" void dec_units(int heads, int l, int items, int tokens, int64_t layer_stride, int64_t token_stride, int64_t* o) {
+  const DecUnits u = decode_units_plan(heads, l, items, tokens, layer_stride, token_stride);
+  o[0] = u.blocks; o[1] = u.plane_group;
+}
 """
 
 
@@ -40,7 +44,7 @@ def plans(tmp_path_factory):
 
     def call(name, *args):
         out = (ctypes.c_int64 * 8)()
-        wide = 4 if name == "dec_plan" else len(args)  # the strides
+        wide = 4 if name in ("dec_plan", "dec_units") else len(args)  # the strides
         getattr(lib, name)(*[ctypes.c_int64(a) if i >= wide else a for i, a in enumerate(args)], out)
         return list(out)
 
@@ -274,3 +278,20 @@ def test_gpu_tests_reach_the_transcoder_forms_they_name(plans):
 
     for heads, items in t.FORMS.items():
         assert [plans("tc_units", heads, 2, i, 300)[0] for i in items] == ([4, 8, 0] if heads <= 16 else [0])
+
+
+def test_decode_units_of_whole_spans(plans):
+    """Launches of whole spans of up to 192 MiB: enough one-wave blocks for K's sets of 4 heads x 16 rows and for V's 64 slots."""
+    for heads in (8, 16, 24, 64):
+        for l, items, n in ((1, 1, 1), (4, 1, 256), (3, 2, 17), (32, 1, 256), (80, 1, 33), (2, 1, 4001)):
+            if l * items * n * heads > 192 * 2048:
+                continue
+            blocks, group = plans("dec_units", heads, l, items, n, *dense(128 * heads, n * items))[:2]
+            assert blocks >= ceil(n, 16) * (heads // 4) and blocks * 64 >= n * heads and 1 <= group <= 2 * l
+    at = lambda heads, l, items, n, strides=None: plans("dec_units", heads, l, items, n, *(strides or dense(128 * heads, n * items)))[:2]
+    assert at(8, 32, 6, 256) == [32, 4] and at(8, 32, 1, 320)[1] == 8 and at(8, 32, 1, 321)[1] == 4 and at(8, 2, 1, 256)[1] == 4
+    assert at(8, 32, 6, 257)[0] == 0 and at(16, 32, 3, 257)[0] == 0 and at(8, 32767, 65535, 2**31 - 1)[0] == 0
+    assert at(8, 32, 6, 256, (1024, 32 * 1024)) == [32, 64]
+    assert not any(at(h, 1, 1, 1)[0] for h in (1, 2, 3, 4, 5, 6, 7, 9, 12, 20))
+    # what tests/test_gpu_row_lengths.py decodes in units and in spans
+    assert at(8, 2, 1, 300)[0] and not at(8, 2, 96, 300)[0] and not at(16, 2, 48, 300)[0] and at(8, 9, 1, 640)[0] and not at(8, 9, 1, 8191)[0]
