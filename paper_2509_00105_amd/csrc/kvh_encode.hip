@@ -8,7 +8,7 @@
 //     quantises its own registers.
 //   V (statistics over the 128 channels of a head): a head is 16 lanes x 8 channels, reduced
 //     with a 4-step rotate-and-combine inside the 16-lane DPP row.
-// Rows that leave many lanes of the last strip idle take units of (row, head) slots, see encode_k_slots and encode_row_slots.
+// Rows that leave lanes of the last strip idle, and small launches, take units of (row, head) slots, see encode_k_slots and encode_row_slots.
 // Quantised codes are produced with the packed float->u8 convert, which rounds to nearest even
 // and inserts the byte in one instruction; narrow codes are routed to their byte at that point.
 #include "kvh_common.hpp"
@@ -501,7 +501,7 @@ __device__ __forceinline__ void encode_v_block(const EncodeParams& a, const kvh_
   }
 }
 
-// ---- rows that leave many lanes of a strip idle (encode_plan has the rule) -------------------------------
+// ---- rows that leave lanes of a strip idle, and small launches (encode_plan and encode_units_plan have the rules) -------------------------------
 // Strips of 512 channels leave lanes without work when a row ends inside one: three of four with rows of 128 channels.
 // Here the 64 lanes x 16 accesses of a wave are 64 (row, head) slots, slot 4 i + j being lanes 16 j .. 16 j + 15 of
 // access i.
@@ -511,7 +511,7 @@ __device__ __forceinline__ void encode_v_block(const EncodeParams& a, const kvh_
 //   V, raw level: 64 consecutive (row, head) pairs in memory order, so codes and metadata are contiguous.
 // Consecutive slots are consecutive rows or heads, so that an access covers whole cache lines of codes where it can.
 // 80 layers x 8192 tokens x 128 channels in 512-token items, 2 bits: 168 -> 68 us (2.3 -> 5.6 TB/s); 20 x 3001 x 640 fp16
-// in one item, 4 bits: 47.2 -> 39.2 us; 32 x 12000 x 256, 4 bits: 107 -> 83 us.  Bound by memory now, as strips are.
+// in one item, 4 bits: 47.2 -> 39.2 us, in blocks of 4 waves 37.3; 32 x 12000 x 256, 4 bits: 107 -> 83 us.  Bound by memory now, as strips are.
 template <int DT, int BITS, bool PLAIN = false>
 __device__ __forceinline__ void encode_k_slots(const EncodeParams& a, const kvh_enc_item& it, uint8_t* layer_base,
                                                const LayerGeom& geo, int lam, int bx, float* red, int split, int64_t jump) {
@@ -814,7 +814,9 @@ __global__ __launch_bounds__(kEncThreads) __attribute__((amdgpu_waves_per_eu(4, 
 
 int launch_encode(const EncodeParams& a, int dt, int n_items, int max_tokens, hipStream_t stream) {
   const int heads = a.c / kGroup, nstrips = (a.c + kStripCh - 1) / kStripCh;
-  const EncPlan plan = encode_plan(heads, a.l, n_items, max_tokens);
+  EncPlan plan = encode_plan(heads, a.l, n_items, max_tokens);
+  if (const EncUnits units = encode_units_plan(heads, a.l, n_items, max_tokens); units.waves != 0)
+    plan = EncPlan{true, true, heads % 2 == 1, units.waves, units.blocks};
   const int64_t gx = plan.blocks;
   EncodeParams b = a;
   b.max_tokens = max_tokens;

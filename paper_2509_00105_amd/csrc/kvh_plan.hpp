@@ -258,4 +258,26 @@ inline EncPlan encode_plan(int heads, int l, int n_items, int max_tokens) {
   return p;
 }
 
+// Slots in blocks of 4 waves for rows of 3 heads and more.  A block of 4 waves is a K set of 2 heads (or two of one head) x a
+// token-group, half a strip: twice the blocks, each half as long.  250 launches of 0.5 MiB to 1.3 GiB, 2 to 80 layers, against
+// the layouts above, by the blocks of strips B a launch has:
+//   rows that are not whole strips (3, 5, 6, 7, 9, 10, 11, 14 heads): 0.97 to 1.49 times as fast at any size, 1.10 on average (5 heads,
+//   20 x 3,001 at 4 bits 39.6 -> 37.3 us, 32 x 8,192 at 2 bits 150 -> 137; 10 heads, 14 x 220 raw 9.6 -> 7.0; least: 14 heads, 20 x 367,
+//   0.93), but with B from 145 to 256, where a block of strips finds a compute unit for itself, 0.85 to 1.11, 1.01 on average;
+//   whole strips: B up to 144 0.99 to 1.39 (8 heads, 24 x 83 at 8 bits 8.6 -> 7.2), 257 to 400, where some compute units get a second
+//   block, 1.03 to 1.36 (17 x 477 raw 16.2 -> 11.9); 145 to 256 0.87 to 1.07 (one raw 1.27), beyond 400 0.94 to 1.06.
+struct EncUnits {
+  int waves;       // of a block, 0: the layouts above
+  int64_t blocks;  // of a (layer, K|V) plane
+};
+inline EncUnits encode_units_plan(int heads, int l, int n_items, int max_tokens) {
+  const int64_t groups = ((int64_t)max_tokens + 127) / 128;
+  const double b = 2.0 * l * n_items * (double)groups * ((heads + 3) / 4);
+  EncUnits u{};
+  if (heads < 3 || (b > 144 && b <= 256) || (heads % 4 == 0 && b > 400)) return u;
+  u.waves = 4;
+  u.blocks = (groups * heads + 1) / 2;
+  return u;
+}
+
 }  // namespace kvh

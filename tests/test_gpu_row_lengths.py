@@ -177,6 +177,30 @@ def test_turns_of_planes_through_all_items(kvh, l, items, m):
     assert out.any()
 
 
+# heads -> items of 2 layers x 300 tokens in launches of up to 144, 256 and 400 blocks of strips, and more
+ENCODER_ITEMS = {heads: items for group, items in (((3, 4), (1, 13, 22, 40)), ((5, 6, 7, 8), (1, 7, 11, 20)), ((9, 10, 12), (1, 5, 8, 14)),
+                                                   ((16,), (1, 4, 6, 10))) for heads in group}
+
+
+@pytest.mark.parametrize("dt", [gen.F16, gen.BF16])
+@pytest.mark.parametrize("heads", list(ENCODER_ITEMS))
+def test_encode_forms(kvh, heads, dt):
+    """The same rows encoded as often as it takes for the launch to go through slots in blocks of 4 waves and through the layouts
+    of middling and of large launches.  Every blob equals the oracle's, and nothing is written between them."""
+    l, n, c = 2, 300, 128 * heads
+    k, v = gen.make_kv(l, n, c, dt, seed=heads)
+    kd, vd = device(k, dt), device(v, dt)
+    for level in range(4):
+        want = torch.from_numpy(oracle.encode(k, v, dt, level)).cuda()
+        for items in ENCODER_ITEMS[heads]:
+            out = torch.full((items, want.numel() + 32), 0xAB, dtype=torch.uint8, device="cuda")
+            ptrs = [out.data_ptr() + i * out.shape[1] for i in range(items)]
+            kvh.encode_batch(kvh.make_enc_items(ptrs, [0] * items, [n] * items, [level] * items, "cuda"), items, n, kd, vd)
+            torch.cuda.synchronize()
+            assert torch.equal(out[:, : want.numel()], want.expand(items, -1)), (level, items)
+            assert (out[:, want.numel():] == 0xAB).all(), (level, items)
+
+
 @pytest.mark.parametrize("dt", [gen.F16, gen.BF16])
 @pytest.mark.parametrize("heads,copies", [(8, 1), (8, 96), (16, 48)])
 def test_one_blob_many_times(kvh, heads, copies, dt):

@@ -22,6 +22,10 @@ extern "C" void enc_plan(int heads, int l, int items, int tokens, int64_t* o) {
   const EncPlan p = encode_plan(heads, l, items, tokens);
   o[0] = p.slots; o[1] = p.k_slots; o[2] = p.waves; o[3] = p.blocks;
 }
+extern "C" void enc_units(int heads, int l, int items, int tokens, int64_t* o) {
+  const EncUnits u = encode_units_plan(heads, l, items, tokens);
+  o[0] = u.waves; o[1] = u.blocks;
+}
 extern "C" void dec_plan(int heads, int l, int items, int tokens, int64_t layer_stride, int64_t token_stride, int64_t* o) {
   const DecPlan p = decode_plan(heads, l, items, tokens, layer_stride, token_stride);
   o[0] = p.slots; o[1] = p.short_launch; o[2] = p.waves; o[3] = p.blocks; o[4] = p.plane_group; o[5] = p.row_tile;
@@ -295,3 +299,24 @@ def test_decode_units_of_whole_spans(plans):
     assert not any(at(h, 1, 1, 1)[0] for h in (1, 2, 3, 4, 5, 6, 7, 9, 12, 20))
     # what tests/test_gpu_row_lengths.py decodes in units and in spans
     assert at(8, 2, 1, 300)[0] and not at(8, 2, 96, 300)[0] and not at(16, 2, 48, 300)[0] and at(8, 9, 1, 640)[0] and not at(8, 9, 1, 8191)[0]
+
+
+@pytest.mark.parametrize("heads", list(range(1, 26)) + [33, 64])
+def test_encode_units_cover_rows_and_heads(plans, heads):
+    s, strips = (1 if heads & 1 else 2), ceil(heads, 4)
+    for l, items in ((1, 1), (4, 1), (7, 3), (32, 16)):
+        for n in (1, 127, 129, 300, 3001):
+            waves, blocks = plans("enc_units", heads, l, items, n)[:2]
+            b = 2 * l * items * ceil(n, 128) * strips
+            assert (waves != 0) == (heads >= 3 and not 144 < b <= 256 and (heads % 4 != 0 or b <= 400)), (l, items, n)
+            if waves:  # sets of s heads x a token-group take 2 s waves; V and raw 64 slots a wave
+                assert waves == 4 and blocks * (waves // (2 * s)) >= ceil(n, 128) * (heads // s) and blocks * waves * 64 >= n * heads
+    assert plans("enc_units", 2**24 - 4, 32767, 65535, 2**31 - 1)[0] == 0
+
+
+def test_gpu_tests_reach_the_encoder_forms_they_name(plans):
+    import test_gpu_row_lengths as t
+
+    for heads, items in t.ENCODER_ITEMS.items():
+        taken = [plans("enc_units", heads, 2, i, 300)[0] for i in items]
+        assert taken == ([4, 0, 4, 0] if heads % 4 == 0 else [4, 0, 4, 4]), heads
