@@ -69,6 +69,9 @@ struct DecPlan {
 //   80 to 896 MiB, 1024 channels, more than 10 planes of 4.5 to 16 MiB: turns of 4 0.98 to 1.2 times as fast as groups of 8, 1.02
 //   on average (10 x 5,000 at 4 bits 44.7 -> 41.5 us); smaller planes 0.88 to 1.06, larger ones 0.88 to 1.02, 2048 channels 0.98 to
 //   1.05, 10 planes 0.90 to 1.04.
+// Not for items of less than 512 tokens where layers lie a multiple of 16 MiB apart (8,192 tokens x 1024 channels): inputs not in a
+// cache, 32 x 8,192 at 8 / 4 / 2 bits 276 / 220 / 201 us as before, 280 / 219 / 219 in turns, 32 x 16,384 at 2 bits 401 and 432 (pages: 307 / 255 / 243
+// and 305 / 248 / 247); 48 x 6,000 gains 4 to 9 % at every level, 80 x 4,096 3 to 7 %, 32 x 8,192 in 1,024-token items 1 to 11 %.
 // For a single item groups and turns are the same order.  Items of more than 8,192 tokens that are alone stay plane by plane
 // (1.00 to 1.1).
 // Launches of whole spans of up to 80 MiB would also get two blocks per CU (they run in units of slots now, see
@@ -108,6 +111,7 @@ inline DecPlan decode_plan(int heads, int l, int n_items, int max_tokens, int64_
   if (!p.slots && !side_by_side && mib > 80) {
     const double plane = mib / planes;
     if (mib <= 896) turn = heads == 8 && planes > 10 && plane >= 4.5 && plane <= 16 ? 4 : 0;
+    else if (max_tokens < 512 && layer_stride % ((int64_t)8 << 20) == 0) turn = 0;
     else if (plane <= (max_tokens < 512 ? 40 : max_tokens < 1024 ? 64 : 128)) turn = mib <= 1400 ? 4 : 8;
   }
   if (turn > 0 && turn < planes && (n_items > 1 || max_tokens <= 8192)) {

@@ -210,7 +210,9 @@ def test_decode_turns(plans):
         assert t == group or (items == 1 and t < group and tile == 1)
         return t, group
 
-    assert turn(8, 32, 32, 256) == (4, 4) and turn(8, 32, 64, 256) == (8, 8)        # 1 and 2 GiB
+    assert turn(8, 32, 32, 250) == (4, 4) and turn(8, 32, 64, 250) == (8, 8)        # 1 and 2 GiB
+    assert turn(8, 32, 32, 256) == (64, 64) and turn(8, 32, 64, 256) == (64, 64)    # layers 16 and 32 MiB apart
+    assert turn(8, 32, 16, 512) == (4, 4) and turn(8, 80, 16, 256) == (4, 4)        # 16 MiB, longer items; 8 MiB
     assert turn(8, 32, 128, 256)[0] == 64                                           # planes of 64 MiB
     assert turn(8, 32, 64, 512) == (8, 8) and turn(8, 32, 64, 1024) == (8, 8) and turn(8, 32, 256, 1024)[0] == 64
     assert turn(8, 48, 1, 6000) == (4, 96) and turn(8, 80, 1, 8192) == (8, 160) and turn(8, 80, 1, 8193) == (160, 160)
