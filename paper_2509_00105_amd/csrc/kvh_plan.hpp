@@ -134,6 +134,12 @@ inline DecPlan decode_plan(int heads, int l, int n_items, int max_tokens, int64_
 // beyond, spans win: 256 MiB 0.93 to 1.07, 512 MiB 0.95 to 1.06, 1 GiB 0.83 to 1.08.
 // Planes 8 at a time up to 40 MiB, 4 at a time beyond (64 x 256 raw: 8 at a time 0.90 of the speed of spans, 4 at a time 1.05),
 // all at once where the layers of a token lie side by side (66 x 279 raw: 8 at a time 0.88, all 1.02).
+// A launch that fills no more than half of its planes (a chunk that goes back into a longer cache) takes all planes at once, and
+// units only up to 48 MiB: planes a power of two apart then meet on the same memory channels when few of them are taken at a time.
+// 110 such streams of launches over 4 to 80 layers, against spans: 32 x 256 tokens of an 8,192-token cache at 8 / 4 / 2 bits
+// 11.7 / 9.8 / 9.1 us in spans, 12.4 / 11.0 / 10.7 in units with planes 8 at a time, 11.0 / 9.1 / 8.4 with all; 64 x 128 of 2,048 at 2 bits
+// 9.6, 10.5, 9.4.  Up to 48 MiB 0.95 to 1.49 times as fast as spans (raw 32 x 256: 0.92), beyond 0.83 to 1.14 with nothing to tell
+// the two by (64 x 256 of 8,192 at 4 bits 0.99, 32 x 508 of 2048 channels at 2 bits 0.83, 12 x 2,368 at 8 bits 1.12).
 struct DecUnits {
   int64_t blocks;   // of a (layer, K|V) plane, a wave each; 0: the layouts above
   int plane_group;
@@ -141,9 +147,10 @@ struct DecUnits {
 inline DecUnits decode_units_plan(int heads, int l, int n_items, int max_tokens, int64_t layer_stride, int64_t token_stride) {
   DecUnits u{};
   const double mib = 4.0 * l * heads * 128 * max_tokens * n_items / (1 << 20);  // of 16-bit rows
-  if (heads % 8 != 0 || mib > 192) return u;
+  const bool sparse = (int64_t)n_items * max_tokens * token_stride <= layer_stride / 2;
+  if (heads % 8 != 0 || mib > (sparse ? 48 : 192)) return u;
   u.blocks = ((int64_t)max_tokens + 15) / 16 * (heads / 4);  // K: sets of 4 heads x 16 rows; V has no more units
-  const int most = layer_stride < token_stride ? 2 * l : mib <= 40 ? 8 : 4;
+  const int most = sparse || layer_stride < token_stride ? 2 * l : mib <= 40 ? 8 : 4;
   u.plane_group = most < 2 * l ? most : 2 * l;
   return u;
 }

@@ -298,6 +298,9 @@ def test_decode_units_of_whole_spans(plans):
     assert at(8, 32, 6, 256) == [32, 4] and at(8, 32, 1, 320)[1] == 8 and at(8, 32, 1, 321)[1] == 4 and at(8, 2, 1, 256)[1] == 4
     assert at(8, 32, 6, 257)[0] == 0 and at(16, 32, 3, 257)[0] == 0 and at(8, 32767, 65535, 2**31 - 1)[0] == 0
     assert at(8, 32, 6, 256, (1024, 32 * 1024)) == [32, 64]
+    assert at(8, 32, 1, 256, dense(1024, 8192)) == [32, 64] and at(8, 32, 1, 256, dense(1024, 512)) == [32, 64]   # half a plane and less
+    assert at(8, 32, 1, 256, dense(1024, 511)) == [32, 8] and at(8, 32, 1, 384, dense(1024, 768)) == [48, 64]
+    assert at(8, 32, 1, 385, dense(1024, 770))[0] == 0 and at(8, 32, 1, 385, dense(1024, 769)) == [50, 4]
     assert not any(at(h, 1, 1, 1)[0] for h in (1, 2, 3, 4, 5, 6, 7, 9, 12, 20))
     # what tests/test_gpu_row_lengths.py decodes in units and in spans
     assert at(8, 2, 1, 300)[0] and not at(8, 2, 96, 300)[0] and not at(16, 2, 48, 300)[0] and at(8, 9, 1, 640)[0] and not at(8, 9, 1, 8191)[0]
