@@ -60,8 +60,8 @@ struct DecPlan {
 //   average, 0.92 to 1.24.
 // Turns of whole spans.  Above 80 MiB the planes of a launch are better taken 4 (up to 1,400 MiB) or 8 at a time, one block
 // each, than 8 or all, where a plane is neither small nor large: what is written at one time then lies close together,
-// which counts most for pages of 16 tokens (32 KiB of 1024 channels, in random order: 8,192 tokens of 32 layers at 4 bits 231 ->
-// 219 us, contiguous 208 -> 206).  230 launches over 4 to 80 layers, 1024 and 2048 channels, items of 256 tokens to one item, all
+// which counts most for pages of 16 tokens (32 KiB of 1024 channels, in random order: 4,096 tokens of 80 layers at 4 bits 318 ->
+// 297 us, contiguous 281 -> 274).  230 launches over 4 to 80 layers, 1024 and 2048 channels, items of 256 tokens to one item, all
 // levels, against groups of 8 or the row tiles below:
 //   above 896 MiB with planes of up to 40 MiB (items of less than 512 tokens), 64 MiB (1,024) or 128 MiB: 0.96 to 1.21 times as
 //   fast, 1.04 on average (70 layers x 7,362 tokens in pages 551 -> 500 us, 48 x 6,000 in one item 281 -> 242); with larger
