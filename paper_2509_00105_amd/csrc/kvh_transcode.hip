@@ -1129,7 +1129,7 @@ __device__ __forceinline__ void transcode_units(const TranscodeParams& a, const 
   }
 }
 
-// The job of this block's item; its level pair as bits in * 16 + bits out, or -1: nothing to do.
+// The job of this block's item, for transcode_units_kernel; its level pair as bits in * 16 + bits out, or -1: nothing to do.
 __device__ __forceinline__ int load_job(const TranscodeParams& a, kvh_tc_item& it) {
   if (a.items != nullptr) {
     const uint8_t* p = reinterpret_cast<const uint8_t*>(a.items + blockIdx.z);
@@ -1167,12 +1167,37 @@ __global__ __launch_bounds__(kTcThreads) KVH_TC_OCC void transcode_kernel(Transc
   __shared__ float kquad[3 * kTcLaneCh * kWave];  // 12 KiB, [coefficient][slot][lane]: the 8 -> 2 polynomials
   __shared__ uint32_t kflags[kTcWaves];
   kvh_tc_item it;
-  const int pair = load_job(a, it);
-  if (pair < 0) return;  // block-uniform
+  // The steps of load_job, written out: through it the compiler needs some 280 instructions more for the layouts below, and
+  // large launches take longer (4 -> 2 bits, 1024 channels: 80 layers x 8,192 tokens 211.5 us as it stands, 214.8 through it,
+  // 32 x 32,768 334.4 and 338.2; 8 -> 4 bits no difference).
+  if (a.items != nullptr) {
+    const uint8_t* p = reinterpret_cast<const uint8_t*>(a.items + blockIdx.z);
+    uintx4 lo = gload<uintx4>(p), hi = gload<uintx4>(p + 16);
+    it.src = reinterpret_cast<const void*>((uint64_t)lo.x | (uint64_t)lo.y << 32);
+    it.dst = reinterpret_cast<void*>((uint64_t)lo.z | (uint64_t)lo.w << 32);
+    it.n_tokens = (int32_t)hi.x;
+    it.level_in = (int32_t)hi.y;
+    it.level_out = (int32_t)hi.z;
+    it.reserved = 0;
+  } else {
+    it = a.one;
+  }
+  it.src = uniform(it.src);
+  it.dst = uniform(it.dst);
+  it.n_tokens = uniform(it.n_tokens);
+  it.level_in = uniform(it.level_in);
+  it.level_out = uniform(it.level_out);
   const int bx = blockIdx.x, lay_kv = blockIdx.y;
+  if (it.n_tokens < 1) return;  // block-uniform
+  const int bi = level_bits(it.level_in), bo = level_bits(it.level_out);
+  // refused: a level out of range, the raw level (no codes to transcode), more tokens than the grid covers
+  if (bi < 0 || bo < 0 || bi > 8 || bo > 8 || it.n_tokens > a.max_tokens) {
+    if (a.status != nullptr && threadIdx.x == 0) a.status[blockIdx.z] = KVH_DEV_HEADER_MISMATCH;
+    return;
+  }
 #define KVH_TC_CASE(BI, BO) \
   case BI * 16 + BO: transcode_block<DT, BI, BO, SLOTS>(a, it, blockIdx.z, lay_kv, bx, kpar, kquad, kflags); break;
-  switch (pair) {
+  switch (bi * 16 + bo) {
     KVH_TC_CASE(8, 8) KVH_TC_CASE(8, 4) KVH_TC_CASE(8, 2)
     KVH_TC_CASE(4, 8) KVH_TC_CASE(4, 4) KVH_TC_CASE(4, 2)
     KVH_TC_CASE(2, 8) KVH_TC_CASE(2, 4) KVH_TC_CASE(2, 2)
