@@ -311,7 +311,8 @@ size_t kvh_loader_slot_bytes(const kvh_loader* loader);
  * kvh_decode_batch).  All items are validated before anything is enqueued. */
 int kvh_loader_run(kvh_loader* loader, const kvh_load_item* items, int n_items, kvh_dtype dt, int l, int c,
                    const kvh_kv_view* dst, int block_tokens, int32_t* status_dev, void* stream);
-/* Wait for the loader's copies, then release its stream and events (not the staging buffer). */
+/* Wait for the loader's copies and for the decodes of its slots, then release its stream and events (not the staging
+ * buffer). */
 int kvh_loader_destroy(kvh_loader* loader);
 
 /* Allocation-free form of kvh_loader_run, for callers that cannot allocate or create anything: code under HIP

@@ -322,8 +322,11 @@ int kvh_loader_run(kvh_loader* ld, const kvh_load_item* items, int n_items, kvh_
       rc = KVH_E_HIP;
     if (rc == KVH_OK) rc = launch_decode(a, dt, g.n, max_tokens, compute);
     if (rc == KVH_OK && hipEventRecord(ld->freed[s], compute) != hipSuccess) rc = KVH_E_HIP;
-    if (rc != KVH_OK) {  // no event tells a later run, which may be on another stream, when the slot is free
+    if (rc != KVH_OK) {
+      // No event tells a later run, which may be on another stream, when the slot is free: both the copy that writes it and a
+      // decode that may already read it are waited for here.
       (void)hipStreamSynchronize(copies);
+      if (!one_group) (void)hipStreamSynchronize(compute);
       return rc;
     }
     ld->in_use[s] = true;
