@@ -46,15 +46,15 @@ assert ENC_ITEM.itemsize == 24 and DEC_ITEM.itemsize == 32 and TC_ITEM.itemsize 
 assert KEPT_ENC_ITEM.itemsize == 32 and KEPT_ITEM.itemsize == 48
 
 _lib = None
-_fast = None  # csrc/kvh_fastcall.cpp over the loaded library
+_fast = None  # csrc/kvh_fastcall.cpp over the loaded library, where it is built: without it every call goes through ctypes
 
 
 def lib() -> ctypes.CDLL:
     """Load libkvh.so (built in-tree by `python -m paper_2509_00105_amd.build`)."""
     global _lib, _fast
     if _lib is None:
-        if not os.path.exists(_LIB_PATH) or not os.path.exists(os.path.join(_HERE, "_fastcall.so")):
-            raise ImportError("libkvh.so or _fastcall.so is not built: run `python -m paper_2509_00105_amd.build` "
+        if not os.path.exists(_LIB_PATH):
+            raise ImportError("libkvh.so is not built: run `python -m paper_2509_00105_amd.build` "
                               "(there is no CPU fallback for the HIP path)")
         L = ctypes.CDLL(_LIB_PATH)
         vp, i32, i64, sz = ctypes.c_void_p, ctypes.c_int, ctypes.c_int64, ctypes.c_size_t
@@ -120,9 +120,11 @@ def lib() -> ctypes.CDLL:
                                          view, i64, vp, i32, vp, vp]
         L.kvh_strerror.restype = ctypes.c_char_p
         L.kvh_strerror.argtypes = [i32]
-        from . import _fastcall
-
-        if _raw_stream is not None:
+        try:
+            from . import _fastcall
+        except ImportError:
+            _fastcall = None
+        if _fastcall is not None and _raw_stream is not None:
             _fast = _fastcall.Calls(torch.cuda.current_device, _raw_stream, *[
                 ctypes.cast(f, vp).value for f in (L.kvh_encode, L.kvh_encode_batch, L.kvh_decode, L.kvh_decode_batch,
                                                    L.kvh_encode_kept, L.kvh_decode_kept)])

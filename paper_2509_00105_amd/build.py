@@ -1,14 +1,16 @@
-"""Build the HIP library (libkvh.so) in-tree for gfx950 with hipcc, and the binding's call module (_fastcall.so) with g++."""
+"""Build the HIP library (libkvh.so) in-tree for gfx950 with hipcc, and the binding's call module (_fastcall) with the C++ compiler."""
 from __future__ import annotations
 
 import os
+import shlex
+import shutil
 import subprocess
 import sysconfig
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libkvh.so")
-CALLS = os.path.join(HERE, "_fastcall.so")
+CALLS = os.path.join(HERE, "_fastcall" + sysconfig.get_config_var("EXT_SUFFIX"))  # for the interpreter that builds it alone
 SOURCES = ["kvh_api.hip", "kvh_decode.hip", "kvh_encode.hip", "kvh_transcode.hip", "kvh_loader.hip", "kvh_policy.cpp"]
 
 # -ffp-contract=off: the codec's arithmetic fuses only where the source says fma.
@@ -34,11 +36,23 @@ def _compile(target: str, cmd: list, verbose: bool) -> None:
     os.replace(tmp, target)
 
 
+def _build_calls(verbose: bool) -> None:
+    """The call module makes calls cheaper and is no part of what they need: without Python's headers or a C++ compiler it is
+    left out, and the binding goes through ctypes."""
+    for old in (CALLS, os.path.join(HERE, "_fastcall.so")):  # none is left that does not belong to this library
+        if os.path.exists(old):
+            os.remove(old)
+    include, cxx = sysconfig.get_paths()["include"], shlex.split(os.environ.get("CXX", "g++"))
+    if not os.path.exists(os.path.join(include, "Python.h")) or not cxx or shutil.which(cxx[0]) is None:
+        print("no Python.h or no C++ compiler: calls go through ctypes")
+        return
+    _compile(CALLS, [*cxx, "-O2", "-std=c++17", "-Wall", "-shared", "-fPIC", "-I", include, os.path.join(CSRC, "kvh_fastcall.cpp")], verbose)
+
+
 def build(verbose: bool = False) -> str:
     hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
     _compile(LIB, [hipcc, *HIPCC_FLAGS, *[os.path.join(CSRC, s) for s in SOURCES]], verbose)
-    _compile(CALLS, [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-Wall", "-shared", "-fPIC", "-I", sysconfig.get_paths()["include"],
-                     os.path.join(CSRC, "kvh_fastcall.cpp")], verbose)
+    _build_calls(verbose)
     return LIB
 
 

@@ -319,3 +319,35 @@ def test_native_calls_leave_host_tensors_to_the_binding(lib):
     assert b._fast.decode_kept(u, 0, 128, 1, 1, k, k, 0, False, None, 16, None, None) is None
     with pytest.raises(TypeError):
         b._fast.encode(k, k)
+
+
+def test_the_binding_works_without_the_native_call_module(lib, tmp_path):
+    """A tree that holds the library alone loads it; the module is found by the interpreter it was built for and by no other."""
+    import shutil
+    import subprocess
+    import sys
+    import sysconfig
+
+    from paper_2509_00105_amd import _fastcall
+    from paper_2509_00105_amd import binding as b
+
+    assert os.path.basename(_fastcall.__file__) == "_fastcall" + sysconfig.get_config_var("EXT_SUFFIX") and b._fast is not None
+    package = tmp_path / "paper_2509_00105_amd"
+    shutil.copytree(os.path.join(ROOT, "paper_2509_00105_amd"), package, ignore=shutil.ignore_patterns("_fastcall*", "csrc", "__pycache__"))
+    code = "import paper_2509_00105_amd as k, paper_2509_00105_amd.binding as b; assert k.num_levels() == 3 and b._fast is None; print(b.__file__)"
+    out = subprocess.run([sys.executable, "-c", code], cwd=tmp_path, capture_output=True, text=True)
+    assert out.returncode == 0 and out.stdout.strip() == str(package / "binding.py"), out.stderr
+
+
+def test_build_leaves_the_native_call_module_out_where_it_cannot_be_compiled(monkeypatch, tmp_path, capsys):
+    from paper_2509_00105_amd import build
+
+    for name in ("HERE", "CALLS"):
+        monkeypatch.setattr(build, name, str(tmp_path if name == "HERE" else tmp_path / "_fastcall.so"))
+    (tmp_path / "_fastcall.so").write_text("of an earlier build")
+    monkeypatch.setenv("CXX", "no-such-compiler --flag")
+    build._build_calls(False)
+    assert "ctypes" in capsys.readouterr().out and not list(tmp_path.iterdir())
+    monkeypatch.setenv("CXX", "g++ -O1")
+    build._build_calls(False)
+    assert (tmp_path / "_fastcall.so").exists()
