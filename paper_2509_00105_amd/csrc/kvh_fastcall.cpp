@@ -29,8 +29,8 @@ struct Calls {
   PyObject *current_device, *raw_stream;
 };
 
-// What one call has read so far.  A failed step leaves ok false; a Python exception raised on the way is dropped, because the
-// slow path meets the same one.
+// What one call has read so far.  A failed step leaves ok false; an error raised on the way is dropped, because the slow path
+// meets the same one, but not what is no error of the call (an interrupt, an exit).
 struct Reader {
   bool ok = true;
 
@@ -171,6 +171,7 @@ void* read_stream(Reader& r, Calls* self, PyObject* stream) {
 template <typename F>
 PyObject* finish(const Reader& r, F&& call) {
   if (!r.ok) {
+    if (PyErr_Occurred() != nullptr && !PyErr_ExceptionMatches(PyExc_Exception)) return nullptr;
     PyErr_Clear();
     Py_RETURN_NONE;
   }

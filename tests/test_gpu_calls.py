@@ -158,3 +158,23 @@ def test_what_is_not_ordinary_is_accepted_or_refused_as_by_ctypes(kvh, monkeypat
     assert f.decode(blob, 1, n, out[0], out[1], 0, None, 16, status, None) == 0
     torch.cuda.synchronize()
     assert not status.any() and torch.equal(kvh.encode(k, v, 1), blob)
+
+
+def test_an_interrupt_is_not_dropped(kvh):
+    """Python code runs while the native module asks for the current stream.  What it raises as an error of the call is left to the
+    ctypes way, an interrupt or an exit comes out."""
+    k = torch.zeros((1, 128, 128), dtype=torch.float16, device="cuda")
+    blob = torch.zeros(kvh.blob_size(1, 128, 128, 0), dtype=torch.uint8, device="cuda")
+
+    def raising(what):
+        def current_device():
+            raise what
+
+        return type(kvh.binding._fast)(current_device, kvh.binding._raw_stream, 0, 0, 0, 0, 0, 0)  # no call gets as far as its function
+
+    assert raising(RuntimeError()).encode(k, k, 0, blob, None, None) is None
+    for what in (KeyboardInterrupt, SystemExit):
+        with pytest.raises(what):
+            raising(what()).encode(k, k, 0, blob, None, None)
+        with pytest.raises(what):
+            raising(what()).decode(blob, 0, 128, k, k, 0, None, 16, None, None)
