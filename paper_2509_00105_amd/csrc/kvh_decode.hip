@@ -658,9 +658,11 @@ __device__ __forceinline__ void decode_slots(const DecodeParams& a, const kvh_it
 #ifndef KVH_DEC_WPE
 #define KVH_DEC_WPE 3
 #endif
-// decode_slots, which needs about 85 registers, is held to the same (4 or 5 waves per SIMD make no difference to it).
-template <int DT, bool SLOTS>
-__global__ __launch_bounds__(kDecThreads) __attribute__((amdgpu_waves_per_eu(KVH_DEC_WPE, KVH_DEC_WPE))) void decode_kernel(DecodeParams a) {
+#define KVH_DEC_OCC(SHORT) __attribute__((amdgpu_waves_per_eu((SHORT) ? 4 : KVH_DEC_WPE, (SHORT) ? 4 : KVH_DEC_WPE)))
+// SHORT: two blocks per CU, for spans of launches that write little (see decode_plan).  decode_slots, which needs about 85 registers,
+// is held to one (4 or 5 waves per SIMD make no difference to it).
+template <int DT, bool SLOTS, bool SHORT>
+__global__ __launch_bounds__(kDecThreads) KVH_DEC_OCC(SHORT) void decode_kernel(DecodeParams a) {
   const int item_idx = blockIdx.y;
   // Block order: the (layer, K|V) planes are taken in groups of `plane_group` (grid z), a group through all items (grid
   // y) before the next.  Within an item and group (grid x): `row_tile` consecutive blocks of a plane, then the same
@@ -784,30 +786,24 @@ __global__ __launch_bounds__(kDecThreads) __attribute__((amdgpu_waves_per_eu(KVH
 
 int launch_decode(const DecodeParams& a, int dt, int n_items, int max_tokens, hipStream_t stream) {
   const int heads = a.c / kGroup;
-  const DecPlan plan = decode_plan(heads, a.l, n_items, max_tokens, a.layer_stride, a.token_stride);
-  if (!grid_fits(plan.blocks, plan.plane_group, plan.waves)) return KVH_E_HIP;
-  const DecUnits units = decode_units_plan(heads, a.l, n_items, max_tokens, a.layer_stride, a.token_stride);
+  const DecLaunch plan = decode_launch(heads, a.l, n_items, max_tokens, a.layer_stride, a.token_stride);
+  if (plan.blocks == 0) return KVH_E_HIP;
   DecodeParams b = a;
   b.max_tokens = max_tokens;
   b.row_tile = plan.row_tile;
   b.plane_blocks = (int)plan.blocks;
   b.waves = plan.waves;
-  b.plane_group = plan.turn;
-  if (units.blocks != 0) {
-    b.plane_blocks = (int)units.blocks;
-    b.waves = 1;
-    b.plane_group = units.plane_group;
-  }
-  const dim3 grid((unsigned)(b.plane_blocks * b.plane_group), (unsigned)n_items, (unsigned)((2 * a.l + b.plane_group - 1) / b.plane_group));
+  b.plane_group = plan.plane_group;
+  const dim3 grid((unsigned)(plan.blocks * b.plane_group), (unsigned)n_items, (unsigned)((2 * a.l + b.plane_group - 1) / b.plane_group));
   b.by_group = Divisor((uint32_t)b.plane_group);
   b.by_heads = Divisor((uint32_t)heads);
   b.by_sets = Divisor((uint32_t)(heads >> lowest_bit(heads | 4)));
   auto pick = [&](auto dt_tag) {
     constexpr int D = decltype(dt_tag)::value;
-    return plan.slots || units.blocks != 0 ? decode_kernel<D, true> : decode_kernel<D, false>;
+    return plan.slots ? decode_kernel<D, true, false> : plan.short_launch ? decode_kernel<D, false, true> : decode_kernel<D, false, false>;
   };
   auto kernel = dt == KVH_F16 ? pick(std::integral_constant<int, KVH_F16>{}) : pick(std::integral_constant<int, KVH_BF16>{});
-  launch_kernel(kernel, grid, dim3((unsigned)(b.waves * kWave)), 0u, stream, b);
+  launch_kernel(kernel, grid, dim3((unsigned)(plan.waves * kWave)), 0u, stream, b);
   KVH_HIP_CHECK_LAUNCH();
   return KVH_OK;
 }

@@ -74,10 +74,12 @@ struct DecPlan {
 // and 305 / 248 / 247); 48 x 6,000 gains 4 to 9 % at every level, 80 x 4,096 3 to 7 %, 32 x 8,192 in 1,024-token items 1 to 11 %.
 // For a single item groups and turns are the same order.  Items of more than 8,192 tokens that are alone stay plane by plane
 // (1.00 to 1.1).
-// Launches of whole spans of up to 80 MiB would also get two blocks per CU (they run in units of slots now, see
-// decode_units_plan): what they write is gone before the write stream has settled, and more waves in flight hide the start.  Nine layer counts from 2 to 80, 1024 to 4096 channels, all levels,
-// two blocks against one in the same order: 48 MiB +3 to +8 % on average, 64 MiB +1 to +4, 80 MiB -1, 96 MiB -1 to -3, 128
-// MiB 0 to -2, 192 and 256 MiB -1 to -2 (single cases down to -8 %).
+// Launches of whole spans of up to 80 MiB get two blocks per CU where they stay in spans (see decode_units_plan): what they write
+// is gone before the write stream has settled, and more waves in flight hide the start.  Nine layer counts from 2 to 80, 1024 to
+// 4096 channels, all levels, two blocks against one in the same order: 48 MiB +3 to +8 % on average, 64 MiB +1 to +4, 80 MiB -1, 96
+// MiB -1 to -3, 128 MiB 0 to -2, 192 and 256 MiB -1 to -2 (single cases down to -8 %).  Chunks of 48 to 80 MiB that go back into a
+// cache of 2 to 8 times their size, one block against two: 8 bits 0.92 to 1.06, 0.94 on average, 4 bits 0.91 to 1.04, 0.96, 2 bits
+// 0.97 to 1.07, raw 0.97 to 1.12 (24 x 752 of 3,760 tokens in pages, 8 bits: 22.4 us and 24.6).
 inline DecPlan decode_plan(int heads, int l, int n_items, int max_tokens, int64_t layer_stride, int64_t token_stride) {
   DecPlan p;
   p.slots = heads % 8 != 0;
@@ -153,6 +155,21 @@ inline DecUnits decode_units_plan(int heads, int l, int n_items, int max_tokens,
   const int most = sparse || layer_stride < token_stride ? 2 * l : mib <= 40 ? 8 : 4;
   u.plane_group = most < 2 * l ? most : 2 * l;
   return u;
+}
+
+// What launch_decode launches.
+struct DecLaunch {
+  bool slots, short_launch;   // as in DecPlan: short_launch counts for spans alone
+  int waves;
+  int64_t blocks;             // of a (layer, K|V) plane; 0: refused, the grid would not fit
+  int plane_group, row_tile;
+};
+inline DecLaunch decode_launch(int heads, int l, int n_items, int max_tokens, int64_t layer_stride, int64_t token_stride) {
+  const DecPlan p = decode_plan(heads, l, n_items, max_tokens, layer_stride, token_stride);
+  if (!grid_fits(p.blocks, p.plane_group, p.waves)) return DecLaunch{};
+  const DecUnits u = decode_units_plan(heads, l, n_items, max_tokens, layer_stride, token_stride);
+  if (u.blocks != 0) return DecLaunch{true, false, 1, u.blocks, u.plane_group, 1};
+  return DecLaunch{p.slots, p.short_launch, p.waves, p.blocks, p.turn, p.row_tile};
 }
 
 // ---- transcoder -------------------------------------------------------------------------------------------------

@@ -35,6 +35,10 @@ extern "C" void dec_units(int heads, int l, int items, int tokens, int64_t layer
   const DecUnits u = decode_units_plan(heads, l, items, tokens, layer_stride, token_stride);
   o[0] = u.blocks; o[1] = u.plane_group;
 }
+extern "C" void dec_launch(int heads, int l, int items, int tokens, int64_t layer_stride, int64_t token_stride, int64_t* o) {
+  const DecLaunch d = decode_launch(heads, l, items, tokens, layer_stride, token_stride);
+  o[0] = d.slots; o[1] = d.short_launch; o[2] = d.waves; o[3] = d.blocks; o[4] = d.plane_group; o[5] = d.row_tile;
+}
 """
 
 
@@ -48,7 +52,7 @@ def plans(tmp_path_factory):
 
     def call(name, *args):
         out = (ctypes.c_int64 * 8)()
-        wide = 4 if name in ("dec_plan", "dec_units") else len(args)  # the strides
+        wide = 4 if name in ("dec_plan", "dec_units", "dec_launch") else len(args)  # the strides
         getattr(lib, name)(*[ctypes.c_int64(a) if i >= wide else a for i, a in enumerate(args)], out)
         return list(out)
 
@@ -180,6 +184,21 @@ def test_decode_two_blocks_per_cu_only_for_small_launches(plans):
             if n:
                 assert plans("dec_plan", heads, l, 1, n, *dense(128 * heads, n))[1] == int(n * row_mib <= 80), (heads, l, mib)
     assert not any(plans("dec_plan", heads, 4, 1, 256, *dense(128 * heads, 256))[1] for heads in (1, 2, 4, 5, 12))
+
+
+def test_decode_launches_the_form_that_is_planned(plans):
+    """Units of slots, one wave a block, for small launches of whole spans; two blocks per CU for those of 48 to 80 MiB that fill at
+    most half of their planes, which stay in spans (24 x 752 tokens of 3,760 at 8 bits: 24.6 us with one block, 22.4 with two)."""
+    at = lambda heads, l, items, n, strides=None: plans("dec_launch", heads, l, items, n, *(strides or dense(128 * heads, n * items)))[:6]
+    assert at(8, 32, 1, 256) == [1, 0, 1, 32, 8, 1] and at(8, 32, 6, 256) == [1, 0, 1, 32, 4, 1]
+    assert at(8, 24, 1, 752, dense(1024, 3760)) == [0, 1, 8, 12, 8, 1] and at(8, 24, 1, 752, dense(1024, 1503))[0] == 1
+    assert at(8, 32, 1, 512, dense(1024, 8192))[:2] == [0, 1] and at(8, 32, 1, 640, dense(1024, 8192))[:2] == [0, 1]
+    assert at(8, 32, 1, 641, dense(1024, 8192))[:2] == [0, 0] and at(8, 32, 1, 384, dense(1024, 8192))[0] == 1
+    for heads, l, items, n in ((8, 32, 7, 256), (8, 80, 16, 256), (5, 32, 1, 256), (8, 20, 1, 15000), (8, 48, 1, 6000)):
+        strides = dense(128 * heads, items * n)
+        slots, _, waves, blocks, _, tile, fits, turn = plans("dec_plan", heads, l, items, n, *strides)
+        assert fits and at(heads, l, items, n) == [slots, 0, waves, blocks, turn, tile]
+    assert not any(at(8, 1, 1, 2**31 - 1, dense(1024, 1))[:4])  # refused
 
 
 def test_decode_small_launches_of_slots_take_small_blocks(plans):
