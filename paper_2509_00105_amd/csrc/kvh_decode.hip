@@ -4,7 +4,7 @@
 //
 // Streaming kernel, in two forms by row length.  Rows of whole 1024-channel spans: the unit of work is one wave
 // decoding 8 consecutive token rows of a span (two 512-channel segments), i.e. 16 KiB of contiguous output when
-// c = 1024.  Any other row length, and launches of up to 192 MiB, take units of 64 (row, head) slots, see decode_slots.
+// c = 1024.  Any other row length, and launches of up to 48 MiB, take units of 64 (row, head) slots, see decode_slots.
 // A lane owns 8 channels per segment, so each store is one 128-bit access and the wave writes
 // 1 KiB of a row per instruction.  A block is 8 such units: 64 consecutive rows of one span, which
 // always lie in one K token-group.  K metadata (per channel) is turned into fp32 parameters either
@@ -507,7 +507,7 @@ __device__ __forceinline__ void decode_raw_unit(const DecodeParams& a, const kvh
 //     and their parameters through the unit.  The rows of a unit lie in one token-group (64 / S divides 128).
 // 32 x 8192 tokens or the like, % of HBM peak before / after: 80 layers of 128 channels 8 bits 17 / 77, of 256 channels
 // 8 bits into pages 31 / 66, 4 bits 32 / 80, 32 layers of 512 channels 4 bits 55 / 75, of 640 channels 8 bits 58 / 70,
-// of 1280 channels 4 bits 54 / 68.  What bounds it now is the write stream, as for whole spans.  Launches of whole spans up to 192
+// of 1280 channels 4 bits 54 / 68.  What bounds it now is the write stream, as for whole spans.  Launches of whole spans up to 48
 // MiB take the same units, a wave a block (decode_units_plan): what bounds those is the start, and the last blocks.
 // Lane 16 j + i owns slot 4 i + j: it finds its destination (page table included) and, for V, prepares its group;
 // access i fetches both by a row broadcast from lane i.  Waves are independent: no LDS, no barrier.

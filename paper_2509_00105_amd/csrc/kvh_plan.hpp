@@ -74,7 +74,7 @@ struct DecPlan {
 // and 305 / 248 / 247); 48 x 6,000 gains 4 to 9 % at every level, 80 x 4,096 3 to 7 %, 32 x 8,192 in 1,024-token items 1 to 11 %.
 // For a single item groups and turns are the same order.  Items of more than 8,192 tokens that are alone stay plane by plane
 // (1.00 to 1.1).
-// Launches of whole spans of up to 80 MiB get two blocks per CU where they stay in spans (see decode_units_plan): what they write
+// Launches of whole spans of up to 80 MiB get two blocks per CU where they are not in units of slots (decode_units_plan): what they write
 // is gone before the write stream has settled, and more waves in flight hide the start.  Nine layer counts from 2 to 80, 1024 to
 // 4096 channels, all levels, two blocks against one in the same order: 48 MiB +3 to +8 % on average, 64 MiB +1 to +4, 80 MiB -1, 96
 // MiB -1 to -3, 128 MiB 0 to -2, 192 and 256 MiB -1 to -2 (single cases down to -8 %).  Chunks of 48 to 80 MiB that go back into a
@@ -128,20 +128,17 @@ inline DecPlan decode_plan(int heads, int l, int n_items, int max_tokens, int64_
 }
 
 // Whole spans, small launches.  A block of spans is 64 rows, 8 waves and (at 8 bits) a barrier, and its waves write 16 KiB a
-// piece: 4 layers x 256 tokens make 32 blocks.  Up to 192 MiB of rows they run in units of slots, one wave a block (4 heads x 16
-// rows, or 64 slots in memory order), which start sooner and spread evenly: 400 launches of 0.3 to 260 MiB over 2 to 80 layers, 8
-// to 32 heads, all levels, against spans (one or two blocks per CU, turns of planes): up to 12 MiB 1.05 to 1.65 times as fast (4 x
-// 256 tokens at 8 bits, pages: 6.9 -> 4.2 us), 12 to 40 MiB 0.93 to 1.24, 1.07 on average (below 1 mostly the raw level at 14 to 25
-// MiB, 0.94 to 0.99), 40 to 192 MiB 0.94 to 1.26, 1.05 on average (30 x 939 at 8 bits 34.8 -> 33.6, 9 x 2,817 at 2 bits 25.1 -> 20.0);
-// beyond, spans win: 256 MiB 0.93 to 1.07, 512 MiB 0.95 to 1.06, 1 GiB 0.83 to 1.08.
-// Planes 8 at a time up to 40 MiB, 4 at a time beyond (64 x 256 raw: 8 at a time 0.90 of the speed of spans, 4 at a time 1.05),
-// all at once where the layers of a token lie side by side (66 x 279 raw: 8 at a time 0.88, all 1.02).
-// A launch that fills no more than half of its planes (a chunk that goes back into a longer cache) takes all planes at once, and
-// units only up to 48 MiB: planes a power of two apart then meet on the same memory channels when few of them are taken at a time.
-// 110 such streams of launches over 4 to 80 layers, against spans: 32 x 256 tokens of an 8,192-token cache at 8 / 4 / 2 bits
-// 11.7 / 9.8 / 9.1 us in spans, 12.4 / 11.0 / 10.7 in units with planes 8 at a time, 11.0 / 9.1 / 8.4 with all; 64 x 128 of 2,048 at 2 bits
-// 9.6, 10.5, 9.4.  Up to 48 MiB 0.95 to 1.49 times as fast as spans (raw 32 x 256: 0.92), beyond 0.83 to 1.14 with nothing to tell
-// the two by (64 x 256 of 8,192 at 4 bits 0.99, 32 x 508 of 2048 channels at 2 bits 0.83, 12 x 2,368 at 8 bits 1.12).
+// piece: 4 layers x 256 tokens make 32 blocks.  Up to 48 MiB of rows they run in units of slots, one wave a block (4 heads x 16
+// rows, or 64 slots in memory order), which start sooner and spread evenly.  320 streams of launches over 2 to 80 layers, 8 and 16
+// heads, all levels, inputs changing from launch to launch, against spans (two blocks per CU up to 80 MiB): up to 20 MiB 0.99 to 1.44
+// times as fast (raw 0.92 to 1.21), 20 to 34 MiB 0.97 to 1.5 (raw 0.91 to 1.26), 34 to 48 MiB 1.0 to 1.4, 1.2 on average; beyond, spans win:
+// 48 to 64 MiB 1.02 / 0.96 / 1.00 / 0.99 on average at 8 / 4 / 2 bits and raw, 100 to 130 MiB 1.01 / 0.97 / 1.00 / 1.01, 130 to 192
+// MiB 0.99 / 0.96 / 0.98 / 0.99.  (4 x 256 tokens at 8 bits, pages: 6.9 -> 4.2 us by the kernel's own events.)
+// Planes 8 at a time (4 at a time 0.96 to 1.0 of that), all at once where the layers of a token lie side by side (66 x 279 raw: 8 at
+// a time 0.88, all 1.02), and where a launch fills no more than half of its planes (a chunk that goes back into a longer cache):
+// planes a power of two apart then meet on the same memory channels when few of them are taken at a time.  32 x 256 tokens of
+// an 8,192-token cache at 8 / 4 / 2 bits 11.7 / 9.8 / 9.1 us in spans, 12.4 / 11.0 / 10.7 in units with planes 8 at a time, 11.0 / 9.1 / 8.4
+// with all; 50 such streams of 10 to 48 MiB into caches of 4,096 to 16,384 tokens 0.98 to 1.45 times as fast as spans.
 struct DecUnits {
   int64_t blocks;   // of a (layer, K|V) plane, a wave each; 0: the layouts above
   int plane_group;
@@ -149,10 +146,10 @@ struct DecUnits {
 inline DecUnits decode_units_plan(int heads, int l, int n_items, int max_tokens, int64_t layer_stride, int64_t token_stride) {
   DecUnits u{};
   const double mib = 4.0 * l * heads * 128 * max_tokens * n_items / (1 << 20);  // of 16-bit rows
-  const bool sparse = (int64_t)n_items * max_tokens * token_stride <= layer_stride / 2;
-  if (heads % 8 != 0 || mib > (sparse ? 48 : 192)) return u;
+  const bool sparse = 2.0 * n_items * max_tokens * token_stride <= layer_stride;
+  if (heads % 8 != 0 || mib > 48) return u;
   u.blocks = ((int64_t)max_tokens + 15) / 16 * (heads / 4);  // K: sets of 4 heads x 16 rows; V has no more units
-  const int most = sparse || layer_stride < token_stride ? 2 * l : mib <= 40 ? 8 : 4;
+  const int most = sparse || layer_stride < token_stride ? 2 * l : 8;
   u.plane_group = most < 2 * l ? most : 2 * l;
   return u;
 }

@@ -187,13 +187,14 @@ def test_decode_two_blocks_per_cu_only_for_small_launches(plans):
 
 
 def test_decode_launches_the_form_that_is_planned(plans):
-    """Units of slots, one wave a block, for small launches of whole spans; two blocks per CU for those of 48 to 80 MiB that fill at
-    most half of their planes, which stay in spans (24 x 752 tokens of 3,760 at 8 bits: 24.6 us with one block, 22.4 with two)."""
+    """Units of slots, one wave a block, for launches of whole spans of up to 48 MiB, beyond which spans win (4 bits, 48 to 192 MiB:
+    units 0.96 of their speed); two blocks per CU for spans of up to 80 MiB (24 x 752 tokens of 3,760 at 8 bits: 22.4 us, with one block 24.6)."""
     at = lambda heads, l, items, n, strides=None: plans("dec_launch", heads, l, items, n, *(strides or dense(128 * heads, n * items)))[:6]
-    assert at(8, 32, 1, 256) == [1, 0, 1, 32, 8, 1] and at(8, 32, 6, 256) == [1, 0, 1, 32, 4, 1]
-    assert at(8, 24, 1, 752, dense(1024, 3760)) == [0, 1, 8, 12, 8, 1] and at(8, 24, 1, 752, dense(1024, 1503))[0] == 1
-    assert at(8, 32, 1, 512, dense(1024, 8192))[:2] == [0, 1] and at(8, 32, 1, 640, dense(1024, 8192))[:2] == [0, 1]
-    assert at(8, 32, 1, 641, dense(1024, 8192))[:2] == [0, 0] and at(8, 32, 1, 384, dense(1024, 8192))[0] == 1
+    assert at(8, 32, 1, 256) == [1, 0, 1, 32, 8, 1] and at(8, 32, 1, 256, dense(1024, 8192)) == [1, 0, 1, 32, 64, 1]
+    for strides in (None, dense(1024, 8192)):
+        assert at(8, 32, 1, 384, strides)[0] == 1 and at(8, 32, 1, 385, strides)[:2] == [0, 1]
+        assert at(8, 32, 1, 640, strides)[:2] == [0, 1] and at(8, 32, 1, 641, strides)[:2] == [0, 0]
+    assert at(8, 24, 1, 752, dense(1024, 3760)) == [0, 1, 8, 12, 8, 1]
     for heads, l, items, n in ((8, 32, 7, 256), (8, 80, 16, 256), (5, 32, 1, 256), (8, 20, 1, 15000), (8, 48, 1, 6000)):
         strides = dense(128 * heads, items * n)
         slots, _, waves, blocks, _, tile, fits, turn = plans("dec_plan", heads, l, items, n, *strides)
@@ -306,20 +307,20 @@ def test_gpu_tests_reach_the_transcoder_forms_they_name(plans):
 
 
 def test_decode_units_of_whole_spans(plans):
-    """Launches of whole spans of up to 192 MiB: enough one-wave blocks for K's sets of 4 heads x 16 rows and for V's 64 slots."""
+    """Launches of whole spans of up to 48 MiB: enough one-wave blocks for K's sets of 4 heads x 16 rows and for V's 64 slots."""
     for heads in (8, 16, 24, 64):
         for l, items, n in ((1, 1, 1), (4, 1, 256), (3, 2, 17), (32, 1, 256), (80, 1, 33), (2, 1, 4001)):
-            if l * items * n * heads > 192 * 2048:
+            if l * items * n * heads > 48 * 2048:
                 continue
             blocks, group = plans("dec_units", heads, l, items, n, *dense(128 * heads, n * items))[:2]
             assert blocks >= ceil(n, 16) * (heads // 4) and blocks * 64 >= n * heads and 1 <= group <= 2 * l
     at = lambda heads, l, items, n, strides=None: plans("dec_units", heads, l, items, n, *(strides or dense(128 * heads, n * items)))[:2]
-    assert at(8, 32, 6, 256) == [32, 4] and at(8, 32, 1, 320)[1] == 8 and at(8, 32, 1, 321)[1] == 4 and at(8, 2, 1, 256)[1] == 4
-    assert at(8, 32, 6, 257)[0] == 0 and at(16, 32, 3, 257)[0] == 0 and at(8, 32767, 65535, 2**31 - 1)[0] == 0
-    assert at(8, 32, 6, 256, (1024, 32 * 1024)) == [32, 64]
+    assert at(8, 32, 3, 128) == [16, 8] and at(8, 32, 1, 384) == [48, 8] and at(8, 2, 1, 256)[1] == 4
+    assert at(8, 32, 3, 129)[0] == 0 and at(16, 32, 1, 193)[0] == 0 and at(8, 32767, 65535, 2**31 - 1)[0] == 0
+    assert at(8, 32, 1, 256, (1024, 32 * 1024)) == [32, 64]
     assert at(8, 32, 1, 256, dense(1024, 8192)) == [32, 64] and at(8, 32, 1, 256, dense(1024, 512)) == [32, 64]   # half a plane and less
     assert at(8, 32, 1, 256, dense(1024, 511)) == [32, 8] and at(8, 32, 1, 384, dense(1024, 768)) == [48, 64]
-    assert at(8, 32, 1, 385, dense(1024, 770))[0] == 0 and at(8, 32, 1, 385, dense(1024, 769)) == [50, 4]
+    assert at(8, 32, 1, 385, dense(1024, 8192))[0] == 0 and at(8, 1, 1, 1, (2**62, 2**31))[0] == 2
     assert not any(at(h, 1, 1, 1)[0] for h in (1, 2, 3, 4, 5, 6, 7, 9, 12, 20))
     # what tests/test_gpu_row_lengths.py decodes in units and in spans
     assert at(8, 2, 1, 300)[0] and not at(8, 2, 96, 300)[0] and not at(16, 2, 48, 300)[0] and at(8, 9, 1, 640)[0] and not at(8, 9, 1, 8191)[0]
