@@ -260,7 +260,7 @@ int kvh_decode(const void* blob_dev, kvh_dtype dt, int l, int n_tokens, int c, i
   a.c = c;
   a.block_tokens = page_table_dev != nullptr ? block_tokens : 1;
   a.split = kNoSplit;
-  return launch_decode(a, dt, 1, n_tokens, static_cast<hipStream_t>(stream));
+  return launch_decode(a, dt, 1, n_tokens, level == kRawLevel, static_cast<hipStream_t>(stream));
 }
 
 int kvh_decode_chunked(const void* blobs_dev, const size_t* blob_offsets, const int8_t* levels, kvh_dtype dt, int l, int N,
@@ -293,15 +293,17 @@ int kvh_decode_chunked(const void* blobs_dev, const size_t* blob_offsets, const 
   // the descriptors ride in the kernel arguments, kInlineItems chunks per launch
   for (int i0 = 0; i0 < n_chunks; i0 += kInlineItems) {
     const int cnt = n_chunks - i0 < kInlineItems ? n_chunks - i0 : kInlineItems;
+    bool raw = true;
     for (int j = 0; j < cnt; ++j) {
       const int i = i0 + j;
       const int n = (i + 1) * (int64_t)chunk <= N ? chunk : N - i * chunk;
+      raw = raw && levels[i] == kRawLevel;
       a.inline_items[j] = kvh_item{static_cast<const uint8_t*>(blobs_dev) + blob_offsets[i], n, levels[i],
                                    dst_token0 + (int64_t)i * chunk, page_table_dev};
     }
     a.n_inline = cnt;
     a.status = status_dev != nullptr ? status_dev + i0 : nullptr;
-    if (int rc = launch_decode(a, dt, cnt, chunk, static_cast<hipStream_t>(stream))) return rc;
+    if (int rc = launch_decode(a, dt, cnt, chunk, raw, static_cast<hipStream_t>(stream))) return rc;
   }
   return KVH_OK;
 }
@@ -324,7 +326,7 @@ int kvh_decode_batch(const kvh_item* items_dev, int n_items, int max_tokens_per_
   a.c = c;
   a.block_tokens = block_tokens;
   a.split = kNoSplit;
-  return launch_decode(a, dt, n_items, max_tokens_per_item, static_cast<hipStream_t>(stream));
+  return launch_decode(a, dt, n_items, max_tokens_per_item, false, static_cast<hipStream_t>(stream));
 }
 
 int kvh_kept_tokens(int N, int sink, int window) {
@@ -389,7 +391,7 @@ int kvh_decode_kept(const void* blob_dev, kvh_dtype dt, int l, int N, int c, int
   a.hdr_orig_tokens = (uint32_t)N;
   a.hdr_sink = (uint32_t)sink;
   a.hdr_window = (uint32_t)window;
-  return launch_decode(a, dt, 1, n, static_cast<hipStream_t>(stream));
+  return launch_decode(a, dt, 1, n, level == kRawLevel, static_cast<hipStream_t>(stream));
 }
 
 int kvh_transcode(const void* src_dev, kvh_dtype dt, int l, int n_tokens, int c, int level_in, int level_out,
@@ -459,7 +461,7 @@ int kvh_decode_kept_batch(const kvh_kept_item* items_dev, int n_items, int max_t
   a.c = c;
   a.block_tokens = block_tokens;
   a.split = kNoSplit;
-  return launch_decode(a, dt, n_items, max_tokens_per_item, static_cast<hipStream_t>(stream));
+  return launch_decode(a, dt, n_items, max_tokens_per_item, false, static_cast<hipStream_t>(stream));
 }
 
 int kvh_copy_probe(void* dst_dev, const void* src_dev, size_t bytes, void* stream) {

@@ -784,9 +784,9 @@ __global__ __launch_bounds__(kDecThreads) KVH_DEC_OCC(SHORT) void decode_kernel(
   }
 }
 
-int launch_decode(const DecodeParams& a, int dt, int n_items, int max_tokens, hipStream_t stream) {
+int launch_decode(const DecodeParams& a, int dt, int n_items, int max_tokens, bool raw, hipStream_t stream) {
   const int heads = a.c / kGroup;
-  const DecLaunch plan = decode_launch(heads, a.l, n_items, max_tokens, a.layer_stride, a.token_stride);
+  const DecLaunch plan = decode_launch(heads, a.l, n_items, max_tokens, a.layer_stride, a.token_stride, raw);
   if (plan.blocks == 0) return KVH_E_HIP;
   DecodeParams b = a;
   b.max_tokens = max_tokens;

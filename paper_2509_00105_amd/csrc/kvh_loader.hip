@@ -116,11 +116,12 @@ int validate_load(const kvh_load_item* items, int n_items, kvh_dtype dt, int l, 
 }
 
 // Pack consecutive blobs, starting at items[first], into one slot of `capacity` bytes for blobs; returns how many
-// went in (at least one: every blob has been checked against the capacity) and their largest token count.
+// went in (at least one: every blob has been checked against the capacity), their largest token count and whether all are raw.
 int pack_group(const kvh_load_item* items, int first, int n_items, int l, int c, uint8_t* slot, size_t capacity,
-               CopyGroup& g, int& max_tokens) {
+               CopyGroup& g, int& max_tokens, bool& raw) {
   size_t used = 0;
   max_tokens = 0;
+  raw = true;
   g.n = 0;
   g.tiles = 0;
   for (uint32_t& end : g.tile_end) end = 0xffffffffu;
@@ -134,6 +135,7 @@ int pack_group(const kvh_load_item* items, int first, int n_items, int l, int c,
     g.item[g.n] = kvh_kept_item{slot + kDescBytes + used, it.n_tokens, it.level, it.dst_token0, it.page_table,
                                 it.orig_tokens, it.sink, it.window, it.compact};
     if (it.n_tokens > max_tokens) max_tokens = it.n_tokens;
+    raw = raw && it.level == kRawLevel;
     used += bytes;
     ++g.n;
   }
@@ -309,8 +311,9 @@ int kvh_loader_run(kvh_loader* ld, const kvh_load_item* items, int n_items, kvh_
     uint8_t* slot = ld->staging + (size_t)s * ld->slot_pitch;
     CopyGroup g{};
     int max_tokens = 0;
+    bool raw = false;
     if (!one_group && last == n_items) last = cut_last_group(items, first, n_items, l, c, ld->slot_bytes, ld->n_slots);
-    pack_group(items, first, last, l, c, slot, ld->slot_bytes, g, max_tokens);
+    pack_group(items, first, last, l, c, slot, ld->slot_bytes, g, max_tokens, raw);
     if (first + g.n == last) last = n_items;
     // the slot may still be read by the decode that used it last (in this run or an earlier one)
     if (ld->in_use[s] && hipStreamWaitEvent(copies, ld->freed[s], 0) != hipSuccess) return KVH_E_HIP;
@@ -320,7 +323,7 @@ int kvh_loader_run(kvh_loader* ld, const kvh_load_item* items, int n_items, kvh_
     int rc = KVH_OK;
     if (!one_group && (hipEventRecord(ld->copied[s], copies) != hipSuccess || hipStreamWaitEvent(compute, ld->copied[s], 0) != hipSuccess))
       rc = KVH_E_HIP;
-    if (rc == KVH_OK) rc = launch_decode(a, dt, g.n, max_tokens, compute);
+    if (rc == KVH_OK) rc = launch_decode(a, dt, g.n, max_tokens, raw, compute);
     if (rc == KVH_OK && hipEventRecord(ld->freed[s], compute) != hipSuccess) rc = KVH_E_HIP;
     if (rc != KVH_OK) {
       // No event tells a later run, which may be on another stream, when the slot is free: both the copy that writes it and a
@@ -358,11 +361,12 @@ int kvh_load_static(const kvh_load_item* items, int n_items, kvh_dtype dt, int l
   for (int first = 0; first < n_items;) {
     CopyGroup g{};
     int max_tokens = 0;
-    pack_group(items, first, n_items, l, c, slot, capacity, g, max_tokens);
+    bool raw = false;
+    pack_group(items, first, n_items, l, c, slot, capacity, g, max_tokens, raw);
     if (int rc = launch_copy(g, slot, compute)) return rc;
     a.kept_items = reinterpret_cast<const kvh_kept_item*>(slot);
     a.status = status_dev != nullptr ? status_dev + first : nullptr;
-    if (int rc = launch_decode(a, dt, g.n, max_tokens, compute)) return rc;
+    if (int rc = launch_decode(a, dt, g.n, max_tokens, raw, compute)) return rc;
     first += g.n;
   }
   return KVH_OK;

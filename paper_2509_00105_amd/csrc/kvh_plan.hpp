@@ -139,15 +139,22 @@ inline DecPlan decode_plan(int heads, int l, int n_items, int max_tokens, int64_
 // planes a power of two apart then meet on the same memory channels when few of them are taken at a time.  32 x 256 tokens of
 // an 8,192-token cache at 8 / 4 / 2 bits 11.7 / 9.8 / 9.1 us in spans, 12.4 / 11.0 / 10.7 in units with planes 8 at a time, 11.0 / 9.1 / 8.4
 // with all; 50 such streams of 10 to 48 MiB into caches of 4,096 to 16,384 tokens 0.98 to 1.45 times as fast as spans.
+// The raw level has no parameters to prepare and no barrier in spans, whose blocks only have to find a compute unit each: with more
+// than 160 and up to 256 of them spans are the faster form.  Chunks into a longer cache by their blocks in spans, spans against units:
+// 144 to 160 0.98 to 1.06, 168 to 256 0.99 to 1.1 (32 x 256 tokens of 8,192: 15.6 us and 17.1; 24 x 256 of 4,096 1.10), 280 to 384 0.82
+// to 1.02; tensors of the launch's own size, inputs changing, 168 to 256 0.95 to 1.05, 264 and more 0.79 to 0.95.
+// `raw`: every item is known to be of that level, as for a single blob; the descriptors of a batch are out of the launcher's sight.
 struct DecUnits {
   int64_t blocks;   // of a (layer, K|V) plane, a wave each; 0: the layouts above
   int plane_group;
 };
-inline DecUnits decode_units_plan(int heads, int l, int n_items, int max_tokens, int64_t layer_stride, int64_t token_stride) {
+inline DecUnits decode_units_plan(int heads, int l, int n_items, int max_tokens, int64_t layer_stride, int64_t token_stride, bool raw) {
   DecUnits u{};
   const double mib = 4.0 * l * heads * 128 * max_tokens * n_items / (1 << 20);  // of 16-bit rows
   const bool sparse = 2.0 * n_items * max_tokens * token_stride <= layer_stride;
   if (heads % 8 != 0 || mib > 48) return u;
+  const int64_t spans = ((int64_t)max_tokens + 63) / 64 * (heads / 8) * 2 * l * n_items;  // blocks of them
+  if (raw && spans > 160 && spans <= 256) return u;
   u.blocks = ((int64_t)max_tokens + 15) / 16 * (heads / 4);  // K: sets of 4 heads x 16 rows; V has no more units
   const int most = sparse || layer_stride < token_stride ? 2 * l : 8;
   u.plane_group = most < 2 * l ? most : 2 * l;
@@ -161,10 +168,10 @@ struct DecLaunch {
   int64_t blocks;             // of a (layer, K|V) plane; 0: refused, the grid would not fit
   int plane_group, row_tile;
 };
-inline DecLaunch decode_launch(int heads, int l, int n_items, int max_tokens, int64_t layer_stride, int64_t token_stride) {
+inline DecLaunch decode_launch(int heads, int l, int n_items, int max_tokens, int64_t layer_stride, int64_t token_stride, bool raw) {
   const DecPlan p = decode_plan(heads, l, n_items, max_tokens, layer_stride, token_stride);
   if (!grid_fits(p.blocks, p.plane_group, p.waves)) return DecLaunch{};
-  const DecUnits u = decode_units_plan(heads, l, n_items, max_tokens, layer_stride, token_stride);
+  const DecUnits u = decode_units_plan(heads, l, n_items, max_tokens, layer_stride, token_stride, raw);
   if (u.blocks != 0) return DecLaunch{true, false, 1, u.blocks, u.plane_group, 1};
   return DecLaunch{p.slots, p.short_launch, p.waves, p.blocks, p.turn, p.row_tile};
 }
