@@ -230,7 +230,12 @@ struct TcUnits {
 //   8 are 0.87 to 1.6 times as fast, 1.16 on average, up to 2,000;
 //   1 and 2 heads up to 2,900: 1.0 to 1.8 (2,900 to 10,000: 0.88 to 1.2); items of up to 256 tokens fill half or a quarter of a
 //   block of slots: 1 head 1.5 to 2.0 at any size (18 x 17,072, 4 -> 2: 30.2 -> 18.9 us), 2 heads 1.0 to 1.3 up to 10,000.
-inline TcUnits transcode_units_plan(int heads, int l, int n_items, int max_tokens) {
+// From 4 to 2 bits an element is a table look-up, and K's parameters, prepared once a block, weigh more: with 5 heads and more, where units
+// of 8 make more blocks than the chip has compute units and the layouts above do not, units are 0.81 to 1.02 times as fast, 0.94 on
+// average (6 heads, 20 x 200 in two items 0.92; 8 -> 4 bits there 1.06 to 1.3).  `narrow`: every item is known to go from 4 to 2 bits, as for
+// a single blob; the descriptors of a batch are out of the launcher's sight, and it keeps units.  Fewer heads 1.0 to 1.26.  Slower and without a rule: 16
+// heads x 16 tokens from 4 to 2 bits (0.89).
+inline TcUnits transcode_units_plan(int heads, int l, int n_items, int max_tokens, bool narrow) {
   const int64_t groups = ((int64_t)max_tokens + 127) / 128;
   const double w = 2.0 * l * n_items * (double)groups * heads;
   const int lanes = (heads + 7) / 8 * 8, idle = lanes - heads;
@@ -247,6 +252,9 @@ inline TcUnits transcode_units_plan(int heads, int l, int n_items, int max_token
   if (u.groups > groups) u.groups = (int)groups;
   u.waves = u.parts > 1 ? (u.units + u.parts - 1) / u.parts : u.units * u.groups;
   u.blocks = u.parts > 1 ? groups * u.parts : (groups + u.groups - 1) / u.groups;
+  const int64_t planes = 2 * (int64_t)l * n_items;
+  if (narrow && heads >= 5 && u.accesses == 8 && u.blocks * planes > 256 && transcode_plan(heads, l, n_items, max_tokens).blocks * planes <= 256)
+    return TcUnits{};
   return u;
 }
 

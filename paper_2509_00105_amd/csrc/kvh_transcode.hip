@@ -1225,11 +1225,11 @@ __global__ __launch_bounds__(kTcThreads) KVH_TC_OCC void transcode_units_kernel(
 #undef KVH_TC_CASE
 }
 
-int launch_transcode(const TranscodeParams& a, int dt, int n_items, int max_tokens, hipStream_t stream) {
+int launch_transcode(const TranscodeParams& a, int dt, int n_items, int max_tokens, bool narrow, hipStream_t stream) {
   const int heads = a.c / kGroup;
   TranscodeParams b = a;
   b.by_heads = Divisor((uint32_t)heads);
-  const TcUnits u = transcode_units_plan(heads, a.l, n_items, max_tokens);
+  const TcUnits u = transcode_units_plan(heads, a.l, n_items, max_tokens, narrow);
   if (u.accesses != 0) {
     b.max_tokens = max_tokens;
     b.waves = u.waves;

@@ -15,7 +15,7 @@ extern "C" void tc_plan(int heads, int l, int items, int tokens, int64_t* o) {
   o[0] = p.slots; o[1] = p.log_s; o[2] = p.sets; o[3] = p.blocks;
 }
 extern "C" void tc_units(int heads, int l, int items, int tokens, int64_t* o) {
-  const TcUnits u = transcode_units_plan(heads, l, items, tokens);
+  const TcUnits u = transcode_units_plan(heads, l, items, tokens, o[0] != 0);
   o[0] = u.accesses; o[1] = u.period; o[2] = u.units; o[3] = u.parts; o[4] = u.groups; o[5] = u.waves; o[6] = u.blocks;
 }
 extern "C" void enc_plan(int heads, int l, int items, int tokens, int64_t* o) {
@@ -50,8 +50,8 @@ def plans(tmp_path_factory):
     subprocess.run(["g++", "-std=c++17", "-O1", "-Wall", "-Werror", "-shared", "-fPIC", "-I", CSRC, "-o", so, str(d / "shim.cpp")], check=True)
     lib = ctypes.CDLL(so)
 
-    def call(name, *args, raw=False):
-        out = (ctypes.c_int64 * 8)(raw)
+    def call(name, *args, known=False):  # known: that all items are raw (decoder), go from 4 to 2 bits (transcoder)
+        out = (ctypes.c_int64 * 8)(known)
         wide = 4 if name in ("dec_plan", "dec_units", "dec_launch") else len(args)  # the strides
         getattr(lib, name)(*[ctypes.c_int64(a) if i >= wide else a for i, a in enumerate(args)], out)
         return list(out)
@@ -206,7 +206,7 @@ def test_decode_raw_launches_of_up_to_one_block_of_spans_a_compute_unit_stay_in_
     """32 x 256 raw tokens into an 8,192-token cache: 15.6 us in spans, 17.1 in units.  With more blocks than compute units, or with
     many of them idle, units win."""
     def slots(l, n, strides, heads=8, items=1, raw=True):
-        return plans("dec_launch", heads, l, items, n, *strides, raw=raw)[0]
+        return plans("dec_launch", heads, l, items, n, *strides, known=raw)[0]
 
     cache = dense(1024, 8192)
     assert [slots(32, n, cache) for n in (64, 128, 129, 192, 256, 257, 384)] == [1, 1, 0, 0, 0, 1, 1]
@@ -310,6 +310,17 @@ def test_transcode_units_only_where_they_are_the_faster_form(plans):
     assert acc(1, 32, 100, 256) == 8 and acc(1, 32, 100, 257) == 0 and acc(2, 32, 39, 256) == 8 and acc(2, 32, 40, 256) == 0
     assert acc(16, 2, 1, 300) == 4 and acc(17, 1, 1, 1) == 0 and acc(8, 32, 32, 256) == 0
     assert acc(2**24 - 1, 32767, 65535, 2**31 - 1) == 0
+
+
+def test_transcode_from_4_to_2_bits_keeps_launches_of_one_block_a_compute_unit(plans):
+    """Units of 8 make 320 blocks of 20 layers x 400 tokens of 6 heads, spans 160: 4 -> 2 bits 0.91 of the speed in units, 8 -> 4 bits 1.2."""
+    acc = lambda *a: (plans("tc_units", *a)[0], plans("tc_units", *a, known=True)[0])
+    assert acc(6, 20, 1, 400) == (8, 0) and acc(6, 16, 1, 400) == (8, 8) and acc(6, 40, 1, 171) == (8, 0)
+    assert acc(13, 10, 1, 420) == (8, 0) and acc(4, 20, 1, 987) == (8, 8) and acc(3, 20, 1, 1108) == (8, 8) and acc(5, 3, 1, 2048) == (4, 4)
+    assert acc(5, 10, 1, 1032) == (8, 0) and acc(9, 10, 1, 1082) == (8, 0) and acc(9, 6, 8, 256) == (8, 8)
+    for heads in range(1, 17):
+        for l, n in ((1, 1), (80, 16), (10, 3001), (32, 300)):
+            assert acc(heads, l, 1, n)[1] in (0, acc(heads, l, 1, n)[0])
 
 
 def test_gpu_tests_reach_the_transcoder_forms_they_name(plans):
