@@ -60,18 +60,22 @@ struct DecPlan {
 //   average, 0.92 to 1.24.
 // Turns of whole spans.  Above 80 MiB the planes of a launch are better taken 4 (up to 1,400 MiB) or 8 at a time, one block
 // each, than 8 or all, where a plane is neither small nor large: what is written at one time then lies close together,
-// which counts most for pages of 16 tokens (32 KiB of 1024 channels, in random order: 4,096 tokens of 80 layers at 4 bits 318 ->
-// 297 us, contiguous 281 -> 274).  230 launches over 4 to 80 layers, 1024 and 2048 channels, items of 256 tokens to one item, all
-// levels, against groups of 8 or the row tiles below:
-//   above 896 MiB with planes of up to 40 MiB (items of less than 512 tokens), 64 MiB (1,024) or 128 MiB: 0.96 to 1.21 times as
-//   fast, 1.04 on average (70 layers x 7,362 tokens in pages 551 -> 500 us, 48 x 6,000 in one item 281 -> 242); with larger
-//   planes 0.89 to 1.07 (32 x 32,768 in 256-token items at 2 bits 787 -> 856), 2 planes at a time 0.87 to 1.2;
-//   80 to 896 MiB, 1024 channels, more than 10 planes of 4.5 to 16 MiB: turns of 4 0.98 to 1.2 times as fast as groups of 8, 1.02
-//   on average (10 x 5,000 at 4 bits 44.7 -> 41.5 us); smaller planes 0.88 to 1.06, larger ones 0.88 to 1.02, 2048 channels 0.98 to
-//   1.05, 10 planes 0.90 to 1.04.
-// Not for items of less than 512 tokens where layers lie a multiple of 16 MiB apart (8,192 tokens x 1024 channels): inputs not in a
-// cache, 32 x 8,192 at 8 / 4 / 2 bits 276 / 220 / 201 us as before, 280 / 219 / 219 in turns, 32 x 16,384 at 2 bits 401 and 432 (pages: 307 / 255 / 243
-// and 305 / 248 / 247); 48 x 6,000 gains 4 to 9 % at every level, 80 x 4,096 3 to 7 %, 32 x 8,192 in 1,024-token items 1 to 11 %.
+// which counts most for pages of 16 tokens (32 KiB of 1024 channels, in random order).  Against groups of 8 or the row tiles below,
+// inputs in no cache, 8 / 4 / 2 bits:
+//   above 896 MiB, planes of up to 40 MiB (items of less than 512 tokens), 60 MiB (1,024) or 128 MiB.  50 launches of 256- and 384-token items
+//   over 16 to 80 layers 0.98 to 1.10 / 0.98 to 1.11 / 0.98 to 1.15 (48 x 6,000 1.02 / 1.03 / 1.10, in pages 1.06 / 1.07 / 1.08; 80 x 3,727 in
+//   pages 1.10 / 1.11 / 1.12); 512- to 2,048-token items of 24 to 80 layers x 4,096 to 40,000 tokens 0.98 to 1.09 at 8 bits, 0.99 to 1.1 at 4,
+//   0.99 to 1.2 at 2 (below 1 where layers lie a multiple of 32 MiB apart), one item of 4,000 to 8,192 tokens 1.06 to 1.14 / 1.09 to 1.12 / 1.11 to 1.19;
+//   larger planes 0.97 to 1.02 (32 x 32,768 in 512-token items 0.97 / 1.00 / 0.99);
+//   80 to 896 MiB, 1024 channels, more than 10 planes of 4.5 to 16 MiB, turns of 4: items of 1,024 tokens and more, 60 launches 0.98 to 1.09
+//   at 8 bits, 0.96 to 1.2 at 4, 1.0 to 1.29 at 2 (48 x 4,255 1.05 / 1.20 / 1.25); shorter items of 8 to 16 layers 0.98 to 1.12, 1.03 on average, but of 6
+//   and 7 layers 0.93 to 1.04 and of 20 and more 0.96 to 1.05, 1.00 on average: these keep their groups.
+// Not for items of less than 512 tokens where layers lie a multiple of 16 MiB apart (8,192 tokens x 1024 channels: 32 x 8,192 0.98 / 1.04 / 0.93, in
+// pages 1.01 / 1.01 / 0.98; 32 x 16,384 0.99 / 1.02 / 0.94), nor of up to 128 tokens (ten launches 0.97 to 1.05 / 0.91 to 1.04 /
+// 0.89 to 1.10, 0.99 on average).  Not where an item has just the blocks that run at a time, so that the previous order writes it all at
+// once: 32 and 33 layers in 256-token items, 40 lengths from 7,400 to 9,200 tokens, 0.95 to 1.05 at 8 bits, 1.0 to 1.05 at 4 and 0.90 to 1.04 at 2,
+// 0.96 on average there, three lengths apart (7,680 1.07, 8,128 1.22 and 8,256 1.28, whose previous order is as slow); 34 layers 0.99 to 1.01 and 0.94
+// to 0.99, 30 layers 0.98 to 1.01 and 1.04 to 1.1; 16 layers in 512-token items 1.00 to 1.02 / 1.00 to 1.06 / 0.97 to 1.03.
 // For a single item groups and turns are the same order.  Items of more than 8,192 tokens that are alone stay plane by plane
 // (1.00 to 1.1).
 // Launches of whole spans of up to 80 MiB get two blocks per CU where they are not in units of slots (decode_units_plan): what they write
@@ -112,9 +116,13 @@ inline DecPlan decode_plan(int heads, int l, int n_items, int max_tokens, int64_
   int turn = 0;
   if (!p.slots && !side_by_side && mib > 80) {
     const double plane = mib / planes;
-    if (mib <= 896) turn = heads == 8 && planes > 10 && plane >= 4.5 && plane <= 16 ? 4 : 0;
-    else if (max_tokens < 512 && layer_stride % ((int64_t)8 << 20) == 0) turn = 0;
-    else if (plane <= (max_tokens < 512 ? 40 : max_tokens < 1024 ? 64 : 128)) turn = mib <= 1400 ? 4 : 8;
+    const int64_t item = p.blocks * planes;
+    if (mib <= 896)
+      turn = heads == 8 && plane >= 4.5 && plane <= 16 && (max_tokens >= 1024 ? planes > 10 : planes >= 16 && planes <= 32) ? 4 : 0;
+    else if ((max_tokens < 512 && (max_tokens <= 128 || layer_stride % ((int64_t)8 << 20) == 0)) || (item >= 248 && item <= 272))
+      turn = 0;
+    else if (plane <= (max_tokens < 512 ? 40 : max_tokens < 1024 ? 60 : 128))
+      turn = mib <= 1400 ? 4 : 8;
   }
   if (turn > 0 && turn < planes && (n_items > 1 || max_tokens <= 8192)) {
     p.row_tile = 1;

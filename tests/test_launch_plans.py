@@ -243,14 +243,18 @@ def test_decode_turns(plans):
         assert t == group or (items == 1 and t < group and tile == 1)
         return t, group
 
-    assert turn(8, 32, 32, 250) == (4, 4) and turn(8, 32, 64, 250) == (8, 8)        # 1 and 2 GiB
+    assert turn(8, 40, 28, 256) == (4, 4) and turn(8, 80, 28, 256) == (8, 8)        # 1.1 and 2.2 GiB
+    assert [turn(8, l, 40, 250)[0] for l in (30, 31, 32, 33, 34, 35)] == [4, 62, 64, 66, 68, 4]  # an item of 248 to 272 blocks
+    assert turn(8, 40, 56, 128) == (80, 80) and turn(8, 40, 56, 129) == (4, 4)
     assert turn(8, 32, 32, 256) == (64, 64) and turn(8, 32, 64, 256) == (64, 64)    # layers 16 and 32 MiB apart
     assert turn(8, 32, 16, 512) == (4, 4) and turn(8, 80, 16, 256) == (4, 4)        # 16 MiB, longer items; 8 MiB
     assert turn(8, 32, 128, 256)[0] == 64                                           # planes of 64 MiB
-    assert turn(8, 32, 64, 512) == (8, 8) and turn(8, 32, 64, 1024) == (8, 8) and turn(8, 32, 256, 1024)[0] == 64
+    assert turn(8, 32, 48, 512) == (8, 8) and turn(8, 32, 64, 512)[0] == 64 and turn(8, 32, 64, 1024) == (8, 8) and turn(8, 32, 256, 1024)[0] == 64
     assert turn(8, 48, 1, 6000) == (4, 96) and turn(8, 80, 1, 8192) == (8, 160) and turn(8, 80, 1, 8193) == (160, 160)
     assert turn(8, 11, 8, 300) == (4, 4) and turn(8, 11, 1, 2400) == (4, 8)
-    assert turn(8, 32, 16, 256) == (4, 4) and turn(8, 32, 4, 256) == (8, 8) and turn(16, 32, 8, 256) == (8, 8)
+    assert turn(8, 16, 16, 256) == (4, 4) and turn(8, 17, 16, 256) == (8, 8) and turn(8, 7, 16, 256)[0] == 14  # 16 to 32 planes
+    assert turn(8, 32, 4, 1024) == (4, 4) and turn(8, 32, 4, 1023) == (8, 8) and turn(8, 7, 4, 1024) == (4, 4)
+    assert turn(8, 32, 4, 256) == (8, 8) and turn(16, 32, 2, 1024) == (8, 8)
     assert turn(8, 32, 32, 256, (1024, 32 * 1024)) == (64, 64) and turn(5, 32, 32, 256) == (8, 8)
 
 
