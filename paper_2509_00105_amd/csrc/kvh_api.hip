@@ -179,7 +179,7 @@ int kvh_encode(const kvh_kv_view* kv, kvh_dtype dt, int l, int N, int c, int lev
   a.l = l;
   a.c = c;
   a.split = kNoSplit;
-  return launch_encode(a, dt, 1, N, static_cast<hipStream_t>(stream));
+  return launch_encode(a, dt, 1, N, level == kRawLevel, static_cast<hipStream_t>(stream));
 }
 
 int kvh_encode_chunked(const kvh_kv_view* kv, kvh_dtype dt, int l, int N, int c, int chunk, const int8_t* levels,
@@ -211,13 +211,15 @@ int kvh_encode_chunked(const kvh_kv_view* kv, kvh_dtype dt, int l, int N, int c,
   // the descriptors ride in the kernel arguments, kInlineItems chunks per launch
   for (int i0 = 0; i0 < n_chunks; i0 += kInlineItems) {
     const int cnt = n_chunks - i0 < kInlineItems ? n_chunks - i0 : kInlineItems;
+    bool raw = true;
     for (int j = 0; j < cnt; ++j) {
       const int i = i0 + j;
       const int n = (i + 1) * (int64_t)chunk <= N ? chunk : N - i * chunk;
+      raw = raw && levels[i] == kRawLevel;
       a.inline_items[j] = kvh_enc_item{static_cast<uint8_t*>(blobs_dev) + blob_offsets[i], (int64_t)i * chunk, n, levels[i]};
     }
     a.n_inline = cnt;
-    if (int rc = launch_encode(a, dt, cnt, chunk, static_cast<hipStream_t>(stream))) return rc;
+    if (int rc = launch_encode(a, dt, cnt, chunk, raw, static_cast<hipStream_t>(stream))) return rc;
   }
   return KVH_OK;
 }
@@ -236,7 +238,7 @@ int kvh_encode_batch(const kvh_enc_item* items_dev, int n_items, int max_tokens_
   a.l = l;
   a.c = c;
   a.split = kNoSplit;
-  return launch_encode(a, dt, n_items, max_tokens_per_item, static_cast<hipStream_t>(stream));
+  return launch_encode(a, dt, n_items, max_tokens_per_item, false, static_cast<hipStream_t>(stream));
 }
 
 int kvh_decode(const void* blob_dev, kvh_dtype dt, int l, int n_tokens, int c, int level, const kvh_kv_view* dst,
@@ -359,7 +361,7 @@ int kvh_encode_kept(const kvh_kv_view* kv, kvh_dtype dt, int l, int N, int c, in
   a.hdr_orig_tokens = (uint32_t)N;
   a.hdr_sink = (uint32_t)sink;
   a.hdr_window = (uint32_t)window;
-  return launch_encode(a, dt, 1, n, static_cast<hipStream_t>(stream));
+  return launch_encode(a, dt, 1, n, level == kRawLevel, static_cast<hipStream_t>(stream));
 }
 
 int kvh_decode_kept(const void* blob_dev, kvh_dtype dt, int l, int N, int c, int sink, int window, int level,
@@ -440,7 +442,7 @@ int kvh_encode_kept_batch(const kvh_kept_enc_item* items_dev, int n_items, int m
   a.l = l;
   a.c = c;
   a.split = kNoSplit;
-  return launch_encode(a, dt, n_items, max_kept_tokens_per_item, static_cast<hipStream_t>(stream));
+  return launch_encode(a, dt, n_items, max_kept_tokens_per_item, false, static_cast<hipStream_t>(stream));
 }
 
 int kvh_decode_kept_batch(const kvh_kept_item* items_dev, int n_items, int max_tokens_per_item, kvh_dtype dt, int l,

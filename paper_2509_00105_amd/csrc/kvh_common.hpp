@@ -277,9 +277,9 @@ struct TranscodeParams {
   Divisor by_units, by_parts, by_period;  // units and blocks of a token-group (1 block where it holds several), accesses after which heads repeat
 };
 
-// raw: every item is known on the host to be of the raw level
+// raw: every item is known on the host to be of the raw level (both)
 int launch_decode(const DecodeParams& a, int dt, int n_items, int max_tokens, bool raw, hipStream_t stream);
-int launch_encode(const EncodeParams& a, int dt, int n_items, int max_tokens, hipStream_t stream);
+int launch_encode(const EncodeParams& a, int dt, int n_items, int max_tokens, bool raw, hipStream_t stream);
 // narrow: every item is known on the host to go from 4 to 2 bits
 int launch_transcode(const TranscodeParams& a, int dt, int n_items, int max_tokens, bool narrow, hipStream_t stream);
 

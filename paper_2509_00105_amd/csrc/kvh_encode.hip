@@ -781,7 +781,8 @@ __global__ __launch_bounds__(kEncThreads) __attribute__((amdgpu_waves_per_eu(4, 
         default:
           // Single heads out of a longer row leave gaps between the 32-byte pieces an access writes, which other waves fill;
           // ordinary stores let the L2 put them together (5 heads: 310 -> 303 us in 512-token items of 32 x 16384 tokens,
-          // 233 -> 209 in one item of 12,000; with 1 head, where there are no gaps, and with 6, 1 to 7 % slower).
+          // 233 -> 209 in one item of 12,000; with 1 head, where there are no gaps, and with 6, 1 to 7 % slower; in blocks of 4 waves,
+          // 700 to 6,000 tokens of 4 to 80 layers, 3 heads 0.97 to 1.03 times as fast, 5 to 13 heads 1.00 to 1.1).
           if (a.k_slots == 2) encode_k_slots<DT, 2, true>(a, it, layer_base, geo, lam, bx, red, split, jump);
           else encode_k_slots<DT, 2>(a, it, layer_base, geo, lam, bx, red, split, jump);
           break;
@@ -812,10 +813,10 @@ __global__ __launch_bounds__(kEncThreads) __attribute__((amdgpu_waves_per_eu(4, 
   }
 }
 
-int launch_encode(const EncodeParams& a, int dt, int n_items, int max_tokens, hipStream_t stream) {
+int launch_encode(const EncodeParams& a, int dt, int n_items, int max_tokens, bool raw, hipStream_t stream) {
   const int heads = a.c / kGroup, nstrips = (a.c + kStripCh - 1) / kStripCh;
   EncPlan plan = encode_plan(heads, a.l, n_items, max_tokens);
-  if (const EncUnits units = encode_units_plan(heads, a.l, n_items, max_tokens); units.waves != 0)
+  if (const EncUnits units = encode_units_plan(heads, a.l, n_items, max_tokens, raw); units.waves != 0)
     plan = EncPlan{true, true, heads % 2 == 1, units.waves, units.blocks};
   const int64_t gx = plan.blocks;
   EncodeParams b = a;

@@ -275,11 +275,13 @@ struct EncPlan {
   int64_t blocks;  // of a (layer, K|V) plane
 };
 
+// The layouts of launches that encode_units_plan does not take: all of 1 and 2 heads, those of one block of strips a compute unit, and
+// large ones of whole strips and of 15 heads and more.
 // Rows of whole strips, and of 3 heads: a block is one token-group of a strip.  Any other row length: V and raw blocks are
-// units of slots, a wave each.  K slots take idle lanes away but read and write single heads or pairs: taken where more than
+// units of slots, a wave each, in blocks of 8.  K slots in blocks of 8 take idle lanes away but read and write single heads or pairs: taken where more than
 // a quarter of the strips' lanes idle, or a quarter and the heads come in pairs.  32 layers x 2,048 to 16,384 tokens in
 // items of 256 to 12,000, strips (with slots for V) against slots: 1 head 1.35 to 2.3 times faster, 2 heads 1.1 to 1.25, 5
-// heads 1.02 to 1.24, 6 heads 0.99 to 1.16, 3 heads 0.9 to 0.95, 7 to 18 heads 0.89 to 1.01.  With 3 heads slots bring V
+// heads 1.02 to 1.24, 6 heads 0.99 to 1.16, 3 heads 0.9 to 0.95, 7 to 18 heads 0.89 to 1.01.  With 3 heads slots in blocks of 8 bring V
 // and the raw level nothing either (15 shapes, all levels: strips 1.00 to 1.11 times as fast as before slots, slots 0.89 to
 // 1.14: 4 x 3,001 raw 8.9 -> 10.0 us, 32 x 1,024 in 256-token items raw 19.2 -> 21.0).
 // Waves of a block: a set of slots takes 2 a head, so that the token-group of 1 or 2 heads is 2 or 4 waves.  Blocks of 8
@@ -309,20 +311,30 @@ inline EncPlan encode_plan(int heads, int l, int n_items, int max_tokens) {
 // Slots in blocks of 4 waves for rows of 3 heads and more.  A block of 4 waves is a K set of 2 heads (or two of one head) x a
 // token-group, half a strip: twice the blocks, each half as long.  250 launches of 0.5 MiB to 1.3 GiB, 2 to 80 layers, against
 // the layouts above, by the blocks of strips B a launch has:
-//   rows that are not whole strips (3, 5, 6, 7, 9, 10, 11, 14 heads): 0.97 to 1.49 times as fast at any size, 1.10 on average (5 heads,
+//   rows that are not whole strips (3, 5, 6, 7, 9, 10, 11, 13, 14 heads): 0.97 to 1.49 times as fast at any size, 1.10 on average (5 heads,
 //   20 x 3,001 at 4 bits 39.6 -> 37.3 us, 32 x 8,192 at 2 bits 150 -> 137; 10 heads, 14 x 220 raw 9.6 -> 7.0; least: 14 heads, 20 x 367,
 //   0.93), but with B from 145 to 256, where a block of strips finds a compute unit for itself, 0.85 to 1.11, 1.01 on average;
 //   whole strips: B up to 144 0.99 to 1.39 (8 heads, 24 x 83 at 8 bits 8.6 -> 7.2), 257 to 400, where some compute units get a second
-//   block, 1.03 to 1.36 (17 x 477 raw 16.2 -> 11.9); 145 to 256 0.87 to 1.07 (one raw 1.27), beyond 400 0.94 to 1.06.
+//   block, 1.03 to 1.36 (17 x 477 raw 16.2 -> 11.9); 145 to 256 0.87 to 1.07 (one raw 1.27), beyond 400 0.94 to 1.06;
+//   from 15 heads on few lanes of strips idle, and rows that are no whole strips follow the same limits: up to 144 and 257 to 400 0.98 to
+//   1.46, 1.15 on average over 85 launches (66 heads, 4 x 128 at 8 bits 0.93); beyond, at 8 / 4 / 2 bits and raw, 0.91 to 1.04 / 0.92 to 1.07 / 0.98
+//   to 1.11 / 0.97 to 1.01 (20 x 3,001 in one item at 8 bits: 15 to 33 heads but 21 and 23 0.91 to 0.94).
+// Raw rows that are no whole strips were in slots before, in blocks of 8 waves, which they fill: where these are 145 to 256, blocks of 4
+// lose as well (4 to 14 heads, B 264 to 320 0.87 to 0.98; 17 heads, 4 x 960 0.80).  `raw`: every item is known to be of that level, as for a
+// single blob; the descriptors of a batch are out of the launcher's sight.
 struct EncUnits {
   int waves;       // of a block, 0: the layouts above
   int64_t blocks;  // of a (layer, K|V) plane
 };
-inline EncUnits encode_units_plan(int heads, int l, int n_items, int max_tokens) {
+inline EncUnits encode_units_plan(int heads, int l, int n_items, int max_tokens, bool raw) {
   const int64_t groups = ((int64_t)max_tokens + 127) / 128;
-  const double b = 2.0 * l * n_items * (double)groups * ((heads + 3) / 4);
+  const double planes = 2.0 * l * n_items;
+  const bool whole = heads % 4 == 0;
+  auto one_a_unit = [](double blocks) { return blocks > 144 && blocks <= 256; };
+  const double b = planes * (double)groups * ((heads + 3) / 4);
   EncUnits u{};
-  if (heads < 3 || (b > 144 && b <= 256) || (heads % 4 == 0 && b > 400)) return u;
+  if (heads < 3 || one_a_unit(b) || ((whole || heads >= 15) && b > 400)) return u;
+  if (raw && !whole && heads > 3 && one_a_unit(planes * (double)(((int64_t)max_tokens * heads + 511) / 512))) return u;
   u.waves = 4;
   u.blocks = (groups * heads + 1) / 2;
   return u;

@@ -179,7 +179,7 @@ def test_turns_of_planes_through_all_items(kvh, l, items, m):
 
 # heads -> items of 2 layers x 300 tokens in launches of up to 144, 256 and 400 blocks of strips, and more
 ENCODER_ITEMS = {heads: items for group, items in (((3, 4), (1, 13, 22, 40)), ((5, 6, 7, 8), (1, 7, 11, 20)), ((9, 10, 12), (1, 5, 8, 14)),
-                                                   ((16,), (1, 4, 6, 10))) for heads in group}
+                                                   ((16,), (1, 4, 6, 10)), ((17,), (1, 3, 5, 7))) for heads in group}
 
 
 @pytest.mark.parametrize("dt", [gen.F16, gen.BF16])
