@@ -19,7 +19,6 @@ struct DecPlan {
   int waves;            // of a block
   int64_t blocks;       // of a (layer, K|V) plane
   int plane_group, row_tile;  // block order, see decode_kernel
-  int turn;             // planes taken, one block each, before the next rows; below plane_group only for a single item
 };
 
 // Rows of whole 1024-channel spans: a block is 64 rows of a span.  Any other row length: units of 64 (row, head) slots, a
@@ -76,8 +75,7 @@ struct DecPlan {
 // once: 32 and 33 layers in 256-token items, 40 lengths from 7,400 to 9,200 tokens, 0.95 to 1.05 at 8 bits, 1.0 to 1.05 at 4 and 0.90 to 1.04 at 2,
 // 0.96 on average there, three lengths apart (7,680 1.07, 8,128 1.22 and 8,256 1.28, whose previous order is as slow); 34 layers 0.99 to 1.01 and 0.94
 // to 0.99, 30 layers 0.98 to 1.01 and 1.04 to 1.1; 16 layers in 512-token items 1.00 to 1.02 / 1.00 to 1.06 / 0.97 to 1.03.
-// For a single item groups and turns are the same order.  Items of more than 8,192 tokens that are alone stay plane by plane
-// (1.00 to 1.1).
+// Items of more than 8,192 tokens that are alone stay plane by plane (1.00 to 1.1).
 // Launches of whole spans of up to 80 MiB get two blocks per CU where they are not in units of slots (decode_units_plan): what they write
 // is gone before the write stream has settled, and more waves in flight hide the start.  Nine layer counts from 2 to 80, 1024 to
 // 4096 channels, all levels, two blocks against one in the same order: 48 MiB +3 to +8 % on average, 64 MiB +1 to +4, 80 MiB -1, 96
@@ -126,12 +124,9 @@ inline DecPlan decode_plan(int heads, int l, int n_items, int max_tokens, int64_
   }
   if (turn > 0 && turn < planes && (n_items > 1 || max_tokens <= 8192)) {
     p.row_tile = 1;
-    if (n_items > 1) p.plane_group = turn;
-  } else {
-    turn = p.plane_group;
+    p.plane_group = turn;
   }
   while (p.plane_group > 1 && !grid_fits(p.blocks, p.plane_group, p.waves)) p.plane_group = (p.plane_group + 1) / 2;
-  p.turn = turn < p.plane_group ? turn : p.plane_group;
   return p;
 }
 
@@ -181,7 +176,7 @@ inline DecLaunch decode_launch(int heads, int l, int n_items, int max_tokens, in
   if (!grid_fits(p.blocks, p.plane_group, p.waves)) return DecLaunch{};
   const DecUnits u = decode_units_plan(heads, l, n_items, max_tokens, layer_stride, token_stride, raw);
   if (u.blocks != 0) return DecLaunch{true, false, 1, u.blocks, u.plane_group, 1};
-  return DecLaunch{p.slots, p.short_launch, p.waves, p.blocks, p.turn, p.row_tile};
+  return DecLaunch{p.slots, p.short_launch, p.waves, p.blocks, p.plane_group, p.row_tile};
 }
 
 // ---- transcoder -------------------------------------------------------------------------------------------------
@@ -199,9 +194,9 @@ struct TcPlan {
 // 1.04, 17 heads 0.90 to 1.14, 33 heads 0.86 to 1.02.  So the share of idle lanes has to be the larger the smaller the
 // pieces are: over 3/8 of a row's lanes with single heads, over 1/4 with pairs, 1/4 with fours.  (V alone in slots, K in
 // spans: 5 to 33 heads 0.82 to 1.3.)
-// A small launch of slots has an eighth to a half of the blocks that spans have: below 128 blocks rows of 3 heads and more
-// would keep spans (most such launches are taken by units of slots, below; 4 x 3,001 tokens x 384 channels, 8 -> 4 bits: spans 13.2 us, slots 14.6; 32 x 256: 12.4 and 13.3; rows of 1
-// and 2 heads are 0.96 to 1.8 times as fast in slots even there).
+// A small launch of slots has an eighth to a half of the blocks that spans have: below 128 blocks rows of 3 heads and more keep spans
+// (4 x 3,001 tokens x 384 channels, 8 -> 4 bits: spans 13.2 us, slots 14.6; rows of 1 and 2 heads are 0.96 to 1.8 times as fast in
+// slots even there).  Units of slots, below, take all such launches but those of 9 and 10 heads from 4 to 2 bits that they leave here.
 inline TcPlan transcode_plan(int heads, int l, int n_items, int max_tokens) {
   const int spans = (heads + 7) / 8, lanes = spans * 8, idle = lanes - heads;
   const int s = 1 << lowest_bit(heads);

@@ -29,7 +29,7 @@ extern "C" void enc_units(int heads, int l, int items, int tokens, int64_t* o) {
 extern "C" void dec_plan(int heads, int l, int items, int tokens, int64_t layer_stride, int64_t token_stride, int64_t* o) {
   const DecPlan p = decode_plan(heads, l, items, tokens, layer_stride, token_stride);
   o[0] = p.slots; o[1] = p.short_launch; o[2] = p.waves; o[3] = p.blocks; o[4] = p.plane_group; o[5] = p.row_tile;
-  o[6] = grid_fits(p.blocks, p.plane_group, p.waves); o[7] = p.turn;
+  o[6] = grid_fits(p.blocks, p.plane_group, p.waves);
 }
 extern "C" void dec_units(int heads, int l, int items, int tokens, int64_t layer_stride, int64_t token_stride, int64_t* o) {
   const DecUnits u = decode_units_plan(heads, l, items, tokens, layer_stride, token_stride, o[0] != 0);
@@ -170,9 +170,11 @@ def test_decode_whole_spans_take_groups_of_eight_planes_or_none(plans):
         for n in (128, 512, 2048, 4096):
             mib = l * n / 256
             group, tile = plans("dec_plan", 8, l, 1, n, *dense(1024, n))[4:6]
-            assert group in (8, 2 * l)
-            grouped = mib <= 896 and (l % 4 == 0 or (l > 8 and mib > 80))
-            assert group == (8 if grouped else 2 * l) and (not grouped or tile == 1), (l, n)
+            assert group in (4, 8, 2 * l)
+            turned = mib > 80 and n >= 2048 and (l > 5 if mib <= 896 else True)  # planes of 4 to 8 MiB in turns
+            turned = turned and (mib > 896 or n * 2 / 1024 >= 4.5)
+            grouped = turned or (mib <= 896 and (l % 4 == 0 or (l > 8 and mib > 80)))
+            assert group == (4 if turned else 8 if grouped else 2 * l) and (not grouped or tile == 1), (l, n)
 
 
 def test_decode_two_blocks_per_cu_only_for_small_launches(plans):
@@ -197,8 +199,8 @@ def test_decode_launches_the_form_that_is_planned(plans):
     assert at(8, 24, 1, 752, dense(1024, 3760)) == [0, 1, 8, 12, 8, 1]
     for heads, l, items, n in ((8, 32, 7, 256), (8, 80, 16, 256), (5, 32, 1, 256), (8, 20, 1, 15000), (8, 48, 1, 6000)):
         strides = dense(128 * heads, items * n)
-        slots, _, waves, blocks, _, tile, fits, turn = plans("dec_plan", heads, l, items, n, *strides)
-        assert fits and at(heads, l, items, n) == [slots, 0, waves, blocks, turn, tile]
+        slots, _, waves, blocks, group, tile, fits = plans("dec_plan", heads, l, items, n, *strides)[:7]
+        assert fits and at(heads, l, items, n) == [slots, 0, waves, blocks, group, tile]
     assert not any(at(8, 1, 1, 2**31 - 1, dense(1024, 1))[:4])  # refused
 
 
@@ -229,39 +231,38 @@ def test_gpu_tests_reach_the_orders_they_name(plans):
     """The shapes of tests/test_gpu_row_lengths.py: uneven last plane groups, row tiles with a remainder, plane by plane."""
     groups = {(h, l): plans("dec_plan", h, l, 1, 300, *dense(128 * h, 300))[4] for h, l in ((4, 5), (5, 10), (5, 11))}
     assert groups == {(4, 5): 4, (5, 10): 7, (5, 11): 8}                                     # of 10, 20 and 22 planes
-    assert plans("dec_plan", 8, 9, 1, 8191, *dense(1024, 8191))[4:6] == [8, 1]               # of 18 planes
+    assert plans("dec_plan", 8, 9, 1, 8191, *dense(1024, 8191))[4:6] == [4, 1]               # of 18 planes
     assert plans("dec_plan", 8, 20, 1, 15000, *dense(1024, 15000))[4:6] == [40, 0x7fffffff]
     slots, short, _, blocks, group, tile = plans("dec_plan", 8, 9, 100, 300, *dense(1024, 30000))[:6]
     assert (slots, short, blocks, group, tile) == (0, 0, 5, 18, 4)
 
 
 def test_decode_turns(plans):
-    """Turns of 4 or 8 planes where a launch is large and its planes are neither small nor large; they are the plane group where
-    there are several items, and a part of it for one item, whose row tiles they replace."""
+    """Turns of 4 or 8 planes where a launch is large and its planes are neither small nor large."""
     def turn(heads, l, items, n, strides=None):
-        group, tile, _, t = plans("dec_plan", heads, l, items, n, *(strides or dense(128 * heads, n * items)))[4:8]
-        assert t == group or (items == 1 and t < group and tile == 1)
-        return t, group
+        group, tile = plans("dec_plan", heads, l, items, n, *(strides or dense(128 * heads, n * items)))[4:6]
+        assert tile == 1 or group == 2 * l
+        return group
 
-    assert turn(8, 40, 28, 256) == (4, 4) and turn(8, 80, 28, 256) == (8, 8)        # 1.1 and 2.2 GiB
-    assert [turn(8, l, 40, 250)[0] for l in (30, 31, 32, 33, 34, 35)] == [4, 62, 64, 66, 68, 4]  # an item of 248 to 272 blocks
-    assert turn(8, 40, 56, 128) == (80, 80) and turn(8, 40, 56, 129) == (4, 4)
-    assert turn(8, 32, 32, 256) == (64, 64) and turn(8, 32, 64, 256) == (64, 64)    # layers 16 and 32 MiB apart
-    assert turn(8, 32, 16, 512) == (4, 4) and turn(8, 80, 16, 256) == (4, 4)        # 16 MiB, longer items; 8 MiB
-    assert turn(8, 32, 128, 256)[0] == 64                                           # planes of 64 MiB
-    assert turn(8, 32, 48, 512) == (8, 8) and turn(8, 32, 64, 512)[0] == 64 and turn(8, 32, 64, 1024) == (8, 8) and turn(8, 32, 256, 1024)[0] == 64
-    assert turn(8, 48, 1, 6000) == (4, 96) and turn(8, 80, 1, 8192) == (8, 160) and turn(8, 80, 1, 8193) == (160, 160)
-    assert turn(8, 11, 8, 300) == (4, 4) and turn(8, 11, 1, 2400) == (4, 8)
-    assert turn(8, 16, 16, 256) == (4, 4) and turn(8, 17, 16, 256) == (8, 8) and turn(8, 7, 16, 256)[0] == 14  # 16 to 32 planes
-    assert turn(8, 32, 4, 1024) == (4, 4) and turn(8, 32, 4, 1023) == (8, 8) and turn(8, 7, 4, 1024) == (4, 4)
-    assert turn(8, 32, 4, 256) == (8, 8) and turn(16, 32, 2, 1024) == (8, 8)
-    assert turn(8, 32, 32, 256, (1024, 32 * 1024)) == (64, 64) and turn(5, 32, 32, 256) == (8, 8)
+    assert turn(8, 40, 28, 256) == 4 and turn(8, 80, 28, 256) == 8        # 1.1 and 2.2 GiB
+    assert [turn(8, l, 40, 250) for l in (30, 31, 32, 33, 34, 35)] == [4, 62, 64, 66, 68, 4]  # an item of 248 to 272 blocks
+    assert turn(8, 40, 56, 128) == 80 and turn(8, 40, 56, 129) == 4
+    assert turn(8, 32, 32, 256) == 64 and turn(8, 32, 64, 256) == 64    # layers 16 and 32 MiB apart
+    assert turn(8, 32, 16, 512) == 4 and turn(8, 80, 16, 256) == 4        # 16 MiB, longer items; 8 MiB
+    assert turn(8, 32, 128, 256) == 64                                           # planes of 64 MiB
+    assert turn(8, 32, 48, 512) == 8 and turn(8, 32, 64, 512) == 64 and turn(8, 32, 64, 1024) == 8 and turn(8, 32, 256, 1024) == 64
+    assert turn(8, 48, 1, 6000) == 4 and turn(8, 80, 1, 8192) == 8 and turn(8, 80, 1, 8193) == 160
+    assert turn(8, 11, 8, 300) == 4 and turn(8, 11, 1, 2400) == 4
+    assert turn(8, 16, 16, 256) == 4 and turn(8, 17, 16, 256) == 8 and turn(8, 7, 16, 256) == 14  # 16 to 32 planes
+    assert turn(8, 32, 4, 1024) == 4 and turn(8, 32, 4, 1023) == 8 and turn(8, 7, 4, 1024) == 4
+    assert turn(8, 32, 4, 256) == 8 and turn(16, 32, 2, 1024) == 8
+    assert turn(8, 32, 32, 256, (1024, 32 * 1024)) == 64 and turn(5, 32, 32, 256) == 8
 
 
 def test_gpu_tests_reach_the_turns_they_name(plans):
     for l, items, n, group in ((11, 8, 300, 4), (31, 13, 600, 4), (57, 10, 660, 8)):
-        assert plans("dec_plan", 8, l, items, n, *dense(1024, n * items))[4:8:3] == [group, group] and 2 * l % group
-    assert plans("dec_plan", 8, 9, 1, 8191, *dense(1024, 8191))[7] == 4 and 18 % 4
+        assert plans("dec_plan", 8, l, items, n, *dense(1024, n * items))[4] == group and 2 * l % group
+    assert plans("dec_plan", 8, 9, 1, 8191, *dense(1024, 8191))[4] == 4 and 18 % 4
 
 
 @pytest.mark.parametrize("heads", range(1, 17))
