@@ -1,0 +1,216 @@
+"""Refusals, broken headers, token-dropping words, padded rows and non-finite input in the layouts of large launches.  Small blobs
+take other layouts, with checks of their own, so the blobs here are repeated until the launch is large enough; which layout each
+count reaches is asserted without a GPU in test_launch_plans.py.  Bit equality with the oracle throughout."""
+import numpy as np
+import pytest
+
+import kv_inputs as gen
+import oracle
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+TDT = {gen.F16: torch.float16, gen.BF16: torch.bfloat16}
+L, N = 2, 300
+DECODE = [(8, 30), (8, 96), (16, 48)]  # heads, items of up to N tokens: spans with two blocks a compute unit (70 MiB), with one (225)
+TRANSCODE = {1: 260, 2: 130, 5: 36, 8: 12, 12: 12, 17: 12}  # heads -> items
+ENCODE = [(heads, items) for heads, items in ((3, 20), (5, 10), (8, 10), (8, 26), (17, 4), (17, 11))]  # of 129 tokens
+
+
+@pytest.fixture(scope="module")
+def kvh():
+    import paper_2509_00105_amd as m
+
+    m.lib()
+    return m
+
+
+def device(bits, dt):
+    return torch.from_numpy(bits.view(np.int16)).cuda().view(TDT[dt])
+
+
+def broken(blob, byte, value):
+    b = blob.clone()
+    b[byte] = value
+    return b
+
+
+def with_words(blob, orig, sink, window):
+    b = blob.clone()
+    b[32:44] = torch.from_numpy(np.array([orig, sink, window], np.uint32).view(np.uint8)).cuda()
+    return b
+
+
+@pytest.mark.parametrize("dt", [gen.F16, gen.BF16])
+@pytest.mark.parametrize("how", ["contiguous", "paged", "kept"])
+@pytest.mark.parametrize("heads,copies", DECODE)
+def test_decode_refuses_items_one_by_one(kvh, heads, copies, how, dt):
+    """Items that break the call's limits or whose header does not match leave their rows as they were and set their status; the
+    others land in rows padded by 8 channels, which keep every byte."""
+    c = 128 * heads
+    k, v = gen.make_kv(L, N + 1, c, dt, seed=heads + copies)
+    kn, vn = np.ascontiguousarray(k[:, :N]), np.ascontiguousarray(v[:, :N])
+    blobs = [torch.from_numpy(oracle.encode(kn, vn, dt, lv)).cuda() for lv in range(4)]
+    rows = [torch.stack([device(x, dt) for x in oracle.decode(b.cpu().numpy(), dt, L, N, c, lv)]) for lv, b in enumerate(blobs)]
+    longer = torch.from_numpy(oracle.encode(k, v, dt, 0)).cuda()
+    bad = {1: broken(blobs[1], 0, 0), 6: broken(blobs[2], 12, 45), 11: broken(blobs[3], 16, 1), 16: broken(blobs[0], 24, 1),
+           20: with_words(blobs[0], 340, 100, 200)}
+    lengths, levels = [N] * copies, [i % 4 for i in range(copies)]
+    lengths[3], lengths[9], levels[13] = N + 1, N + 1, 7  # 17 is an 8-bit blob called a 4-bit one
+    span = -(-N // 16) * 16
+    at = [0 if how == "paged" else i * span for i in range(copies)]
+    at[7], at[10] = 2**31 - 60, -8
+    src = [bad.get(i, longer if lengths[i] > N else blobs[0] if i == 17 else blobs[i % 4]) for i in range(copies)]
+    refused = sorted({1, 3, 6, 7, 9, 10, 11, 13, 16, 17, 20})
+    ptrs = [b.data_ptr() for b in src]
+    status = torch.zeros(copies, dtype=torch.int32, device="cuda")
+    out = torch.full((2, L, copies * span // 16, 16, c + 8), 9.0, dtype=TDT[dt], device="cuda")
+    if how == "paged":
+        order = torch.randperm(copies * span // 16, generator=torch.Generator().manual_seed(heads)).to(torch.int32)
+        tables = order.view(copies, -1).cuda()
+        kvh.decode_batch(kvh.make_dec_items(ptrs, lengths, levels, at, [t.data_ptr() for t in tables], "cuda"), copies, N, out[0, ..., :c],
+                         out[1, ..., :c], paged=True, status=status)
+        got = out[:, :, tables.long().flatten()]
+    else:
+        flat = out.view(2, L, copies * span, c + 8)
+        if how == "contiguous":
+            kvh.decode_batch(kvh.make_dec_items(ptrs, lengths, levels, at, [0] * copies, "cuda"), copies, N, flat[0, ..., :c], flat[1, ..., :c],
+                             status=status)
+        else:
+            words = np.zeros((copies, 3), int)
+            words[20] = 340, 100, 199  # one token less than the item says
+            kvh.decode_kept_batch(kvh.make_kept_items(ptrs, lengths, levels, at, [0] * copies, words[:, 0], words[:, 1], words[:, 2], [1] * copies,
+                                                      "cuda"), copies, N, flat[0, ..., :c], flat[1, ..., :c], status=status)
+        got = out
+    torch.cuda.synchronize()
+    assert np.flatnonzero(status.cpu().numpy()).tolist() == refused and int(status.max()) == 1
+    got = got.reshape(2, L, copies, span, c + 8).view(torch.int16)
+    nine = int(torch.tensor(9.0, dtype=TDT[dt]).view(torch.int16))
+    assert (got[..., c:] == nine).all() and (got[:, :, :, N:] == nine).all()
+    for i in range(copies):
+        want = nine if i in refused else rows[levels[i]].view(torch.int16)
+        assert (got[:, :, i, :N, :c] == want).all(), i
+
+
+@pytest.mark.parametrize("dt", [gen.F16, gen.BF16])
+@pytest.mark.parametrize("heads", list(TRANSCODE))
+def test_transcode_refuses_items_one_by_one(kvh, heads, dt):
+    """The same for the transcoder, with the raw level among what it refuses; the token-dropping words of a blob are carried over."""
+    c, items = 128 * heads, TRANSCODE[heads]
+    pairs = [(a, b) for a in range(3) for b in range(3)]
+    k, v = gen.make_kv(L, N + 1, c, dt, seed=heads)
+    kn, vn = np.ascontiguousarray(k[:, :N]), np.ascontiguousarray(v[:, :N])
+    blobs = [torch.from_numpy(oracle.encode(kn, vn, dt, lv)).cuda() for lv in range(4)]
+    low = [torch.from_numpy(oracle.transcode(blobs[a].cpu().numpy(), dt, L, N, c, a, b)).cuda() for a, b in pairs]
+    longer = torch.from_numpy(oracle.encode(k, v, dt, 0)).cuda()
+    size = max(x.numel() for x in low + [longer]) + 64
+    out = torch.full((items, size), 0xAB, dtype=torch.uint8, device="cuda")
+    src, lengths, levels, to, want = [], [], [], [], []
+    for i in range(items):
+        a, b = pairs[(i // 2) % 9] if i % 2 else pairs[(i * 7) % 9]
+        s, n, w = blobs[a], N, low[pairs.index((a, b))]
+        if i == 2:
+            s, w = broken(s, 8, 3), None
+        elif i == 4:
+            s, n, a, w = longer, N + 1, 0, None
+        elif i == 5:
+            s, a, w = blobs[3], 3, None
+        elif i == 7:
+            b, w = 9, None
+        elif i == 8:
+            s, w = with_words(s, 340, 100, 200), with_words(w, 340, 100, 200)
+        elif i == 9:
+            s, w = with_words(s, 340, 100, 300), None  # keeps all 340, not 300
+        src.append(s)
+        lengths.append(n)
+        levels.append(a)
+        to.append(b)
+        want.append(w)
+    status = torch.zeros(items, dtype=torch.int32, device="cuda")
+    kvh.transcode_batch(kvh.make_tc_items([s.data_ptr() for s in src], [o.data_ptr() for o in out], lengths, levels, to, "cuda"), items, N, dt, L, c,
+                        status=status)
+    torch.cuda.synchronize()
+    assert np.flatnonzero(status.cpu().numpy()).tolist() == [i for i, w in enumerate(want) if w is None] == [2, 4, 5, 7, 9]
+    for i, w in enumerate(want):
+        used = 0 if w is None else w.numel()
+        assert (w is None or torch.equal(out[i, :used], w)) and (out[i, used:] == 0xAB).all(), (i, levels[i], to[i])
+
+
+@pytest.mark.parametrize("dt", [gen.F16, gen.BF16])
+@pytest.mark.parametrize("heads,items", ENCODE)
+def test_encode_skips_items_and_keeps_to_the_blob(kvh, heads, items, dt):
+    """An item of more tokens than the launch covers and one of an unknown level write nothing.  Rows with infinities and NaN write
+    nothing outside their blob, the header is as for finite input, and V groups of finite values are stored as the oracle stores
+    them; finite items beside them equal the oracle."""
+    n, c = 129, 128 * heads
+    k, v = gen.make_kv(L, 2 * n + 1, c, dt, seed=heads)
+    k, v = np.ascontiguousarray(k), np.ascontiguousarray(v)
+    hit = np.random.default_rng(heads).random((L, n, c)) < 1 / 256
+    values = np.resize(np.array((0x7C00, 0xFC00, 0x7E00) if dt == gen.F16 else (0x7F80, 0xFF80, 0x7FC0), np.uint16), hit.shape)
+    part = lambda x, t, m=n: np.ascontiguousarray(x[:, t:t + m])
+    k0, v0 = np.where(hit, 0, part(k, 0)).astype(np.uint16), np.where(hit, 0, part(v, 0)).astype(np.uint16)
+    clean = ~hit.reshape(L, n, heads, 128).any(-1)
+    k[:, :n], v[:, :n] = np.where(hit, values, part(k, 0)), np.where(hit, values, part(v, 0))
+    kd, vd = device(k, dt), device(v, dt)
+    assert 0.3 < clean.mean() < 0.9
+    for level in range(4):
+        size, bits = kvh.blob_size(L, n, c, level), kvh.level_bits(level)
+        out = torch.full((items, kvh.blob_size(L, n + 1, c, level) + 64), 0xEE, dtype=torch.uint8, device="cuda")
+        starts = [0 if i % 2 else n for i in range(items)]
+        lengths, levels = [n] * items, [level] * items
+        lengths[0], levels[2] = n + 1, 7
+        kvh.encode_batch(kvh.make_enc_items([o.data_ptr() for o in out], starts, lengths, levels, "cuda"), items, n, kd, vd)
+        torch.cuda.synchronize()
+        got = out.cpu().numpy()
+        assert (got[[0, 2]] == 0xEE).all() and (got[:, size:] == 0xEE).all(), level
+        finite = oracle.encode(part(k, n), part(v, n), dt, level)
+        assert all(np.array_equal(got[i, :size], finite) for i in range(4, items, 2)), level
+        want = oracle.encode(k0, v0, dt, level)
+        for i in range(1, items, 2):
+            assert np.array_equal(got[i, :64], want[:64]), (level, i)
+            if level == 3:
+                assert np.array_equal(got[i, :size], oracle.encode(part(k, 0), part(v, 0), dt, 3)), i  # stored as they are
+                continue
+            for lam in range(L):
+                off = oracle.section_offsets(L, n, c, level, lam)
+                for section, width in (("vcodes", 16 * bits), ("vmeta", 4)):
+                    a, b = (x[off[section]:off[section] + n * heads * width].reshape(n, heads, width) for x in (got[i], want))
+                    assert np.array_equal(a[clean[lam]], b[clean[lam]]), (level, i, lam, section)
+
+
+RAW = [(8, 32, 130), (8, 24, 256), (16, 12, 200), (9, 4, 1536), (17, 4, 960)]  # heads, layers, tokens
+
+
+@pytest.mark.parametrize("heads,l,n", RAW)
+def test_raw_blobs_of_one_block_a_compute_unit(kvh, heads, l, n):
+    """Raw launches whose level is known on the host keep the layouts of larger ones: the blob holds the rows as they are, and single,
+    chunked and loaded blobs come back into a cache of four times their length, which keeps all else."""
+    c = 128 * heads
+    kv = gen.make_kv_device(l, n, c, gen.F16, seed=n)
+    blob = kvh.encode(kv[0], kv[1], 3)
+    parts = [kvh.encode(kv[0][:, t:t + 128], kv[1][:, t:t + 128], 3) for t in range(0, n, 128)]
+    torch.cuda.synchronize()
+    head = oracle.encode(np.zeros((l, n, c), np.uint16), np.zeros((l, n, c), np.uint16), gen.F16, 3)[:64]
+    assert np.array_equal(blob[:64].cpu().numpy(), head)
+    assert torch.equal(blob[64:].view(torch.int16).view(l, 2, n, c).transpose(0, 1), kv.view(torch.int16))
+    together, offs = torch.cat(parts), np.concatenate([[0], np.cumsum([p.numel() for p in parts])])[:-1]
+    hosts = [torch.empty(p.numel(), dtype=torch.uint8, pin_memory=True) for p in (blob, *parts)]
+    for h, p in zip(hosts, (blob, *parts)):
+        h.copy_(p)
+    loader = kvh.Loader(torch.empty(blob.numel() * 4 + 4096, dtype=torch.uint8, device="cuda"), n_slots=2)
+    lengths = [p.numel() // (4 * l * c) for p in parts]
+    for what in ("single", "chunked", "loaded", "loaded chunks"):
+        out = torch.full((2, l, 4 * n, c), 9.0, dtype=torch.float16, device="cuda")
+        at, status = n + 3, torch.zeros(len(parts), dtype=torch.int32, device="cuda")
+        if what == "single":
+            kvh.decode(blob, 3, n, out[0], out[1], dst_token0=at, status=status)
+        elif what == "chunked":
+            kvh.decode_chunked(together, offs, [3] * len(parts), 128, n, out[0], out[1], dst_token0=at, status=status)
+        elif what == "loaded":
+            loader.run(hosts[:1], [n], [3], [at], out[0], out[1], status=status)
+        else:
+            loader.run(hosts[1:], lengths, [3] * len(parts), [at + 128 * i for i in range(len(parts))], out[0], out[1], status=status)
+        torch.cuda.synchronize()
+        assert not status.any() and torch.equal(out[:, :, at:at + n].view(torch.int16), kv.view(torch.int16)), what
+        assert (out[:, :, :at] == 9.0).all() and (out[:, :, at + n:] == 9.0).all(), what
+    loader.close()

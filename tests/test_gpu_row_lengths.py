@@ -100,8 +100,9 @@ def test_row_lengths_batch(kvh, heads):
 
 @pytest.mark.parametrize("l,n", [(9, 8191), (20, 15000)])
 def test_launch_sizes(kvh, l, n):
-    """Whole spans on both sides of the sizes at which the decoder changes its block order and occupancy: 288 MiB of rows walk
-    turns of 4 planes, the last of 2, 1.1 GiB plane by plane, the pieces (18 to 54 MiB) units of slots.  Every row equals what 640-token pieces of the entry give."""
+    """Whole spans on both sides of the sizes at which the decoder changes its layout, block order and occupancy: 288 MiB of rows walk
+    turns of 4 planes, the last of 2, 1.1 GiB plane by plane, the pieces of 22 MiB are units of slots, those of 50 MiB spans with two
+    blocks a compute unit.  Every row equals what 640-token pieces of the entry give."""
     c = 1024
     kv = gen.make_kv_device(l, n, c, gen.BF16, seed=n)
     for level in range(4):
@@ -204,7 +205,7 @@ def test_encode_forms(kvh, heads, dt):
 @pytest.mark.parametrize("dt", [gen.F16, gen.BF16])
 @pytest.mark.parametrize("heads,copies", [(8, 1), (8, 96), (16, 48)])
 def test_one_blob_many_times(kvh, heads, copies, dt):
-    """One blob decoded once (units of slots) and so often that the launch takes spans (over 192 MiB): groups whose maximum is close
+    """One blob decoded once (units of slots) and so often that the launch takes spans (225 MiB): groups whose maximum is close
     to zero (the explicit top-code rule) among others, 300 tokens (a last block of 44 rows), contiguous, paged, and token-dropped
     with the kept tokens back in their places.  Every copy equals the oracle."""
     l, n, c = 2, 300, 128 * heads

@@ -383,3 +383,21 @@ def test_gpu_tests_reach_the_encoder_forms_they_name(plans):
     for heads, items in t.ENCODER_ITEMS.items():
         taken = [plans("enc_units", heads, 2, i, 300)[0] for i in items]
         assert taken == ([4, 0, 4, 0] if heads % 4 == 0 or heads >= 15 else [4, 0, 4, 4]), heads
+
+
+def test_gpu_tests_reach_the_large_forms_they_name(plans):
+    import test_gpu_large_forms as t
+
+    def spans(heads, items, rows):  # [slots, two blocks a compute unit]
+        c = 128 * heads
+        return plans("dec_launch", heads, t.L, items, t.N, items * rows * (c + 8), c + 8)[:2]
+
+    assert [spans(h, n, 304) for h, n in t.DECODE] == [[0, 1], [0, 0], [0, 0]]
+    assert all(plans("tc_units", h, t.L, n, t.N)[0] == 0 for h, n in t.TRANSCODE.items())
+    assert [plans("tc_plan", h, t.L, n, t.N)[0] for h, n in t.TRANSCODE.items()] == [1, 1, 0, 0, 1, 0]  # slots, spans
+    assert not any(plans("enc_units", h, t.L, n, 129)[0] for h, n in t.ENCODE)
+    assert [plans("enc_plan", h, t.L, n, 129)[:2] for h, n in t.ENCODE] == [[0, 0], [1, 1], [0, 0], [0, 0], [1, 0], [1, 0]]
+    for h, l, n in t.RAW:
+        name, args = ("dec_launch", dense(128 * h, 4 * n)) if h % 8 == 0 else ("enc_units", ())
+        a, b = (plans(name, h, l, 1, n, *args, known=known)[0] for known in (False, True))
+        assert (a, b) == ((1, 0) if h % 8 == 0 else (4, 0)), (h, l, n)
