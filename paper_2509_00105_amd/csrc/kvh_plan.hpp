@@ -67,8 +67,8 @@ struct DecPlan {
 //   0.99 to 1.2 at 2 (below 1 where layers lie a multiple of 32 MiB apart), one item of 4,000 to 8,192 tokens 1.06 to 1.14 / 1.09 to 1.12 / 1.11 to 1.19;
 //   larger planes 0.97 to 1.02 (32 x 32,768 in 512-token items 0.97 / 1.00 / 0.99);
 //   80 to 896 MiB, 1024 channels, more than 10 planes of 4.5 to 16 MiB, turns of 4: items of 1,024 tokens and more, 60 launches 0.98 to 1.09
-//   at 8 bits, 0.96 to 1.2 at 4, 1.0 to 1.29 at 2 (48 x 4,255 1.05 / 1.20 / 1.25); shorter items of 8 to 16 layers 0.98 to 1.12, 1.03 on average, but of 6
-//   and 7 layers 0.93 to 1.04 and of 20 and more 0.96 to 1.05, 1.00 on average: these keep their groups.
+//   at 8 bits, 0.96 to 1.2 at 4, 1.0 to 1.29 at 2 (48 x 4,255 1.05 / 1.20 / 1.25); shorter items of 8 to 16 layers 0.98 to 1.12, 1.03 on average, of
+//   20 to 80 0.96 to 1.09, 1.01 on average (30 x 4,128 in 512-token items in pages at 2 bits 94.4 -> 89.2 us), but of 6 and 7 layers 0.93 to 1.04.
 // Not for items of less than 512 tokens where layers lie a multiple of 16 MiB apart (8,192 tokens x 1024 channels: 32 x 8,192 0.98 / 1.04 / 0.93, in
 // pages 1.01 / 1.01 / 0.98; 32 x 16,384 0.99 / 1.02 / 0.94), nor of up to 128 tokens (ten launches 0.97 to 1.05 / 0.91 to 1.04 /
 // 0.89 to 1.10, 0.99 on average).  Not where an item has just the blocks that run at a time, so that the previous order writes it all at
@@ -116,7 +116,7 @@ inline DecPlan decode_plan(int heads, int l, int n_items, int max_tokens, int64_
     const double plane = mib / planes;
     const int64_t item = p.blocks * planes;
     if (mib <= 896)
-      turn = heads == 8 && plane >= 4.5 && plane <= 16 && (max_tokens >= 1024 ? planes > 10 : planes >= 16 && planes <= 32) ? 4 : 0;
+      turn = heads == 8 && plane >= 4.5 && plane <= 16 && planes > (max_tokens >= 1024 ? 10 : 14) ? 4 : 0;
     else if ((max_tokens < 512 && (max_tokens <= 128 || layer_stride % ((int64_t)8 << 20) == 0)) || (item >= 248 && item <= 272))
       turn = 0;
     else if (plane <= (max_tokens < 512 ? 40 : max_tokens < 1024 ? 60 : 128))

@@ -253,8 +253,7 @@ def test_decode_turns(plans):
     assert turn(8, 32, 48, 512) == 8 and turn(8, 32, 64, 512) == 64 and turn(8, 32, 64, 1024) == 8 and turn(8, 32, 256, 1024) == 64
     assert turn(8, 48, 1, 6000) == 4 and turn(8, 80, 1, 8192) == 8 and turn(8, 80, 1, 8193) == 160
     assert turn(8, 11, 8, 300) == 4 and turn(8, 11, 1, 2400) == 4
-    assert turn(8, 16, 16, 256) == 4 and turn(8, 17, 16, 256) == 8 and turn(8, 7, 16, 256) == 14  # 16 to 32 planes
-    assert turn(8, 32, 4, 1024) == 4 and turn(8, 32, 4, 1023) == 8 and turn(8, 7, 4, 1024) == 4
+    assert turn(8, 8, 16, 256) == 4 and turn(8, 40, 16, 256) == 4 and turn(8, 7, 16, 256) == 14 and turn(8, 7, 4, 1024) == 4
     assert turn(8, 32, 4, 256) == 8 and turn(16, 32, 2, 1024) == 8
     assert turn(8, 32, 32, 256, (1024, 32 * 1024)) == 64 and turn(5, 32, 32, 256) == 8
 
