@@ -23,13 +23,14 @@ constexpr size_t kDescBytes = (size_t)kMaxGroup * sizeof(kvh_kept_item);  // des
 constexpr int kCopyThreads = 256;
 constexpr int kCopyUnroll = 4;                                  // 16-byte loads in flight per thread
 constexpr uint64_t kTileWords = kCopyThreads * kCopyUnroll;     // 16-byte words of a tile: 16 KiB
-// Blocks of a copy.  A block reads about 3 GB/s over the bus whatever it has in flight (2, 4 or 8 loads a thread), so 24 fill
-// it; 64 MiB of pinned memory in blocks of 256 threads: 16 blocks 46.7 GB/s, 24 56.2, 32 57.0, 64 57.2, 96 55.7, 256 57.0, the
-// copy engine 56.7.  While a decode runs beside the copy more of them help (2,427 tokens of 27 layers at 8 bits: 24 blocks 2,664
-// us, 32 2,568, 40 2,530, 64 2,520), until a full bus holds up the decodes of short groups (41 blobs of 1.4 MB in groups
-// of 4: 40 blocks 1,201 us, 64 1,218).  Tiles are dealt over the whole group: with 4 blocks for each blob the bus ran at 50 GB/s on eight blobs
-// of mixed levels, because the last and largest had 4 blocks alone.
-constexpr uint32_t kCopyBlocks = 48;
+// Blocks of a copy.  They have to fill the bus (57 GB/s) and not hold up the decodes that run beside the copy, whose arguments and
+// packets lie in host memory behind the same bus.  Runs of several groups of 4 blobs, 16 / 48 blocks, against 4 blocks for each blob (which
+// left the bus at 50 GB/s on blobs of mixed sizes, because the last and largest had 4 blocks alone): groups of 0.7 to 5 MB 1.00 to 1.03 / 0.94 to
+// 1.01 times as fast (32 blobs of 0.37 MB 351 and 378 us), 5.5 to 12 MB 1.00 to 1.04 / 1.00 to 1.03, 12 to 25 MB 1.01 to 1.05 / 1.01 to 1.06, larger
+// ones 1.02 to 1.06 / 1.02 to 1.06, 48 ahead by 0.3 % on average; runs of one group the same within 1 %.  24 and 32 blocks are slower than
+// either in every run of several groups (0.80 to 0.96), 12, 20 and 64 by up to 2 %.
+constexpr uint32_t kCopyBlocks = 48, kCopyBlocksSmall = 16;
+constexpr uint32_t kSmallTiles = (12u << 20) / (kTileWords * 16);  // of a group that is copied by the fewer ones
 
 typedef uint32_t uintx4 __attribute__((ext_vector_type(4)));
 
@@ -73,7 +74,8 @@ __global__ __launch_bounds__(kCopyThreads) void load_group_kernel(CopyGroup g, u
 }
 
 int launch_copy(const CopyGroup& g, uint8_t* slot, hipStream_t stream) {
-  const uint32_t blocks = g.tiles < kCopyBlocks ? g.tiles : kCopyBlocks;
+  const uint32_t most = g.tiles <= kSmallTiles ? kCopyBlocksSmall : kCopyBlocks;
+  const uint32_t blocks = g.tiles < most ? g.tiles : most;
   hipLaunchKernelGGL(load_group_kernel, dim3(blocks + 1), dim3(kCopyThreads), 0, stream, g, slot);
   KVH_HIP_CHECK_LAUNCH();
   return KVH_OK;

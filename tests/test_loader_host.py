@@ -50,10 +50,11 @@ int hipGetDevice(int* d) { *d = 0; return 0; }
 int hipGetSymbolAddress(void** p, const void*) { *p = (void*)0x100000; return 0; }
 int hipPointerGetAttributes(int* at, const void*) { *at = 1; return 0; }  // hipMemoryTypeHost
 struct Dim3 { uint32_t x, y, z; };
-int hipLaunchKernel(const void*, Dim3, Dim3, void**, size_t, void* s) { return fails("copy", s, 0); }
+int hipLaunchKernel(const void*, Dim3 g, Dim3, void**, size_t, void* s) { return fails("copy", s, (void*)(size_t)g.x); }
 static void* launch_stream;
-int __hipPushCallConfiguration(Dim3, Dim3, size_t, void* s) { launch_stream = s; return 0; }
-int __hipPopCallConfiguration(Dim3* g, Dim3* b, size_t* n, void** s) { *g = *b = {1, 1, 1}; *n = 0; *s = launch_stream; return 0; }
+static Dim3 launch_grid;
+int __hipPushCallConfiguration(Dim3 g, Dim3, size_t, void* s) { launch_stream = s; launch_grid = g; return 0; }
+int __hipPopCallConfiguration(Dim3* g, Dim3* b, size_t* n, void** s) { *g = launch_grid; *b = {1, 1, 1}; *n = 0; *s = launch_stream; return 0; }
 void** __hipRegisterFatBinary(const void*) { static void* h; return &h; }
 void __hipRegisterFunction(void**, const void*, char*, const char*, unsigned, void*, void*, void*, void*, int*) {}
 void __hipRegisterVar(void**, void*, char*, const char*, int, size_t, int, int) {}
@@ -96,17 +97,17 @@ COMPUTE = 7  # the caller's stream
 class Session:
     """A loader of two slots that hold 4 blobs of 16 KiB each."""
 
-    def __init__(self, lib):
+    def __init__(self, lib, slot=4 * 16384):
         self.lib, self.ld = lib, ctypes.c_void_p()
         lib.restart()
-        assert lib.kvh_loader_create(ctypes.byref(self.ld), ctypes.c_void_p(0x10000), ctypes.c_size_t(2 * (1536 + 4 * 16384)), 2) == 0
+        assert lib.kvh_loader_create(ctypes.byref(self.ld), ctypes.c_void_p(0x10000), ctypes.c_size_t(2 * (1536 + slot)), 2) == 0
 
     def log(self):
         return [ln.split() for ln in self.lib.log_text().decode().splitlines()]
 
-    def run(self, blobs, fail_at=-1, stream=COMPUTE):
+    def run(self, blobs, fail_at=-1, stream=COMPUTE, tokens=16):
         items = np.zeros(blobs, dtype=ITEM)
-        items["blob_host"], items["n_tokens"] = 0x20000, 16
+        items["blob_host"], items["n_tokens"] = 0x20000, tokens
         view = View(0x30000, 0x30000, 1024 * 1024, 1024)
         self.lib.log_clear(ctypes.c_long(fail_at))
         rc = self.lib.kvh_loader_run(self.ld, ctypes.c_void_p(items.ctypes.data), blobs, 1, 1, 1024, ctypes.byref(view), 16, None, ctypes.c_void_p(stream))
@@ -164,3 +165,12 @@ def test_destroy_waits_for_the_copies_first(loader):
     s.run(3)
     what = [w for w, *_ in s.destroy()]
     assert what[:2] == ["sync", "event_sync"] and what.count("stream_destroy") == 1 and what.count("event_destroy") == 5
+
+
+def test_blocks_of_a_copy(loader):
+    """A block for each tile of 16 KiB up to 16, 48 for groups above 12 MiB, and one that writes the descriptors.  Between them lies
+    what is slower than either: 32 blobs of 0.37 MB in groups of 4 took 351 us with 16 blocks, 360 to 445 with 24 and 32, 378 with 48."""
+    s = Session(loader, slot=16 << 20)
+    grid = lambda blobs, tokens: [int(b) for w, _, b in s.run(blobs, tokens=tokens)[1] if w == "copy"]
+    assert grid(1, 1) == [2] and grid(4, 16) == [5] and grid(32, 16) == [17] and grid(3, 256 * 16) == [17]
+    assert grid(1, 768 * 16) == [17] and grid(1, 768 * 16 + 1) == [49] and grid(4, 256 * 16) == [49] and grid(5, 256 * 16) == [49, 17]
