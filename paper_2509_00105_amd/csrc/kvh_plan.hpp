@@ -64,7 +64,8 @@ struct DecPlan {
 //   above 896 MiB, planes of up to 40 MiB (items of less than 512 tokens), 60 MiB (1,024) or 128 MiB.  50 launches of 256- and 384-token items
 //   over 16 to 80 layers 0.98 to 1.10 / 0.98 to 1.11 / 0.98 to 1.15 (48 x 6,000 1.02 / 1.03 / 1.10, in pages 1.06 / 1.07 / 1.08; 80 x 3,727 in
 //   pages 1.10 / 1.11 / 1.12); 512- to 2,048-token items of 24 to 80 layers x 4,096 to 40,000 tokens 0.98 to 1.09 at 8 bits, 0.99 to 1.1 at 4,
-//   0.99 to 1.2 at 2 (below 1 where layers lie a multiple of 32 MiB apart), one item of 4,000 to 8,192 tokens 1.06 to 1.14 / 1.09 to 1.12 / 1.11 to 1.19;
+//   0.99 to 1.2 at 2 (below 1 where layers lie a multiple of 32 MiB apart), of 6 to 18 layers 0.98 to 1.15, 1.03 on average (11 layers in
+//   512-token items 0.93 to 1.02), one item of 4,000 to 8,192 tokens 1.06 to 1.14 / 1.09 to 1.12 / 1.11 to 1.19;
 //   larger planes 0.97 to 1.02 (32 x 32,768 in 512-token items 0.97 / 1.00 / 0.99);
 //   80 to 896 MiB, 1024 channels, more than 10 planes of 4.5 to 16 MiB, turns of 4: items of 1,024 tokens and more, 60 launches 0.98 to 1.09
 //   at 8 bits, 0.96 to 1.2 at 4, 1.0 to 1.29 at 2 (48 x 4,255 1.05 / 1.20 / 1.25); shorter items of 8 to 16 layers 0.98 to 1.12, 1.03 on average, of
