@@ -272,7 +272,7 @@ struct EncPlan {
 };
 
 // The layouts of launches that encode_units_plan does not take: all of 1 and 2 heads, those of one block of strips a compute unit, and
-// large ones of whole strips, of 15 heads and more and of 9 to 11 in short items.
+// large ones of whole strips, of 15 heads and more and of 9 to 11 in short items above 1 GiB.
 // Rows of whole strips, and of 3 heads: a block is one token-group of a strip.  Any other row length: V and raw blocks are
 // units of slots, a wave each, in blocks of 8.  K slots in blocks of 8 take idle lanes away but read and write single heads or pairs: taken where more than
 // a quarter of the strips' lanes idle, or a quarter and the heads come in pairs.  32 layers x 2,048 to 16,384 tokens in
@@ -310,9 +310,9 @@ inline EncPlan encode_plan(int heads, int l, int n_items, int max_tokens) {
 //   rows that are not whole strips (3, 5, 6, 7, 9, 10, 11, 14 heads): 0.93 to 1.49 times as fast, 1.10 on average (5 heads, 20 x 3,001 at 4
 //   bits 39.6 -> 37.3 us, 32 x 8,192 at 2 bits 150 -> 137; 10 heads, 14 x 220 raw 9.6 -> 7.0; least: 14 heads, 20 x 367), but with B from
 //   145 to 256, where a block of strips finds a compute unit for itself, 0.85 to 1.11, 1.01 on average; large launches (200 to 3,000 MiB, inputs
-//   changing) at 8 / 4 / 2 bits and raw on average: 5 and 6 heads 1.04 / 1.04 / 1.05 / 1.01, 7 1.00 / 1.01 / 1.07 / 1.00, 13 and 14 1.03 / 1.03 / 1.06 / 1.00, 9 to 11
-//   in items of 1,024 tokens and more 1.00 / 1.01 / 1.06 / 1.00, in shorter ones 0.98 / 0.99 / 1.01 / 0.97 (9 heads, 40 x 6,000 in 512-token items 0.91
-//   / 0.98 / 1.00 / 0.94): these stay as they are above B = 400;
+//   changing) at 8 / 4 / 2 bits and raw on average: 5 and 6 heads 1.04 / 1.04 / 1.06 / 1.01, 7 1.00 / 1.01 / 1.07 / 1.00, 13 and 14 1.03 / 1.03 / 1.06 / 1.00, 9 and 10
+//   1.02 / 1.02 / 1.07 / 1.01 and 11 0.98 / 0.99 / 1.05 / 1.01, but above 1 GiB in items of up to 512 tokens, where planes are taken 8 at a time, 9 to 11 heads 0.96
+//   / 0.97 / 1.00 / 0.99 (64 x 6,000 of 10 heads 0.98 at every level, 48 x 8,192 of 9 0.91 / 0.97 / 0.99 / 0.96): these stay as they are;
 //   whole strips: B up to 144 0.99 to 1.39 (8 heads, 24 x 83 at 8 bits 8.6 -> 7.2), 257 to 400, where some compute units get a second
 //   block, 1.03 to 1.36 (17 x 477 raw 16.2 -> 11.9); 145 to 256 0.87 to 1.07 (one raw 1.27), beyond 400 0.94 to 1.06;
 //   from 15 heads on few lanes of strips idle, and rows that are no whole strips follow the same limits: up to 144 and 257 to 400 0.98 to
@@ -332,8 +332,8 @@ inline EncUnits encode_units_plan(int heads, int l, int n_items, int max_tokens,
   auto one_a_unit = [](double blocks) { return blocks > 144 && blocks <= 256; };
   const double b = planes * (double)groups * ((heads + 3) / 4);
   EncUnits u{};
-  const bool short_wide = heads >= 9 && heads <= 11 && max_tokens < 1024;
-  if (heads < 3 || one_a_unit(b) || ((whole || heads >= 15 || short_wide) && b > 400)) return u;
+  const bool far_apart = heads >= 9 && heads <= 11 && max_tokens <= 512 && planes * heads * 256 * max_tokens > ((int64_t)1 << 30);
+  if (heads < 3 || one_a_unit(b) || far_apart || ((whole || heads >= 15) && b > 400)) return u;
   if (raw && !whole && heads > 3 && one_a_unit(planes * (double)(((int64_t)max_tokens * heads + 511) / 512))) return u;
   u.waves = 4;
   u.blocks = (groups * heads + 1) / 2;

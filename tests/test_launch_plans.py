@@ -361,7 +361,7 @@ def test_encode_units_cover_rows_and_heads(plans, heads):
         for n in (1, 127, 129, 300, 3001):
             waves, blocks = plans("enc_units", heads, l, items, n)[:2]
             b = 2 * l * items * ceil(n, 128) * strips
-            assert (waves != 0) == (heads >= 3 and not 144 < b <= 256 and (b <= 400 or (heads % 4 != 0 and heads < (9 if n < 1024 else 15)) or heads in (13, 14))), (l, items, n)
+            assert (waves != 0) == (heads >= 3 and not 144 < b <= 256 and (b <= 400 or (heads % 4 != 0 and heads < 15))), (l, items, n)
             if waves:  # sets of s heads x a token-group take 2 s waves; V and raw 64 slots a wave
                 assert waves == 4 and blocks * (waves // (2 * s)) >= ceil(n, 128) * (heads // s) and blocks * waves * 64 >= n * heads
     assert plans("enc_units", 2**24 - 4, 32767, 65535, 2**31 - 1)[0] == 0
@@ -374,7 +374,8 @@ def test_encode_raw_slots_of_one_block_a_compute_unit_keep_their_blocks(plans):
     assert waves(9, 6, 1, 1152) == (4, 0) and waves(9, 8, 1, 1024) == (4, 4) and waves(10, 16, 1, 128) == (4, 4)
     assert waves(3, 20, 1, 876) == (4, 4) and waves(8, 17, 1, 477) == (4, 4)  # in strips before
     assert all(waves(h, 20, 1, 3001) == (0, 0) for h in (15, 17, 19, 22, 25, 33)) and waves(14, 20, 1, 3001) == (4, 4)
-    assert [waves(h, 32, 8, 1023)[0] for h in (7, 9, 10, 11, 13)] == [4, 0, 0, 0, 4] and waves(10, 32, 8, 1024) == (4, 4)
+    assert [waves(h, 32, 32, 256)[0] for h in (7, 9, 10, 11, 13)] == [4, 0, 0, 0, 4]  # above 1 GiB in short items
+    assert waves(10, 32, 25, 256) == (4, 4) and waves(10, 32, 16, 513) == (4, 4) and waves(10, 32, 1, 1024) == (4, 4)
 
 
 def test_gpu_tests_reach_the_encoder_forms_they_name(plans):
@@ -382,7 +383,7 @@ def test_gpu_tests_reach_the_encoder_forms_they_name(plans):
 
     for heads, items in t.ENCODER_ITEMS.items():
         taken = [plans("enc_units", heads, 2, i, 300)[0] for i in items]
-        assert taken == ([4, 0, 4, 0] if heads % 4 == 0 or heads >= 9 else [4, 0, 4, 4]), heads
+        assert taken == ([4, 0, 4, 0] if heads % 4 == 0 or heads >= 15 else [4, 0, 4, 4]), heads
 
 
 def test_gpu_tests_reach_the_large_forms_they_name(plans):
