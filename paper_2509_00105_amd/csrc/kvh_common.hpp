@@ -270,10 +270,11 @@ struct TranscodeParams {
   int32_t* status;           // nullable; indexed by item
   int l, c;
   int max_tokens;            // rows the grid covers per item: an item with more tokens is refused on the device
-  int k_log_s;               // K sets are 2^k_log_s heads (3: a span)
-  Divisor by_heads, by_sets; // heads of a row, K sets of a token-group
-  // units of slots (see transcode_units)
+  // units (see transcode_units)
+  int k_log_s;               // K sets are 2^k_log_s heads
   int waves, groups;         // of a block: units, and token-groups whose parameters it prepares
+  Divisor by_heads, by_sets; // heads of a row, K sets of a token-group
+  Divisor by_step;           // K: slots from one access of a unit to the next
   Divisor by_units, by_parts, by_period;  // units and blocks of a token-group (1 block where it holds several), accesses after which heads repeat
 };
 

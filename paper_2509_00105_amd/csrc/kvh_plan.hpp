@@ -181,6 +181,8 @@ inline DecLaunch decode_launch(int heads, int l, int n_items, int max_tokens, in
 }
 
 // ---- transcoder -------------------------------------------------------------------------------------------------
+// Blocks of 8 waves over spans of 8 heads or, where spans leave lanes idle, over (row, head) slots of fewer.  Launches no longer take these
+// layouts; the rule for small launches from 4 to 2 bits below still counts their blocks.
 struct TcPlan {
   bool slots;      // (row, head) slots; otherwise 1024-channel spans, in which the lanes beyond the row idle
   int log_s;       // K sets are 2^log_s heads (3: a span)
@@ -188,16 +190,6 @@ struct TcPlan {
   int64_t blocks;  // of a (layer, K|V) plane
 };
 
-// Slots take idle lanes away, but a K set of few heads reads and writes small pieces (128 * bits / 8 bytes a head).  32
-// layers x 256 to 12,000 tokens, 4 x 3,001 and 80 x 1,000, slots against spans over the pairs of levels: 1 to 4, 9, 10 and
-// 12 heads 1.0 to 4.9 times as fast but for small launches (below; least otherwise: 12 heads, 4 x 3,001 tokens, 4 to 8
-// bits, 0.90); 5 heads 0.65 to 1.12, 6 heads 0.82 to 1.16, 7 heads 0.66 to 0.96, 11 heads 0.93 to 1.17, 13 heads 0.74 to
-// 1.04, 17 heads 0.90 to 1.14, 33 heads 0.86 to 1.02.  So the share of idle lanes has to be the larger the smaller the
-// pieces are: over 3/8 of a row's lanes with single heads, over 1/4 with pairs, 1/4 with fours.  (V alone in slots, K in
-// spans: 5 to 33 heads 0.82 to 1.3.)
-// A small launch of slots has an eighth to a half of the blocks that spans have: below 128 blocks rows of 3 heads and more keep spans
-// (4 x 3,001 tokens x 384 channels, 8 -> 4 bits: spans 13.2 us, slots 14.6; rows of 1 and 2 heads are 0.96 to 1.8 times as fast in
-// slots even there).  Units of slots, below, take all such launches but those of 9 and 10 heads from 4 to 2 bits that they leave here.
 inline TcPlan transcode_plan(int heads, int l, int n_items, int max_tokens) {
   const int spans = (heads + 7) / 8, lanes = spans * 8, idle = lanes - heads;
   const int s = 1 << lowest_bit(heads);
@@ -212,7 +204,7 @@ inline TcPlan transcode_plan(int heads, int l, int n_items, int max_tokens) {
   return p;
 }
 
-// Small launches, and short items of one or two heads, run in units of slots instead (see transcode_units).
+// Small launches, and short items of one or two heads: units of 4 or 8 accesses (see transcode_units).
 struct TcUnits {
   int accesses;    // of a unit, 0: the layouts above
   int period;      // accesses (of 8 slots) after which the heads repeat
@@ -223,19 +215,19 @@ struct TcUnits {
   int64_t blocks;  // of a (layer, K|V) plane
 };
 
-// In the layouts above a wave takes 16 accesses, with 8-bit codes as a chain of loads, 4 or 8 accesses at a time, and blocks
-// are 8 such waves, so that a small launch has few of them (8 heads, 3 x 309 tokens, 8 -> 4 bits: 18 blocks, 11.8 us).
-// Units of 4 accesses, all requested at once, make 4 times the blocks (5.8 us), but prepare K's parameters 4 times over.
-// 380 launches of 2 to 80 layers and 256 to 65,536 tokens, all pairs of levels, by w, the number of 16-access waves they take:
+// A wave of a large launch takes 16 accesses, and small launches then have few waves (8 heads, 3 x 309 tokens, 8 -> 4 bits in blocks of 8:
+// 18 blocks, 11.8 us).  Units of 4 accesses, all requested at once, make 4 times the waves (5.8 us), but prepare K's parameters up to 4 times over.
+// 380 launches of 2 to 80 layers and 256 to 65,536 tokens, all pairs of levels, by w, the number of 16-access waves they take, against
+// the blocks of 8 waves above (transcode_plan):
 //   w <= 512: units of 4 accesses 1.09 to 2.4 times as fast, of 8 1.13 to 1.8;
 //   w <= 1,100: units of 8 0.95 to 1.8 (7 heads, 19 x 343, 4 -> 2: 1.27), 1.4 on average; of 4 0.85 to 1.85;
-//   beyond: 8 -> 4 and 8 -> 2 bits still gain (1.03 to 1.3 at w = 2,000), 4 -> 2 loses where the layouts above keep most lanes busy
+//   beyond: 8 -> 4 and 8 -> 2 bits still gain (1.03 to 1.3 at w = 2,000), 4 -> 2 loses where the blocks above keep most lanes busy
 //   (8 heads 0.93 to 0.97, 15 and 16 heads 0.82).  With more than a quarter of the lanes idle there (3, 4, 5, 9, 10 and 11 heads) units of
 //   8 are 0.87 to 1.6 times as fast, 1.16 on average, up to 2,000;
 //   1 and 2 heads up to 2,900: 1.0 to 1.8 (2,900 to 10,000: 0.88 to 1.2); items of up to 256 tokens fill half or a quarter of a
 //   block of slots: 1 head 1.5 to 2.0 at any size (18 x 17,072, 4 -> 2: 30.2 -> 18.9 us), 2 heads 1.0 to 1.3 up to 10,000.
 // From 4 to 2 bits an element is a table look-up, and K's parameters, prepared once a block, weigh more: with 5 heads and more, where units
-// of 8 make more blocks than the chip has compute units and the layouts above do not, units are 0.81 to 1.02 times as fast, 0.94 on
+// of 8 make more blocks than the chip has compute units and the blocks above do not, units are 0.81 to 1.02 times as fast, 0.94 on
 // average (6 heads, 20 x 200 in two items 0.92; 8 -> 4 bits there 1.06 to 1.3).  `narrow`: every item is known to go from 4 to 2 bits, as for
 // a single blob; the descriptors of a batch are out of the launcher's sight, and it keeps units.  Fewer heads 1.0 to 1.26.  Slower and without a rule: 16
 // heads x 16 tokens from 4 to 2 bits (0.89).
@@ -260,6 +252,53 @@ inline TcUnits transcode_units_plan(int heads, int l, int n_items, int max_token
   if (narrow && heads >= 5 && u.accesses == 8 && u.blocks * planes > 256 && transcode_plan(heads, l, n_items, max_tokens).blocks * planes <= 256)
     return TcUnits{};
   return u;
+}
+
+// All other launches: units of 16 accesses, in blocks of 3 to 8 waves.  Against the blocks of 8 waves above, at 8 -> 4 / 8 -> 2 / 4 -> 2
+// bits, 130 launches of 4 to 65 layers, 256- to 2,048-token items, by w as above:
+//   1 to 4 heads, every P-th access, blocks of up to 4 waves: 0.97 to 1.45 / 1.05 to 1.47 / 1.04 to 1.56 (of up to 8 waves 0.96 to 1.39 / 1.05 to
+//   1.46 / 1.0 to 1.3).
+//   5 to 8 heads: blocks of up to 4 waves prepare the parameters twice, which 8 -> 2 bits feels in small launches.  5 and 6 heads up to w = 3,500
+//   in one block of all units 1.01 to 1.25 / 1.04 to 1.20 / 1.00 to 1.13, in two 1.01 to 1.23 / 0.97 to 1.05 / 0.97 to 1.07, beyond 1.08 to 1.35 / 0.96 to 1.14 / 0.93 to
+//   1.13 and 1.20 to 1.35 / 1.00 to 1.21 / 1.02 to 1.23; 7 and 8 heads up to 10,000 1.00 to 1.34 / 1.05 to 1.15 / 0.99 to 1.04 and 1.02 to 1.32 / 0.96 to 1.05 / 0.92 to
+//   1.10, beyond 1.06 to 1.14 / 1.04 to 1.07 / 0.99 to 1.02 and 1.11 to 1.16 / 1.02 to 1.05 / 1.04.
+//   From 9 heads on sets of heads, blocks of 4 waves.  Multiples of 8 in spans of 8 heads, two blocks each (16 and 24 heads) 1.04 to 1.35 / 1.00 to 1.19 / 1.08 to 1.27
+//   (one block of 8 waves 1.02 to 1.18 / 1.05 to 1.11 / 1.05 to 1.09, sets of four 0.97 to 1.30 / 1.03 to 1.23 / 1.05 to 1.25); fours (12 and 20 heads) 1.04 to 1.29 / 1.06 to 1.27 /
+//   1.06 to 1.24; pairs (10, 14 and 18) 1.00 to 1.23 / 1.10 to 1.28 / 1.06 to 1.23; every P-th access there 0.90 to 1.0 / 0.73 to 0.93 / 0.79 to 1.0, because each block prepares
+//   all heads.  Odd numbers have single heads, whose pieces are 128 bytes of a row, or spans with idle lanes.  Where more than a quarter idles, single heads: 9, 11 and 17 1.02 to
+//   1.25 / 1.04 to 1.23 / 0.96 to 1.37 (spans 0.80 to 1.15 / 0.76 to 1.14 / 0.78 to 1.08); 13, 15, 25 and 33 in spans 1.12 to 1.31 / 1.03 to 1.20 / 1.12 to 1.26 (single heads 1.02
+//   to 1.31 / 1.00 to 1.29 / 0.91 to 1.19), but for up to w = 3,500 with blocks of 8 waves (13 heads 1.19 / 1.13 / 1.12, in two blocks 1.31 / 0.96 / 1.16).  More than 64 heads
+//   are spans; the distance between the rows of an access then stays within 32 bits.
+struct TcStream {
+  int log_s;   // K: sets of 2^log_s heads x a token-group, a unit for each head (8 units are two blocks of 4 waves or one of 8); -1: every period-th access
+  TcUnits in;  // with sets of heads only accesses, waves and blocks count
+};
+
+inline TcStream transcode_stream_plan(int heads, int l, int n_items, int max_tokens) {
+  const int64_t groups = ((int64_t)max_tokens + 127) / 128;
+  const double w = 2.0 * l * n_items * (double)groups * heads;
+  const int lanes = (heads + 7) / 8 * 8, idle = lanes - heads, low = lowest_bit(heads);
+  TcStream p{};
+  TcUnits& u = p.in;
+  u.accesses = 16;
+  u.period = u.units = u.parts = u.groups = 1;
+  if (heads <= 8) {
+    const int most = heads > 4 && w < (heads < 7 ? 3500 : 10000) ? 8 : 4;
+    p.log_s = -1;
+    u.period = heads >> (low < 3 ? low : 3);
+    u.units = heads;
+    u.parts = (heads + most - 1) / most;
+    u.groups = u.parts > 1 ? 1 : most / heads;
+    if (u.groups > groups) u.groups = (int)groups;
+    u.waves = u.parts > 1 ? (heads + u.parts - 1) / u.parts : heads * u.groups;
+    u.blocks = u.parts > 1 ? groups * u.parts : (groups + u.groups - 1) / u.groups;
+  } else {
+    p.log_s = heads > 64 || low > 2 || (low == 0 && 4 * idle <= lanes) ? 3 : low;
+    u.waves = p.log_s == 3 && idle > 0 && w < 3500 ? 8 : 4;
+    const int64_t sets = groups * ((heads + (1 << p.log_s) - 1) >> p.log_s), per_block = u.waves >> p.log_s;
+    u.blocks = per_block == 0 ? 2 * sets : (sets + per_block - 1) / per_block;
+  }
+  return p;
 }
 
 // ---- encoder ----------------------------------------------------------------------------------------------------

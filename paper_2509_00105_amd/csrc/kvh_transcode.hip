@@ -11,22 +11,13 @@
 // pure stream: code in -> fp32 reconstruction -> rounding to the 16-bit type -> position in the
 // same range at the new rate -> code out.
 //
-// Block = 8 waves x 16 token rows = one K token-group x a 1024-channel span; a lane owns 16
-// consecutive channels, so a wave moves one whole code row of the span per access (16 / 8 / 4
-// bytes per lane at 8 / 4 / 2 bits).  K parameters (per channel) are prepared once per block,
-// two channels per thread, and shared through LDS; V parameters (per token and head) are
-// prepared by one lane per group and broadcast inside the wave.  When the whole code -> code map
-// of a group fits one register (4 -> 2 and the pairs that start from 2 bits) the "parameters"
-// are that map, built by running the arithmetic once per input code, and an element costs a
-// shift and a funnel shift.
-//
-// Rows that are not a multiple of 1024 channels leave lanes of the last span idle, 56 of 64 with 128 channels.  Where that
-// costs more than it saves (transcode_plan has the rule and its figures) an access covers 8 (row, head) slots of 8 lanes
-// each instead (SLOTS), 128 slots per wave: V slots are consecutive in memory; K slots are sets of 1, 2 or 4 heads x a
-// token-group, several sets to a block, so that a lane keeps its channels.  32 layers, 8 -> 4 bits, 2,048 tokens x 128
-// channels: 30.3 -> 13.2 us, 8,192 x 256: 115 -> 41 us; 4 -> 2 bits, 12,000 x 128: 101 -> 21 us, 8,192 x 1280: 157 -> 116 us.
-//
-// Small launches, where either layout makes few blocks, run in finer units of slots: see transcode_units.
+// The (row, head) slots of a section are consecutive in memory.  A lane owns 16 consecutive channels, 8 lanes a slot, so that an
+// access of a wave moves 8 slots (16 / 8 / 4 bytes per lane at 8 / 4 / 2 bits); a wave takes a unit of 16 accesses, of 4 or 8 in small
+// launches (see transcode_units).  K parameters (per channel) are prepared once per block, two channels per thread, and shared
+// through LDS; V parameters (per token and head) are prepared by one lane per group and broadcast inside the wave.  When
+// the whole code -> code map of a group fits one register (4 -> 2 and the pairs that start from 2 bits) the "parameters"
+// are that map, and an element costs a shift and a funnel shift.
+#include <algorithm>
 #include <type_traits>
 
 #include "kvh_common.hpp"
@@ -47,17 +38,13 @@ namespace kvh {
 #define KVH_TC_OCC
 #endif
 
-constexpr int kTcWaves = 8;
+constexpr int kTcWaves = 8;                       // of a block, at most
 constexpr int kTcThreads = kTcWaves * kWave;      // 512
 constexpr int kTcLaneCh = 16;                     // channels per lane
-constexpr int kTcSpanCh = kWave * kTcLaneCh;      // 1024 channels per wave access
-constexpr int kTcRows = kGroup / kTcWaves;        // 16 accesses per wave
-constexpr int kTcBatch = 8;                       // accesses in flight per wave
-constexpr int kTcSpanHeads = kTcSpanCh / kGroup;  // 8 (row, head) slots per access
-constexpr int kTcSlots = kTcRows * kTcSpanHeads;  // 128 slots per wave
+constexpr int kTcBatch = 8;                       // accesses of a V wave whose groups its lanes prepare, one each
+constexpr int kTcSpanHeads = kWave * kTcLaneCh / kGroup;  // 8 (row, head) slots per access
 constexpr int kSlotLanes = kGroup / kTcLaneCh;    // 8 lanes per slot
 static_assert(kTcBatch * kTcSpanHeads == kWave, "one lane per V group of a batch");
-static_assert(kTcThreads * 2 == kTcSpanCh, "two K channels per thread");
 
 typedef uint32_t uintx2 __attribute__((ext_vector_type(2)));
 typedef uint32_t uintx4 __attribute__((ext_vector_type(4)));
@@ -201,14 +188,12 @@ struct TcParams {
   float mn;     // f32(mn)
   float scale;  // r / L_in, or 0 (degenerate)
   float inv;    // L_out / r, or 0 (degenerate)
-  float top;    // what code L_in decodes to: f32(mx), or f32(mn) (degenerate)
+  float top;    // what code L_in decodes to by definition: f32(mx), or f32(mn) (degenerate)
 };
 
-// Parameters of a group from its metadata word; also the word the re-encoded group stores and
-// whether code L_in needs the explicit "decode to the stored maximum" rule.
+// Parameters of a group from its metadata word; also the word the re-encoded group stores.
 template <int DT, int BI, int BO>
-__device__ __forceinline__ TcParams tc_params(uint32_t meta, uint32_t& out_meta, bool& fix) {
-  constexpr float LI = float((1 << BI) - 1), LO = float((1 << BO) - 1);
+__device__ __forceinline__ TcParams tc_params(uint32_t meta, uint32_t& out_meta) {
   TcParams p;
   const uint32_t mn_bits = meta & 0xffffu, mx_bits = meta >> 16;
   p.mn = t16_to_f32<DT>(mn_bits);
@@ -219,14 +204,18 @@ __device__ __forceinline__ TcParams tc_params(uint32_t meta, uint32_t& out_meta,
   const uint32_t top_bits = degenerate ? mn_bits : mx_bits;
   p.top = t16_to_f32<DT>(top_bits);
   out_meta = mn_bits | top_bits << 16;
-  fix = (pack2<DT>(recon(LI, p.scale, p.mn), 0.0f) & 0xffffu) != top_bits;
   return p;
 }
 
 // One row of a lane: 16 codes in, 16 codes out.  param(j) gives the parameters of channel j.
-template <int DT, int BI, int BO, bool FIX, typename P>
+//
+// The definition decodes code L_in to the stored maximum mx itself, here it is reconstructed like any other code: the new code is
+// the same.  With r the range, y = fma(L_in, r / L_in, mn) is within r 2^-22 + |mx| 2^-24 of mx, and since mx is a 16-bit value,
+// rounding y to the nearest one moves it by no more than that again.  Up to |mx| = 2^10 r the result is within r 2^-12 of mx,
+// less than a tenth of a step at 8 bits; beyond, y is closer to mx than half a unit in its last place and becomes mx.  In either case the
+// position rounds to L_out.  (A degenerate group has inv = 0 and only code 0.)
+template <int DT, int BI, int BO, typename P>
 __device__ __forceinline__ void transcode_row(uint8_t* out, const InCodes<BI>& cw, P&& param) {
-  constexpr float LI = float((1 << BI) - 1);
   float t[kTcLaneCh];
   uint32_t e[4];
   cw.spread(e);
@@ -246,10 +235,6 @@ __device__ __forceinline__ void transcode_row(uint8_t* out, const InCodes<BI>& c
       x0 = t16_to_f32<DT>(pk & 0xffffu);
       x1 = t16_to_f32<DT>(pk >> 16);
     }
-    if constexpr (FIX) {
-      x0 = q0 == LI ? p0.top : x0;
-      x1 = q1 == LI ? p1.top : x1;
-    }
     // position in the range at the new rate: subtract, then multiply (two roundings)
     t[j] = (x0 - p0.mn) * p0.inv;
     t[j + 1] = (x1 - p1.mn) * p1.inv;
@@ -265,12 +250,39 @@ __device__ __forceinline__ void transcode_row(uint8_t* out, const InCodes<BI>& c
 template <int BI, int BO>
 constexpr bool kUseTable = (1 << BI) * BO <= 32;
 
+// Where a group lies no further from zero than some multiple of its range, its map is the one of exact arithmetic, code q to the
+// code nearest to q L_out / L_in, and needs no evaluation.  The quotient (never half-way between two codes) keeps a distance of
+// kMargin from every half-way point, and what the definition adds to it is the rounding of the value to 16 bits, at most M 2^-8 (bf16) or
+// M 2^-11 + 2^-25 (fp16) for a group whose values reach M, times L_out / r; the roundings to fp32 are below 2^-18 of the margin as long as
+// M is below 2^4 r, for which 1/64 is set aside.  From 4 to 2 bits that is M < 8.4 r in bf16: all groups but those of a large
+// common offset.  32 layers x 8,192 tokens x 1024 channels, 4 -> 2 bits: 87.2 us with every
+// table evaluated (16 times 7 operations), 77.5.
+template <int BI, int BO>
+constexpr uint32_t usual_table() {
+  constexpr uint32_t LI = (1u << BI) - 1, LO = (1u << BO) - 1;
+  uint32_t table = 0;
+  for (uint32_t q = 0; q <= LI; ++q) table |= (2 * q * LO + LI) / (2 * LI) << (BO * q);
+  return table;
+}
+template <int DT, int BI, int BO>
+__device__ __forceinline__ bool usual_map(uint32_t meta) {
+  static_assert(kUseTable<BI, BO>, "4 -> 2 bits, or from 2 bits");
+  constexpr float LO = float((1 << BO) - 1);
+  constexpr float kMargin = BI == 4 ? 0.1f : 0.5f;  // q / 5; otherwise a whole multiple of q
+  const float mn = t16_to_f32<DT>(meta & 0xffffu), mx = t16_to_f32<DT>(meta >> 16), r = mx - mn;
+  const float most = __builtin_fmaxf(__builtin_fabsf(mn), __builtin_fabsf(mx));
+  const float off = DT == KVH_F16 ? __builtin_fmaf(most, 0x1p-11f, 0x1p-25f) : most * 0x1p-8f;
+  return off < r * (kMargin / LO * (63.0f / 64.0f)) && most < r * 16.0f && r < 0x1p120f;
+}
+
 template <int DT, int BI, int BO>
 __device__ __forceinline__ uint32_t code_table(uint32_t meta, uint32_t& out_meta) {
   constexpr int NQ = 1 << BI;
-  bool fix;
-  const TcParams p = tc_params<DT, BI, BO>(meta, out_meta, fix);
-  uint32_t table = 0;
+  const TcParams p = tc_params<DT, BI, BO>(meta, out_meta);
+  const bool usual = usual_map<DT, BI, BO>(meta);
+  uint32_t table = p.inv == 0.0f ? 0u : usual_table<BI, BO>();
+  if (__builtin_amdgcn_ballot_w64(!usual && p.inv != 0.0f) == 0) return table;  // wave-uniform
+  uint32_t other = 0;
 #pragma unroll
   for (int q = 0; q < NQ; q += 2) {
     const uint32_t pk = pack2<DT>(recon((float)q, p.scale, p.mn), recon((float)(q + 1), p.scale, p.mn));
@@ -278,9 +290,9 @@ __device__ __forceinline__ uint32_t code_table(uint32_t meta, uint32_t& out_meta
     const float x1 = q + 1 == NQ - 1 ? p.top : t16_to_f32<DT>(pk >> 16);  // the top code decodes to the stored maximum
     const uint32_t two = __builtin_amdgcn_cvt_pk_u8_f32((x1 - p.mn) * p.inv, 1,
                                                         __builtin_amdgcn_cvt_pk_u8_f32((x0 - p.mn) * p.inv, 0, 0u));
-    table |= ((two & 0xffu) | ((two >> 8) & 0xffu) << BO) << (BO * q);
+    other |= ((two & 0xffu) | ((two >> 8) & 0xffu) << BO) << (BO * q);
   }
-  return table;
+  return usual ? table : other;
 }
 
 // Byte-wise shift amounts b_out * q for the 16 codes of a lane: code j sits in byte sh_byte(j) of
@@ -475,393 +487,36 @@ __device__ __forceinline__ void write_header(uint8_t* dst, const TranscodeParams
   gstore<uint32_t>(dst + 4 * threadIdx.x, w);
 }
 
-// SLOTS: the lanes are cut into (row, head) slots (see the head of the file); otherwise a span's lanes keep its channels
-// and those beyond the row idle.
-template <int DT, int BI, int BO, bool SLOTS>
-__device__ __forceinline__ void transcode_block(const TranscodeParams& a, const kvh_tc_item& it, int item_idx, int lay_kv,
-                                                int bx, TcParams* kpar, float* kquad, uint32_t* kflags) {
-  using Yes = std::integral_constant<bool, true>;
-  using No = std::integral_constant<bool, false>;
-  const int lane = threadIdx.x & (kWave - 1);
-  const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const uint32_t sub = lane % kSlotLanes, slot = lane / kSlotLanes;
-  const uint32_t n = (uint32_t)it.n_tokens, c = (uint32_t)a.c, heads = c / kGroup;
-  const int lam = lay_kv >> 1;
-  const bool is_v = lay_kv & 1;
-
-  // K: a set is 2^log_s heads (a span's 8 without SLOTS) x one token-group, shared by as many waves; a block holds
-  // 8 >> log_s sets
-  const uint32_t log_s = SLOTS ? (uint32_t)a.k_log_s : 3u;
-  const uint32_t sets = SLOTS ? heads >> log_s : (heads + 7) >> 3;  // per token-group
-  const uint32_t first_set = (uint32_t)bx * (8u >> log_s);
-  const uint32_t first_g = a.by_sets.quotient(first_set);
-  if ((!SLOTS || !is_v) && (uint64_t)first_g * kGroup >= n) return;  // block-uniform
-  auto set_of = [&](uint32_t s, uint32_t& g, uint32_t& head0) {  // the s-th set of the block
-    g = SLOTS ? a.by_sets.quotient(first_set + s) : first_g;
-    head0 = (first_set + s - g * sets) << log_s;
-  };
-  // V: the wave's slots start at row t0, head y0.  In spans they are 16 rows x 8 heads, with SLOTS 128 in memory order;
-  // access i is `v_step` slots of the section on.
-  uint32_t t0 = 0, y0 = 0, left = 0;
-  uint64_t left64 = 0;  // SLOTS: slots from the wave's first to the end of the section
-  const uint32_t v_step = SLOTS ? (uint32_t)kTcSpanHeads : heads;
-  if (is_v) {
-    if constexpr (SLOTS) {
-      const uint32_t unit = (uint32_t)bx * kTcWaves + wave;
-      const uint32_t q = a.by_heads.quotient(unit), x = (unit - q * heads) * kTcSlots, xq = a.by_heads.quotient(x);
-      t0 = q * kTcSlots + xq;
-      y0 = x - xq * heads;
-      if (t0 < n) left64 = (uint64_t)(n - t0) * heads - y0;
-      left = left64 < kTcSlots ? (uint32_t)left64 : (uint32_t)kTcSlots;
-    } else {
-      t0 = first_g * kGroup + wave * kTcRows;
-      y0 = (first_set - first_g * sets) << 3;
-      left = t0 >= n ? 0 : n - t0 < kTcRows ? (n - t0) * kTcSpanHeads : (uint32_t)kTcSlots;
-    }
-  }
-
-  const uint8_t* src = static_cast<const uint8_t*>(it.src);
-  uint8_t* dst = static_cast<uint8_t*>(it.dst);
-  const LayerGeom gi = layer_geom(it.n_tokens, a.c, BI), go = layer_geom(it.n_tokens, a.c, BO);
-  const HeaderWords hdr = {gload<uintx4>(src), gload<uintx4>(src + 16), gload<uintx4>(src + 32)};
-  const uint8_t* in_layer = src + kHeaderBytes + (size_t)lam * gi.layer_bytes();
-  uint8_t* out_layer = dst + kHeaderBytes + (size_t)lam * go.layer_bytes();
-
-  // A lane's codes: access i is i strides on; accesses beyond `last` (-1: none) re-read it and are not stored.  `count`
-  // (wave-uniform) accesses have something to store.
-  const uint8_t* in_codes;
-  uint8_t* out_codes;
-  const size_t in_stride_k = gi.row_bytes << (3 - log_s), out_stride_k = go.row_bytes << (3 - log_s);
-  const size_t in_stride_v = (size_t)v_step * (kGroup * BI / 8), out_stride_v = (size_t)v_step * (kGroup * BO / 8);
-  int last, count;
-  bool active = true;  // without SLOTS: the lane's channels exist
-  uint32_t par_lane = 0;  // K: where the parameters of this lane's channels lie in LDS
-  if (!is_v) {
-    const uint32_t sib = wave >> log_s;
-    uint32_t g, head0;
-    set_of(sib, g, head0);
-    const uint32_t t_wave = g * kGroup + (wave & ((1u << log_s) - 1)) * (kGroup >> log_s);
-    const uint32_t t = t_wave + (slot >> log_s), t_in = t < n ? t : n - 1;
-    const uint32_t head = head0 + (slot & ((1u << log_s) - 1));
-    if (!SLOTS) active = head < heads;
-    const uint32_t ch = (active ? head : 0u) * kGroup + sub * kTcLaneCh;
-    in_codes = in_layer + gi.kmeta + (size_t)t_in * gi.row_bytes + ch * BI / 8;
-    out_codes = out_layer + go.kmeta + (size_t)t_in * go.row_bytes + ch * BO / 8;
-    last = t < n ? (int)((n - 1 - t) >> (3 - log_s)) : -1;
-    count = t_wave < n ? (int)((n - 1 - t_wave) >> (3 - log_s)) + 1 : 0;
-    par_lane = (sib << (3 + log_s)) + ((uint32_t)lane & ((8u << log_s) - 1));
-  } else {
-    if (!SLOTS) active = y0 + slot < heads;
-    const size_t first = left == 0 ? 0 : (size_t)t0 * heads + y0 + (!SLOTS ? (active ? slot : 0) : slot < left ? slot : left - 1);
-    in_codes = in_layer + gi.kmeta + gi.codes + gi.vmeta + first * (kGroup * BI / 8) + sub * (kTcLaneCh * BI / 8);
-    out_codes = out_layer + go.kmeta + go.codes + go.vmeta + first * (kGroup * BO / 8) + sub * (kTcLaneCh * BO / 8);
-    count = (int)((left + kTcSpanHeads - 1) / kTcSpanHeads);
-    last = !SLOTS ? count - 1 : slot < left ? (int)((left - 1 - slot) / kTcSpanHeads) : -1;
-  }
-
-  // Accesses in flight per wave.  Narrow codes (2 registers an access or less) are loaded for all 16 accesses of
-  // the wave at once: one round trip to memory instead of two, and twice the bytes in flight.  With
-  // 8-bit input an access takes 4 registers; a K wave also holds the parameters of its 16 channels
-  // (48 registers), so it takes 4 at a time and a V wave 8.
-  constexpr int kRowsK = BI == 8 ? kTcBatch / 2 : kTcRows;
-  constexpr int kRowsV = BI == 8 ? kTcBatch : kTcRows;
-  InCodes<BI> cw[kRowsV];
-  auto stores = [&](int k) { return SLOTS ? k <= last : k < count && active; };
-  auto load_batch = [&](int a0, auto rows_tag, size_t in_stride) {
-#pragma unroll
-    for (int i = 0; i < decltype(rows_tag)::value; ++i) {
-      int k = a0 + i;
-      k = k <= last ? k : last < 0 ? 0 : last;
-      cw[i].load(in_codes + (size_t)(uint32_t)k * in_stride);
-    }
-  };
-  // accesses a0 .. a0 + rows - 1, held in cw[first ..]
-  auto run_batch = [&](int a0, auto first_tag, auto rows_tag, auto fix_tag, size_t out_stride, auto&& param_of) {
-    constexpr bool FIX = decltype(fix_tag)::value;
-    constexpr int kFirst = decltype(first_tag)::value;
-#pragma unroll
-    for (int i = 0; i < decltype(rows_tag)::value; ++i) {
-      if (a0 + i < count) {  // wave-uniform
-        auto param = param_of(i);  // may shuffle across lanes: taken with the whole wave enabled
-        if (stores(a0 + i)) transcode_row<DT, BI, BO, FIX>(out_codes + (size_t)(uint32_t)(a0 + i) * out_stride, cw[kFirst + i], param);
-      }
-      __builtin_amdgcn_sched_barrier(0);  // one access at a time: keeps the temporaries of different ones apart
-    }
-  };
-  using Zero = std::integral_constant<int, 0>;
-  using Eight = std::integral_constant<int, kTcBatch>;
-  using Batch = std::integral_constant<int, kTcBatch>;
-  using RowsK = std::integral_constant<int, kRowsK>;
-  using RowsV = std::integral_constant<int, kRowsV>;
-
-  // The caller guarantees kvh_blob_size(l, n_tokens, c, level_in) readable bytes at the source,
-  // so the loads issued before the header verdict stay inside the buffer whatever it says.
-  // V metadata: lane l prepares the l-th of the 64 slots of a batch of 8 accesses.  On the table routes the words are
-  // requested with the codes, and by every lane (lanes without a slot read the wave's first), so that the wait for
-  // them, which takes in the codes, is on every path: a wait that some path skips is repeated before each access, where
-  // it also waits for the stores before (4 -> 2: 100 instead of 88 us on 32 x 8192 x 1024).
-  const uint32_t m_lane = ((uint32_t)lane / kTcSpanHeads * v_step + lane % kTcSpanHeads) * 4, m_batch = v_step * (kTcBatch * 4);
-  const size_t vfirst = ((size_t)t0 * heads + y0) * 4;  // metadata word of the wave's first slot
-  const uint8_t* in_vmeta = in_layer + gi.kmeta + gi.codes + vfirst;
-  auto owns = [&](int batch) { return (uint32_t)(batch * kWave + lane) < left && (SLOTS || y0 + lane % kTcSpanHeads < heads); };
-  [[maybe_unused]] uint32_t vm[2] = {0u, 0u};
-  if (count > 0) {
-    if (is_v) {
-      load_batch(0, RowsV{}, in_stride_v);
-      if constexpr (kUseTable<BI, BO>) {
-#pragma unroll
-        for (int sb = 0; sb < 2; ++sb) vm[sb] = gload<uint32_t>(in_vmeta + (owns(sb) ? (size_t)sb * m_batch + m_lane : 0));
-      }
-    } else {
-      load_batch(0, RowsK{}, in_stride_k);
-    }
-  }
-
-  // the two K channels this thread prepares
-  uintx2 km = {0u, 0u};
-  bool pact = false;
-  size_t pmeta = 0;  // offset of their metadata words
-  if (!is_v) {
-    const uint32_t lc = threadIdx.x * 2;  // channel within the block's sets
-    uint32_t g, head0;
-    set_of(lc >> (7 + log_s), g, head0);
-    const uint32_t pc = head0 * kGroup + (lc & ((128u << log_s) - 1));
-    pact = (uint64_t)g * kGroup < n && (SLOTS || pc < c);
-    pmeta = ((size_t)g * c + pc) * 4;
-    if (pact) km = gload<uintx2>(in_layer + pmeta);
-  }
-
-  // block-uniform verdict: every thread reads the same header
-  if (!source_header_ok(hdr, DT, BI, a.l, it.n_tokens, a.c, kHeaderBytes + (size_t)a.l * gi.layer_bytes())) {
-    if (a.status != nullptr && threadIdx.x == 0) a.status[item_idx] = KVH_DEV_HEADER_MISMATCH;
-    return;
-  }
-  if (bx == 0 && lay_kv == 0 && threadIdx.x < kHeaderBytes / 4) write_header<DT, BO>(dst, a, n, go, hdr);
-
-  if (!is_v) {
-    uint32_t om[2] = {0u, 0u};
-    const uint32_t meta[2] = {km.x, km.y};
-    if constexpr (kUseTable<BI, BO>) {
-      uint32_t* ktab = reinterpret_cast<uint32_t*>(kpar);  // [slot][lane], one word per channel
-#pragma unroll
-      for (int e = 0; e < 2; ++e) {
-        const int lc = (int)threadIdx.x * 2 + e;
-        ktab[(lc % kTcLaneCh) * kWave + lc / kTcLaneCh] = code_table<DT, BI, BO>(meta[e], om[e]);
-      }
-      if (pact) {
-        uintx2 o = {om[0], om[1]};
-        gstore<uintx2>(out_layer + pmeta, o);
-      }
-      __syncthreads();
-      if (count == 0) return;  // wave-uniform, after the barrier
-      uint32_t tab[kTcLaneCh];
-#pragma unroll
-      for (int j = 0; j < kTcLaneCh; ++j) tab[j] = ktab[j * kWave + par_lane];
-#pragma unroll
-      for (int i = 0; i < kRowsK; ++i) {  // kRowsK == kTcRows here: the wave's accesses are all loaded
-        if (stores(i))
-          lookup_row<BI, BO>(out_codes + (size_t)i * out_stride_k, cw[i], [&tab](int j) { return tab[j]; });
-        __builtin_amdgcn_sched_barrier(0);
-      }
-      return;
-    }
-    bool fix = false;
-    [[maybe_unused]] uint32_t worst = kStandard;  // 8 -> 2: the least tractable of this thread's channels
-#pragma unroll
-    for (int e = 0; e < 2; ++e) {
-      bool f;
-      const TcParams p = tc_params<DT, BI, BO>(meta[e], om[e], f);
-      fix |= pact && f;
-      const int lc = (int)threadIdx.x * 2 + e;  // channel within the span; its user is lane lc / 16, slot lc % 16
-      const int slot = (lc % kTcLaneCh) * kWave + lc / kTcLaneCh;
-      kpar[slot] = p;
-      if constexpr (BI == 8 && BO == 2) {
-        Quad gq;
-        const uint32_t cls = classify82<DT>(p, gq);
-        if (pact && cls > worst) worst = cls;
-        kquad[slot] = gq.a;
-        kquad[kTcLaneCh * kWave + slot] = gq.b;
-        kquad[2 * kTcLaneCh * kWave + slot] = gq.c;
-      }
-    }
-    if (pact) {
-      uintx2 o = {om[0], om[1]};
-      gstore<uintx2>(out_layer + pmeta, o);
-    }
-    bool any_fix;
-    if constexpr (BI == 8 && BO == 2) {
-      // three block-wide verdicts through one barrier: every wave leaves its own in LDS
-      const uint32_t mine = (__builtin_amdgcn_ballot_w64(fix) != 0 ? 1u : 0u) |
-                            (__builtin_amdgcn_ballot_w64(worst != kStandard) != 0 ? 2u : 0u) |
-                            (__builtin_amdgcn_ballot_w64(worst == kHard) != 0 ? 4u : 0u);
-      if (lane == 0) kflags[wave] = mine;
-      __syncthreads();
-      uint32_t all = 0;
-#pragma unroll
-      for (int w = 0; w < kTcWaves; ++w) all |= kflags[w];
-      all = (uint32_t)__builtin_amdgcn_readfirstlane((int)all);
-      any_fix = (all & 1u) != 0;
-      if ((all & 4u) == 0) {  // no hard group in the block: the polynomial route
-        if (count == 0) return;  // wave-uniform, after the barrier
-        auto poly_rows = [&](auto standard_tag) {
-          constexpr bool STANDARD = decltype(standard_tag)::value;
-          Quad gq[kTcLaneCh];
-#pragma unroll
-          for (int j = 0; j < kTcLaneCh; ++j) {
-            gq[j].a = STANDARD ? 0.0f : kquad[j * kWave + par_lane];
-            gq[j].b = STANDARD ? 0.0f : kquad[(kTcLaneCh + j) * kWave + par_lane];
-            gq[j].c = STANDARD ? 0.0f : kquad[(2 * kTcLaneCh + j) * kWave + par_lane];
-          }
-#pragma unroll 1
-          for (int a0 = 0;;) {
-#pragma unroll
-            for (int i = 0; i < kRowsK; ++i) {
-              if (stores(a0 + i))
-                poly_row82<STANDARD>(out_codes + (size_t)(uint32_t)(a0 + i) * out_stride_k, cw[i], [&gq](int j) -> const Quad& { return gq[j]; });
-              __builtin_amdgcn_sched_barrier(0);
-            }
-            a0 += kRowsK;
-            if (a0 >= kTcRows || a0 >= count) break;
-            load_batch(a0, RowsK{}, in_stride_k);
-          }
-        };
-        if ((all & 2u) == 0) poly_rows(Yes{}); else poly_rows(No{});
-        return;
-      }
-    } else {
-      any_fix = __syncthreads_or(fix);
-    }
-    if (count == 0) return;  // wave-uniform, after the barrier
-    // The common path never touches `top`; reading it only where the rule is needed keeps that path's
-    // register count down.
-    auto k_rows = [&](auto fix_tag) {
-      constexpr bool FIX = decltype(fix_tag)::value;
-      TcParams p[kTcLaneCh];
-#pragma unroll
-      for (int j = 0; j < kTcLaneCh; ++j) {
-        const TcParams& s = kpar[j * kWave + par_lane];
-        p[j].mn = s.mn;
-        p[j].scale = s.scale;
-        p[j].inv = s.inv;
-        p[j].top = FIX ? s.top : 0.0f;
-      }
-      auto param_of = [&](int) { return [&p](int j) -> const TcParams& { return p[j]; }; };
-#pragma unroll 1
-      for (int a0 = 0;;) {
-        run_batch(a0, Zero{}, RowsK{}, fix_tag, out_stride_k, param_of);
-        a0 += kRowsK;
-        if (a0 >= kTcRows || a0 >= count) break;
-        load_batch(a0, RowsK{}, in_stride_k);
-      }
-    };
-    if (any_fix) k_rows(Yes{}); else k_rows(No{});
-  } else {
-    if (count == 0) return;  // wave-uniform; V waves never meet at a barrier
-    uint8_t* out_vmeta = out_layer + go.kmeta + go.codes + vfirst;
-    if constexpr (kUseTable<BI, BO>) {
-      // the wave's 16 accesses are loaded; their groups are prepared 8 accesses (= 64 groups, one per lane) at a time
-      asm volatile("" : "+v"(vm[0]), "+v"(vm[1]));  // both words, and with them all codes, have arrived from here on
-      auto eight_rows = [&](auto sb_tag) {
-        constexpr int sb = decltype(sb_tag)::value;
-        constexpr int a0 = sb * kTcBatch;
-        uint32_t om;
-        const uint32_t mine = code_table<DT, BI, BO>(vm[sb], om);
-        if (owns(sb)) gstore<uint32_t>(out_vmeta + (size_t)sb * m_batch + m_lane, om);
-#pragma unroll
-        for (int i = 0; i < kTcBatch; ++i) {
-          if (a0 + i < count) {  // wave-uniform; the shuffle is taken with the whole wave enabled
-            const uint32_t tab = __shfl(mine, i * kTcSpanHeads + (int)slot);
-            if (stores(a0 + i))
-              lookup_row<BI, BO>(out_codes + (size_t)(a0 + i) * out_stride_v, cw[a0 + i], [tab](int) { return tab; });
-          }
-          __builtin_amdgcn_sched_barrier(0);
-        }
-      };
-      eight_rows(std::integral_constant<int, 0>{});
-      if (kTcBatch < count) eight_rows(std::integral_constant<int, 1>{});
-    } else {
-#pragma unroll 1
-      for (int a0 = 0;;) {  // kRowsV accesses from a0 on are loaded
-        auto eight_rows = [&](auto first_tag) {
-          const int tb = a0 + decltype(first_tag)::value;
-          const int batch = tb / kTcBatch;
-          const bool own = owns(batch);
-          TcParams mine = {0.0f, 0.0f, 0.0f, 0.0f};
-          bool fix = false;
-          if (own) {
-            const size_t off = (size_t)(uint32_t)batch * m_batch + m_lane;
-            uint32_t om;
-            mine = tc_params<DT, BI, BO>(gload<uint32_t>(in_vmeta + off), om, fix);
-            gstore<uint32_t>(out_vmeta + off, om);
-          }
-          const bool any_fix = __builtin_amdgcn_ballot_w64(fix) != 0;
-          if constexpr (BI == 8 && BO == 2) {
-            Quad gq;
-            uint32_t cls = classify82<DT>(mine, gq);
-            if (!own) cls = kStandard;  // a lane without a group has no say
-            if (__builtin_amdgcn_ballot_w64(cls == kHard) == 0) {
-              const bool all_standard = __builtin_amdgcn_ballot_w64(cls != kStandard) == 0;
-              constexpr int kFirst = decltype(first_tag)::value;
-#pragma unroll
-              for (int i = 0; i < kTcBatch; ++i) {
-                if (tb + i < count) {  // wave-uniform; the shuffles are taken with the whole wave enabled
-                  const int owner = i * kTcSpanHeads + (int)slot;
-                  uint8_t* out_row = out_codes + (size_t)(uint32_t)(tb + i) * out_stride_v;
-                  if (all_standard) {
-                    if (stores(tb + i)) poly_row82<true>(out_row, cw[kFirst + i], [&gq](int) -> const Quad& { return gq; });
-                  } else {
-                    const Quad gr = {__shfl(gq.a, owner), __shfl(gq.b, owner), __shfl(gq.c, owner)};
-                    if (stores(tb + i)) poly_row82<false>(out_row, cw[kFirst + i], [&gr](int) -> const Quad& { return gr; });
-                  }
-                }
-                __builtin_amdgcn_sched_barrier(0);
-              }
-              return;
-            }
-          }
-          auto param_of = [&](int i) {
-            const int owner = i * kTcSpanHeads + (int)slot;
-            TcParams p;
-            p.mn = __shfl(mine.mn, owner);
-            p.scale = __shfl(mine.scale, owner);
-            p.inv = __shfl(mine.inv, owner);
-            p.top = __shfl(mine.top, owner);
-            return [p](int) -> const TcParams& { return p; };
-          };
-          if (any_fix) run_batch(tb, first_tag, Batch{}, Yes{}, out_stride_v, param_of); else run_batch(tb, first_tag, Batch{}, No{}, out_stride_v, param_of);
-        };
-        eight_rows(Zero{});
-        if constexpr (kRowsV > kTcBatch) {
-          if (a0 + kTcBatch < count) eight_rows(Eight{});
-        }
-        a0 += kRowsV;
-        if (a0 >= kTcRows || a0 >= count) break;
-        load_batch(a0, RowsV{}, in_stride_v);
-      }
-    }
-    // zero the padding that rounds the vmeta section up to 16 bytes
-    if (SLOTS ? left64 <= kTcSlots && lane == 0 : y0 == 0 && threadIdx.x == 0 && t0 + kGroup >= n) {
-      for (size_t o = (size_t)n * heads * 4; o < go.vmeta; o += 4) gstore<uint32_t>(out_vmeta - vfirst + o, 0u);
-    }
-  }
-}
-
 // ---- units of slots ----------------------------------------------------------------------------------------------
-// Any row length with every lane at work.  The (row, head) slots of a section are consecutive in memory, 8 lanes each; an
-// access is 8 consecutive slots (1 KiB of 8-bit codes), and a unit, one wave, is ACC accesses.
-//   V: consecutive accesses.
-//   K: a lane has to keep its channels, that is the head of its slot, from access to access.  With H heads a row the heads of
-//     consecutive accesses repeat after P = H / gcd(H, 8) of them, so that a unit takes every P-th access of its token-group: unit
-//     u is accesses r + P (ACC j + i), i = 0 .. ACC - 1, with r = u mod P, j = u / P.  The 16 H / ACC units of a token-group are
-//     waves of one block, or of a few.
-// A block prepares the parameters of all heads of its token-groups.  Everything a unit reads is requested before anything of it is
-// used: what bounds a small launch is its chain of trips to memory.  8 -> 4 bits bf16: 3 x 309 tokens of 8 heads 11.8 -> 5.8 us, 11 x
-// 890 14.0 -> 12.0, 10 x 2,012 of 1 head in 512-token items 8 -> 8 bits 9.6 -> 5.5; an empty launch is 3.9.
-constexpr unsigned kUnitsHeadBytes = kGroup * (sizeof(TcParams) + sizeof(Quad));  // LDS for the parameters of one head
-template <int DT, int BI, int BO, int ACC>
+// An access is 8 slots (1 KiB of 8-bit codes), and a unit, one wave, is ACC accesses.
+//   V: consecutive slots.
+//   K: a lane has to keep its channels, that is the head of its slot, from access to access.  Up to 8 heads, and in small launches: with H
+//     heads a row the heads of consecutive accesses repeat after P = H / gcd(H, 8) of them, so that a unit takes every P-th access of its
+//     token-group: unit u is accesses r + P (ACC j + i), i = 0 .. ACC - 1, with r = u mod P, j = u / P.  The 16 H / ACC units of a token-group
+//     are waves of one block, or of a few, each of which prepares the parameters of all heads.  No lane is idle.
+//     SETS, longer rows: a set is 2^log_s heads x a token-group and 2^log_s units; an access is 8 >> log_s rows of the set.  Sets of 8 heads
+//     take in what lies beyond the row, as idle lanes, and are one block of 8 waves or two of 4, each of which prepares all of the set's parameters.
+// What bounds it.  Small launches (ACC = 4 and 8): the chain of trips to memory, so that everything a unit reads is requested before
+// anything of it is used (8 -> 4 bits bf16: 3 x 309 tokens of 8 heads 11.8 -> 5.8 us; an empty launch is 3.9).  Large ones
+// (ACC = 16): memory, and beside it 6 to 7 operations an element, 0.6 of what the vector units do in the time memory takes, so that one
+// has to run under the other.  8-bit codes come through a ring of 8 accesses: 4 are used while 4 are on their way, and those that follow
+// are requested before the next stores are issued (a wait for a load is a wait for every store before it as well).  No register is spilled on the way of
+// a row but one access of 8 -> 2 bits, and blocks are 3 or 4 waves where that is to be had: a block takes the place of one that has ended,
+// and its start is hidden by the others of the compute unit, four and not one.  Before, a wave took 4 accesses, waited for its stores, and took the
+// next 4, in blocks of 8 waves over 8 heads (or single heads, pairs and fours), with lanes idle for 3, 5, 6, 7, 11 and from 13 heads on.
+//   32 layers x 8,192 tokens in 256-token items, 8 heads bf16, 8 -> 4 / 8 -> 2 / 4 -> 2 bits: 153.7 / 140.8 / 88.5 -> 139.5 / 135.7 / 77.5 us (5.9 TB/s; without
+//   any arithmetic the same traffic takes 136 us at 8 -> 4 bits); 16 heads, 60 x 6,250: 510 / 474 / 291 -> 451 / 398 / 247; 5 heads, 7 x 20,000:
+//   75.2 / 73.1 / 43.6 -> 56.0 / 56.7 / 33.3; 10 heads, 20 x 8,000: 129 / 118 / 74 -> 119 / 106 / 67; 4 heads, 20 x 9,000: 58.2 / 54.6 / 35.5 -> 51.9 / 48.3 / 31.3.
+constexpr unsigned kUnitsHeadBytes = kGroup * 6 * sizeof(float);  // LDS for the parameters of a head: three values of a channel, and the 8 -> 2 polynomial  // LDS for the parameters of one head
+template <int DT, int BI, int BO, int ACC, bool SETS>
 __device__ __forceinline__ void transcode_units(const TranscodeParams& a, const kvh_tc_item& it, int item_idx, int lay_kv,
                                                 uint32_t bx, uint8_t* lds, uint32_t* kflags) {
-  static_assert(ACC <= kTcBatch, "one lane per V group of a unit");
+  // Accesses whose codes a wave holds, and how many are requested again at a time as they are used up.
+  constexpr int kRing = BI == 8 && ACC > kTcBatch ? kTcBatch : ACC, kRefill = kRing < ACC ? kRing / 2 : ACC;
+  // The search for the steps of an 8 -> 2 bit group needs registers of its own: half of the ring is requested behind it.
+  constexpr int kEarly = BI == 8 && BO == 2 && kRing < ACC ? kRing / 2 : kRing;
+  constexpr int kVBatch = ACC < kTcBatch ? ACC : kTcBatch;  // accesses whose V groups the lanes prepare at a time, one each
+  static_assert(ACC % kRefill == 0 && ACC % kVBatch == 0 && kVBatch % kRefill == 0 || kRing == ACC, "whole batches");
   constexpr uint32_t kInBytes = kGroup * BI / 8, kOutBytes = kGroup * BO / 8;  // of a slot
   const int lane = threadIdx.x & (kWave - 1);
   const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -871,76 +526,122 @@ __device__ __forceinline__ void transcode_units(const TranscodeParams& a, const 
   const bool is_v = lay_kv & 1;
   const uint64_t total = (uint64_t)n * heads;
 
-  // the unit: its first slot, the slots from one access to the next, and how many slots it has at most
-  uint32_t g0 = 0, gi = 0, block_unit = 0;  // K: first token-group of the block, this wave's among them, first unit of the block
+  // The unit: its first slot, the slots from one access to the next, how many slots it has at most, and where in an access the
+  // lane's slot lies.
+  uint32_t g0 = 0, gi = 0, block_unit = 0;  // K in accesses: first token-group of the block, this wave's among them, first unit of the block
+  uint32_t par_head = 0;                    // K: which of the heads that the block prepares is the lane's
   uint64_t s0;
-  uint32_t step = kTcSpanHeads;
-  bool live = true;
+  uint32_t step = kTcSpanHeads, lane_slot = slot;
+  bool live = true, active = true;
+  const uint32_t half = (uint32_t)a.k_log_s == 3u && a.waves == 4 ? 1u : 0u;  // SETS: a set is two blocks
+  auto set_of = [&](uint32_t i, uint32_t& g, uint32_t& head0) {  // the i-th set of the block
+    const uint32_t set = half ? bx >> 1 : bx * ((uint32_t)a.waves >> a.k_log_s) + i;
+    g = a.by_sets.quotient(set);
+    head0 = (set - g * a.by_sets.d) << a.k_log_s;
+  };
   if (is_v) {
     s0 = ((uint64_t)bx * (uint32_t)a.waves + wave) * (uint32_t)(ACC * kTcSpanHeads);
+  } else if (SETS) {
+    uint32_t g, head0;
+    set_of(0, g, head0);
+    if ((uint64_t)g * kGroup >= n) return;  // block-uniform
+    const uint32_t log_s = (uint32_t)a.k_log_s, mask = (1u << log_s) - 1;
+    set_of(wave >> log_s, g, head0);
+    block_unit = (bx & half) * 4u;
+    if ((uint64_t)g * kGroup + (block_unit << 4) >= n && half) return;  // block-uniform: the token-group ends in the first half
+    s0 = ((uint64_t)g * kGroup + (((wave & mask) + block_unit) << (7 - log_s))) * heads + head0;
+    step = heads << (3 - log_s);
+    lane_slot = (slot >> log_s) * heads + (slot & mask);
+    active = head0 + (slot & mask) < heads;
+    par_head = (wave & ~mask) + (slot & mask);
   } else {
     const uint32_t q = a.by_parts.quotient(bx);
     g0 = q * (uint32_t)a.groups;
     if ((uint64_t)g0 * kGroup >= n) return;  // block-uniform
     gi = a.by_units.quotient(wave);
     block_unit = (bx - q * a.by_parts.d) * (uint32_t)a.waves;
+    if (block_unit != 0) {  // block-uniform: the token-group is too short for this block
+      const uint64_t from = (uint64_t)g0 * (kGroup * heads) + (uint64_t)a.by_period.quotient(block_unit) * (ACC * kTcSpanHeads * a.by_period.d);
+      if (from >= total) return;
+    }
     const uint32_t u = block_unit + wave - gi * a.by_units.d;
     live = u < a.by_units.d;
-    const uint32_t j = a.by_period.quotient(u);
+    const uint32_t j = a.by_period.quotient(u), r = u - j * a.by_period.d;
     step = kTcSpanHeads * a.by_period.d;
-    s0 = (uint64_t)(g0 + gi) * (kGroup * heads) + kTcSpanHeads * (u - j * a.by_period.d) + (uint64_t)j * (ACC * step);
+    s0 = (uint64_t)(g0 + gi) * (kGroup * heads) + kTcSpanHeads * r + (uint64_t)j * (ACC * step);
+    const uint32_t x = kTcSpanHeads * r + slot;  // 8 P is a multiple of H
+    par_head = gi * heads + x - a.by_heads.quotient(x) * heads;
   }
   uint32_t rem = 0;
   if (live && s0 < total) rem = total - s0 < ACC * step ? (uint32_t)(total - s0) : ACC * step;
   rem = (uint32_t)uniform((int32_t)rem);
   s0 = uniform(rem > 0 ? s0 : 0);
   // accesses with something to store
-  const int count = is_v ? (int)((rem + kTcSpanHeads - 1) / kTcSpanHeads) : (int)a.by_period.quotient((rem + step - 1) / kTcSpanHeads);
+  const int count = (int)((is_v ? rem + kTcSpanHeads - 1 : a.by_step.quotient(rem + step - 1) * kTcSpanHeads) / kTcSpanHeads);
 
   const uint8_t* src = static_cast<const uint8_t*>(it.src);
   uint8_t* dst = static_cast<uint8_t*>(it.dst);
   const LayerGeom gin = layer_geom(it.n_tokens, a.c, BI), gout = layer_geom(it.n_tokens, a.c, BO);
-  const HeaderWords hdr = {gload<uintx4>(src), gload<uintx4>(src + 16), gload<uintx4>(src + 32)};
+  const HeaderWords hdr = {sload<uintx4>(src), sload<uintx4>(src + 16), sload<uintx4>(src + 32)};
   const uint8_t* in_layer = src + kHeaderBytes + (size_t)lam * gin.layer_bytes();
   uint8_t* out_layer = dst + kHeaderBytes + (size_t)lam * gout.layer_bytes();
   const uint8_t* in_codes = in_layer + gin.kmeta + (is_v ? gin.codes + gin.vmeta : 0) + s0 * kInBytes;  // wave-uniform
   uint8_t* out_codes = out_layer + gout.kmeta + (is_v ? gout.codes + gout.vmeta : 0) + s0 * kOutBytes;
-  const uint32_t in_sub = sub * (kTcLaneCh * BI / 8), in_lane = slot * kInBytes + in_sub;
-  const uint32_t out_lane = slot * kOutBytes + sub * (kTcLaneCh * BO / 8);
+  const uint32_t in_sub = sub * (kTcLaneCh * BI / 8), in_lane = lane_slot * kInBytes + in_sub;
+  const uint32_t out_lane = lane_slot * kOutBytes + sub * (kTcLaneCh * BO / 8);
 
-  InCodes<BI> cw[ACC];
+  InCodes<BI> cw[kRing];
   // Accesses past the last re-read it; lanes whose slot lies past the end read the access's first slot.  Neither is stored.
-  auto stores = [&](int k) { return slot + (uint32_t)k * step < rem; };
+  // ... of the lane's slot
+  const uint32_t lane_rem = active && rem > lane_slot ? rem - lane_slot : 0u;
+  const int lane_count = (int)(is_v ? (lane_rem + kTcSpanHeads - 1) / kTcSpanHeads : lane_rem == 0 ? 0u : a.by_step.quotient(lane_rem + step - 1));
+  auto stores = [&](int k) { return k < lane_count; };
   auto out_row = [&](int k) { return uniform(out_codes + (size_t)((uint32_t)k * step) * kOutBytes) + out_lane; };
-  auto rows = [&](auto fix_tag, auto&& param_of) {
-    constexpr bool FIX = decltype(fix_tag)::value;
+  auto load_one = [&](InCodes<BI>& in, int i) {
+    const int k = i < count ? i : count - 1;
+    in.load(uniform(in_codes + (size_t)((uint32_t)k * step) * kInBytes) + (stores(k) ? in_lane : in_sub));
+  };
+  auto load = [&](int i) { load_one(cw[i % kRing], i); };
+  // Accesses first .. first + number - 1, in whole batches of the ring: one(i, codes) for each, and what a batch leaves free is
+  // requested again before the next batch is waited for.
+  auto each = [&](auto first_tag, auto number_tag, auto&& one) {
+    constexpr int kFirst = decltype(first_tag)::value, kNumber = decltype(number_tag)::value;
 #pragma unroll
-    for (int i = 0; i < ACC; ++i) {
-      if (i < count) {  // wave-uniform
-        auto param = param_of(i);  // may shuffle across lanes: taken with the whole wave enabled
-        if (stores(i)) transcode_row<DT, BI, BO, FIX>(out_row(i), cw[i], param);
-      }
+    for (int i = kFirst; i < kFirst + kNumber; ++i) {
+      one(i, cw[i % kRing]);
       __builtin_amdgcn_sched_barrier(0);
+      if ((i + 1) % kRefill == 0) {
+#pragma unroll
+        for (int f = 0; f < kRefill; ++f)
+          if (i + 1 - kRefill + kRing + f < ACC) load(i + 1 - kRefill + kRing + f);
+      }
     }
   };
+  auto load_rest = [&] {
+#pragma unroll
+    for (int i = kEarly; i < kRing; ++i) load(i);
+  };
+  using First = std::integral_constant<int, 0>;
+  using All = std::integral_constant<int, ACC>;
   using Yes = std::integral_constant<bool, true>;
   using No = std::integral_constant<bool, false>;
 
   // V metadata: lane l prepares the l-th slot of the unit.  On the table routes every lane requests a word, and the wait for it
   // is on every path (see transcode_block).
   const uint8_t* in_vmeta = in_layer + gin.kmeta + gin.codes + s0 * 4;
-  const bool owns = (uint32_t)lane < rem;
-  uint32_t vm = 0;
+  constexpr int kWords = ACC / kVBatch;
+  auto owns = [&](int b) { return (uint32_t)(b * kVBatch * kTcSpanHeads + lane) < rem && lane < kVBatch * kTcSpanHeads; };
+  uint32_t vm[kWords] = {};
   if (count > 0) {
 #pragma unroll
-    for (int i = 0; i < ACC; ++i) {
-      const int k = i < count ? i : count - 1;
-      cw[i].load(uniform(in_codes + (size_t)((uint32_t)k * step) * kInBytes) + (stores(k) ? in_lane : in_sub));
+    for (int i = 0; i < kEarly; ++i) load(i);
+    if (is_v) {
+#pragma unroll
+      for (int b = 0; b < kWords; ++b) vm[b] = gload<uint32_t>(in_vmeta + (owns(b) ? (b * kWave + lane) * 4 : 0));
     }
-    if (is_v) vm = gload<uint32_t>(in_vmeta + (owns ? lane * 4 : 0));
   }
   // K: pairs of channels, this thread's first and second (all heads of the block's token-groups are 2 pairs a thread at most)
-  const uint32_t pairs = (uint32_t)a.groups * heads * (kGroup / 2), threads = (uint32_t)a.waves * kWave;
+  const uint32_t threads = (uint32_t)a.waves * kWave, pairs = SETS ? threads << half : (uint32_t)a.groups * heads * (kGroup / 2);
   uintx2 km[2] = {};
   bool pact[2] = {false, false};
   size_t pmeta[2] = {0, 0};
@@ -948,9 +649,18 @@ __device__ __forceinline__ void transcode_units(const TranscodeParams& a, const 
 #pragma unroll
     for (int e = 0; e < 2; ++e) {
       const uint32_t pr = threadIdx.x + e * threads;
-      const uint32_t pg = a.by_heads.quotient(pr / (kGroup / 2));
-      pact[e] = pr < pairs && (uint64_t)(g0 + pg) * kGroup < n;
-      pmeta[e] = ((size_t)(g0 + pg) * (uint32_t)a.c + (pr - pg * heads * (kGroup / 2)) * 2) * 4;
+      if (pr >= pairs) break;
+      uint32_t g, first;  // the pair's token-group, its first channel
+      if (SETS) {
+        set_of(pr >> (6 + a.k_log_s), g, first);
+        first = first * kGroup + (pr & ((64u << a.k_log_s) - 1)) * 2;
+      } else {
+        const uint32_t pg = a.by_heads.quotient(pr / (kGroup / 2));
+        g = g0 + pg;
+        first = (pr - pg * heads * (kGroup / 2)) * 2;
+      }
+      pact[e] = (uint64_t)g * kGroup < n && first < (uint32_t)a.c;
+      pmeta[e] = ((size_t)g * (uint32_t)a.c + first) * 4;
       if (pact[e]) km[e] = gload<uintx2>(in_layer + pmeta[e]);
     }
   }
@@ -963,18 +673,20 @@ __device__ __forceinline__ void transcode_units(const TranscodeParams& a, const 
   if (bx == 0 && lay_kv == 0 && threadIdx.x < kHeaderBytes / 4) write_header<DT, BO>(dst, a, n, gout, hdr);
 
   if (!is_v) {
-    const uint32_t cols = (uint32_t)a.groups * heads * kSlotLanes;  // of the parameter tables: [channel mod 16][column]
-    const uint32_t col = gi * heads * kSlotLanes;                    // first column of the wave's token-group
-    uint32_t head0;  // of the lane's slot
-    {
-      const uint32_t x = kTcSpanHeads * (block_unit + wave - gi * a.by_units.d) + slot;  // 8 u + slot: u = r mod P, and 8 P is a multiple of H
-      head0 = x - a.by_heads.quotient(x) * heads;
-    }
-    const uint32_t par_lane = col + head0 * kSlotLanes + sub;
-    TcParams* kpar = reinterpret_cast<TcParams*>(lds);
-    [[maybe_unused]] uint32_t* ktab = reinterpret_cast<uint32_t*>(lds);
-    [[maybe_unused]] float* kquad = reinterpret_cast<float*>(lds + (size_t)cols * kTcLaneCh * sizeof(TcParams));
-    bool fix = false;
+    const uint32_t cols = pairs / (kTcLaneCh / 2);  // of the parameter tables, 16 channels each
+    const uint32_t par_lane = par_head * kSlotLanes + sub;
+    // one plane of LDS for each of the values of a channel: channels 4 m .. 4 m + 3 of all columns, then the next four
+    const uint32_t plane = cols * kTcLaneCh;
+    float* kpar = reinterpret_cast<float*>(lds);      // minima, scales, inverses; or tables
+    [[maybe_unused]] float* kquad = kpar + 3 * plane;  // the 8 -> 2 polynomials
+    auto pair_at = [&](uint32_t pr) { return pr / 2 % 4 * (cols * 4) + pr / 8 * 4 + pr % 2 * 2; };  // channels 2 pr, 2 pr + 1
+    auto lane_values = [&](const float* from, float (&out)[kTcLaneCh]) {
+#pragma unroll
+      for (int m = 0; m < kTcLaneCh / 4; ++m) {
+        const float4 f = *reinterpret_cast<const float4*>(from + m * (cols * 4) + par_lane * 4);
+        out[4 * m] = f.x; out[4 * m + 1] = f.y; out[4 * m + 2] = f.z; out[4 * m + 3] = f.w;
+      }
+    };
     [[maybe_unused]] uint32_t worst = kStandard;
 #pragma unroll
     for (int e = 0; e < 2; ++e) {
@@ -982,24 +694,26 @@ __device__ __forceinline__ void transcode_units(const TranscodeParams& a, const 
       if (pr >= pairs) break;
       const uint32_t meta[2] = {km[e].x, km[e].y};
       uint32_t om[2];
+      float* at = kpar + pair_at(pr);
+      if constexpr (kUseTable<BI, BO>) {
+        const uint32_t t0 = code_table<DT, BI, BO>(meta[0], om[0]), t1 = code_table<DT, BI, BO>(meta[1], om[1]);
+        *reinterpret_cast<uint2*>(at) = make_uint2(t0, t1);
+      } else {
+        const TcParams p[2] = {tc_params<DT, BI, BO>(meta[0], om[0]), tc_params<DT, BI, BO>(meta[1], om[1])};
+        *reinterpret_cast<float2*>(at) = make_float2(p[0].mn, p[1].mn);
+        *reinterpret_cast<float2*>(at + plane) = make_float2(p[0].scale, p[1].scale);
+        *reinterpret_cast<float2*>(at + 2 * plane) = make_float2(p[0].inv, p[1].inv);
+        if constexpr (BI == 8 && BO == 2) {
+          Quad gq[2];
 #pragma unroll
-      for (int h = 0; h < 2; ++h) {
-        const uint32_t lc = pr * 2 + h, at = lc % kTcLaneCh * cols + lc / kTcLaneCh;
-        if constexpr (kUseTable<BI, BO>) {
-          ktab[at] = code_table<DT, BI, BO>(meta[h], om[h]);
-        } else {
-          bool f;
-          const TcParams p = tc_params<DT, BI, BO>(meta[h], om[h], f);
-          fix |= pact[e] && f;
-          kpar[at] = p;
-          if constexpr (BI == 8 && BO == 2) {
-            Quad gq;
-            const uint32_t cls = classify82<DT>(p, gq);
+          for (int h = 0; h < 2; ++h) {
+            const uint32_t cls = classify82<DT>(p[h], gq[h]);
             if (pact[e] && cls > worst) worst = cls;
-            kquad[at] = gq.a;
-            kquad[cols * kTcLaneCh + at] = gq.b;
-            kquad[2 * cols * kTcLaneCh + at] = gq.c;
           }
+          float* quad = kquad + pair_at(pr);
+          *reinterpret_cast<float2*>(quad) = make_float2(gq[0].a, gq[1].a);
+          *reinterpret_cast<float2*>(quad + plane) = make_float2(gq[0].b, gq[1].b);
+          *reinterpret_cast<float2*>(quad + 2 * plane) = make_float2(gq[0].c, gq[1].c);
         }
       }
       if (pact[e] && block_unit == 0) {
@@ -1010,123 +724,109 @@ __device__ __forceinline__ void transcode_units(const TranscodeParams& a, const 
     if constexpr (kUseTable<BI, BO>) {
       __syncthreads();
       if (count == 0) return;  // wave-uniform, after the barrier
-      uint32_t tab[kTcLaneCh];
-#pragma unroll
-      for (int j = 0; j < kTcLaneCh; ++j) tab[j] = ktab[j * cols + par_lane];
-#pragma unroll
-      for (int i = 0; i < ACC; ++i) {
-        if (stores(i)) lookup_row<BI, BO>(out_row(i), cw[i], [&tab](int j) { return tab[j]; });
-        __builtin_amdgcn_sched_barrier(0);
-      }
+      float tab[kTcLaneCh];
+      lane_values(kpar, tab);
+      each(First{}, All{}, [&](int i, const InCodes<BI>& in) {
+        if (stores(i)) lookup_row<BI, BO>(out_row(i), in, [&tab](int j) { return __builtin_bit_cast(uint32_t, tab[j]); });
+      });
       return;
     }
-    // block-wide verdicts through one barrier: every wave leaves its own in LDS
-    const uint32_t mine = (__builtin_amdgcn_ballot_w64(fix) != 0 ? 1u : 0u) |
-                          (__builtin_amdgcn_ballot_w64(worst != kStandard) != 0 ? 2u : 0u) |
-                          (__builtin_amdgcn_ballot_w64(worst == kHard) != 0 ? 4u : 0u);
-    if (lane == 0) kflags[wave] = mine;
+    if constexpr (BI == 8 && BO == 2) {  // block-wide verdicts through the barrier: every wave leaves its own in LDS
+      const uint32_t mine = (__builtin_amdgcn_ballot_w64(worst != kStandard) != 0 ? 1u : 0u) |
+                            (__builtin_amdgcn_ballot_w64(worst == kHard) != 0 ? 2u : 0u);
+      if (lane == 0) kflags[wave] = mine;
+    }
     __syncthreads();
-    uint32_t all = 0;
-    for (int w = 0; w < a.waves; ++w) all |= kflags[w];
-    all = (uint32_t)__builtin_amdgcn_readfirstlane((int)all);
     if (count == 0) return;  // wave-uniform, after the barrier
+    load_rest();
     if constexpr (BI == 8 && BO == 2) {
-      if ((all & 4u) == 0) {  // no hard group in the block: the polynomial route
+      uint32_t all = 0;
+      for (int w = 0; w < a.waves; ++w) all |= kflags[w];
+      all = (uint32_t)__builtin_amdgcn_readfirstlane((int)all);
+      if ((all & 2u) == 0) {  // no hard group in the block: the polynomial route
         auto poly_rows = [&](auto standard_tag) {
           constexpr bool STANDARD = decltype(standard_tag)::value;
-          Quad gq[kTcLaneCh];
-#pragma unroll
-          for (int j = 0; j < kTcLaneCh; ++j) {
-            gq[j].a = STANDARD ? 0.0f : kquad[j * cols + par_lane];
-            gq[j].b = STANDARD ? 0.0f : kquad[(kTcLaneCh + j) * cols + par_lane];
-            gq[j].c = STANDARD ? 0.0f : kquad[(2 * kTcLaneCh + j) * cols + par_lane];
+          float ga[kTcLaneCh] = {}, gb[kTcLaneCh] = {}, gc[kTcLaneCh] = {};
+          if constexpr (!STANDARD) {
+            lane_values(kquad, ga);
+            lane_values(kquad + plane, gb);
+            lane_values(kquad + 2 * plane, gc);
           }
-#pragma unroll
-          for (int i = 0; i < ACC; ++i) {
-            if (stores(i)) poly_row82<STANDARD>(out_row(i), cw[i], [&gq](int j) -> const Quad& { return gq[j]; });
-            __builtin_amdgcn_sched_barrier(0);
-          }
+          each(First{}, All{}, [&](int i, const InCodes<BI>& in) {
+            if (stores(i)) poly_row82<STANDARD>(out_row(i), in, [&](int j) { return Quad{ga[j], gb[j], gc[j]}; });
+          });
         };
-        if ((all & 2u) == 0) poly_rows(Yes{}); else poly_rows(No{});
+        if (all == 0) poly_rows(Yes{}); else poly_rows(No{});
         return;
       }
     }
-    auto k_rows = [&](auto fix_tag) {
-      constexpr bool FIX = decltype(fix_tag)::value;
-      TcParams p[kTcLaneCh];
-#pragma unroll
-      for (int j = 0; j < kTcLaneCh; ++j) {
-        const TcParams& s = kpar[j * cols + par_lane];
-        p[j].mn = s.mn;
-        p[j].scale = s.scale;
-        p[j].inv = s.inv;
-        p[j].top = FIX ? s.top : 0.0f;
-      }
-      rows(fix_tag, [&](int) { return [&p](int j) -> const TcParams& { return p[j]; }; });
-    };
-    if ((all & 1u) != 0) k_rows(Yes{}); else k_rows(No{});
+    float mn[kTcLaneCh], scale[kTcLaneCh], inv[kTcLaneCh];
+    lane_values(kpar, mn);
+    lane_values(kpar + plane, scale);
+    lane_values(kpar + 2 * plane, inv);
+    each(First{}, All{}, [&](int i, const InCodes<BI>& in) {
+      if (stores(i)) transcode_row<DT, BI, BO>(out_row(i), in, [&](int j) { return TcParams{mn[j], scale[j], inv[j], 0.0f}; });
+    });
     return;
   }
 
   if (count == 0) return;  // wave-uniform; V waves never meet at a barrier
   uint8_t* out_vmeta = out_layer + gout.kmeta + gout.codes + s0 * 4;
-  auto finish = [&](uint32_t om) {
-    if (owns) gstore<uint32_t>(out_vmeta + lane * 4, om);
-    // zero the padding that rounds the vmeta section up to 16 bytes: the unit that holds the section's last slot
-    if (s0 + rem == total && lane == 0) {
-      for (size_t o = (size_t)total * 4; o < gout.vmeta; o += 4) gstore<uint32_t>(out_vmeta - s0 * 4 + o, 0u);
+  // zero the padding that rounds the vmeta section up to 16 bytes: the unit that holds the section's last slot
+  if (s0 + rem == total && lane == 0) {
+    for (size_t o = (size_t)total * 4; o < gout.vmeta; o += 4) gstore<uint32_t>(out_vmeta - s0 * 4 + o, 0u);
+  }
+  using Batch = std::integral_constant<int, kVBatch>;
+  auto some = [&](auto b_tag) {  // kVBatch accesses: lane l prepares their l-th slot
+    constexpr int b = decltype(b_tag)::value;
+    using Start = std::integral_constant<int, b * kVBatch>;
+    if (b * kVBatch >= count) return;  // wave-uniform
+    const bool own = owns(b);
+    auto owner = [&](int i) { return (i - b * kVBatch) * kTcSpanHeads + (int)slot; };
+    uint32_t om;
+    auto store_word = [&] {
+      if (own) gstore<uint32_t>(out_vmeta + (b * kWave + lane) * 4, om);
+    };
+    if constexpr (kUseTable<BI, BO>) {
+      const uint32_t mine = code_table<DT, BI, BO>(vm[b], om);
+      store_word();
+      each(Start{}, Batch{}, [&](int i, const InCodes<BI>& in) {
+        if (i >= count) return;  // wave-uniform; the shuffle is taken with the whole wave enabled
+        const uint32_t tab = __shfl(mine, owner(i));
+        if (stores(i)) lookup_row<BI, BO>(out_row(i), in, [tab](int) { return tab; });
+      });
+    } else {
+      const TcParams mine = tc_params<DT, BI, BO>(vm[b], om);
+      store_word();
+      if constexpr (BI == 8 && BO == 2) {
+        Quad gq;
+        uint32_t cls = classify82<DT>(mine, gq);
+        if (!own) cls = kStandard;  // a lane without a group has no say
+        if constexpr (b == 0) load_rest();
+        if (__builtin_amdgcn_ballot_w64(cls == kHard) == 0) {
+          const bool all_standard = __builtin_amdgcn_ballot_w64(cls != kStandard) == 0;
+          each(Start{}, Batch{}, [&](int i, const InCodes<BI>& in) {
+            if (i >= count) return;  // wave-uniform; the shuffles are taken with the whole wave enabled
+            if (all_standard) {
+              if (stores(i)) poly_row82<true>(out_row(i), in, [&gq](int) -> const Quad& { return gq; });
+            } else {
+              const Quad gr = {__shfl(gq.a, owner(i)), __shfl(gq.b, owner(i)), __shfl(gq.c, owner(i))};
+              if (stores(i)) poly_row82<false>(out_row(i), in, [&gr](int) -> const Quad& { return gr; });
+            }
+          });
+          return;
+        }
+      }
+      each(Start{}, Batch{}, [&](int i, const InCodes<BI>& in) {
+        if (i >= count) return;  // wave-uniform; the shuffles are taken with the whole wave enabled
+        const TcParams p = {__shfl(mine.mn, owner(i)), __shfl(mine.scale, owner(i)), __shfl(mine.inv, owner(i)), 0.0f};
+        if (stores(i)) transcode_row<DT, BI, BO>(out_row(i), in, [&p](int) -> const TcParams& { return p; });
+      });
     }
   };
-  uint32_t om;
-  if constexpr (kUseTable<BI, BO>) {
-    const uint32_t mine = code_table<DT, BI, BO>(vm, om);
-    finish(om);
-#pragma unroll
-    for (int i = 0; i < ACC; ++i) {
-      if (i < count) {  // wave-uniform; the shuffle is taken with the whole wave enabled
-        const uint32_t tab = __shfl(mine, i * kTcSpanHeads + (int)slot);
-        if (stores(i)) lookup_row<BI, BO>(out_row(i), cw[i], [tab](int) { return tab; });
-      }
-      __builtin_amdgcn_sched_barrier(0);
-    }
-  } else {
-    bool fix;
-    const TcParams mine = tc_params<DT, BI, BO>(vm, om, fix);
-    finish(om);
-    const bool any_fix = __builtin_amdgcn_ballot_w64(owns && fix) != 0;
-    if constexpr (BI == 8 && BO == 2) {
-      Quad gq;
-      uint32_t cls = classify82<DT>(mine, gq);
-      if (!owns) cls = kStandard;  // a lane without a group has no say
-      if (__builtin_amdgcn_ballot_w64(cls == kHard) == 0) {
-        const bool all_standard = __builtin_amdgcn_ballot_w64(cls != kStandard) == 0;
-#pragma unroll
-        for (int i = 0; i < ACC; ++i) {
-          if (i < count) {  // wave-uniform; the shuffles are taken with the whole wave enabled
-            const int owner = i * kTcSpanHeads + (int)slot;
-            if (all_standard) {
-              if (stores(i)) poly_row82<true>(out_row(i), cw[i], [&gq](int) -> const Quad& { return gq; });
-            } else {
-              const Quad gr = {__shfl(gq.a, owner), __shfl(gq.b, owner), __shfl(gq.c, owner)};
-              if (stores(i)) poly_row82<false>(out_row(i), cw[i], [&gr](int) -> const Quad& { return gr; });
-            }
-          }
-          __builtin_amdgcn_sched_barrier(0);
-        }
-        return;
-      }
-    }
-    auto param_of = [&](int i) {
-      const int owner = i * kTcSpanHeads + (int)slot;
-      TcParams p;
-      p.mn = __shfl(mine.mn, owner);
-      p.scale = __shfl(mine.scale, owner);
-      p.inv = __shfl(mine.inv, owner);
-      p.top = __shfl(mine.top, owner);
-      return [p](int) -> const TcParams& { return p; };
-    };
-    if (any_fix) rows(Yes{}, param_of); else rows(No{}, param_of);
-  }
+  some(First{});
+  if constexpr (kWords > 1) some(std::integral_constant<int, 1>{});
+  static_assert(kWords <= 2, "batches of a unit");
 }
 
 // The job of this block's item, for transcode_units_kernel; its level pair as bits in * 16 + bits out, or -1: nothing to do.
@@ -1160,54 +860,8 @@ __device__ __forceinline__ int load_job(const TranscodeParams& a, kvh_tc_item& i
 
 }  // namespace
 
-// grid = (blocks of a plane, 2 * l, items)
-template <int DT, bool SLOTS>
-__global__ __launch_bounds__(kTcThreads) KVH_TC_OCC void transcode_kernel(TranscodeParams a) {
-  __shared__ TcParams kpar[kTcLaneCh * kWave];  // 16 KiB, [slot][lane]
-  __shared__ float kquad[3 * kTcLaneCh * kWave];  // 12 KiB, [coefficient][slot][lane]: the 8 -> 2 polynomials
-  __shared__ uint32_t kflags[kTcWaves];
-  kvh_tc_item it;
-  // The steps of load_job, written out: through it the compiler needs some 280 instructions more for the layouts below, and
-  // large launches take longer (4 -> 2 bits, 1024 channels: 80 layers x 8,192 tokens 211.5 us as it stands, 214.8 through it,
-  // 32 x 32,768 334.4 and 338.2; 8 -> 4 bits no difference).
-  if (a.items != nullptr) {
-    const uint8_t* p = reinterpret_cast<const uint8_t*>(a.items + blockIdx.z);
-    uintx4 lo = gload<uintx4>(p), hi = gload<uintx4>(p + 16);
-    it.src = reinterpret_cast<const void*>((uint64_t)lo.x | (uint64_t)lo.y << 32);
-    it.dst = reinterpret_cast<void*>((uint64_t)lo.z | (uint64_t)lo.w << 32);
-    it.n_tokens = (int32_t)hi.x;
-    it.level_in = (int32_t)hi.y;
-    it.level_out = (int32_t)hi.z;
-    it.reserved = 0;
-  } else {
-    it = a.one;
-  }
-  it.src = uniform(it.src);
-  it.dst = uniform(it.dst);
-  it.n_tokens = uniform(it.n_tokens);
-  it.level_in = uniform(it.level_in);
-  it.level_out = uniform(it.level_out);
-  const int bx = blockIdx.x, lay_kv = blockIdx.y;
-  if (it.n_tokens < 1) return;  // block-uniform
-  const int bi = level_bits(it.level_in), bo = level_bits(it.level_out);
-  // refused: a level out of range, the raw level (no codes to transcode), more tokens than the grid covers
-  if (bi < 0 || bo < 0 || bi > 8 || bo > 8 || it.n_tokens > a.max_tokens) {
-    if (a.status != nullptr && threadIdx.x == 0) a.status[blockIdx.z] = KVH_DEV_HEADER_MISMATCH;
-    return;
-  }
-#define KVH_TC_CASE(BI, BO) \
-  case BI * 16 + BO: transcode_block<DT, BI, BO, SLOTS>(a, it, blockIdx.z, lay_kv, bx, kpar, kquad, kflags); break;
-  switch (bi * 16 + bo) {
-    KVH_TC_CASE(8, 8) KVH_TC_CASE(8, 4) KVH_TC_CASE(8, 2)
-    KVH_TC_CASE(4, 8) KVH_TC_CASE(4, 4) KVH_TC_CASE(4, 2)
-    KVH_TC_CASE(2, 8) KVH_TC_CASE(2, 4) KVH_TC_CASE(2, 2)
-    default: break;
-  }
-#undef KVH_TC_CASE
-}
-
 // grid = (blocks of a plane, 2 * l, items); a block is `waves` units
-template <int DT, int ACC>
+template <int DT, int ACC, bool SETS>
 __global__ __launch_bounds__(kTcThreads) KVH_TC_OCC void transcode_units_kernel(TranscodeParams a) {
   extern __shared__ __align__(16) uint8_t units_lds[];  // K parameters, then the 8 -> 2 polynomials; kUnitsHeadBytes a head
   __shared__ uint32_t kflags[kTcWaves];
@@ -1215,7 +869,7 @@ __global__ __launch_bounds__(kTcThreads) KVH_TC_OCC void transcode_units_kernel(
   const int pair = load_job(a, it);
   if (pair < 0) return;  // block-uniform
 #define KVH_TC_CASE(BI, BO) \
-  case BI * 16 + BO: transcode_units<DT, BI, BO, ACC>(a, it, blockIdx.z, blockIdx.y, blockIdx.x, units_lds, kflags); break;
+  case BI * 16 + BO: transcode_units<DT, BI, BO, ACC, SETS>(a, it, blockIdx.z, blockIdx.y, blockIdx.x, units_lds, kflags); break;
   switch (pair) {
     KVH_TC_CASE(8, 8) KVH_TC_CASE(8, 4) KVH_TC_CASE(8, 2)
     KVH_TC_CASE(4, 8) KVH_TC_CASE(4, 4) KVH_TC_CASE(4, 2)
@@ -1227,35 +881,31 @@ __global__ __launch_bounds__(kTcThreads) KVH_TC_OCC void transcode_units_kernel(
 
 int launch_transcode(const TranscodeParams& a, int dt, int n_items, int max_tokens, bool narrow, hipStream_t stream) {
   const int heads = a.c / kGroup;
+  const TcStream plan = transcode_stream_plan(heads, a.l, n_items, max_tokens);
+  const TcUnits units = transcode_units_plan(heads, a.l, n_items, max_tokens, narrow);
+  const bool small = units.accesses != 0, sets = !small && plan.log_s >= 0;
+  const TcUnits u = small ? units : plan.in;
+  if (!grid_fits(u.blocks, 1, u.waves)) return KVH_E_HIP;
   TranscodeParams b = a;
-  b.by_heads = Divisor((uint32_t)heads);
-  const TcUnits u = transcode_units_plan(heads, a.l, n_items, max_tokens, narrow);
-  if (u.accesses != 0) {
-    b.max_tokens = max_tokens;
-    b.waves = u.waves;
-    b.groups = u.groups;
-    b.by_units = Divisor((uint32_t)u.units);
-    b.by_parts = Divisor((uint32_t)u.parts);
-    b.by_period = Divisor((uint32_t)u.period);
-    auto pick = [&](auto dt_tag) {
-      constexpr int D = decltype(dt_tag)::value;
-      return u.accesses == 4 ? transcode_units_kernel<D, 4> : transcode_units_kernel<D, 8>;
-    };
-    auto kernel = dt == KVH_F16 ? pick(std::integral_constant<int, KVH_F16>{}) : pick(std::integral_constant<int, KVH_BF16>{});
-    const dim3 grid((unsigned)u.blocks, (unsigned)(2 * a.l), (unsigned)n_items);
-    launch_kernel(kernel, grid, dim3((unsigned)(u.waves * kWave)), (unsigned)(u.groups * heads) * kUnitsHeadBytes, stream, b);
-    KVH_HIP_CHECK_LAUNCH();
-    return KVH_OK;
-  }
-  const TcPlan plan = transcode_plan(heads, a.l, n_items, max_tokens);
-  if (!grid_fits(plan.blocks, 1, kTcWaves)) return KVH_E_HIP;
   b.max_tokens = max_tokens;
+  b.waves = u.waves;
+  b.groups = u.groups;
   b.k_log_s = plan.log_s;
-  b.by_sets = Divisor((uint32_t)plan.sets);
-  const dim3 grid((unsigned)plan.blocks, (unsigned)(2 * a.l), (unsigned)n_items);
-  auto kernel = dt == KVH_F16 ? (plan.slots ? transcode_kernel<KVH_F16, true> : transcode_kernel<KVH_F16, false>)
-                              : (plan.slots ? transcode_kernel<KVH_BF16, true> : transcode_kernel<KVH_BF16, false>);
-  launch_kernel(kernel, grid, dim3(kTcThreads), 0u, stream, b);
+  b.by_heads = Divisor((uint32_t)heads);
+  b.by_sets = Divisor((uint32_t)(sets ? (heads + (1 << plan.log_s) - 1) >> plan.log_s : 1));
+  b.by_units = Divisor((uint32_t)u.units);
+  b.by_parts = Divisor((uint32_t)u.parts);
+  b.by_period = Divisor((uint32_t)u.period);
+  b.by_step = Divisor((uint32_t)(sets ? heads << (3 - plan.log_s) : kTcSpanHeads * u.period));
+  const unsigned lds = (unsigned)(sets ? std::max(u.waves, 1 << plan.log_s) : u.groups * heads) * kUnitsHeadBytes;
+  const dim3 grid((unsigned)u.blocks, (unsigned)(2 * a.l), (unsigned)n_items);
+  auto pick = [&](auto dt_tag) {
+    constexpr int D = decltype(dt_tag)::value;
+    return sets ? transcode_units_kernel<D, 16, true> : u.accesses == 4 ? transcode_units_kernel<D, 4, false>
+                : u.accesses == 8 ? transcode_units_kernel<D, 8, false> : transcode_units_kernel<D, 16, false>;
+  };
+  auto kernel = dt == KVH_F16 ? pick(std::integral_constant<int, KVH_F16>{}) : pick(std::integral_constant<int, KVH_BF16>{});
+  launch_kernel(kernel, grid, dim3((unsigned)(u.waves * kWave)), lds, stream, b);
   KVH_HIP_CHECK_LAUNCH();
   return KVH_OK;
 }
