@@ -95,6 +95,10 @@ __device__ __forceinline__ void gstore16(uint16_t* p, const uint4& v) {
 // Six shapes from 1 to 16 GiB (8K to 128K tokens, 32 and 80 layers), % of HBM peak, plain / device-scope stores, each
 // with the better K-parameter form: 8 bits 70.8 / 73.4 on average (better on every shape, +1.3 to +3.3), 4 bits
 // 73.4 / 76.8 (every shape, +0.9 to +6.2), 2 bits 73.9 / 74.0 (from -5 on the 8K shape to +3).
+// Small pages at 2 bits are an exception (small_pages): rows that go into pages of up to 32 KiB, such as 16 tokens of 1024 channels, in random
+// order.  Plain / device-scope stores there, in launches of 500 MiB to 4 GiB of rows, 5.04 / 5.3 TB/s on 32 x 8,192 (244 and 230 us),
+// 1.03 to 1.08 times as fast on eight shapes (64 KiB pages 0.95 to 1.1, contiguous 0.95 to 1.06), in smaller launches of spans 0.93 to 0.99;
+// slots into pages of any size, and small launches, 1.00 to 1.06 on twelve shapes (40 x 8,000 x 640: 192 and 181 us).
 template <int BITS>
 constexpr bool kStoreThrough = KVH_DEC_THROUGH < 0 ? (BITS == 8 || BITS == 4) : KVH_DEC_THROUGH != 0;
 
@@ -313,7 +317,7 @@ __device__ __forceinline__ void decode_unit(const DecodeParams& a, const kvh_ite
 
   // the row loop of one unit, instantiated with and without the explicit top-code rule
   int32_t rows[kDecRows];
-  auto run = [&](int t0, auto fix_tag, auto&& param_of) {
+  auto run_rows = [&](int t0, auto fix_tag, auto&& param_of, auto through_tag) {
     constexpr bool FIX = decltype(fix_tag)::value;
 #pragma unroll
     for (int i = 0; i < kDecRows; ++i) {
@@ -326,13 +330,19 @@ __device__ __forceinline__ void decode_unit(const DecodeParams& a, const kvh_ite
           // of its own, and the values of the next row are not computed ahead of it.  Without it the 2-bit level takes
           // 208 instead of 199 us on the 32 x 8192 x 1024 shape and 855 instead of 833 on 32 x 32768 x 1024; no difference
           // at 8 and 4 bits.  A scheduling barrier after the store does not have the effect.
-          if (ch[s] < (uint32_t)c) gstore16<kStoreThrough<BITS>>(row + ch[s], out);
+          if (ch[s] < (uint32_t)c) gstore16<decltype(through_tag)::value>(row + ch[s], out);
         }
       }
     }
   };
   using Yes = std::integral_constant<bool, true>;
   using No = std::integral_constant<bool, false>;
+  auto run = [&](int t0, auto fix_tag, auto&& param_of) {
+    if constexpr (BITS == 2 && !kStoreThrough<BITS>) {
+      if (a.small_pages != 0 && it.page_table != nullptr) return run_rows(t0, fix_tag, param_of, Yes{});  // wave-uniform
+    }
+    run_rows(t0, fix_tag, param_of, std::integral_constant<bool, kStoreThrough<BITS>>{});
+  };
 
   if (!is_v) {
     // Every thread of the block prepares its channels of the span; the three arrays (minimum, scale,
@@ -601,14 +611,20 @@ __device__ __forceinline__ void decode_slots(const DecodeParams& a, const kvh_it
   const int64_t own_off = valid ? (int64_t)row_of(ref, a.block_tokens) * a.token_stride + head * (uint32_t)kGroup : -1;
   const int off_lo = (int)(uint32_t)(uint64_t)own_off, off_hi = (int)(own_off >> 32);
   uint16_t* dst = (is_v ? a.v : a.k) + (int64_t)lam * a.layer_stride + sub * kLaneCh;
-  auto store_all = [&](auto&& value_of) {
+  auto store_slots = [&](auto&& value_of, auto through_tag) {
     auto one = [&](auto idx) {
       constexpr int i = decltype(idx)::value;
       const int lo = row_bcast<i>(off_lo), hi = row_bcast<i>(off_hi);
       const uint4 out = value_of(idx);
-      if (hi >= 0) gstore16<kSlotStoreThrough<BITS>>(dst + ((int64_t)((uint64_t)(uint32_t)hi << 32 | (uint32_t)lo)), out);
+      if (hi >= 0) gstore16<decltype(through_tag)::value>(dst + ((int64_t)((uint64_t)(uint32_t)hi << 32 | (uint32_t)lo)), out);
     };
     for_each_index(one, std::make_integer_sequence<int, kAccesses>{});
+  };
+  auto store_all = [&](auto&& value_of) {
+    if constexpr (BITS == 2 && !kSlotStoreThrough<BITS>) {
+      if (it.page_table != nullptr) return store_slots(value_of, std::true_type{});  // wave-uniform
+    }
+    store_slots(value_of, std::integral_constant<bool, kSlotStoreThrough<BITS>>{});
   };
   if constexpr (BITS == 16) {
     store_all([&](auto idx) {
@@ -794,6 +810,7 @@ int launch_decode(const DecodeParams& a, int dt, int n_items, int max_tokens, bo
   b.plane_blocks = (int)plan.blocks;
   b.waves = plan.waves;
   b.plane_group = plan.plane_group;
+  b.small_pages = (int64_t)a.block_tokens * a.c * 2 <= (32 << 10) && 4.0 * a.l * a.c * max_tokens * n_items > 550.0 * (1 << 20);
   const dim3 grid((unsigned)(plan.blocks * b.plane_group), (unsigned)n_items, (unsigned)((2 * a.l + b.plane_group - 1) / b.plane_group));
   b.by_group = Divisor((uint32_t)b.plane_group);
   b.by_heads = Divisor((uint32_t)heads);
