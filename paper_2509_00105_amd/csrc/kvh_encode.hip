@@ -11,6 +11,8 @@
 // Rows that leave lanes of the last strip idle, and small launches, take units of (row, head) slots, see encode_k_slots and encode_row_slots.
 // Quantised codes are produced with the packed float->u8 convert, which rounds to nearest even
 // and inserts the byte in one instruction; narrow codes are routed to their byte at that point.
+#include <type_traits>
+
 #include "kvh_common.hpp"
 #include "kvh_plan.hpp"
 
@@ -54,8 +56,12 @@ __device__ __forceinline__ T gload_rows(const void* p) {
   return *reinterpret_cast<const __attribute__((address_space(1))) T*>(reinterpret_cast<uintptr_t>(p));
 #endif
 }
-template <typename T>
+template <bool PLAIN = false, typename T>
 __device__ __forceinline__ void gstore_codes(void* p, T v) {
+  if constexpr (PLAIN) {
+    gstore<T>(p, v);
+    return;
+  }
 #if KVH_ENC_NT
   __builtin_nontemporal_store(v, reinterpret_cast<__attribute__((address_space(1))) T*>(reinterpret_cast<uintptr_t>(p)));
 #else
@@ -115,9 +121,7 @@ __device__ __forceinline__ uint32_t codes2(float t0, float t1) {
 // (For finite input every code is <= L, so fields never overlap.)
 template <int BITS, bool PLAIN = false, typename P>
 __device__ __forceinline__ void quantise_store8(uint8_t* p, const float (&x)[8], P&& param) {
-  auto store = [](uint8_t* q, auto v) {
-    if constexpr (PLAIN) gstore<decltype(v)>(q, v); else gstore_codes<decltype(v)>(q, v);
-  };
+  auto store = [](uint8_t* q, auto v) { gstore_codes<PLAIN>(q, v); };
   float t[8];
 #pragma unroll
   for (int j = 0; j < 8; ++j) t[j] = position(x[j], param(j).x, param(j).y);
@@ -205,7 +209,7 @@ __device__ __forceinline__ void channel_params(float (&mn)[8], float (&mx)[8], u
   }
 }
 
-template <int DT, int BITS>
+template <int DT, int BITS, bool PLAIN>
 __device__ __forceinline__ void encode_k_block(const EncodeParams& a, const kvh_enc_item& it, uint8_t* layer_base,
                                                const LayerGeom& geo, int lam, int g, int strip, float* red,
                                                int split, int64_t jump) {
@@ -279,7 +283,7 @@ __device__ __forceinline__ void encode_k_block(const EncodeParams& a, const kvh_
     if (t < n) {  // wave-uniform
       float x[8];
       unpack8<DT>(d[i], x);
-      quantise_store8<BITS>(uniform(codes + (size_t)t * geo.row_bytes) + lane_code_off, x, [&](int j) { return par[j]; });
+      quantise_store8<BITS, PLAIN>(uniform(codes + (size_t)t * geo.row_bytes) + lane_code_off, x, [&](int j) { return par[j]; });
     }
     __builtin_amdgcn_sched_barrier(0);
   }
@@ -287,7 +291,7 @@ __device__ __forceinline__ void encode_k_block(const EncodeParams& a, const kvh_
 
 // Raw level: the rows of the block's tile and strip go into the blob as they are (K rows, then V rows, per layer).  Rows of
 // whole strips have a form without idle lanes (a test per store: 2 % slower on average, up to 10 on small launches).
-template <int DT, bool IDLE>
+template <int DT, bool IDLE, bool PLAIN>
 __device__ __forceinline__ void encode_raw_block(const EncodeParams& a, const kvh_enc_item& it, uint8_t* layer_base,
                                                  const LayerGeom& geo, int lam, bool is_v, int tile, int strip, int split,
                                                  int64_t jump) {
@@ -311,7 +315,7 @@ __device__ __forceinline__ void encode_raw_block(const EncodeParams& a, const kv
 #pragma unroll
   for (int i = 0; i < kEncRows; ++i) {
     const int t = t_first + i;
-    if (t < n && active) gstore_codes<uintx4>(uniform(rows + (size_t)t * geo.row_bytes) + (uint32_t)ch0 * 2u, d[i]);
+    if (t < n && active) gstore_codes<PLAIN, uintx4>(uniform(rows + (size_t)t * geo.row_bytes) + (uint32_t)ch0 * 2u, d[i]);
   }
 }
 
@@ -430,7 +434,7 @@ __device__ __forceinline__ uint32_t batch_stats(const uintx4 (&d)[kEncRows], int
   return lo | hi << 16;
 }
 
-template <int DT, int BITS>
+template <int DT, int BITS, bool PLAIN>
 __device__ __forceinline__ void encode_v_block(const EncodeParams& a, const kvh_enc_item& it, uint8_t* layer_base,
                                                const LayerGeom& geo, int lam, int tile, int strip, int split,
                                                int64_t jump) {
@@ -486,7 +490,7 @@ __device__ __forceinline__ void encode_v_block(const EncodeParams& a, const kvh_
             asm volatile("" : "+v"(w));
             float x[8];
             unpack8<DT>(w, x);
-            quantise_store8<BITS>(code_row + lane_code_off, x, [&](int) { return par; });
+            quantise_store8<BITS, PLAIN>(code_row + lane_code_off, x, [&](int) { return par; });
           }
         }
       };
@@ -512,7 +516,7 @@ __device__ __forceinline__ void encode_v_block(const EncodeParams& a, const kvh_
 // Consecutive slots are consecutive rows or heads, so that an access covers whole cache lines of codes where it can.
 // 80 layers x 8192 tokens x 128 channels in 512-token items, 2 bits: 168 -> 68 us (2.3 -> 5.6 TB/s); 20 x 3001 x 640 fp16
 // in one item, 4 bits: 47.2 -> 39.2 us, in blocks of 4 waves 37.3; 32 x 12000 x 256, 4 bits: 107 -> 83 us.  Bound by memory now, as strips are.
-template <int DT, int BITS, bool PLAIN = false>
+template <int DT, int BITS, bool PLAIN>
 __device__ __forceinline__ void encode_k_slots(const EncodeParams& a, const kvh_enc_item& it, uint8_t* layer_base,
                                                const LayerGeom& geo, int lam, int bx, float* red, int split, int64_t jump) {
   const int lane = threadIdx.x & (kWave - 1);
@@ -589,7 +593,7 @@ __device__ __forceinline__ void encode_k_slots(const EncodeParams& a, const kvh_
 }
 
 // Slots in memory order: V at the quantised levels, both tensors at the raw level (BITS = 16).
-template <int DT, int BITS>
+template <int DT, int BITS, bool PLAIN>
 __device__ __forceinline__ void encode_row_slots(const EncodeParams& a, const kvh_enc_item& it, uint8_t* layer_base,
                                                  const LayerGeom& geo, int lam, bool is_v, int bx, int split, int64_t jump) {
   constexpr uint32_t kGroupBytes = kGroup * BITS / 8;
@@ -629,7 +633,7 @@ __device__ __forceinline__ void encode_row_slots(const EncodeParams& a, const kv
     uint8_t* rows = layer_base + (is_v ? geo.codes : 0) + first * kGroupBytes + quad * kGroupBytes + sub * (kLaneCh * 2u);
 #pragma unroll
     for (uint32_t i = 0; i < kEncRows; ++i)
-      if (4 * i + quad < left) gstore_codes<uintx4>(rows + i * (4 * kGroupBytes), d[i]);
+      if (4 * i + quad < left) gstore_codes<PLAIN, uintx4>(rows + i * (4 * kGroupBytes), d[i]);
   } else {
     uint8_t* vmeta = layer_base + geo.kmeta + geo.codes;
     uint8_t* codes = vmeta + geo.vmeta + first * kGroupBytes + quad * kGroupBytes + sub * BITS;
@@ -651,7 +655,7 @@ __device__ __forceinline__ void encode_row_slots(const EncodeParams& a, const kv
           asm volatile("" : "+v"(w));  // unpacked a second time, see encode_v_block
           float x[8];
           unpack8<DT>(w, x);
-          quantise_store8<BITS>(codes + i * (4 * kGroupBytes), x, [&](int) { return par; });
+          quantise_store8<BITS, PLAIN>(codes + i * (4 * kGroupBytes), x, [&](int) { return par; });
         }
       };
       for_each_index(row, std::make_integer_sequence<int, R>{});
@@ -664,8 +668,15 @@ __device__ __forceinline__ void encode_row_slots(const EncodeParams& a, const kv
   }
 }
 
+// Stores of the codes.  A blob is written once and read later, if at all on this device, so that its codes are stored non-temporally: on
+// buffers in no cache 1.01 to 1.15 times as fast as plain stores.  A blob of the token-dropping calls is the exception (KEEP): what is kept of an entry goes
+// back into the cache from it, compacted, and as long as it fits the 256 MiB of the memory-side cache the decoder finds it there.  encode_kept with
+// decode_kept, 13 entries of 2 to 50 MB of rows up to 2 GB, buffers in no cache, at 8 / 4 / 2 bits and raw: blobs of up to 281 MB 1.02 to 1.16 / 1.03 to 1.10 /
+// 1.01 to 1.09 / 1.07 to 1.20 times as fast (16,000 tokens of 32 x 1024, of which 4,064 are kept, 2 bits: 206.8 -> 192.4 us), 377 MB and more 0.93 to 0.97.
+constexpr size_t kKeepBytes = size_t(272) << 20;
+
 // grid = (blocks of a plane x planes of a group, plane groups, items)
-template <int DT, bool SLOTS>
+template <int DT, bool SLOTS, bool KEEP>
 __global__ __launch_bounds__(kEncThreads) __attribute__((amdgpu_waves_per_eu(4, 4))) void encode_kernel(EncodeParams a) {
   __shared__ float red[2 * kEncWaves * kStripCh];  // 32 KiB
   const int item_idx = blockIdx.z;
@@ -764,10 +775,10 @@ __global__ __launch_bounds__(kEncThreads) __attribute__((amdgpu_waves_per_eu(4, 
   if constexpr (SLOTS) {
     if (is_v || bits == 16) {
       switch (bits) {
-        case 16: encode_row_slots<DT, 16>(a, it, layer_base, geo, lam, is_v, bx, split, jump); break;
-        case 8: encode_row_slots<DT, 8>(a, it, layer_base, geo, lam, true, bx, split, jump); break;
-        case 4: encode_row_slots<DT, 4>(a, it, layer_base, geo, lam, true, bx, split, jump); break;
-        default: encode_row_slots<DT, 2>(a, it, layer_base, geo, lam, true, bx, split, jump); break;
+        case 16: encode_row_slots<DT, 16, KEEP>(a, it, layer_base, geo, lam, is_v, bx, split, jump); break;
+        case 8: encode_row_slots<DT, 8, KEEP>(a, it, layer_base, geo, lam, true, bx, split, jump); break;
+        case 4: encode_row_slots<DT, 4, KEEP>(a, it, layer_base, geo, lam, true, bx, split, jump); break;
+        default: encode_row_slots<DT, 2, KEEP>(a, it, layer_base, geo, lam, true, bx, split, jump); break;
       }
       return;
     }
@@ -776,15 +787,15 @@ __global__ __launch_bounds__(kEncThreads) __attribute__((amdgpu_waves_per_eu(4, 
       const int heads = a.c / kGroup, log_s = (heads & 1) ? 0 : 1;
       if ((int64_t)a.by_sets.quotient((uint32_t)bx * ((uint32_t)a.waves >> (1 + log_s))) * kGroup >= it.n_tokens) return;
       switch (bits) {
-        case 8: encode_k_slots<DT, 8>(a, it, layer_base, geo, lam, bx, red, split, jump); break;
-        case 4: encode_k_slots<DT, 4>(a, it, layer_base, geo, lam, bx, red, split, jump); break;
+        case 8: encode_k_slots<DT, 8, KEEP>(a, it, layer_base, geo, lam, bx, red, split, jump); break;
+        case 4: encode_k_slots<DT, 4, KEEP>(a, it, layer_base, geo, lam, bx, red, split, jump); break;
         default:
           // Single heads out of a longer row leave gaps between the 32-byte pieces an access writes, which other waves fill;
           // ordinary stores let the L2 put them together (5 heads: 310 -> 303 us in 512-token items of 32 x 16384 tokens,
           // 233 -> 209 in one item of 12,000; with 1 head, where there are no gaps, and with 6, 1 to 7 % slower; in blocks of 4 waves,
           // 700 to 6,000 tokens of 4 to 80 layers, 3 heads 0.97 to 1.03 times as fast, 5 to 13 heads 1.00 to 1.1).
           if (a.k_slots == 2) encode_k_slots<DT, 2, true>(a, it, layer_base, geo, lam, bx, red, split, jump);
-          else encode_k_slots<DT, 2>(a, it, layer_base, geo, lam, bx, red, split, jump);
+          else encode_k_slots<DT, 2, KEEP>(a, it, layer_base, geo, lam, bx, red, split, jump);
           break;
       }
       return;
@@ -793,23 +804,23 @@ __global__ __launch_bounds__(kEncThreads) __attribute__((amdgpu_waves_per_eu(4, 
   }
   if constexpr (!SLOTS) {
     if (bits == 16) {
-      if (a.c % kStripCh == 0) encode_raw_block<DT, false>(a, it, layer_base, geo, lam, is_v, tile, strip, split, jump);
-      else encode_raw_block<DT, true>(a, it, layer_base, geo, lam, is_v, tile, strip, split, jump);
+      if (a.c % kStripCh == 0) encode_raw_block<DT, false, KEEP>(a, it, layer_base, geo, lam, is_v, tile, strip, split, jump);
+      else encode_raw_block<DT, true, KEEP>(a, it, layer_base, geo, lam, is_v, tile, strip, split, jump);
       return;
     }
     if (is_v) {
       switch (bits) {
-        case 8: encode_v_block<DT, 8>(a, it, layer_base, geo, lam, tile, strip, split, jump); break;
-        case 4: encode_v_block<DT, 4>(a, it, layer_base, geo, lam, tile, strip, split, jump); break;
-        default: encode_v_block<DT, 2>(a, it, layer_base, geo, lam, tile, strip, split, jump); break;
+        case 8: encode_v_block<DT, 8, KEEP>(a, it, layer_base, geo, lam, tile, strip, split, jump); break;
+        case 4: encode_v_block<DT, 4, KEEP>(a, it, layer_base, geo, lam, tile, strip, split, jump); break;
+        default: encode_v_block<DT, 2, KEEP>(a, it, layer_base, geo, lam, tile, strip, split, jump); break;
       }
       return;
     }
   }
   switch (bits) {
-    case 8: encode_k_block<DT, 8>(a, it, layer_base, geo, lam, tile, strip, red, split, jump); break;
-    case 4: encode_k_block<DT, 4>(a, it, layer_base, geo, lam, tile, strip, red, split, jump); break;
-    default: encode_k_block<DT, 2>(a, it, layer_base, geo, lam, tile, strip, red, split, jump); break;
+    case 8: encode_k_block<DT, 8, KEEP>(a, it, layer_base, geo, lam, tile, strip, red, split, jump); break;
+    case 4: encode_k_block<DT, 4, KEEP>(a, it, layer_base, geo, lam, tile, strip, red, split, jump); break;
+    default: encode_k_block<DT, 2, KEEP>(a, it, layer_base, geo, lam, tile, strip, red, split, jump); break;
   }
 }
 
@@ -843,9 +854,18 @@ int launch_encode(const EncodeParams& a, int dt, int n_items, int max_tokens, bo
   b.by_heads = Divisor((uint32_t)heads);
   b.by_sets = Divisor((uint32_t)((heads & 1) ? heads : heads / 2));
   const unsigned n_groups = (unsigned)((2 * a.l + b.plane_group - 1) / b.plane_group);
+  const bool one_dropped = a.items == nullptr && a.kept_items == nullptr && a.n_inline == 0 && (a.hdr_orig_tokens | a.hdr_sink | a.hdr_window) != 0;
+  const bool keep = one_dropped && kvh_blob_size(a.l, a.one.n_tokens, a.c, a.one.level) <= kKeepBytes;
   const dim3 grid((unsigned)(gx * b.plane_group), n_groups, (unsigned)n_items);
-  auto kernel = dt == KVH_F16 ? (plan.slots ? encode_kernel<KVH_F16, true> : encode_kernel<KVH_F16, false>)
-                              : (plan.slots ? encode_kernel<KVH_BF16, true> : encode_kernel<KVH_BF16, false>);
+  auto pick = [&](auto dt_tag, auto keep_tag) {
+    constexpr int D = decltype(dt_tag)::value;
+    constexpr bool KEEP = decltype(keep_tag)::value;
+    return plan.slots ? encode_kernel<D, true, KEEP> : encode_kernel<D, false, KEEP>;
+  };
+  using F16 = std::integral_constant<int, KVH_F16>;
+  using BF16 = std::integral_constant<int, KVH_BF16>;
+  auto kernel = keep ? (dt == KVH_F16 ? pick(F16{}, std::true_type{}) : pick(BF16{}, std::true_type{}))
+                     : (dt == KVH_F16 ? pick(F16{}, std::false_type{}) : pick(BF16{}, std::false_type{}));
   launch_kernel(kernel, grid, dim3((unsigned)(plan.waves * kWave)), 0u, stream, b);
   KVH_HIP_CHECK_LAUNCH();
   return KVH_OK;
