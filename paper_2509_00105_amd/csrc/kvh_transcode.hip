@@ -499,12 +499,12 @@ __device__ __forceinline__ void write_header(uint8_t* dst, const TranscodeParams
 // What bounds it.  Small launches (ACC = 4 and 8): the chain of trips to memory, so that everything a unit reads is requested before
 // anything of it is used (8 -> 4 bits bf16: 3 x 309 tokens of 8 heads 11.8 -> 5.8 us; an empty launch is 3.9).  Large ones
 // (ACC = 16): memory, and beside it 6 to 7 operations an element, 0.6 of what the vector units do in the time memory takes, so that one
-// has to run under the other.  8-bit codes come through a ring of 8 accesses: 4 are used while 4 are on their way, and those that follow
+// has to run under the other.  8-bit codes come through a ring of 8 accesses (or 6): 4 are used while 4 are on their way, and those that follow
 // are requested before the next stores are issued (a wait for a load is a wait for every store before it as well).  No register is spilled on the way of
-// a row but one access of 8 -> 2 bits, and blocks are 3 or 4 waves where that is to be had: a block takes the place of one that has ended,
+// a row but one access of 8 -> 2 bits in fp16, and blocks are 3 or 4 waves where that is to be had: a block takes the place of one that has ended,
 // and its start is hidden by the others of the compute unit, four and not one.  Before, a wave took 4 accesses, waited for its stores, and took the
 // next 4, in blocks of 8 waves over 8 heads (or single heads, pairs and fours), with lanes idle for 3, 5, 6, 7, 11 and from 13 heads on.
-//   32 layers x 8,192 tokens in 256-token items, 8 heads bf16, 8 -> 4 / 8 -> 2 / 4 -> 2 bits: 153.7 / 140.8 / 88.5 -> 139.5 / 135.7 / 77.5 us (5.9 TB/s; without
+//   32 layers x 8,192 tokens in 256-token items, 8 heads bf16, 8 -> 4 / 8 -> 2 / 4 -> 2 bits: 153.7 / 140.8 / 88.5 -> 142 / 130.7 / 77.5 us (5.9 TB/s; without
 //   any arithmetic the same traffic takes 136 us at 8 -> 4 bits); 16 heads, 60 x 6,250: 510 / 474 / 291 -> 451 / 398 / 247; 5 heads, 7 x 20,000:
 //   75.2 / 73.1 / 43.6 -> 56.0 / 56.7 / 33.3; 10 heads, 20 x 8,000: 129 / 118 / 74 -> 119 / 106 / 67; 4 heads, 20 x 9,000: 58.2 / 54.6 / 35.5 -> 51.9 / 48.3 / 31.3.
 constexpr unsigned kUnitsHeadBytes = kGroup * 6 * sizeof(float);  // LDS for the parameters of a head: three values of a channel, and the 8 -> 2 polynomial  // LDS for the parameters of one head
@@ -512,7 +512,10 @@ template <int DT, int BI, int BO, int ACC, bool SETS>
 __device__ __forceinline__ void transcode_units(const TranscodeParams& a, const kvh_tc_item& it, int item_idx, int lay_kv,
                                                 uint32_t bx, uint8_t* lds, uint32_t* kflags) {
   // Accesses whose codes a wave holds, and how many are requested again at a time as they are used up.
-  constexpr int kRing = BI == 8 && ACC > kTcBatch ? kTcBatch : ACC, kRefill = kRing < ACC ? kRing / 2 : ACC;
+  // From 8 to 2 bits bf16 groups mostly need the fitted polynomial, whose coefficients leave registers for 6 (8 spilled one: 32 x 8,192 x 1024 135.7 -> 130.7 us);
+  // fp16 groups are standard ones and run best with 8 (115.6 us, 120.6 with 6).
+  constexpr bool kTight = DT == KVH_BF16 && BO == 2;
+  constexpr int kRing = BI == 8 && ACC > kTcBatch ? (kTight ? 6 : kTcBatch) : ACC, kRefill = kRing < ACC ? (kTight ? 2 : kRing / 2) : ACC;
   // The search for the steps of an 8 -> 2 bit group needs registers of its own: half of the ring is requested behind it.
   constexpr int kEarly = BI == 8 && BO == 2 && kRing < ACC ? kRing / 2 : kRing;
   constexpr int kVBatch = ACC < kTcBatch ? ACC : kTcBatch;  // accesses whose V groups the lanes prepare at a time, one each
