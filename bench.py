@@ -716,7 +716,7 @@ def main():
         avg = sum(durs) / len(durs)
         ba, bb = kvh.level_bits(a), kvh.level_bits(b)
         moved = blobs[a].numel() + tc_out[(a, b)].numel()
-        transcode.append({"kernel": "transcode_kernel", "bits_in": ba, "bits_out": bb, "avg_ms": avg, "min_ms": min(durs),
+        transcode.append({"kernel": "transcode_units_kernel", "bits_in": ba, "bits_out": bb, "avg_ms": avg, "min_ms": min(durs),
                           "algorithmic_bytes": moved, "hbm_frac": moved / avg / 1e6 / HBM_PEAK_GBPS,
                           "traffic": MEASURED_TRAFFIC_BYTES.get(("transcode", ba, bb)) if args.workload == "llama3_8b_8k" else None,
                           "elements_per_s": 2 * l * N * c / avg * 1e3,
