@@ -668,14 +668,7 @@ __device__ __forceinline__ void encode_row_slots(const EncodeParams& a, const kv
   }
 }
 
-// Stores of the codes.  A blob is written once and read later, if at all on this device, so that its codes are stored non-temporally: on
-// buffers in no cache 1.01 to 1.15 times as fast as plain stores.  A blob of the token-dropping calls is the exception (KEEP): what is kept of an entry goes
-// back into the cache from it, compacted, and as long as it fits the 256 MiB of the memory-side cache the decoder finds it there.  encode_kept with
-// decode_kept, 13 entries of 2 to 50 MB of rows up to 2 GB, buffers in no cache, at 8 / 4 / 2 bits and raw: blobs of up to 281 MB 1.02 to 1.16 / 1.03 to 1.10 /
-// 1.01 to 1.09 / 1.07 to 1.20 times as fast (16,000 tokens of 32 x 1024, of which 4,064 are kept, 2 bits: 206.8 -> 192.4 us), 377 MB and more 0.93 to 0.97.
-constexpr size_t kKeepBytes = size_t(272) << 20;
-
-// grid = (blocks of a plane x planes of a group, plane groups, items)
+// grid = (blocks of a plane x planes of a group, plane groups, items); KEEP: see encode_keeps
 template <int DT, bool SLOTS, bool KEEP>
 __global__ __launch_bounds__(kEncThreads) __attribute__((amdgpu_waves_per_eu(4, 4))) void encode_kernel(EncodeParams a) {
   __shared__ float red[2 * kEncWaves * kStripCh];  // 32 KiB
@@ -855,7 +848,7 @@ int launch_encode(const EncodeParams& a, int dt, int n_items, int max_tokens, bo
   b.by_sets = Divisor((uint32_t)((heads & 1) ? heads : heads / 2));
   const unsigned n_groups = (unsigned)((2 * a.l + b.plane_group - 1) / b.plane_group);
   const bool one_dropped = a.items == nullptr && a.kept_items == nullptr && a.n_inline == 0 && (a.hdr_orig_tokens | a.hdr_sink | a.hdr_window) != 0;
-  const bool keep = one_dropped && kvh_blob_size(a.l, a.one.n_tokens, a.c, a.one.level) <= kKeepBytes;
+  const bool keep = one_dropped && encode_keeps(kvh_blob_size(a.l, a.one.n_tokens, a.c, a.one.level));
   const dim3 grid((unsigned)(gx * b.plane_group), n_groups, (unsigned)n_items);
   auto pick = [&](auto dt_tag, auto keep_tag) {
     constexpr int D = decltype(dt_tag)::value;
