@@ -216,7 +216,7 @@ struct DecodeParams {
   int plane_blocks; // blocks of an item's plane
   int row_tile;     // of these, how many are taken before the next plane of the group
   int waves;        // units of slots in a block
-  int small_pages;  // whole spans: pages of the destination count as small, see kStoreThrough
+  int page_through; // slots of 2 bits into pages are stored with device scope (see decode_launch)
   Divisor by_group, by_heads, by_sets;  // plane_group; heads of a row; K sets of slots in a row
   // Token-dropped entries (single-item calls only): token t >= split lands `jump` rows further on,
   // and the header must carry these three words (all zero for an ordinary blob).

@@ -95,10 +95,7 @@ __device__ __forceinline__ void gstore16(uint16_t* p, const uint4& v) {
 // Six shapes from 1 to 16 GiB (8K to 128K tokens, 32 and 80 layers), % of HBM peak, plain / device-scope stores, each
 // with the better K-parameter form: 8 bits 70.8 / 73.4 on average (better on every shape, +1.3 to +3.3), 4 bits
 // 73.4 / 76.8 (every shape, +0.9 to +6.2), 2 bits 73.9 / 74.0 (from -5 on the 8K shape to +3).
-// Small pages at 2 bits are an exception (small_pages): rows that go into pages of up to 32 KiB, such as 16 tokens of 1024 channels, in random
-// order.  Plain / device-scope stores there, in launches of 500 MiB to 4 GiB of rows, 5.04 / 5.3 TB/s on 32 x 8,192 (244 and 230 us),
-// 1.03 to 1.08 times as fast on eight shapes (64 KiB pages 0.95 to 1.1, contiguous 0.95 to 1.06), in smaller launches of spans 0.93 to 0.99;
-// slots into pages of any size, and small launches, 1.00 to 1.06 on twelve shapes (40 x 8,000 x 640: 192 and 181 us).
+// (2-bit rows into pages: see decode_launch.)
 template <int BITS>
 constexpr bool kStoreThrough = KVH_DEC_THROUGH < 0 ? (BITS == 8 || BITS == 4) : KVH_DEC_THROUGH != 0;
 
@@ -317,7 +314,7 @@ __device__ __forceinline__ void decode_unit(const DecodeParams& a, const kvh_ite
 
   // the row loop of one unit, instantiated with and without the explicit top-code rule
   int32_t rows[kDecRows];
-  auto run_rows = [&](int t0, auto fix_tag, auto&& param_of, auto through_tag) {
+  auto run = [&](int t0, auto fix_tag, auto&& param_of) {
     constexpr bool FIX = decltype(fix_tag)::value;
 #pragma unroll
     for (int i = 0; i < kDecRows; ++i) {
@@ -330,19 +327,13 @@ __device__ __forceinline__ void decode_unit(const DecodeParams& a, const kvh_ite
           // of its own, and the values of the next row are not computed ahead of it.  Without it the 2-bit level takes
           // 208 instead of 199 us on the 32 x 8192 x 1024 shape and 855 instead of 833 on 32 x 32768 x 1024; no difference
           // at 8 and 4 bits.  A scheduling barrier after the store does not have the effect.
-          if (ch[s] < (uint32_t)c) gstore16<decltype(through_tag)::value>(row + ch[s], out);
+          if (ch[s] < (uint32_t)c) gstore16<kStoreThrough<BITS>>(row + ch[s], out);
         }
       }
     }
   };
   using Yes = std::integral_constant<bool, true>;
   using No = std::integral_constant<bool, false>;
-  auto run = [&](int t0, auto fix_tag, auto&& param_of) {
-    if constexpr (BITS == 2 && !kStoreThrough<BITS>) {
-      if (a.small_pages != 0 && it.page_table != nullptr) return run_rows(t0, fix_tag, param_of, Yes{});  // wave-uniform
-    }
-    run_rows(t0, fix_tag, param_of, std::integral_constant<bool, kStoreThrough<BITS>>{});
-  };
 
   if (!is_v) {
     // Every thread of the block prepares its channels of the span; the three arrays (minimum, scale,
@@ -622,7 +613,7 @@ __device__ __forceinline__ void decode_slots(const DecodeParams& a, const kvh_it
   };
   auto store_all = [&](auto&& value_of) {
     if constexpr (BITS == 2 && !kSlotStoreThrough<BITS>) {
-      if (it.page_table != nullptr) return store_slots(value_of, std::true_type{});  // wave-uniform
+      if (a.page_through != 0 && it.page_table != nullptr) return store_slots(value_of, std::true_type{});  // wave-uniform
     }
     store_slots(value_of, std::integral_constant<bool, kSlotStoreThrough<BITS>>{});
   };
@@ -810,7 +801,7 @@ int launch_decode(const DecodeParams& a, int dt, int n_items, int max_tokens, bo
   b.plane_blocks = (int)plan.blocks;
   b.waves = plan.waves;
   b.plane_group = plan.plane_group;
-  b.small_pages = (int64_t)a.block_tokens * a.c * 2 <= (32 << 10) && 4.0 * a.l * a.c * max_tokens * n_items > 550.0 * (1 << 20);
+  b.page_through = plan.page_through;
   const dim3 grid((unsigned)(plan.blocks * b.plane_group), (unsigned)n_items, (unsigned)((2 * a.l + b.plane_group - 1) / b.plane_group));
   b.by_group = Divisor((uint32_t)b.plane_group);
   b.by_heads = Divisor((uint32_t)heads);

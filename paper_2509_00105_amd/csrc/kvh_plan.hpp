@@ -171,13 +171,18 @@ struct DecLaunch {
   int waves;
   int64_t blocks;             // of a (layer, K|V) plane; 0: refused, the grid would not fit
   int plane_group, row_tile;
+  bool page_through;          // 2-bit rows into pages are stored with device scope
 };
+// Rows of 2 bits: whole spans are stored without device scope, into pages as elsewhere.  32 KiB pages (1024 channels x 16 tokens) and smaller ones, 1,130
+// launches of 100 MiB to 4 GiB over buffers in turn, device scope against none: pages in random order 0.92 to 0.96 times as fast up to 1,000 MiB, 1.02 to
+// 1.5 GiB and 0.995 beyond; in order 0.93 to 0.95, 1.00 and 0.97; in runs of 8 pages 0.94 to 0.98, 1.03 and 1.00.  (A launch that the card is idle before
+// and after is 1.1 times as fast on 32 x 8,192: what it leaves in the memory-side cache is written back in the time of what follows.)
 inline DecLaunch decode_launch(int heads, int l, int n_items, int max_tokens, int64_t layer_stride, int64_t token_stride, bool raw) {
   const DecPlan p = decode_plan(heads, l, n_items, max_tokens, layer_stride, token_stride);
   if (!grid_fits(p.blocks, p.plane_group, p.waves)) return DecLaunch{};
   const DecUnits u = decode_units_plan(heads, l, n_items, max_tokens, layer_stride, token_stride, raw);
-  if (u.blocks != 0) return DecLaunch{true, false, 1, u.blocks, u.plane_group, 1};
-  return DecLaunch{p.slots, p.short_launch, p.waves, p.blocks, p.plane_group, p.row_tile};
+  if (u.blocks != 0) return DecLaunch{true, false, 1, u.blocks, u.plane_group, 1, true};
+  return DecLaunch{p.slots, p.short_launch, p.waves, p.blocks, p.plane_group, p.row_tile, p.slots};
 }
 
 // ---- transcoder -------------------------------------------------------------------------------------------------

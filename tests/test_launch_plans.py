@@ -39,6 +39,7 @@ extern "C" void dec_units(int heads, int l, int items, int tokens, int64_t layer
 extern "C" void dec_launch(int heads, int l, int items, int tokens, int64_t layer_stride, int64_t token_stride, int64_t* o) {
   const DecLaunch d = decode_launch(heads, l, items, tokens, layer_stride, token_stride, o[0] != 0);
   o[0] = d.slots; o[1] = d.short_launch; o[2] = d.waves; o[3] = d.blocks; o[4] = d.plane_group; o[5] = d.row_tile;
+  o[6] = d.page_through;
 }
 """
 
@@ -203,6 +204,13 @@ def test_decode_launches_the_form_that_is_planned(plans):
         slots, _, waves, blocks, group, tile, fits = plans("dec_plan", heads, l, items, n, *strides)[:7]
         assert fits and at(heads, l, items, n) == [slots, 0, waves, blocks, group, tile]
     assert not any(at(8, 1, 1, 2**31 - 1, dense(1024, 1))[:4])  # refused
+
+
+def test_decode_2_bit_rows_of_whole_spans_are_stored_alike_everywhere(plans):
+    """With device scope, pages of 32 KiB and less: 600 to 1,000 MiB 0.96 in random order, 0.93 to 0.95 in order."""
+    through = lambda heads, l, items, n: plans("dec_launch", heads, l, items, n, *dense(128 * heads, n * items))[6]
+    assert not any(through(8, l, items, 256) for l, items in ((32, 2), (32, 18), (32, 32), (80, 256)))
+    assert through(8, 32, 1, 256) and through(2, 32, 1, 256)
 
 
 def test_decode_raw_launches_of_up_to_one_block_of_spans_a_compute_unit_stay_in_spans(plans):
