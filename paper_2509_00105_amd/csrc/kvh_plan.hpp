@@ -177,12 +177,17 @@ struct DecLaunch {
 // launches of 100 MiB to 4 GiB over buffers in turn, device scope against none: pages in random order 0.92 to 0.96 times as fast up to 1,000 MiB, 1.02 to
 // 1.5 GiB and 0.995 beyond; in order 0.93 to 0.95, 1.00 and 0.97; in runs of 8 pages 0.94 to 0.98, 1.03 and 1.00.  (A launch that the card is idle before
 // and after is 1.1 times as fast on 32 x 8,192: what it leaves in the memory-side cache is written back in the time of what follows.)
+// Slots of 2 bits into pages take device scope in small launches, whose rows are out before the kernel ends, and in large ones.  6,400 launches of 4 to 80
+// layers, 128 to 3072 channels, pages of 8 to 64 tokens in random order and in order: up to 16 MiB 1.02 to 1.10, 16 to 40 MiB 0.99 to 1.04, 40 to 48 0.99; 48 to
+// 100 MiB 0.98 to 0.995, 100 to 1,000 MiB 0.93 to 0.97 and 0.95 to 0.975; 1 to 1.5 GiB 1.02 and 1.03, beyond 1.01 to 1.03 and 1.03.
+inline bool decode_page_through(double mib) { return mib <= 40 || mib >= 1024; }  // of 16-bit rows
 inline DecLaunch decode_launch(int heads, int l, int n_items, int max_tokens, int64_t layer_stride, int64_t token_stride, bool raw) {
   const DecPlan p = decode_plan(heads, l, n_items, max_tokens, layer_stride, token_stride);
   if (!grid_fits(p.blocks, p.plane_group, p.waves)) return DecLaunch{};
   const DecUnits u = decode_units_plan(heads, l, n_items, max_tokens, layer_stride, token_stride, raw);
-  if (u.blocks != 0) return DecLaunch{true, false, 1, u.blocks, u.plane_group, 1, true};
-  return DecLaunch{p.slots, p.short_launch, p.waves, p.blocks, p.plane_group, p.row_tile, p.slots};
+  const bool through = decode_page_through(4.0 * l * heads * 128 * max_tokens * n_items / (1 << 20));
+  if (u.blocks != 0) return DecLaunch{true, false, 1, u.blocks, u.plane_group, 1, through};
+  return DecLaunch{p.slots, p.short_launch, p.waves, p.blocks, p.plane_group, p.row_tile, p.slots && through};
 }
 
 // ---- transcoder -------------------------------------------------------------------------------------------------

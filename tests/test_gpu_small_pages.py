@@ -8,7 +8,7 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("l, c, lens, page", [(32, 1024, [256] * 17 + [203], 16), (4, 1024, [256, 100, 1], 16), (3, 640, [300, 129], 32), (5, 128, [515], 16),
-                                              (40, 640, [256] * 9, 16)])
+                                              (40, 640, [256] * 9, 16), (80, 640, [256] * 20 + [203], 16)])
 @pytest.mark.parametrize("dt", [torch.float16, torch.bfloat16])
 def test_rows_of_small_pages(l, c, lens, page, dt):
     import paper_2509_00105_amd as kvh

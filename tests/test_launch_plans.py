@@ -210,7 +210,14 @@ def test_decode_2_bit_rows_of_whole_spans_are_stored_alike_everywhere(plans):
     """With device scope, pages of 32 KiB and less: 600 to 1,000 MiB 0.96 in random order, 0.93 to 0.95 in order."""
     through = lambda heads, l, items, n: plans("dec_launch", heads, l, items, n, *dense(128 * heads, n * items))[6]
     assert not any(through(8, l, items, 256) for l, items in ((32, 2), (32, 18), (32, 32), (80, 256)))
-    assert through(8, 32, 1, 256) and through(2, 32, 1, 256)
+
+
+def test_decode_2_bit_slots_take_device_scope_into_pages_in_small_and_large_launches_only(plans):
+    """4 heads, 100 to 1,000 MiB: 0.93 to 0.97 in random order (48 x 10 x 512 tokens, 480 MiB: 88 us, 91 with device scope)."""
+    through = lambda heads, l, items, n: plans("dec_launch", heads, l, items, n, *dense(128 * heads, n * items))[6]
+    assert through(8, 32, 1, 256) and through(8, 32, 1, 320) and not through(8, 32, 1, 321)
+    assert through(2, 80, 2, 256) and through(5, 4, 1, 300) and not through(4, 48, 10, 512) and not through(2, 80, 16, 512) and not through(5, 40, 9, 256)
+    assert through(2, 80, 27, 512) and through(5, 80, 21, 256) and not through(5, 80, 20, 256)
 
 
 def test_decode_raw_launches_of_up_to_one_block_of_spans_a_compute_unit_stay_in_spans(plans):
