@@ -364,9 +364,12 @@ inline EncPlan encode_plan(int heads, int l, int n_items, int max_tokens) {
 //   / 0.97 / 1.00 / 0.99 (64 x 6,000 of 10 heads 0.98 at every level, 48 x 8,192 of 9 0.91 / 0.97 / 0.99 / 0.96): these stay as they are;
 //   whole strips: B up to 144 0.99 to 1.39 (8 heads, 24 x 83 at 8 bits 8.6 -> 7.2), 257 to 400, where some compute units get a second
 //   block, 1.03 to 1.36 (17 x 477 raw 16.2 -> 11.9); 145 to 256 0.87 to 1.07 (one raw 1.27), beyond 400 0.94 to 1.06, but where a few blocks are
-//   left over when the chip, which holds 512, has been filled once or twice: 20 launches of 3 to 65 layers, buffers in no cache, at 8 / 4 / 2 bits and raw 0.98 to 1.11 /
-//   1.02 to 1.15 / 1.06 to 1.19 / 1.00 to 1.10 (8 heads, 10 x 1,627, B = 520: 24.6 / 21.6 / 20.7 / 27.6 -> 23.7 / 20.2 / 18.9 / 27.2 us; 4 x 8,411, B = 1,056: 44.4 / 38.3 /
-//   35.8 / 55.2 -> 42.9 / 36.0 / 33.0 / 50.4); with 64 left over 0.99 / 1.03 / 1.06 / 1.05, with 128 0.96 / 0.96 / 0.99 / 1.04.  (15 heads raw 0.97);
+//   left over (few_left) when the chip, which holds 512, has been filled once or twice.  3,800 launches of 4 to 33 heads over 1 to 33 layers, 1 to 63 left over,
+//   batches of one length and of mixed ones, at 8 / 4 / 2 bits and raw on average: whole strips after one turn 1.05 / 1.07 / 1.10 / 1.05, after two 1.03 / 1.05 /
+//   1.09 / 1.05 (three 1.03 / 1.04 / 1.07 / 1.04, six 1.01 / 1.01 / 1.03 / 1.03; not taken), a tenth of them below 1.00 / 1.02 / 1.03 / 0.98; 15 heads and more that are no
+//   whole strips 1.05 / 1.11 / 1.12 and 1.01 / 1.045 / 1.085, raw 1.03 and 1.08 in batches, 0.98 and 1.02 as single blobs, which stay (8 heads, 10 x 1,627, B = 520: 24.6 /
+//   21.6 / 20.7 / 27.6 -> 23.7 / 20.2 / 18.9 / 27.2 us).  Raw items of less than 128 tokens have all their rows in the first blocks of a token-group: 0.90 on average, down to
+//   0.49 (8 heads, 135 items of 2 x 28 tokens 0.56), and a batch's levels are out of the launcher's sight;
 //   from 15 heads on few lanes of strips idle, and rows that are no whole strips follow the same limits: up to 144 and 257 to 400 0.98 to
 //   1.46, 1.15 on average over 85 launches (66 heads, 4 x 128 at 8 bits 0.93); beyond, at 8 / 4 / 2 bits and raw, 0.91 to 1.04 / 0.92 to 1.07 / 0.98
 //   to 1.11 / 0.97 to 1.01 (20 x 3,001 in one item at 8 bits: 15 to 33 heads but 21 and 23 0.91 to 0.94).
@@ -385,7 +388,10 @@ inline EncUnits encode_units_plan(int heads, int l, int n_items, int max_tokens,
   const double b = planes * (double)groups * ((heads + 3) / 4);
   EncUnits u{};
   const bool far_apart = heads >= 9 && heads <= 11 && max_tokens <= 512 && planes * heads * 256 * max_tokens > ((int64_t)1 << 30);
-  const bool few_left = ((b > 512 && b < 576) || (b > 1024 && b < 1088)) && (whole || !raw);
+  constexpr int kChip = 512, kTurns = 2;  // blocks of strips that run at a time; turns after which a few left over count
+  const int turns = b < (kTurns + 1) * kChip ? (int)b / kChip : 0;
+  const double left = b - turns * kChip;
+  const bool few_left = turns >= 1 && left > 0 && left < 64 && max_tokens >= 128 && (whole || !raw);
   if (heads < 3 || one_a_unit(b) || far_apart || ((whole || heads >= 15) && b > 400 && !few_left)) return u;
   if (raw && !whole && heads > 3 && one_a_unit(planes * (double)(((int64_t)max_tokens * heads + 511) / 512))) return u;
   u.waves = 4;

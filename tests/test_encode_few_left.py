@@ -16,6 +16,9 @@ def test_rule(plans):  # noqa: F811
     form = lambda a, known=False: plans("enc_units", a[0], a[1], a[2], a[3], known=known)[0]
     assert all(form(a) == 4 for a in LEFT) and not any(form(a) for a in EVEN)
     assert form((15, 1, 17, 500), True) == 0 and form((8, 10, 1, 1627), True) == 4  # raw rows that are no whole strips
+    # three turns; items that do not fill a token-group, whose raw rows lie in few blocks (8 heads, 135 x 2 x 28 raw: 0.56 of the speed of strips)
+    assert not form((8, 1, 1, 49209)) and not any(form((8, 2, 135, n)) for n in (28, 68, 127)) and form((8, 2, 135, 128)) == 4
+    assert not any(form((8, l, items, n)) for l, items, n in ((33, 4, 28), (8, 17, 68))) and form((8, 32767, 65535, 2**31 - 1)) == 0
 
 
 @pytest.mark.gpu
