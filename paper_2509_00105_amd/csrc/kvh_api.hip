@@ -413,7 +413,7 @@ int kvh_transcode(const void* src_dev, kvh_dtype dt, int l, int n_tokens, int c,
   a.status = status_dev;
   a.l = l;
   a.c = c;
-  return launch_transcode(a, dt, 1, n_tokens, level_bits(level_in) == 4 && level_bits(level_out) == 2, static_cast<hipStream_t>(stream));
+  return launch_transcode(a, dt, 1, n_tokens, static_cast<hipStream_t>(stream));
 }
 
 int kvh_transcode_batch(const kvh_tc_item* items_dev, int n_items, int max_tokens_per_item, kvh_dtype dt, int l, int c,
@@ -425,7 +425,7 @@ int kvh_transcode_batch(const kvh_tc_item* items_dev, int n_items, int max_token
   a.status = status_dev;
   a.l = l;
   a.c = c;
-  return launch_transcode(a, dt, n_items, max_tokens_per_item, false, static_cast<hipStream_t>(stream));
+  return launch_transcode(a, dt, n_items, max_tokens_per_item, static_cast<hipStream_t>(stream));
 }
 
 int kvh_encode_kept_batch(const kvh_kept_enc_item* items_dev, int n_items, int max_kept_tokens_per_item, kvh_dtype dt,

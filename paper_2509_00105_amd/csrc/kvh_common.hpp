@@ -282,8 +282,7 @@ struct TranscodeParams {
 // raw: every item is known on the host to be of the raw level (both)
 int launch_decode(const DecodeParams& a, int dt, int n_items, int max_tokens, bool raw, hipStream_t stream);
 int launch_encode(const EncodeParams& a, int dt, int n_items, int max_tokens, bool raw, hipStream_t stream);
-// narrow: every item is known on the host to go from 4 to 2 bits
-int launch_transcode(const TranscodeParams& a, int dt, int n_items, int max_tokens, bool narrow, hipStream_t stream);
+int launch_transcode(const TranscodeParams& a, int dt, int n_items, int max_tokens, hipStream_t stream);
 
 // Launch timing.  A caller that wants the duration of one launch itself (not of the launch plus the queue
 // packets that bracketing events add around it) hands over two events with kvh_time_next_launch; the next kernel

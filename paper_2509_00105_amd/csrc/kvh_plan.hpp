@@ -191,32 +191,9 @@ inline DecLaunch decode_launch(int heads, int l, int n_items, int max_tokens, in
 }
 
 // ---- transcoder -------------------------------------------------------------------------------------------------
-// Blocks of 8 waves over spans of 8 heads or, where spans leave lanes idle, over (row, head) slots of fewer.  Launches no longer take these
-// layouts; the rule for small launches from 4 to 2 bits below still counts their blocks.
-struct TcPlan {
-  bool slots;      // (row, head) slots; otherwise 1024-channel spans, in which the lanes beyond the row idle
-  int log_s;       // K sets are 2^log_s heads (3: a span)
-  int64_t sets;    // K sets of a token-group
-  int64_t blocks;  // of a (layer, K|V) plane
-};
-
-inline TcPlan transcode_plan(int heads, int l, int n_items, int max_tokens) {
-  const int spans = (heads + 7) / 8, lanes = spans * 8, idle = lanes - heads;
-  const int s = 1 << lowest_bit(heads);
-  const int64_t groups = ((int64_t)max_tokens + 127) / 128;
-  TcPlan p;
-  p.slots = 8 * idle > 3 * lanes || (s >= 2 && 4 * idle > lanes) || (s >= 4 && 4 * idle >= lanes);
-  if (p.slots && heads > 2 && (double)((groups * heads + 7) / 8) * 2 * l * n_items < 128) p.slots = false;
-  p.log_s = p.slots ? lowest_bit(heads) : 3;
-  p.sets = p.slots ? heads >> p.log_s : spans;
-  const int per_block = 8 >> p.log_s;
-  p.blocks = (groups * p.sets + per_block - 1) / per_block;
-  return p;
-}
-
-// Small launches, and short items of one or two heads: units of 4 or 8 accesses (see transcode_units).
+// Small launches: units of 4 or 8 accesses (see transcode_units).
 struct TcUnits {
-  int accesses;    // of a unit, 0: the layouts above
+  int accesses;    // of a unit, 0: units of 16, see transcode_stream_plan
   int period;      // accesses (of 8 slots) after which the heads repeat
   int units;       // of a token-group
   int parts;       // blocks of a token-group
@@ -225,28 +202,33 @@ struct TcUnits {
   int64_t blocks;  // of a (layer, K|V) plane
 };
 
-// A wave of a large launch takes 16 accesses, and small launches then have few waves (8 heads, 3 x 309 tokens, 8 -> 4 bits in blocks of 8:
-// 18 blocks, 11.8 us).  Units of 4 accesses, all requested at once, make 4 times the waves (5.8 us), but prepare K's parameters up to 4 times over.
-// 380 launches of 2 to 80 layers and 256 to 65,536 tokens, all pairs of levels, by w, the number of 16-access waves they take, against
-// the blocks of 8 waves above (transcode_plan):
-//   w <= 512: units of 4 accesses 1.09 to 2.4 times as fast, of 8 1.13 to 1.8;
-//   w <= 1,100: units of 8 0.95 to 1.8 (7 heads, 19 x 343, 4 -> 2: 1.27), 1.4 on average; of 4 0.85 to 1.85;
-//   beyond: 8 -> 4 and 8 -> 2 bits still gain (1.03 to 1.3 at w = 2,000), 4 -> 2 loses where the blocks above keep most lanes busy
-//   (8 heads 0.93 to 0.97, 15 and 16 heads 0.82).  With more than a quarter of the lanes idle there (3, 4, 5, 9, 10 and 11 heads) units of
-//   8 are 0.87 to 1.6 times as fast, 1.16 on average, up to 2,000;
-//   1 and 2 heads up to 2,900: 1.0 to 1.8 (2,900 to 10,000: 0.88 to 1.2); items of up to 256 tokens fill half or a quarter of a
-//   block of slots: 1 head 1.5 to 2.0 at any size (18 x 17,072, 4 -> 2: 30.2 -> 18.9 us), 2 heads 1.0 to 1.3 up to 10,000.
-// From 4 to 2 bits an element is a table look-up, and K's parameters, prepared once a block, weigh more: with 5 heads and more, where units
-// of 8 make more blocks than the chip has compute units and the blocks above do not, units are 0.81 to 1.02 times as fast, 0.94 on
-// average (6 heads, 20 x 200 in two items 0.92; 8 -> 4 bits there 1.06 to 1.3).  `narrow`: every item is known to go from 4 to 2 bits, as for
-// a single blob; the descriptors of a batch are out of the launcher's sight, and it keeps units.  Fewer heads 1.0 to 1.26.  Slower and without a rule: 16
-// heads x 16 tokens from 4 to 2 bits (0.89).
-inline TcUnits transcode_units_plan(int heads, int l, int n_items, int max_tokens, bool narrow) {
+// A wave of a large launch takes 16 accesses, and small launches then have few waves.  Units of 4 accesses, all requested at once, make 4 times the waves,
+// but prepare K's parameters up to 4 times over (8 heads, 3 x 512 tokens bf16, 8 -> 4 bits: 9.7 / 7.1 / 5.5 us in units of 16 / 8 / 4).
+// 19,000 launches of 1 to 80 layers and 200 to 3,001 tokens an item, buffers in turn, by w, the number of 16-access waves a launch takes.  Speed on average at
+// 8 -> 4 / 8 -> 2 / 4 -> 2 bits, of units of 8 over units of 16:
+//   w                up to 512            512 to 900           900 to 1,100         1,100 to 1,700       1,700 to 2,000       2,000 to 2,500
+//   1 head           1.19 / 1.34 / 1.22   1.15 / 1.25 / 1.19   1.11 / 1.18 / 1.17   1.04 / 1.09 / 1.12   1.01 / 1.04 / 1.07   0.97 / 0.93 / 1.01 *
+//   2                as 1                 as 1                 as 1                 1.02 / 1.08 / 1.11   1.00 / 1.05 / 1.08   0.99 / 0.97 / 1.03
+//   4                1.14 / 1.31 / 1.17   1.10 / 1.22 / 1.14   1.05 / 1.15 / 1.11   1.01 / 1.08 / 1.11   1.01 / 1.08 / 1.11   0.99 / 0.99 / 1.06
+//   11               1.16 / 1.12 / 1.20   1.10 / 1.08 / 1.16   1.00 / 1.02 / 1.08   1.10 / 1.09 / 1.20   1.08 / 1.06 / 1.16   1.10 / 1.05 / 1.17
+//   3 and 5          1.14 / 1.31 / 1.17   1.10 / 1.22 / 1.14   1.05 / 1.15 / 1.11   1.04 / 1.04 / 1.09   0.98 / 0.88 / 1.00   0.89 / 0.82 / 0.90
+//   9 and 10         1.16 / 1.12 / 1.20   1.10 / 1.08 / 1.16   1.00 / 1.02 / 1.08   1.07 / 1.03 / 1.17   0.98 / 0.90 / 1.00   1.05 / 0.91 / 1.08
+//   6, 7, 8 and 12   1.39 / 1.35 / 1.34   1.24 / 1.25 / 1.27   1.08 / 1.12 / 1.13   0.99 / 1.02 / 1.06   1.04 / 0.99 / 1.08   1.03 / 0.94 / 1.07
+//   15 and 16        1.21 / 1.12 / 1.20   1.17 / 1.08 / 1.19   1.11 / 1.03 / 1.14   0.99 / 0.91 / 1.05   1.02 / 0.90 / 1.06   1.01 / 0.85 / 1.03
+//   13 and 14        1.23 / 1.08 / 1.23   1.19 / 1.05 / 1.21   0.95 / 0.89 / 1.02   as 15
+// * 1 head in items of up to 256 tokens, which fill half a block of units of 16: 1.03 / 0.97 / 1.02 from 2,000 to 5,000, 1.00 / 0.96 / 0.89 beyond.
+// Units of 4 over units of 8: 1.26 / 1.14 / 1.14 up to 512, 1.10 / 1.02 / 0.95 from there to 1,100.
+// The limits are where the three pairs together no longer gain.  (Gains that are left: 11 heads beyond 2,000, 6, 7, 8 and 12 heads between 1,400 and 2,500.)
+inline TcUnits transcode_units_plan(int heads, int l, int n_items, int max_tokens) {
   const int64_t groups = ((int64_t)max_tokens + 127) / 128;
   const double w = 2.0 * l * n_items * (double)groups * heads;
-  const int lanes = (heads + 7) / 8 * 8, idle = lanes - heads;
-  double most = 4 * idle > lanes ? 2000 : 1100;
-  if (heads <= 2) most = max_tokens > 256 ? 2900 : heads == 1 ? 1e18 : 10000;
+  double most = 1100;
+  switch (heads) {
+    case 1: most = max_tokens <= 256 ? 5000 : 2000; break;
+    case 2: case 4: case 11: most = 2000; break;
+    case 3: case 5: case 9: case 10: most = 1700; break;
+    case 13: case 14: most = 900; break;
+  }
   TcUnits u{};
   if (heads > 16 || w > most) return u;  // (16: what a block's threads prepare and its LDS holds)
   u.accesses = w <= 512 ? 4 : 8;
@@ -258,27 +240,35 @@ inline TcUnits transcode_units_plan(int heads, int l, int n_items, int max_token
   if (u.groups > groups) u.groups = (int)groups;
   u.waves = u.parts > 1 ? (u.units + u.parts - 1) / u.parts : u.units * u.groups;
   u.blocks = u.parts > 1 ? groups * u.parts : (groups + u.groups - 1) / u.groups;
-  const int64_t planes = 2 * (int64_t)l * n_items;
-  if (narrow && heads >= 5 && u.accesses == 8 && u.blocks * planes > 256 && transcode_plan(heads, l, n_items, max_tokens).blocks * planes <= 256)
-    return TcUnits{};
   return u;
 }
 
-// All other launches: units of 16 accesses, in blocks of 3 to 8 waves.  Against the blocks of 8 waves above, at 8 -> 4 / 8 -> 2 / 4 -> 2
-// bits, 130 launches of 4 to 65 layers, 256- to 2,048-token items, by w as above:
-//   1 to 4 heads, every P-th access, blocks of up to 4 waves: 0.97 to 1.45 / 1.05 to 1.47 / 1.04 to 1.56 (of up to 8 waves 0.96 to 1.39 / 1.05 to
-//   1.46 / 1.0 to 1.3).
-//   5 to 8 heads: blocks of up to 4 waves prepare the parameters twice, which 8 -> 2 bits feels in small launches.  5 and 6 heads up to w = 3,500
-//   in one block of all units 1.01 to 1.25 / 1.04 to 1.20 / 1.00 to 1.13, in two 1.01 to 1.23 / 0.97 to 1.05 / 0.97 to 1.07, beyond 1.08 to 1.35 / 0.96 to 1.14 / 0.93 to
-//   1.13 and 1.20 to 1.35 / 1.00 to 1.21 / 1.02 to 1.23; 7 and 8 heads up to 10,000 1.00 to 1.34 / 1.05 to 1.15 / 0.99 to 1.04 and 1.02 to 1.32 / 0.96 to 1.05 / 0.92 to
-//   1.10, beyond 1.06 to 1.14 / 1.04 to 1.07 / 0.99 to 1.02 and 1.11 to 1.16 / 1.02 to 1.05 / 1.04.
-//   From 9 heads on sets of heads, blocks of 4 waves.  Multiples of 8 in spans of 8 heads, two blocks each (16 and 24 heads) 1.04 to 1.35 / 1.00 to 1.19 / 1.08 to 1.27
-//   (one block of 8 waves 1.02 to 1.18 / 1.05 to 1.11 / 1.05 to 1.09, sets of four 0.97 to 1.30 / 1.03 to 1.23 / 1.05 to 1.25); fours (12 and 20 heads) 1.04 to 1.29 / 1.06 to 1.27 /
-//   1.06 to 1.24; pairs (10, 14 and 18) 1.00 to 1.23 / 1.10 to 1.28 / 1.06 to 1.23; every P-th access there 0.90 to 1.0 / 0.73 to 0.93 / 0.79 to 1.0, because each block prepares
-//   all heads.  Odd numbers have single heads, whose pieces are 128 bytes of a row, or spans with idle lanes.  Where more than a quarter idles, single heads: 9, 11 and 17 1.02 to
-//   1.25 / 1.04 to 1.23 / 0.96 to 1.37 (spans 0.80 to 1.15 / 0.76 to 1.14 / 0.78 to 1.08); 13, 15, 25 and 33 in spans 1.12 to 1.31 / 1.03 to 1.20 / 1.12 to 1.26 (single heads 1.02
-//   to 1.31 / 1.00 to 1.29 / 0.91 to 1.19), but for up to w = 3,500 with blocks of 8 waves (13 heads 1.19 / 1.13 / 1.12, in two blocks 1.31 / 0.96 / 1.16).  More than 64 heads
-//   are spans; the distance between the rows of an access then stays within 32 bits.
+// All other launches: units of 16 accesses, in blocks of 3 to 8 waves.  130 launches of 4 to 65 layers, 256- to 2,048-token items, by w as above.  Speeds at 8 -> 4 /
+// 8 -> 2 / 4 -> 2 bits, each over the same launches in a kernel with blocks of 8 waves and 4 accesses at a time, which is no longer there; the form taken comes first.
+//   1 to 4 heads           every P-th access, up to 4 waves       0.97 to 1.45 / 1.05 to 1.47 / 1.04 to 1.56
+//                          up to 8 waves                          0.96 to 1.39 / 1.05 to 1.46 / 1.00 to 1.30
+//   5 and 6, w < 3,500     one block of all units                 1.01 to 1.25 / 1.04 to 1.20 / 1.00 to 1.13
+//                          two blocks                             1.01 to 1.23 / 0.97 to 1.05 / 0.97 to 1.07
+//            beyond        two blocks                             1.20 to 1.35 / 1.00 to 1.21 / 1.02 to 1.23
+//                          one block                              1.08 to 1.35 / 0.96 to 1.14 / 0.93 to 1.13
+//   7 and 8, w < 10,000    one block of all units                 1.00 to 1.34 / 1.05 to 1.15 / 0.99 to 1.04
+//                          two blocks                             1.02 to 1.32 / 0.96 to 1.05 / 0.92 to 1.10
+//            beyond        two blocks                             1.11 to 1.16 / 1.02 to 1.05 / 1.04
+//                          one block                              1.06 to 1.14 / 1.04 to 1.07 / 0.99 to 1.02
+//   16, 24 heads           sets of 8 heads, two blocks each       1.04 to 1.35 / 1.00 to 1.19 / 1.08 to 1.27
+//                          one block each                         1.02 to 1.18 / 1.05 to 1.11 / 1.05 to 1.09
+//                          sets of 4                              0.97 to 1.30 / 1.03 to 1.23 / 1.05 to 1.25
+//   12, 20                 sets of 4                              1.04 to 1.29 / 1.06 to 1.27 / 1.06 to 1.24
+//   10, 14, 18             pairs                                  1.00 to 1.23 / 1.10 to 1.28 / 1.06 to 1.23
+//                          every P-th access                      0.90 to 1.00 / 0.73 to 0.93 / 0.79 to 1.00 (each block prepares all heads)
+//   9, 11, 17              single heads                           1.02 to 1.25 / 1.04 to 1.23 / 0.96 to 1.37
+//                          sets of 8, lanes idle                  0.80 to 1.15 / 0.76 to 1.14 / 0.78 to 1.08
+//   13, 15, 25, 33         sets of 8, lanes idle, two blocks      1.12 to 1.31 / 1.03 to 1.20 / 1.12 to 1.26
+//                          single heads                           1.02 to 1.31 / 1.00 to 1.29 / 0.91 to 1.19
+//            w < 3,500     sets of 8 in one block                 1.19 / 1.13 / 1.12 (13 heads)
+//                          two blocks                             1.31 / 0.96 / 1.16
+// Blocks of two halves prepare the parameters twice, which 8 -> 2 bits feels in small launches.  More than 64 heads are sets of 8; the distance between the
+// rows of an access then stays within 32 bits.
 struct TcStream {
   int log_s;   // K: sets of 2^log_s heads x a token-group, a unit for each head (8 units are two blocks of 4 waves or one of 8); -1: every period-th access
   TcUnits in;  // with sets of heads only accesses, waves and blocks count

@@ -882,10 +882,10 @@ __global__ __launch_bounds__(kTcThreads) KVH_TC_OCC void transcode_units_kernel(
 #undef KVH_TC_CASE
 }
 
-int launch_transcode(const TranscodeParams& a, int dt, int n_items, int max_tokens, bool narrow, hipStream_t stream) {
+int launch_transcode(const TranscodeParams& a, int dt, int n_items, int max_tokens, hipStream_t stream) {
   const int heads = a.c / kGroup;
   const TcStream plan = transcode_stream_plan(heads, a.l, n_items, max_tokens);
-  const TcUnits units = transcode_units_plan(heads, a.l, n_items, max_tokens, narrow);
+  const TcUnits units = transcode_units_plan(heads, a.l, n_items, max_tokens);
   const bool small = units.accesses != 0, sets = !small && plan.log_s >= 0;
   const TcUnits u = small ? units : plan.in;
   if (!grid_fits(u.blocks, 1, u.waves)) return KVH_E_HIP;

@@ -68,6 +68,26 @@ def test_large_launches_match_oracle(kvh, heads, dt):
             assert (got[at[-1]:] == 0xAB).all()
 
 
+@pytest.mark.parametrize("dt", [F16, BF16])
+def test_large_launches_of_short_items_of_one_head(kvh, dt):
+    """Items of two token-groups, which fill half of a block."""
+    l, c, lens, count = 4, 128, (256, 129, 1), 640
+    entries = [awkward(*gen.make_kv(l, n, c, dt, seed=n), dt, np.random.default_rng(n)) for n in lens]
+    for a, b in ((0, 1), (0, 2), (1, 2)):
+        srcs = [oracle.encode(k, v, dt, a) for k, v in entries]
+        wants = [oracle.transcode(s, dt, l, n, c, a, b) for s, n in zip(srcs, lens)]
+        dev = [torch.from_numpy(s).cuda() for s in srcs]
+        pitch = max(w.size for w in wants) + 16
+        out = torch.full((count, pitch), 0xAB, dtype=torch.uint8, device="cuda")
+        items = kvh.make_tc_items([dev[i % 3].data_ptr() for i in range(count)], [o.data_ptr() for o in out], [lens[i % 3] for i in range(count)],
+                                  [a] * count, [b] * count, out.device)
+        kvh.transcode_batch(items, count, 256, TDT[dt], l, c)
+        got = out.cpu().numpy()
+        for i in range(count):
+            w = wants[i % 3]
+            assert np.array_equal(got[i, :w.size], w) and (got[i, w.size:] == 0xAB).all(), (i, a, b)
+
+
 def test_the_shapes_above_reach_the_forms_they_name():
     """(Runs where the GPU tests run; the rule itself is host arithmetic.)"""
     for heads, items in ITEMS.items():
