@@ -13,7 +13,7 @@ pytestmark = pytest.mark.gpu
 TDT = {gen.F16: torch.float16, gen.BF16: torch.bfloat16}
 L, N = 2, 300
 DECODE = [(8, 30), (8, 96), (16, 48)]  # heads, items of up to N tokens: spans with two blocks a compute unit (70 MiB), with one (225)
-TRANSCODE = {1: 260, 2: 130, 5: 36, 8: 12, 12: 12, 17: 12}  # heads -> items
+TRANSCODE = {1: 260, 2: 130, 5: 36, 8: 12, 12: 12, 16: 12, 17: 12, 25: 12}  # heads -> items; 16 and 25: a set of 8 heads is two blocks
 ENCODE = [(heads, items) for heads, items in ((3, 20), (5, 10), (8, 10), (8, 26), (17, 4), (17, 11))]  # of 129 tokens
 
 

@@ -379,6 +379,17 @@ def test_gpu_tests_reach_the_encoder_forms_they_name(plans):
         assert taken == ([4, 0, 4, 0] if heads % 4 == 0 or heads >= 15 else [4, 0, 4, 4]), heads
 
 
+def test_gpu_tests_reach_the_transcoder_streams_they_name(plans):
+    """tests/test_gpu_transcode_large.py: units of 16 accesses, for 5 to 8 heads in one block and in two, for 13 and 25 in blocks of 8 waves and of 4."""
+    import test_gpu_transcode_large as t
+
+    assert not any(plans("tc_units", h, 1, n, 300)[0] for h, items in t.ITEMS.items() for n in items) and plans("tc_units", 1, 4, 640, 256)[0] == 0
+    forms = {h: [plans("tc_stream", h, 1, n, 300)[:3] for n in items] for h, items in t.ITEMS.items()}
+    assert forms == {1: [[-1, 3, 1]], 2: [[-1, 4, 1]], 3: [[-1, 3, 1]], 4: [[-1, 4, 1]], 5: [[-1, 5, 1], [-1, 3, 2]], 6: [[-1, 6, 1], [-1, 3, 2]],
+                     7: [[-1, 7, 1], [-1, 4, 2]], 8: [[-1, 8, 1], [-1, 4, 2]], 9: [[0, 4, 1]], 10: [[1, 4, 1]], 11: [[0, 4, 1]], 12: [[2, 4, 1]],
+                     13: [[3, 8, 1], [3, 4, 1]], 16: [[3, 4, 1]], 20: [[2, 4, 1]], 24: [[3, 4, 1]], 25: [[3, 8, 1], [3, 4, 1]]}
+
+
 def test_gpu_tests_reach_the_large_forms_they_name(plans):
     import test_gpu_large_forms as t
 
@@ -389,7 +400,7 @@ def test_gpu_tests_reach_the_large_forms_they_name(plans):
     assert [spans(h, n, 304) for h, n in t.DECODE] == [[0, 1], [0, 0], [0, 0]]
     assert all(plans("tc_units", h, t.L, n, t.N)[0] == 0 for h, n in t.TRANSCODE.items())
     forms = {h: plans("tc_stream", h, t.L, n, t.N)[:3] for h, n in t.TRANSCODE.items()}  # log2 of the heads of a set (-1: every P-th access), waves, blocks a token-group
-    assert forms == {1: [-1, 3, 1], 2: [-1, 4, 1], 5: [-1, 5, 1], 8: [-1, 8, 1], 12: [2, 4, 1], 17: [0, 4, 1]}
+    assert forms == {1: [-1, 3, 1], 2: [-1, 4, 1], 5: [-1, 5, 1], 8: [-1, 8, 1], 12: [2, 4, 1], 16: [3, 4, 1], 17: [0, 4, 1], 25: [3, 4, 1]}
     assert not any(plans("enc_units", h, t.L, n, 129)[0] for h, n in t.ENCODE)
     assert [plans("enc_plan", h, t.L, n, 129)[:2] for h, n in t.ENCODE] == [[0, 0], [1, 1], [0, 0], [0, 0], [1, 0], [1, 0]]
     for h, l, n in t.RAW:
