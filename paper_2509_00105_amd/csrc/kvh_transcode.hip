@@ -253,8 +253,9 @@ constexpr bool kUseTable = (1 << BI) * BO <= 32;
 // Where a group lies no further from zero than some multiple of its range, its map is the one of exact arithmetic, code q to the
 // code nearest to q L_out / L_in, and needs no evaluation.  The quotient (never half-way between two codes) keeps a distance of
 // kMargin from every half-way point, and what the definition adds to it is the rounding of the value to 16 bits, at most M 2^-8 (bf16) or
-// M 2^-11 + 2^-25 (fp16) for a group whose values reach M, times L_out / r; the roundings to fp32 are below 2^-18 of the margin as long as
-// M is below 2^4 r, for which 1/64 is set aside.  From 4 to 2 bits that is M < 8.4 r in bf16: all groups but those of a large
+// M 2^-11 + 2^-25 (fp16) for a group whose values reach M, times L_out / r; the roundings to fp32 move the position
+// by less than 20 L_out 2^-24 as long as M is below 2^4 r (the sum by M 2^-24 / r, its quotient, difference and product by 2^-24 each), at most 2^-10 of the margin
+// (2 -> 8 bits), for which 1/64 is set aside.  From 4 to 2 bits that is M < 8.4 r in bf16: all groups but those of a large
 // common offset.  32 layers x 8,192 tokens x 1024 channels, 4 -> 2 bits: 87.2 us with every
 // table evaluated (16 times 7 operations), 77.5.
 template <int BI, int BO>
@@ -501,13 +502,13 @@ __device__ __forceinline__ void write_header(uint8_t* dst, const TranscodeParams
 // (ACC = 16): memory, and beside it 6 to 7 operations an element, 0.6 of what the vector units do in the time memory takes, so that one
 // has to run under the other.  8-bit codes come through a ring of 8 accesses (or 6): 4 are used while 4 are on their way, and those that follow
 // are requested before the next stores are issued (a wait for a load is a wait for every store before it as well).  No register is spilled on the way of
-// a row but one access of 8 -> 2 bits in fp16, and blocks are 3 or 4 waves where that is to be had: a block takes the place of one that has ended,
+// a row but one access of 8 -> 2 bits in fp16 (8 registers; all pairs of fp16 share the kernel and its 20 bytes of scratch a lane), and blocks are 3 or 4 waves where that is to be had: a block takes the place of one that has ended,
 // and its start is hidden by the others of the compute unit, four and not one.  Before, a wave took 4 accesses, waited for its stores, and took the
 // next 4, in blocks of 8 waves over 8 heads (or single heads, pairs and fours), with lanes idle for 3, 5, 6, 7, 11 and from 13 heads on.
 //   32 layers x 8,192 tokens in 256-token items, 8 heads bf16, 8 -> 4 / 8 -> 2 / 4 -> 2 bits: 153.7 / 140.8 / 88.5 -> 142 / 130.7 / 77.5 us (5.9 TB/s; without
 //   any arithmetic the same traffic takes 136 us at 8 -> 4 bits); 16 heads, 60 x 6,250: 510 / 474 / 291 -> 451 / 398 / 247; 5 heads, 7 x 20,000:
 //   75.2 / 73.1 / 43.6 -> 56.0 / 56.7 / 33.3; 10 heads, 20 x 8,000: 129 / 118 / 74 -> 119 / 106 / 67; 4 heads, 20 x 9,000: 58.2 / 54.6 / 35.5 -> 51.9 / 48.3 / 31.3.
-constexpr unsigned kUnitsHeadBytes = kGroup * 6 * sizeof(float);  // LDS for the parameters of a head: three values of a channel, and the 8 -> 2 polynomial  // LDS for the parameters of one head
+constexpr unsigned kUnitsHeadBytes = kGroup * 6 * sizeof(float);  // LDS for the parameters of a head: three values of a channel, and the 8 -> 2 polynomial
 template <int DT, int BI, int BO, int ACC, bool SETS>
 __device__ __forceinline__ void transcode_units(const TranscodeParams& a, const kvh_tc_item& it, int item_idx, int lay_kv,
                                                 uint32_t bx, uint8_t* lds, uint32_t* kflags) {
@@ -594,8 +595,9 @@ __device__ __forceinline__ void transcode_units(const TranscodeParams& a, const 
   const uint32_t out_lane = lane_slot * kOutBytes + sub * (kTcLaneCh * BO / 8);
 
   InCodes<BI> cw[kRing];
-  // Accesses past the last re-read it; lanes whose slot lies past the end read the access's first slot.  Neither is stored.
-  // ... of the lane's slot
+  // The caller guarantees kvh_blob_size(l, n_tokens, c, level_in) readable bytes at the source, so the loads issued before the header verdict stay inside the
+  // buffer whatever it says.  Accesses past the last re-read it; lanes whose slot lies past the end read the access's first slot.  Neither is stored.
+  // lane_count: accesses in which the lane's slot is stored.
   const uint32_t lane_rem = active && rem > lane_slot ? rem - lane_slot : 0u;
   const int lane_count = (int)(is_v ? (lane_rem + kTcSpanHeads - 1) / kTcSpanHeads : lane_rem == 0 ? 0u : a.by_step.quotient(lane_rem + step - 1));
   auto stores = [&](int k) { return k < lane_count; };
@@ -629,8 +631,9 @@ __device__ __forceinline__ void transcode_units(const TranscodeParams& a, const 
   using Yes = std::integral_constant<bool, true>;
   using No = std::integral_constant<bool, false>;
 
-  // V metadata: lane l prepares the l-th slot of the unit.  On the table routes every lane requests a word, and the wait for it
-  // is on every path (see transcode_block).
+  // V metadata: lane l prepares the l-th slot of a batch.  The words are requested with the codes, and by every lane (lanes without a slot read the
+  // unit's first), so that the wait for them, which takes in the codes, is on every path: a wait that some path skips is repeated before each access, where
+  // it also waits for the stores before (4 -> 2 bits, 32 x 8,192 x 1024 in blocks of 8 waves: 100 us instead of 88).
   const uint8_t* in_vmeta = in_layer + gin.kmeta + gin.codes + s0 * 4;
   constexpr int kWords = ACC / kVBatch;
   auto owns = [&](int b) { return (uint32_t)(b * kVBatch * kTcSpanHeads + lane) < rem && lane < kVBatch * kTcSpanHeads; };
