@@ -175,7 +175,8 @@ struct DecLaunch {
 };
 // Rows of 2 bits: whole spans are stored without device scope, into pages as elsewhere.  32 KiB pages (1024 channels x 16 tokens) and smaller ones, 1,130
 // launches of 100 MiB to 4 GiB over buffers in turn, device scope against none: pages in random order 0.92 to 0.96 times as fast up to 1,000 MiB, 1.02 to
-// 1.5 GiB and 0.995 beyond; in order 0.93 to 0.95, 1.00 and 0.97; in runs of 8 pages 0.94 to 0.98, 1.03 and 1.00.  (A launch that the card is idle before
+// 1.5 GiB and 0.995 beyond; in order 0.93 to 0.95, 1.00 and 0.97; in runs of 8 pages 0.94 to 0.98, 1.03 and 1.00.  200 launches of 4 to 14 GiB 1.01, 0.99 and 1.00,
+// of mixed levels 1.00.  (A launch that the card is idle before
 // and after is 1.1 times as fast on 32 x 8,192: what it leaves in the memory-side cache is written back in the time of what follows.)
 // Slots of 2 bits into pages take device scope in small launches, whose rows are out before the kernel ends, and in large ones.  6,400 launches of 4 to 80
 // layers, 128 to 3072 channels, pages of 8 to 64 tokens in random order and in order: up to 16 MiB 1.02 to 1.10, 16 to 40 MiB 0.99 to 1.04, 40 to 48 0.99; 48 to

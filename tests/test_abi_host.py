@@ -253,6 +253,13 @@ def test_bench_traffic_figures_are_those_of_the_committed_profile(lib):
         fetch, write, traffic = int(cells[5]), int(cells[6]), int(cells[7])
         assert traffic == (2 * fetch + write) * 1024, cells[0]
     assert bench.profiled_traffic("/nonexistent/file.md") == {}
+    # the table describes kernels that are there, by the names bench.py prints beside its figures
+    csrc = os.path.join(ROOT, "paper_2509_00105_amd", "csrc")
+    source = "".join(open(os.path.join(csrc, f)).read() for f in sorted(os.listdir(csrc)))
+    there = set(re.findall(r"\b(\w+_kernel)\(", source))
+    profiled = set(re.findall(r"\b(\w+_kernel)\b", open(bench.PROFILE_SUMMARY).read()))
+    printed = set(re.findall(r'"kernel": "(\w+_kernel)"', open(os.path.join(ROOT, "bench.py")).read())) | {"encode_kernel", "decode_kernel"}
+    assert profiled <= there and printed <= profiled, (profiled - there, printed - profiled)
 
 
 def test_bench_refuses_more_than_one_gpu():
