@@ -176,8 +176,8 @@ struct DecLaunch {
 // Rows of 2 bits: whole spans are stored without device scope, into pages as elsewhere.  32 KiB pages (1024 channels x 16 tokens) and smaller ones, 1,130
 // launches of 100 MiB to 4 GiB over buffers in turn, device scope against none: pages in random order 0.92 to 0.96 times as fast up to 1,000 MiB, 1.02 to
 // 1.5 GiB and 0.995 beyond; in order 0.93 to 0.95, 1.00 and 0.97; in runs of 8 pages 0.94 to 0.98, 1.03 and 1.00.  200 launches of 4 to 14 GiB 1.01, 0.99 and 1.00,
-// of mixed levels 1.00.  (A launch that the card is idle before
-// and after is 1.1 times as fast on 32 x 8,192: what it leaves in the memory-side cache is written back in the time of what follows.)
+// of mixed levels 1.00.  (A launch that the card is idle before and after is 1.1 times as fast on 32 x 8,192: what it leaves in the memory-side cache is
+// written back in the time of what follows.)
 // Slots of 2 bits into pages take device scope in small launches, whose rows are out before the kernel ends, and in large ones.  6,400 launches of 4 to 80
 // layers, 128 to 3072 channels, pages of 8 to 64 tokens in random order and in order: up to 16 MiB 1.02 to 1.10, 16 to 40 MiB 0.99 to 1.04, 40 to 48 0.99; 48 to
 // 100 MiB 0.98 to 0.995, 100 to 1,000 MiB 0.93 to 0.97 and 0.95 to 0.975; 1 to 1.5 GiB 1.02 and 1.03, beyond 1.01 to 1.03 and 1.03.
@@ -219,6 +219,7 @@ struct TcUnits {
 //   13 and 14        1.23 / 1.08 / 1.23   1.19 / 1.05 / 1.21   0.95 / 0.89 / 1.02   as 15
 // * 1 head in items of up to 256 tokens, which fill half a block of units of 16: 1.03 / 0.97 / 1.02 from 2,000 to 5,000, 1.00 / 0.96 / 0.89 beyond.
 // Units of 4 over units of 8: 1.26 / 1.14 / 1.14 up to 512, 1.10 / 1.02 / 0.95 from there to 1,100.
+// 2,700 launches of items of 8 to 128 tokens, units as taken over units of 16: 1.1 to 1.7 up to 512, 1.04 to 1.4 up to 1,100, 0.92 to 1.26 beyond (1 head).
 // The limits are where the three pairs together no longer gain.  (Gains that are left: 11 heads beyond 2,000, 6, 7, 8 and 12 heads between 1,400 and 2,500.)
 inline TcUnits transcode_units_plan(int heads, int l, int n_items, int max_tokens) {
   const int64_t groups = ((int64_t)max_tokens + 127) / 128;

@@ -1,0 +1,34 @@
+"""Token-dropped entries on both sides of the size up to which their codes are stored plainly, in device and in pinned host memory: the blob is that of the
+kept rows encoded by themselves (which other tests hold against the oracle), with the token-dropping words in its header, and nothing beyond it is written."""
+import numpy as np
+import pytest
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+# layers, channels, level, kept tokens: blobs just below and just above 48 MiB in strips and in slots, and small ones
+CASES = [(32, 1024, 3, 383), (32, 1024, 3, 384), (40, 640, 3, 491), (40, 640, 3, 492), (40, 640, 0, 900), (40, 640, 0, 1000), (32, 1024, 2, 700), (3, 640, 1, 129)]
+
+
+@pytest.mark.parametrize("l, c, level, kept", CASES)
+def test_blobs(l, c, level, kept):
+    import paper_2509_00105_amd as kvh
+
+    n, sink = kept + 37, 5
+    g = torch.Generator(device="cuda")
+    g.manual_seed(kept)
+    kv = torch.randn((2, l, n, c), generator=g, device="cuda").to(torch.bfloat16)
+    size = kvh.blob_size(l, kept, c, level)
+    want = kvh.encode(*[torch.cat([x[:, :sink], x[:, n - kept + sink:]], dim=1) for x in kv], level).clone()
+    want[32:44] = torch.from_numpy(np.array([n, sink, kept - sink], np.uint32).view(np.uint8)).cuda()
+    for out in (torch.full((size + 64,), 0xAB, dtype=torch.uint8, device="cuda"), torch.full((size + 64,), 0xAB, dtype=torch.uint8).pin_memory()):
+        kvh.encode_kept(kv[0], kv[1], sink, kept - sink, level, blob=out)
+        torch.cuda.synchronize()
+        got = out.cuda()
+        assert torch.equal(got[:size], want[:size]) and (got[size:] == 0xAB).all()
+
+
+def test_the_sizes_lie_on_both_sides():
+    import paper_2509_00105_amd as kvh
+
+    assert [kvh.blob_size(l, kept, c, level) <= 48 << 20 for l, c, level, kept in CASES] == [True, False, True, False, True, False, True, True]
