@@ -848,7 +848,7 @@ int launch_encode(const EncodeParams& a, int dt, int n_items, int max_tokens, bo
   b.by_sets = Divisor((uint32_t)((heads & 1) ? heads : heads / 2));
   const unsigned n_groups = (unsigned)((2 * a.l + b.plane_group - 1) / b.plane_group);
   const bool one_dropped = a.items == nullptr && a.kept_items == nullptr && a.n_inline == 0 && (a.hdr_orig_tokens | a.hdr_sink | a.hdr_window) != 0;
-  const bool keep = one_dropped && encode_keeps(kvh_blob_size(a.l, a.one.n_tokens, a.c, a.one.level));
+  const bool keep = one_dropped && encode_keeps(level_bits(a.one.level), kvh_blob_size(a.l, a.one.n_tokens, a.c, a.one.level));
   const dim3 grid((unsigned)(gx * b.plane_group), n_groups, (unsigned)n_items);
   auto pick = [&](auto dt_tag, auto keep_tag) {
     constexpr int D = decltype(dt_tag)::value;

@@ -394,14 +394,16 @@ inline EncUnits encode_units_plan(int heads, int l, int n_items, int max_tokens,
 // Stores of the codes.  A blob is written once and read later, if at all on this device, so that its codes are stored non-temporally: on
 // buffers in no cache 1.01 to 1.15 times as fast as plain stores.  The blob of one token-dropped entry (kvh_encode_kept; the items of a batch are out of
 // the launcher's sight) may go back into the cache at once, compacted: stored plainly it stays in the 256 MiB of the memory-side cache, where
-// kvh_decode_kept finds it.  That is taken as far as it costs nothing where the blob is not read again.  34 entries of 4 to 80 layers and 128 to 2048
-// channels, all levels, blobs in turn over 1.5 GB so that what is written back later is in the time, speed of plain stores over non-temporal ones on average:
-//   blob          encode_kept alone   followed by an encode, a decode, a copy of other data   by decode_kept
-//   up to 48 MB   0.99 to 1.03        1.02 to 1.03, 1.00, 0.99                                1.02 to 1.11
-//   48 to 64      0.995               1.01, 0.99, 0.99                                        1.10
-//   64 to 280     0.965 to 0.99       0.975 to 1.005, 0.96 to 0.985, 0.97 to 0.99             1.10 to 1.14
-//   above 280     0.97                0.97, 0.955, 0.98                                       0.95
-// Into pinned host memory plain stores are the faster ones (28 MB 527 us, non-temporal 729).
-inline bool encode_keeps(uint64_t blob_bytes) { return blob_bytes <= (uint64_t)48 << 20; }
+// kvh_decode_kept finds it.  That is taken as far as it costs next to nothing where the blob is not read again.  2,048 entries of 4 to 80 layers and 128 to 2048
+// channels, blobs in turn over 1.5 GB so that what is written back later is in the time, speed of plain stores over non-temporal ones on average, of
+// kvh_encode_kept alone / with a decode of other data behind it / with a copy / with kvh_decode_kept of the blob / with that and a decode behind it:
+//   blob            quantised levels                          raw
+//   up to 16 MB     0.99 / 1.00 / 0.99 / 1.05 / 1.02          0.97 / 0.99 / 0.98 / 1.11 / 1.04 (up to 24 MB)
+//   16 to 48        1.01 / 0.995 / 1.00 / 1.09 / 1.05         0.98 / 0.98 / 0.98 / 1.13 / 1.06
+//   48 to 100       0.99 / 0.99 / 1.00 / 1.09 / 1.06          0.96 / 0.97 / 0.98 / 1.14 / 1.08
+//   100 to 170      0.985 / 0.985 / 1.01 / 1.07 / 1.05        0.935 / 0.95 / 0.98 / 1.12 / 1.07
+//   170 to 268      0.98 / 0.98 / 1.02 / 1.06 / 1.06          0.93 / 0.94 / 0.98 / 1.12 / 1.10
+// Beyond the size of the cache both lose (0.95).  Into pinned host memory plain stores are the faster ones (28 MB 527 us, non-temporal 729).
+inline bool encode_keeps(int bits, uint64_t blob_bytes) { return bits <= 8 && blob_bytes <= (uint64_t)96 << 20; }
 
 }  // namespace kvh
