@@ -262,6 +262,19 @@ def test_bench_traffic_figures_are_those_of_the_committed_profile(lib):
     assert profiled <= there and printed <= profiled, (profiled - there, printed - profiled)
 
 
+def test_bench_takes_dropped_entries_in_turn(lib):
+    """One blob written or read again and again stays in the 256 MiB of the memory-side cache, the more so as codes of up to 96 MiB are stored
+    plainly (8 bits, 276 MB: 130 us and 143): between two uses of a blob lie twice that cache, or as many as the smallest workload has."""
+    import sys
+
+    sys.path.insert(0, ROOT)
+    import bench
+
+    sizes = [75497536, 276824128, 1 << 28, 3 << 28, 1 << 34]  # the first two are those of the default workload
+    assert [bench.buffers_in_turn(s) for s in sizes] == [11, 3, 3, 2, 2] and bench.buffers_in_turn(64) == 64
+    assert all((bench.buffers_in_turn(s) - 1) * s >= 512 << 20 for s in sizes)
+
+
 def test_bench_refuses_more_than_one_gpu():
     """The benchmark measures one GPU; asking for more must end with a message, before any GPU work."""
     import subprocess
